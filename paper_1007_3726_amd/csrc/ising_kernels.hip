@@ -519,7 +519,7 @@ __device__ __forceinline__ void process_tile(const TileArgs& a, const TileLane& 
 // shared by neighbouring lanes hit in L1/L2), issues the loads before the
 // Philox stretch and uses them after it.  No block barrier: the four waves
 // of a workgroup work independently.  Spin words are stored write-through.
-template <bool FULL, int WIDEM, bool BUMP_SALU = false, bool LCG = false, bool FLAT = false>
+template <bool FULL, int WIDEM, bool CUT, bool LCG = false, bool FLAT = false>
 __device__ __forceinline__ void process_tile_direct(const TileArgs& a, const TileLane& tl,
                                                     int colour, bool em, int64_t tidx,
                                                     uint32_t& anti, uint32_t& up) {
@@ -606,7 +606,7 @@ __device__ __forceinline__ void process_tile_direct(const TileArgs& a, const Til
         lo = (uint32_t)gy + 16u * (uint32_t)w;
       }
       const int nq = (FULL || w < W - 1) ? 16 : (g.nb_last >> 2);
-      masks_shift<FULL, BUMP_SALU>(lo, hi, nq, a.k0, a.k1, a.t, ctr3, a.t4, a.t8, r4, r8);
+      word_planes<FULL, CUT>(lo, hi, nq, a.k0, a.k1, a.t, ctr3, a.t4, a.t8, a.cut, r4, r8);
     }
     __builtin_amdgcn_sched_barrier(0);
     Nbr n;
@@ -621,7 +621,7 @@ __device__ __forceinline__ void process_tile_direct(const TileArgs& a, const Til
       n.n1 = left ? ((n0 << 1) | bl) : ((n0 >> 1) | br);
     }
     const uint64_t valid = (FULL || w < W - 1) ? ~0ull : low_mask(g.nb_last);
-    const uint64_t s_new = s ^ (flip_mask(s, n, r4, r8) & valid);
+    const uint64_t s_new = s ^ (flip_word<CUT>(s, n, r4, r8) & valid);
     // write-through at device scope (sc1): the XCD L2s then hold no dirty
     // lattice lines for the write-back at the end of the launch
     __hip_atomic_store(&self[off], s_new, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -631,7 +631,7 @@ __device__ __forceinline__ void process_tile_direct(const TileArgs& a, const Til
 
 // Tiles read their neighbour words directly (process_tile_direct): no LDS
 // staging and no barrier until the E/M reduction at the end.
-template <int C, bool EM, bool FULL, bool WIDE, bool LCG, bool FLAT>
+template <int C, bool EM, bool FULL, bool WIDE, bool LCG, bool FLAT, bool CUT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_tile_sweep(
     TileArgs a) {
   __shared__ uint64_t red64[8];
@@ -645,7 +645,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
   uint32_t anti = 0, up = 0;
   const TileLane tl = tile_lane<WIDE ? 1 : 0>(a);
   for (int64_t tidx = lb; tidx < a.tiles; tidx += G)
-    process_tile_direct<FULL, WIDE ? 1 : 0, false, LCG, FLAT>(a, tl, C, EM, tidx, anti, up);
+    process_tile_direct<FULL, WIDE ? 1 : 0, CUT, LCG, FLAT>(a, tl, C, EM, tidx, anti, up);
   if (C == 1 && EM) {
     uint64_t sa, sp;
     block_sum2(anti, up, red, sa, sp);
@@ -854,7 +854,7 @@ __global__ __launch_bounds__(256) void k_share_init(ShareArgs a, int init) {
   }
 }
 
-template <int C, bool EM>
+template <int C, bool EM, bool CUT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_share_sweep(
     ShareArgs a) {
   __shared__ uint64_t red[8];
@@ -879,15 +879,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
     const uint64_t sd = other[row * W + ws];
     const uint64_t g = (uint64_t)y * a.L8 + 16u * w;
     uint64_t r4, r8;
-    masks_shift<true>((uint32_t)g, (uint32_t)(g >> 32), 16, a.k0, a.k1, a.t, ctr3, a.t4, a.t8,
-                      r4, r8);
+    word_planes<true, CUT>((uint32_t)g, (uint32_t)(g >> 32), 16, a.k0, a.k1, a.t, ctr3, a.t4, a.t8,
+                           a.cut, r4, r8);
     __builtin_amdgcn_sched_barrier(0);
     Nbr n;
     n.n0 = n0;
     n.n2 = n2;
     n.n3 = n3;
     n.n1 = left ? ((n0 << 1) | (sd >> 63)) : ((n0 >> 1) | (sd << 63));
-    const uint64_t s_new = s ^ flip_mask(s, n, r4, r8);
+    const uint64_t s_new = s ^ flip_word<CUT>(s, n, r4, r8);
     __hip_atomic_store(&self[row * W + w], s_new, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (C == 1 && EM) count_word(s_new, n, ~0ull, anti, up);
   }
@@ -954,13 +954,21 @@ hipError_t launch_share_init(hipStream_t st, const ShareArgs& a, int init) {
   return hipGetLastError();
 }
 
-hipError_t launch_share_sweep(hipStream_t st, int colour, const ShareArgs& a, int blocks) {
+template <bool CUT>
+static void launch_share_sweep_v(hipStream_t st, int colour, const ShareArgs& a, int blocks) {
   if (colour == 0)
-    hipLaunchKernelGGL((k_share_sweep<0, false>), dim3(blocks), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_share_sweep<0, false, CUT>), dim3(blocks), dim3(256), 0, st, a);
   else if (a.part)
-    hipLaunchKernelGGL((k_share_sweep<1, true>), dim3(blocks), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_share_sweep<1, true, CUT>), dim3(blocks), dim3(256), 0, st, a);
   else
-    hipLaunchKernelGGL((k_share_sweep<1, false>), dim3(blocks), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_share_sweep<1, false, CUT>), dim3(blocks), dim3(256), 0, st, a);
+}
+
+hipError_t launch_share_sweep(hipStream_t st, int colour, const ShareArgs& a, int blocks) {
+  if (a.cut.x)
+    launch_share_sweep_v<true>(st, colour, a, blocks);
+  else
+    launch_share_sweep_v<false>(st, colour, a, blocks);
   return hipGetLastError();
 }
 
@@ -987,7 +995,7 @@ hipError_t launch_share_combine(hipStream_t st, const int64_t* counts, int32_t n
 // workgroup at the end.  Tasks are numbered segment-fastest within a row
 // strip: task = strip * segs + seg.
 // ---------------------------------------------------------------------
-template <int C, bool EM, bool FULL>
+template <int C, bool EM, bool FULL, bool CUT>
 __device__ __forceinline__ void strip_task(const TileArgs& a, int64_t task, uint32_t& anti,
                                            uint32_t& up) {
   const Geom& g = a.g;
@@ -1034,7 +1042,7 @@ __device__ __forceinline__ void strip_task(const TileArgs& a, int64_t task, uint
       lo = (uint32_t)gy + 16u * (uint32_t)w;
     }
     uint64_t r4, r8;
-    masks_shift<FULL>(lo, hi, nq, a.k0, a.k1, a.t, ctr3, a.t4, a.t8, r4, r8);
+    word_planes<FULL, CUT>(lo, hi, nq, a.k0, a.k1, a.t, ctr3, a.t4, a.t8, a.cut, r4, r8);
     // the uniforms need no lattice data: keep the gather below them so that
     // the row's loads have the whole Philox stretch to arrive
     __builtin_amdgcn_sched_barrier(0);
@@ -1048,7 +1056,7 @@ __device__ __forceinline__ void strip_task(const TileArgs& a, int64_t task, uint
       n.n1 = (FULL || w < W - 1) ? ((oc >> 1) | (sd << 63))
                                  : ((oc >> 1) | ((sd & 1ull) << (g.nb_last - 1)));
     }
-    const uint64_t s_new = s ^ (flip_mask(s, n, r4, r8) & valid);
+    const uint64_t s_new = s ^ (flip_word<CUT>(s, n, r4, r8) & valid);
     // written through to memory at device scope: the XCD L2s then hold no
     // dirty lattice lines for the kernel-boundary write-back
     __hip_atomic_store(&self[y * W + w], s_new, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1073,7 +1081,7 @@ __device__ __forceinline__ void strip_task(const TileArgs& a, int64_t task, uint
 
 // 8 waves per SIMD (the gfx950 maximum) need <= 100 SGPRs; without the
 // hint the compiler takes 106 and a CU would hold only 7 workgroups.
-template <int C, bool EM, bool FULL>
+template <int C, bool EM, bool FULL, bool CUT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_strip_sweep(
     TileArgs a) {
   __shared__ uint64_t red64[8];
@@ -1087,7 +1095,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t anti = 0, up = 0;
   for (int64_t task = (int64_t)lb * 4 + wave; task < a.tiles; task += (int64_t)G * 4)
-    strip_task<C, EM, FULL>(a, task, anti, up);
+    strip_task<C, EM, FULL, CUT>(a, task, anti, up);
   if (C == 1 && EM) {
     uint64_t sa, sp;
     block_sum2(anti, up, red, sa, sp);
@@ -1184,10 +1192,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
     uint32_t anti = 0, up = 0;
     // every fused lattice uses the flat mapping (run_fused sets it; for W
     // dividing 64 it is the narrow mapping itself)
-    if (a.g.nb_last == 64)
-      process_tile_direct<true, 2, false, false, true>(a, tl, C, em, ft.local, anti, up);
-    else
-      process_tile_direct<false, 2, false, false, true>(a, tl, C, em, ft.local, anti, up);
+    const bool full = a.g.nb_last == 64;
+    if (a.cut.x != 0) {
+      if (full)
+        process_tile_direct<true, 2, true, false, true>(a, tl, C, em, ft.local, anti, up);
+      else
+        process_tile_direct<false, 2, true, false, true>(a, tl, C, em, ft.local, anti, up);
+    } else {
+      if (full)
+        process_tile_direct<true, 2, false, false, true>(a, tl, C, em, ft.local, anti, up);
+      else
+        process_tile_direct<false, 2, false, false, true>(a, tl, C, em, ft.local, anti, up);
+    }
     if (em) {
       anti = wave_sum(anti);
       up = wave_sum(up);
@@ -1272,46 +1288,43 @@ hipError_t launch_advance(hipStream_t st, uint32_t* kbase, uint32_t by) {
 // ---------------------------------------------------------------------
 // Host-side launchers
 // ---------------------------------------------------------------------
-template <bool LCG, bool FLAT>
-static void launch_tile_sweep_rng(hipStream_t st, int colour, const TileArgs& a, int blocks) {
+template <bool LCG, bool FLAT, bool CUT, bool WIDE>
+static void launch_tile_sweep_v(hipStream_t st, int colour, const TileArgs& a, int blocks) {
   const bool em = (colour == 1) ? (a.part != nullptr) : false;
   const bool full = a.g.nb_last == 64;
-  // the flat mapping does not use the row-group shape: one instantiation
-  const bool wide = !FLAT && a.g.W >= kWideMinWords;
-#define ISING_TILE(C, E, F, WI) \
-  hipLaunchKernelGGL((k_tile_sweep<C, E, F, WI, LCG, FLAT>), dim3(blocks), dim3(256), 0, st, a)
-#define ISING_TILE_FW(C, E)                                   \
-  do {                                                        \
-    if (full) {                                               \
-      if (wide) ISING_TILE(C, E, true, true);                 \
-      else ISING_TILE(C, E, true, false);                     \
-    } else {                                                  \
-      if (wide) ISING_TILE(C, E, false, true);                \
-      else ISING_TILE(C, E, false, false);                    \
-    }                                                         \
-  } while (0)
-  if (colour == 0)
-    ISING_TILE_FW(0, false);
-  else if (em)
-    ISING_TILE_FW(1, true);
-  else
-    ISING_TILE_FW(1, false);
-#undef ISING_TILE_FW
+#define ISING_TILE(C, E, F) \
+  hipLaunchKernelGGL((k_tile_sweep<C, E, F, WIDE, LCG, FLAT, CUT>), dim3(blocks), dim3(256), 0, st, a)
+  if (colour == 0) {
+    if (full) ISING_TILE(0, false, true);
+    else ISING_TILE(0, false, false);
+  } else if (em) {
+    if (full) ISING_TILE(1, true, true);
+    else ISING_TILE(1, true, false);
+  } else {
+    if (full) ISING_TILE(1, false, true);
+    else ISING_TILE(1, false, false);
+  }
 #undef ISING_TILE
 }
 
+template <bool LCG, bool CUT>
+static void launch_tile_sweep_rng(hipStream_t st, int colour, const TileArgs& a, int blocks) {
+  // the flat mapping does not use the row-group shape
+  if (a.flat)
+    launch_tile_sweep_v<LCG, true, CUT, false>(st, colour, a, blocks);
+  else if (a.g.W >= kWideMinWords)
+    launch_tile_sweep_v<LCG, false, CUT, true>(st, colour, a, blocks);
+  else
+    launch_tile_sweep_v<LCG, false, CUT, false>(st, colour, a, blocks);
+}
+
 hipError_t launch_tile_sweep(hipStream_t st, int colour, const TileArgs& a, int blocks) {
-  if (a.lcg) {
-    if (a.flat)
-      launch_tile_sweep_rng<true, true>(st, colour, a, blocks);
-    else
-      launch_tile_sweep_rng<true, false>(st, colour, a, blocks);
-  } else {
-    if (a.flat)
-      launch_tile_sweep_rng<false, true>(st, colour, a, blocks);
-    else
-      launch_tile_sweep_rng<false, false>(st, colour, a, blocks);
-  }
+  if (a.lcg)
+    launch_tile_sweep_rng<true, false>(st, colour, a, blocks);
+  else if (a.cut.x)
+    launch_tile_sweep_rng<false, true>(st, colour, a, blocks);
+  else
+    launch_tile_sweep_rng<false, false>(st, colour, a, blocks);
   return hipGetLastError();
 }
 
@@ -1373,11 +1386,12 @@ hipError_t launch_pool_sweep(hipStream_t st, int colour, const TileArgs& a, int 
   return hipGetLastError();
 }
 
-hipError_t launch_strip_sweep(hipStream_t st, int colour, const TileArgs& a, int blocks) {
+template <bool CUT>
+static void launch_strip_sweep_v(hipStream_t st, int colour, const TileArgs& a, int blocks) {
   const bool em = (colour == 1) ? (a.part != nullptr) : false;
   const bool full = a.g.nb_last == 64;
 #define ISING_STRIP(C, E, F) \
-  hipLaunchKernelGGL((k_strip_sweep<C, E, F>), dim3(blocks), dim3(256), 0, st, a)
+  hipLaunchKernelGGL((k_strip_sweep<C, E, F, CUT>), dim3(blocks), dim3(256), 0, st, a)
   if (colour == 0) {
     if (full) ISING_STRIP(0, false, true);
     else ISING_STRIP(0, false, false);
@@ -1389,6 +1403,13 @@ hipError_t launch_strip_sweep(hipStream_t st, int colour, const TileArgs& a, int
     else ISING_STRIP(1, false, false);
   }
 #undef ISING_STRIP
+}
+
+hipError_t launch_strip_sweep(hipStream_t st, int colour, const TileArgs& a, int blocks) {
+  if (a.cut.x)
+    launch_strip_sweep_v<true>(st, colour, a, blocks);
+  else
+    launch_strip_sweep_v<false>(st, colour, a, blocks);
   return hipGetLastError();
 }
 

@@ -45,6 +45,7 @@ struct TileArgs {
   int64_t plane_words;
   Geom g;
   uint32_t k0, k1, sid4, t, t4, t8;
+  Cut cut;          // three-way cut of (t4, t8), x = 0 when they have none
   int32_t TW;       // tile width in words: 64 when W >= kWideMinWords, else W
   int32_t R;        // rows per row group: 1 when W >= kWideMinWords, else floor(64 / W)
   int32_t RPW;      // row groups per wave in one tile
@@ -163,6 +164,7 @@ struct ShareArgs {
   uint32_t L8;           // L / 8: Philox blocks per colour row
   uint32_t wdiv_m;       // floor(2^32 / W) + 1 (flat word -> row), 0 for W == 1
   uint32_t k0, k1, sid4, t, t4, t8;
+  Cut cut;               // three-way cut of (t4, t8), x = 0 when they have none
   uint64_t* part;        // colour 1 with counts: per-block (anti-aligned bonds, up spins)
 };
 hipError_t launch_share_init(hipStream_t st, const ShareArgs& a, int init);

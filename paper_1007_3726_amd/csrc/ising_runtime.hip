@@ -150,6 +150,7 @@ bool tile_args(const ising_lattice* h, TileArgs* out) {
   a.sid4 = h->stream_id << 2;
   a.t4 = h->t4;
   a.t8 = h->t8;
+  a.cut = h->cut;
   *out = a;
   return true;
 }
@@ -393,6 +394,7 @@ ising_status ising_set_beta(ising_t* h, double beta) {
   h->beta = beta;
   h->t4 = metropolis_threshold(beta, 4);
   h->t8 = metropolis_threshold(beta, 8);
+  h->cut = make_cut(h->t4, h->t8);
   h->l4 = lcg_threshold(beta, 4);
   h->l8 = lcg_threshold(beta, 8);
   h->beta_set = true;

@@ -58,6 +58,7 @@ struct ising_lattice {
   int32_t init;
   double beta;
   uint32_t t4, t8;
+  ising::Cut cut;       // three-way cut of (t4, t8)
   uint32_t l4, l8;      // LCG thresholds min(floor(exp(-beta dE) 2^31), 2^31)
   bool beta_set;
   uint32_t* lcg;        // device: per-thread LCG states [2][L][W] (caller's), or null

@@ -30,6 +30,7 @@ struct ising_strip {
   uint32_t stream_id;
   hipStream_t stream;
   uint32_t t4, t8;
+  ising::Cut cut;
   bool beta_set;
 };
 
@@ -57,6 +58,7 @@ ShareArgs share_args(const ising_strip* h, uint32_t t) {
   a.t = t;
   a.t4 = h->t4;
   a.t8 = h->t8;
+  a.cut = h->cut;
   a.part = nullptr;
   return a;
 }
@@ -130,6 +132,7 @@ ising_status ising_strip_set_beta(ising_strip_t* h, double beta) {
     return fail(ISING_EINVAL, "ising_strip_set_beta: beta must be >= 0 or +inf");
   h->t4 = metropolis_threshold(beta, 4);
   h->t8 = metropolis_threshold(beta, 8);
+  h->cut = make_cut(h->t4, h->t8);
   h->beta_set = true;
   return ISING_OK;
 }
