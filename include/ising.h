@@ -97,6 +97,21 @@ ISING_API size_t ising_lattice_bytes(int64_t L);
 ISING_API ising_status ising_create(int64_t L, uint64_t seed, uint32_t stream_id, int32_t init,
                           void *dev_buf, size_t dev_bytes, void *hip_stream, ising_t **out);
 
+/*
+ * A second copy of the planes, in which a lattice takes several sweeps per
+ * launch: strips of rows read one copy and write the other, so that the
+ * lattice's own planes hold the result again when a call's work is done.
+ * Without one (the default) every colour step is a launch.  dev_spare is the
+ * caller's, 8-byte aligned, at least ising_spare_bytes(L) bytes, and stays
+ * with the handle until it is replaced or the handle destroyed (NULL takes
+ * it away); its contents mean nothing between calls.  ising_spare_bytes is 0
+ * for sides that take none (invalid, or too large to gain by it).  Results
+ * are the same with and without.
+ * Errors: EINVAL (NULL handle, a side that takes none, alignment), ENOMEM.
+ */
+ISING_API size_t ising_spare_bytes(int64_t L);
+ISING_API ising_status ising_set_spare(ising_t *h, void *dev_spare, size_t bytes);
+
 /* Release the handle (never frees dev_buf).  NULL is accepted. */
 ISING_API ising_status ising_destroy(ising_t *h);
 
@@ -236,13 +251,16 @@ typedef struct {
 
 /*
  * Time candidate shapes of the plain sweep for a lattice of side L: the
- * LDS-resident single workgroup for small lattices; tiles with rpw in
+ * LDS-resident single workgroup for small lattices; the size rule (rpw 0);
+ * tiles with rpw in
  * {1, 2, 4} x grid cap in {512, 1024, 2048}; for rows of >= 63 words, strips
  * of {rule, 4, 8, 16, 32} rows x grid cap in {1024, 2048}.  It uses the
  * caller's device buffer as scratch: at least ising_lattice_bytes(L) bytes
  * (rounded up to 256); with 16 * max(trial_sweeps, 2) bytes more, every
  * trial also records its per-sweep (E, M) there, as a run with a series
- * does, and is timed with that cost.  It times trial_sweeps sweeps per
+ * does, and is timed with that cost; with ising_spare_bytes(L) bytes more
+ * behind that (rounded up to 256), the size rule is timed with its several
+ * sweeps per launch.  It times trial_sweeps sweeps per
  * shape, installs the fastest for L's size class [2^k, 2^(k+1)) and returns
  * it in *out.  Handles created afterwards use it; results are bit-identical
  * for every shape.  Synchronises the stream.
@@ -462,8 +480,8 @@ ISING_API ising_status ising_strip_combine(const int64_t *dev_counts, int32_t ns
 /*
  * Barrier perturbation for race tests (process-wide; 0 turns it off, the
  * default).  With a nonzero seed, the kernels that rely on block barriers
- * inside a launch (the LDS-resident small-lattice sweeps and the packed
- * persistent batched kernel) make every wave pause a pseudo-random time,
+ * inside a launch (several sweeps per launch, the packed batched form among
+ * them) make every wave pause a pseudo-random time,
  * drawn from the seed, before each such barrier.  Results must not change;
  * a difference points at a missing barrier.  Applies to launches enqueued
  * after the call.  Always ISING_OK.

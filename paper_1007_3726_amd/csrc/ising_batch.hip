@@ -7,11 +7,13 @@
 //     so every colour step is balanced over the whole GPU.  Long runs are
 //     replayed from a captured hipGraph chunk of K sweeps (a device-side
 //     sweep counter advanced by the last node keeps the chunk reusable);
-//   * packed: when every lattice is small, lattices are packed (longest
-//     first) onto workgroups of one persistent launch (k_batch) that runs all
-//     n sweeps with block barriers only.
+//   * blocks (ising_block.hip): several sweeps per launch on rows held in LDS,
+//     for batches whose colour steps would not fill the GPU for longer than a
+//     launch takes; a batch of small lattices ("packed") gives each one
+//     workgroup and runs all n sweeps in one launch.
 // Lattices the tiled layout does not cover (L % 8 != 0, or Philox block
-// indices crossing 2^32 inside a row) are advanced with the plain path.
+// indices crossing 2^32 inside a row) are advanced with the plain path unless
+// the whole batch takes blocks.
 // The task tables live in a work buffer the caller provides (device
 // memory, batch_work_bytes of it); the library allocates no device memory.
 #include <hip/hip_runtime.h>
@@ -71,17 +73,15 @@ FusedLayout fused_layout(size_t nl, size_t ntiles) {
   return f;
 }
 
-// Byte offsets of the packed form's tables (one item per lattice, at most
-// one workgroup per lattice).
-struct PackedLayout {
-  size_t off_lat = 0, off_items = 0, off_wgs = 0, bytes = 0;
+// Byte offsets of the block form's tables.
+struct BlockLayout {
+  size_t off_tasks = 0, bytes = 0;
 };
 
-PackedLayout packed_layout(size_t nl, size_t nitems, size_t nwgs) {
-  PackedLayout p;
-  p.off_items = align_up(nl * sizeof(BatchLattice), 256);
-  p.off_wgs = align_up(p.off_items + nitems * sizeof(BatchItem), 256);
-  p.bytes = align_up(p.off_wgs + nwgs * sizeof(BatchWG), 256);
+BlockLayout block_layout(size_t nl, size_t ntasks) {
+  BlockLayout p;
+  p.off_tasks = align_up(nl * sizeof(BlockLattice), 256);
+  p.bytes = align_up(p.off_tasks + ntasks * sizeof(BlockTask), 256);
   return p;
 }
 
@@ -92,6 +92,8 @@ int64_t fused_tiles(int64_t plane_words, int32_t rpw) {
 }
 
 }  // namespace
+
+int device_cus(int device) { return cu_count(state_for(device), device); }
 
 // Pack single-workgroup lattices onto `bins` workgroups, longest first.
 std::vector<std::vector<int>> pack_lpt(const std::vector<double>& cost, int bins) {
@@ -266,51 +268,51 @@ static ising_status run_fused(ising_lattice* const* hs, const std::vector<int>& 
   return ISING_OK;
 }
 
-static ising_status run_packed(ising_lattice* const* hs, const std::vector<int>& idx,
-                               const std::vector<TileArgs>& targs, int64_t n, const int64_t* nsw,
-                               int64_t* const* dev_EM, const BatchPlan& plan, char* work,
-                               size_t work_bytes, std::vector<char>* keep_image) {
+// All lattices idx (shapes in plan, in order) in the block form.
+static ising_status run_blocks(ising_lattice* const* hs, const std::vector<int>& idx, int64_t n,
+                               const int64_t* nsw, int64_t* const* dev_EM, const BlockPlan& plan,
+                               char* work, std::vector<char>* keep_image) {
   hipStream_t stream = hs[idx[0]]->stream;
   const int nl = (int)idx.size();
-  std::vector<BatchLattice> lat(nl);
+  std::vector<BlockLattice> lat(nl);
+  std::vector<BlockTask> tasks;
+  int launches = 0, threads = 0;
+  size_t lds = 0;
+  bool finalize = false;
+  // the longest strips first, so that none starts late
+  std::vector<int> order(nl);
+  std::iota(order.begin(), order.end(), 0);
+  std::stable_sort(order.begin(), order.end(), [&](int a, int b) {
+    return plan.shapes[a].step_s > plan.shapes[b].step_s;
+  });
   for (int j = 0; j < nl; ++j) {
     const int i = idx[j];
-    std::memset(&lat[j], 0, sizeof(BatchLattice));
-    lat[j].ta = targs[i];
-    lat[j].ta.t = (uint32_t)hs[i]->sweep;
-    lat[j].ta.perturb = debug_perturb_seed();
-    lat[j].EM = dev_EM ? dev_EM[i] : nullptr;
-    lat[j].nsweeps = nsw ? nsw[i] : n;
+    lat[j] = block_lattice(hs[i], plan.shapes[j], nsw ? nsw[i] : n, plan.all_single,
+                           dev_EM ? dev_EM[i] : nullptr);
+    launches = std::max(launches, (int)lat[j].launches);
+    threads = std::max(threads, (int)lat[j].threads);
+    lds = std::max(lds, plan.shapes[j].lds);
+    finalize = finalize || (lat[j].strips > 1 && lat[j].EM != nullptr);
   }
-  std::vector<BatchWG> wgs(plan.packs.size());
-  std::vector<BatchItem> items;
-  for (size_t b = 0; b < plan.packs.size(); ++b) {
-    wgs[b].first_item = (int32_t)items.size();
-    wgs[b].n_items = (int32_t)plan.packs[b].size();
-    for (int j : plan.packs[b]) items.push_back(BatchItem{j, 0});
-  }
-  const PackedLayout pl = packed_layout(nl, items.size(), wgs.size());
-  if (pl.bytes > work_bytes)
-    return fail(ISING_ENOMEM, "batched sweeps: work buffer of %zu bytes < %zu needed", work_bytes,
-                pl.bytes);
+  for (int j : order)
+    for (int32_t s = 0; s < lat[j].strips; ++s) tasks.push_back(BlockTask{j, s});
+  const BlockLayout bl = block_layout(nl, tasks.size());
   std::vector<char> local;
   std::vector<char>& img = keep_image ? *keep_image : local;
-  img.assign(pl.bytes, 0);
-  std::memcpy(img.data() + pl.off_lat, lat.data(), nl * sizeof(BatchLattice));
-  std::memcpy(img.data() + pl.off_items, items.data(), items.size() * sizeof(BatchItem));
-  std::memcpy(img.data() + pl.off_wgs, wgs.data(), wgs.size() * sizeof(BatchWG));
+  img.assign(bl.bytes, 0);
+  std::memcpy(img.data(), lat.data(), nl * sizeof(BlockLattice));
+  std::memcpy(img.data() + bl.off_tasks, tasks.data(), tasks.size() * sizeof(BlockTask));
   hipError_t e = hipMemcpyAsync(work, img.data(), img.size(), hipMemcpyHostToDevice, stream);
   if (e != hipSuccess) return hip_fail(e, "batched sweeps: table upload");
-  BatchArgs a;
-  a.lat = (const BatchLattice*)(work + pl.off_lat);
-  a.items = (const BatchItem*)(work + pl.off_items);
-  a.wgs = (const BatchWG*)(work + pl.off_wgs);
-  a.n = n;
-  e = launch_batch(stream, a, (int)wgs.size());
+  const BlockLattice* tab = (const BlockLattice*)work;
+  for (int j = 0; j < launches && e == hipSuccess; ++j)
+    e = launch_block_many(stream, tab, (const BlockTask*)(work + bl.off_tasks), (int)tasks.size(),
+                          threads, lds, j);
+  if (e == hipSuccess && finalize) e = launch_block_finalize_many(stream, tab, nl);
   // the host image must outlive the upload: wait before it goes, unless the
   // caller keeps it
   if (e == hipSuccess && !keep_image) e = hipStreamSynchronize(stream);
-  if (e != hipSuccess) return hip_fail(e, "batched sweeps: packed launch");
+  if (e != hipSuccess) return hip_fail(e, "batched sweeps: block launch");
   return ISING_OK;
 }
 
@@ -332,7 +334,7 @@ static void classify(ising_lattice* const* hs, int32_t count, const BatchOptions
       const int64_t tiles1 = ((hs[i]->L + TR1 - 1) / TR1) * ta.segs;
       int rpw = 1;
       for (int r = 2; r <= opt.rpw_max; r *= 2) {
-        if (tiles1 < 128 * (int64_t)r || (r * TR1 + 2) * (ta.TW + 2) > kTileLdsMaxWords) break;
+        if (tiles1 < 128 * (int64_t)r || (r * TR1 + 2) * (ta.TW + 2) > kTileMaxWords) break;
         rpw = r;
       }
       ta.RPW = rpw;
@@ -359,7 +361,7 @@ static size_t work_bytes_for(ising_lattice* const* hs, const std::vector<int>& t
   size_t ntiles = 0;
   for (int i : tiled) ntiles += (size_t)fused_tiles(hs[i]->plane_words, targs[i].RPW);
   const size_t nl = tiled.size();
-  return std::max(fused_layout(nl, ntiles).bytes, packed_layout(nl, nl, nl).bytes);
+  return std::max(fused_layout(nl, ntiles).bytes, block_layout(nl, nl).bytes);
 }
 
 size_t batch_work_bytes(ising_lattice* const* hs, int32_t count, const BatchOptions& opt) {
@@ -373,7 +375,7 @@ size_t batch_work_share(int64_t L) {
   const int64_t plane_words = L * words_per_row(L);
   const size_t fused = sizeof(FusedLattice) +
                        (size_t)fused_tiles(plane_words, 1) * (sizeof(FusedTile) + 64);
-  const size_t packed = sizeof(BatchLattice) + sizeof(BatchItem) + sizeof(BatchWG);
+  const size_t packed = sizeof(BlockLattice) + sizeof(BlockTask);
   return std::max(fused, packed);
 }
 
@@ -393,6 +395,51 @@ ising_status batch_sweeps(ising_lattice* const* hs, int32_t count, int64_t n,
                   "batched sweeps: needs a 256-byte aligned work buffer of %zu bytes (got %zu)",
                   need, work ? work_bytes : (size_t)0);
   }
+  // Blocks for the whole batch, where the caller leaves the form open, every
+  // lattice can take them and the model has them ahead of a launch per colour
+  // step.  (Beside a lattice that cannot, the small ones ride along in its
+  // launches.)  Their tables may need more than the work buffer holds: then
+  // the other forms run.
+  if (opt.force_form < 0 && work && ((uintptr_t)work & 255) == 0) {
+    std::vector<int> all(count);
+    std::iota(all.begin(), all.end(), 0);
+    std::vector<int64_t> Ls;
+    double sites = 0;
+    for (int i = 0; i < count; ++i) {
+      if (!(hs[i]->L <= kBlockMaxL && (hs[i]->spare || block_fits_single(hs[i]->L)))) break;
+      Ls.push_back(hs[i]->L);
+      sites += (double)hs[i]->L * hs[i]->L;
+    }
+    if ((int)Ls.size() == count && sites <= kBlockMaxSites) {
+      const BlockPlan plan = plan_blocks(Ls, std::min(n, kBlockPlanN), device_cus(device));
+      bool ok = !plan.shapes.empty() && plan.sweep_s < launch_per_step_seconds(sites) &&
+                block_layout(count, plan.tasks).bytes <= work_bytes;
+      for (int i = 0; i < count && ok; ++i) ok = plan.shapes[i].strips == 1 || hs[i]->spare;
+      if (ok) {
+        if (form_out) *form_out = plan.all_single ? 1 : 0;
+        return run_blocks(hs, all, n, nsw, dev_EM, plan, (char*)work, opt.keep_image);
+      }
+    }
+  }
+  const int cus = device_cus(device);
+  bool packed = false;
+  BatchPlan plan;
+  if (!tiled.empty()) {
+    if (cus <= 0) return fail(ISING_EDEVICE, "batched sweeps: no device properties");
+    std::vector<int64_t> tiles;
+    for (int i : tiled) tiles.push_back(tile_cost(targs[i].tiles, targs[i].RPW));
+    plan = plan_batch(tiles, cus, opt.model);
+    packed = plan.packed;
+    if (opt.force_form == 0) packed = false;
+    if (opt.force_form == 1) packed = true;
+    if (form_out) *form_out = packed ? 1 : 0;
+  }
+  if (packed) {
+    // one workgroup each; lattices that do not fit one run by themselves
+    std::vector<int> fits;
+    for (int i : tiled) (block_fits_single(hs[i]->L) ? fits : other).push_back(i);
+    tiled.swap(fits);
+  }
   for (int i : other) {
     // the plain path reads the handle's counter: advance a copy of it
     ising_lattice tmp = *hs[i];
@@ -404,18 +451,12 @@ ising_status batch_sweeps(ising_lattice* const* hs, int32_t count, int64_t n,
     hipError_t e = hipStreamSynchronize(hs[0]->stream);
     return e == hipSuccess ? ISING_OK : hip_fail(e, "batched sweeps: synchronize");
   }
-  const int cus = cu_count(state_for(device), device);
-  if (cus <= 0) return fail(ISING_EDEVICE, "batched sweeps: no device properties");
-  std::vector<int64_t> tiles;
-  for (int i : tiled) tiles.push_back(tile_cost(targs[i].tiles, targs[i].RPW));
-  const BatchPlan plan = plan_batch(tiles, cus, opt.model);
-  bool packed = plan.packed;
-  if (opt.force_form == 0) packed = false;
-  if (opt.force_form == 1) packed = true;
-  if (form_out) *form_out = packed ? 1 : 0;
-  if (packed)
-    return run_packed(hs, tiled, targs, n, nsw, dev_EM, plan, (char*)work, work_bytes,
-                      opt.keep_image);
+  if (packed) {
+    BlockPlan singles;
+    singles.all_single = true;
+    for (int i : tiled) singles.shapes.push_back(block_shape_single(hs[i]->L));
+    return run_blocks(hs, tiled, n, nsw, dev_EM, singles, (char*)work, opt.keep_image);
+  }
   // the fused grid walks actual tiles; size it for them
   int64_t ntiles = 0;
   for (int i : tiled) ntiles += targs[i].tiles;

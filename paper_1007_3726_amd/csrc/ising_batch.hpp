@@ -65,4 +65,23 @@ ising_status batch_sweeps(ising_lattice* const* hs, int32_t count, int64_t n,
                           const int64_t* nsw, int64_t* const* dev_EM, const BatchOptions& opt,
                           void* work, size_t work_bytes, int* form_out);
 
+// Several sweeps per launch (ising_block.hip).
+BlockShape block_shape_single(int64_t L);
+bool block_fits_single(int64_t L);
+// Model: seconds per sweep of lattices with `sites` sites in all when every
+// colour step is a launch.
+double launch_per_step_seconds(double sites);
+BlockPlan plan_blocks(const std::vector<int64_t>& Ls, int64_t n, int cus);
+// One lattice's entry for n sweeps; one_launch: a single strip runs them all
+// in its first launch, else as many per launch as the shape's.
+BlockLattice block_lattice(const ising_lattice* h, const BlockShape& s, int64_t n,
+                           bool one_launch, int64_t* EM);
+ising_status enqueue_block_sweeps(ising_lattice* h, const BlockShape& s, int64_t n,
+                                  int64_t* dev_EM);
+hipError_t launch_block_many(hipStream_t st, const BlockLattice* tab, const BlockTask* tasks,
+                             int ntasks, int threads, size_t lds, int j);
+hipError_t launch_block_finalize_many(hipStream_t st, const BlockLattice* tab, int nlat);
+// Compute units of a device (cached), 0 if it has no properties.
+int device_cus(int device);
+
 }  // namespace ising

@@ -1,0 +1,589 @@
+// Several sweeps per launch on rows held in LDS.
+//
+// A lone lattice of up to a few thousand squared, or a batch of them, has
+// too little work per colour step for a launch of its own: a launch costs
+// 5 us whatever it does (the launch itself, the loads, one lane's chain of
+// sixteen Philox blocks), 512^2 has 0.05 us of arithmetic in it.
+// Here a workgroup takes a strip of rows of one lattice with H = 2 K halo
+// rows above and below into LDS, runs K sweeps on them with block barriers
+// between the colour steps, and writes its own rows back.  Each colour step
+// the rows that are still valid shrink by one at either end (their outer
+// neighbours were not updated), so after 2 K steps exactly the strip's own
+// rows are left: the halo rows are computed twice (by this strip and by the
+// one that owns them) with the same uniforms, which is what the launches
+// saved pay for.  Strips read one copy of the planes and write another, so
+// no workgroup waits for another one.  A lattice of one strip needs no
+// halo: its rows wrap and all n sweeps run in one launch.
+//
+// The unit of work is a 32-bit half of a word: its eight Philox blocks are
+// split over ls = 1, 2, 4 or 8 adjacent lanes, so that few rows still make
+// enough waves for the compute unit's four SIMDs.  Every lane of a half
+// decides its own sites and the flips are OR-ed over the half's lanes (DPP
+// within eight lanes).
+//
+// E/M: counted over the strip's own rows after each colour-1 step, summed
+// per wave, then in LDS; a single strip writes (E, M) itself, several strips
+// leave partials that the next launch (or launch_block_finalize after the
+// last) reduces.
+//
+// Bound by the instructions of one workgroup's steps (halves computed in
+// halos included) plus 5 us per launch.  Measured, us per sweep with the
+// (E, M) series, a launch per colour step (or the LDS kernel that this one
+// replaced) before: 64^2 4.29 -> 0.95, 512^2 10.3 -> 2.5, 1002^2 16.6 -> 4.2,
+// 4096^2 11.7 -> 10.4; 24 lattices of 8^2 to 64^2 8.95 -> 1.12.
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+
+#include "ising_batch.hpp"
+#include "ising_block.hpp"
+#include "ising_runtime.hpp"
+
+#if defined(__HIP_DEVICE_COMPILE__)
+#define ISING_CONSTANT_AS __attribute__((address_space(4)))
+#else
+#define ISING_CONSTANT_AS
+#endif
+
+namespace ising {
+namespace {
+
+constexpr int kMaxWaves = 16;  // of one workgroup
+constexpr int kEmSlots = 32;   // sweeps whose counts are kept in LDS at a time
+
+// Sweeps done before launch j of m that share n sweeps.
+__device__ __forceinline__ int64_t sweeps_before(int64_t n, int64_t j, int64_t m) {
+  const int64_t each = n / m, more = n - each * m;  // the first `more` launches take one more
+  return each * j + (j < more ? j : more);
+}
+
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ uint32_t dpp(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, ROWS == 0xf);
+}
+
+// OR over groups of LS adjacent lanes, in every lane.
+template <int LS>
+__device__ __forceinline__ uint32_t lanes_or(uint32_t v) {
+  if (LS >= 2) v |= dpp<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+  if (LS >= 4) v |= dpp<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+  if (LS >= 8) v |= dpp<0x141>(v);  // row_half_mirror
+  return v;
+}
+
+// Sum over the wave, in lane 63.
+__device__ __forceinline__ uint32_t wave_total(uint32_t v) {
+  v += dpp<0x111>(v);
+  v += dpp<0x112>(v);
+  v += dpp<0x114>(v);
+  v += dpp<0x118>(v);
+  v += dpp<0x142, 0xa>(v);
+  v += dpp<0x143, 0xc>(v);
+  return v;
+}
+
+// How a half's uniforms are drawn: rows of whole Philox blocks (L % 8 == 0)
+// with the plain compares or the cut, or rows that start anywhere in a block.
+enum { kCompare = 0, kCut = 1, kAnyRow = 2 };
+
+// Random planes of this lane's 32 / LS sites of a half, at their places in
+// the half (bits of other lanes' sites mean nothing).  `at`: colour-local
+// index of the lane's first site, over 4 unless MODE is kAnyRow.
+template <int LS, int MODE>
+__device__ __forceinline__ void half_planes(uint32_t at, int sub, uint32_t k0, uint32_t k1,
+                                            uint32_t t, uint32_t ctr3, uint32_t t4, uint32_t t8,
+                                            uint32_t cut_x, uint64_t cut_c, uint32_t& a, uint32_t& b) {
+  constexpr int NB = 8 / LS;
+  a = b = 0;
+  if (MODE == kCut) {
+    uint32_t acc[4] = {0, 0, 0, 0};
+    cut_blocks<true, 0, NB - 1, false>(acc, (uint64_t)kM0 * at, 0, 16, k0, k1, t, ctr3, cut_x, cut_c);
+    cut_planes(acc, a, b);
+  } else if (MODE == kCompare) {
+#pragma unroll
+    for (int q = NB - 1; q >= 0; --q) {
+      uint32_t x0 = at + (uint32_t)q, x1 = 0, x2 = t, x3 = ctr3;
+      philox4x32_10(x0, x1, x2, x3, k0, k1);
+      shift_in4(a, b, x0, x1, x2, x3, t4, t8);
+    }
+  } else {
+    // NB + 1 blocks cover the sites; the first block's r lowest outputs
+    // belong to the sites before
+    const uint32_t g = at >> 2, r = at & 3u;
+    for (int q = NB; q >= 1; --q) {
+      uint32_t x0 = g + (uint32_t)q, x1 = 0, x2 = t, x3 = ctr3;
+      philox4x32_10(x0, x1, x2, x3, k0, k1);
+      shift_in4(a, b, x0, x1, x2, x3, t4, t8);
+    }
+    uint32_t x0 = g, x1 = 0, x2 = t, x3 = ctr3, a0 = 0, b0 = 0;
+    philox4x32_10(x0, x1, x2, x3, k0, k1);
+    shift_in4(a0, b0, x0, x1, x2, x3, t4, t8);
+    a = (a << (4u - r)) | (a0 >> r);
+    b = (b << (4u - r)) | (b0 >> r);
+  }
+  if (LS > 1) {
+    a <<= 4 * NB * sub;
+    b <<= 4 * NB * sub;
+  }
+}
+
+// The counts of `cnt` sweeps leave the LDS slots (one (anti, up) pair per
+// wave and sweep): the first of them is sweep k0 of the launch (first sweep
+// s0 of the lattice's series).
+template <typename Lat>
+__device__ __forceinline__ void drain_counts(const Lat& L, uint2* counts, int strip, int j,
+                                             int64_t s0, int k0, int cnt) {
+  for (int i = threadIdx.x; i < cnt; i += L.threads) {
+    uint32_t anti = 0, up = 0;
+    for (int w = 0; w < (L.threads >> 6); ++w) {
+      anti += counts[i * kMaxWaves + w].x;
+      up += counts[i * kMaxWaves + w].y;
+      counts[i * kMaxWaves + w] = make_uint2(0, 0);
+    }
+    if (L.strips == 1) {
+      const int64_t N = (int64_t)L.L * L.L;
+      L.EM[2 * (s0 + k0 + i)] = 2 * (int64_t)anti - 2 * N;
+      L.EM[2 * (s0 + k0 + i) + 1] = 2 * (int64_t)up - N;
+    } else {
+      uint32_t* p = L.part + 2 * (((size_t)(j & 1) * kBlockMaxK + k0 + i) * L.strips + strip);
+      p[0] = anti;
+      p[1] = up;
+    }
+  }
+}
+
+// (anti, up) added to a 64-bit LDS word, nothing returned, complete on return
+// (a block barrier follows).  Written out: the compiler's atomic add first
+// sums over the lanes, one readlane at a time.
+__device__ __forceinline__ void lds_add(uint2* slot, uint32_t anti, uint32_t up) {
+  const uint32_t addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint2*)slot;
+  const uint64_t v = ((uint64_t)up << 32) | anti;
+  asm volatile("ds_add_u64 %0, %1\n\ts_waitcnt lgkmcnt(0)" : : "v"(addr), "v"(v) : "memory");
+}
+
+// K sweeps of the strip's R rows in LDS: local row r is global row y0 + r
+// (mod L); rows H .. H + own - 1 are the strip's own.  A colour step's time
+// is mostly a wave's chain of instructions, so lanes without work take the
+// last row's and only their stores are left out (whole waves without work
+// skip it), and with ONE (a single strip, one row per lane) everything but
+// the uniforms and the spins is loop-invariant.
+template <int LS, int MODE, bool ONE, typename Lat>
+__device__ __forceinline__ void block_steps(const Lat& L, uint32_t* lds, uint2* counts, int strip,
+                                            int j, int R, int H, int own, int y0, int64_t s0,
+                                            int K) {
+  constexpr int NB = 8 / LS;
+  // few lanes count: they add in LDS; many: the wave sums first
+  constexpr bool kAddCounts = LS >= 4;
+  const bool wrap = ONE || L.strips == 1;
+  const bool em = L.EM != nullptr;
+  const int per = L.nh * LS, stride = 2 * L.W, pass = L.pass;
+  int r0 = (int)threadIdx.x / per;
+  const int hw = ((int)threadIdx.x - r0 * per) / LS, sub = (int)threadIdx.x % LS;
+  const bool first_lane = sub == 0;
+  if (r0 >= pass) r0 = 1 << 24;  // a lane of no row
+  const bool last = hw == L.nh - 1;
+  uint32_t mine = last && L.nbl < 32 ? (1u << L.nbl) - 1u : ~0u;  // valid sites of this lane
+  const uint32_t valid = mine;
+  if (LS > 1) mine &= ((1u << (4 * NB & 31)) - 1u) << (4 * NB * sub);
+  // horizontal partners: bit 31 of the half to the left (the last valid bit
+  // of the row for the first half), bit 0 of the half to the right
+  const int hl = hw > 0 ? hw - 1 : L.nh - 1, hr = last ? 0 : hw + 1;
+  const int shl = hw > 0 ? 31 : L.nbl - 1, shr = last ? L.nbl - 1 : 31;
+  const uint32_t rowlen = MODE == kAnyRow ? (uint32_t)L.half : (uint32_t)L.half >> 2;
+  const uint32_t col = MODE == kAnyRow ? 32u * hw + 4u * NB * sub : 8u * hw + NB * (uint32_t)sub;
+  const uint32_t k0 = L.k0, k1 = L.k1, sid4 = L.sid4, t4 = L.t4, t8 = L.t8, cut_x = L.cut.x;
+  const uint64_t cut_c = L.cut.c;
+  const int side = L.L, wave = (int)threadIdx.x >> 6;
+  const int plane = R * stride, lastrow = plane - stride;
+  for (int k = 0; k < K; ++k) {
+    const uint32_t t = L.t + (uint32_t)(s0 + k);
+    uint2* const slot = &counts[(k & (kEmSlots - 1)) * kMaxWaves + wave];
+    uint32_t anti = 0, up = 0;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const int s = 2 * k + c;
+      const int ra = wrap ? 0 : 1 + s, rb = wrap ? R - 1 : R - 2 - s;
+      uint32_t* const self = lds + (c ? plane : 0);
+      const uint32_t* const other = lds + (c ? 0 : plane);
+      auto rows = [&](int want) {
+        const int r = want < rb ? want : rb;
+        int y = y0 + r;
+        y = y >= side ? y - side : y;
+        const int at = (int)__umul24((uint32_t)r, (uint32_t)stride);
+        const int am = wrap && r == 0 ? lastrow : at - stride;
+        const int ap = wrap && at == lastrow ? 0 : at + stride;
+        const uint32_t left = (uint32_t)(((y + c) & 1) - 1);  // all ones: the partner is left
+        const uint32_t s_old = self[at + hw], n0 = other[at + hw];
+        const uint32_t n2 = other[am + hw], n3 = other[ap + hw];
+        const uint32_t sd = other[at + (left ? hl : hr)];
+        uint32_t a, b;
+        half_planes<LS, MODE>((uint32_t)y * rowlen + col, sub, k0, k1, t, sid4 | (uint32_t)c, t4,
+                              t8, cut_x, cut_c, a, b);
+        const uint32_t n1 = bfi(left, (n0 << 1) | (sd >> shl), (n0 >> 1) | (sd << shr));
+        uint32_t f = MODE == kCut ? flip_half_cut(s_old, n0, n1, n2, n3, a, b)
+                                  : flip_half(s_old, n0, n1, n2, n3, a, b);
+        f = lanes_or<LS>(f & mine);
+        const uint32_t s_new = s_old ^ f;
+        const bool store = first_lane && want <= rb;
+        if (store) self[at + hw] = s_new;
+        if (c == 1 && em) {
+          const bool on = store && (uint32_t)(r - H) < (uint32_t)own;
+          const uint32_t da = __popc(s_new ^ n0) + __popc((s_new ^ n1) & valid) +
+                              __popc(s_new ^ n2) + __popc(s_new ^ n3);
+          const uint32_t du = __popc(s_new) + __popc(n0);
+          anti += on ? da : 0u;
+          up += on ? du : 0u;
+        }
+      };
+      if (ONE) {
+        rows(r0);
+      } else {
+        for (int base = ra; base <= rb; base += pass) {
+          // the wave's first lane has its smallest row
+          if (__builtin_amdgcn_readfirstlane(base + r0) <= rb) rows(base + r0);
+        }
+      }
+      if (c == 1 && em) {
+        if (kAddCounts) {
+          if (first_lane) lds_add(slot, anti, up);
+        } else {
+          const uint32_t wa = wave_total(anti), wu = wave_total(up);
+          if ((threadIdx.x & 63) == 63) *slot = make_uint2(wa, wu);
+        }
+      }
+      perturb_wave(L.perturb, (uint32_t)s);
+      __syncthreads();
+    }
+    // the slots are written again only after the next colour-0 barrier
+    if (em && ((k & (kEmSlots - 1)) == kEmSlots - 1 || k == K - 1))
+      drain_counts(L, counts, strip, j, s0, k & ~(kEmSlots - 1), (k & (kEmSlots - 1)) + 1);
+  }
+}
+
+// One wave's share of the partials of one sweep (kBlockMaxStrips / 64 strips
+// per lane).
+struct Parts {
+  uint2 v[kBlockMaxStrips / 64];
+};
+
+// Loads the partials of sweep k of launch j (kept apart from their sum, so
+// that the loads can be issued long before it).
+template <typename Lat>
+__device__ __forceinline__ Parts load_parts(const Lat& L, int j, int k) {
+  const uint2* p = (const uint2*)L.part + ((size_t)(j & 1) * kBlockMaxK + k) * L.strips;
+  Parts q;
+#pragma unroll
+  for (int i = 0; i < kBlockMaxStrips / 64; ++i) {
+    const int at = (int)(threadIdx.x & 63) + 64 * i;
+    q.v[i] = at < L.strips ? p[at] : make_uint2(0, 0);
+  }
+  return q;
+}
+
+// (E, M) of sweep s of the lattice's series (sums below 2^32: L <= kBlockMaxL).
+template <typename Lat>
+__device__ __forceinline__ void store_parts(const Lat& L, const Parts& q, int64_t s) {
+  uint32_t anti = 0, up = 0;
+#pragma unroll
+  for (int i = 0; i < kBlockMaxStrips / 64; ++i) {
+    anti += q.v[i].x;
+    up += q.v[i].y;
+  }
+  anti = wave_total(anti);
+  up = wave_total(up);
+  if ((threadIdx.x & 63) == 63) {
+    const int64_t N = (int64_t)L.L * L.L;
+    L.EM[2 * s] = 2 * (int64_t)anti - 2 * N;
+    L.EM[2 * s + 1] = 2 * (int64_t)up - N;
+  }
+}
+
+// The sweeps first, first + step, ... of the last launch, by one wave.
+template <typename Lat>
+__device__ __forceinline__ void reduce_last(const Lat& L, int first, int step) {
+  const int j = L.launches - 1;
+  const int64_t s0 = sweeps_before(L.n, j, L.launches);
+  for (int k = first; s0 + k < L.n; k += step) store_parts(L, load_parts(L, j, k), s0 + k);
+}
+
+// Lat: BlockLattice, as a kernel argument or in a table (constant memory).
+template <typename Lat>
+__device__ __forceinline__ void block_run(const Lat& L, int strip, int j, uint32_t* lds) {
+  __shared__ uint2 counts[kEmSlots * kMaxWaves];
+  // waves beyond this lattice's share of the workgroup leave at once
+  if ((int)(threadIdx.x & ~63u) >= L.threads || j >= L.launches) return;
+  const bool wrap = L.strips == 1;
+  const int64_t s0 = sweeps_before(L.n, j, L.launches);
+  const int K = (int)(sweeps_before(L.n, j + 1, L.launches) - s0);
+  const int H = wrap ? 0 : 2 * K;
+  const int row0 = strip * L.rows;
+  const int own = L.L - row0 < L.rows ? L.L - row0 : L.rows;
+  const int R = own + 2 * H;
+  int y0 = row0 - H;
+  y0 = y0 < 0 ? y0 + L.L : y0;
+  const int W = L.W, all = L.L * W;
+  const uint64_t* src = L.buf[wrap ? 0 : (j & 1)];
+  uint64_t* dst = L.buf[wrap ? 0 : ((j + 1) & 1)];
+  uint64_t* lds64 = (uint64_t*)lds;
+  for (int i = threadIdx.x; i < kEmSlots * kMaxWaves; i += L.threads) counts[i] = make_uint2(0, 0);
+  for (int i = threadIdx.x; i < R * W; i += L.threads) {
+    int p = y0 * W + i;
+    p = p >= all ? p - all : p;
+    lds64[i] = src[p];
+    lds64[R * W + i] = src[all + p];
+  }
+  // the first strips reduce the E/M partials of the launch before, one sweep
+  // each (a launch has fewer sweeps than strips); loaded now, summed at the end
+  const int64_t sp = wrap || j == 0 ? s0 : sweeps_before(L.n, j - 1, L.launches);
+  const bool reduce = L.EM != nullptr && sp + strip < s0 && threadIdx.x < 64;
+  Parts parts;
+  if (reduce) parts = load_parts(L, j - 1, strip);
+  __syncthreads();
+#define ISING_BLOCK(LS, MODE)                                                           \
+  do {                                                                                  \
+    if (wrap && R <= L.pass)                                                            \
+      block_steps<LS, MODE, true>(L, lds, counts, strip, j, R, H, own, y0, s0, K);      \
+    else                                                                                \
+      block_steps<LS, MODE, false>(L, lds, counts, strip, j, R, H, own, y0, s0, K);     \
+  } while (0)
+  if ((L.half & 3) != 0) {
+    switch (L.ls) {
+      case 8: ISING_BLOCK(8, kAnyRow); break;
+      case 4: ISING_BLOCK(4, kAnyRow); break;
+      case 2: ISING_BLOCK(2, kAnyRow); break;
+      default: ISING_BLOCK(1, kAnyRow); break;
+    }
+  } else if (L.ls >= 4) {
+    // one or two blocks per lane: the transpose of the cut costs as much as
+    // the compares it saves
+    if (L.ls == 8)
+      ISING_BLOCK(8, kCompare);
+    else
+      ISING_BLOCK(4, kCompare);
+  } else if (L.cut.x != 0) {
+    if (L.ls == 2)
+      ISING_BLOCK(2, kCut);
+    else
+      ISING_BLOCK(1, kCut);
+  } else {
+    if (L.ls == 2)
+      ISING_BLOCK(2, kCompare);
+    else
+      ISING_BLOCK(1, kCompare);
+  }
+#undef ISING_BLOCK
+  for (int i = threadIdx.x; i < own * W; i += L.threads) {
+    __hip_atomic_store(&dst[row0 * W + i], lds64[H * W + i], __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&dst[all + row0 * W + i], lds64[(R + H) * W + i], __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (reduce) store_parts(L, parts, sp + strip);
+}
+
+__global__ __launch_bounds__(1024) void k_block(BlockLattice L, int j) {
+  extern __shared__ uint64_t block_lds[];
+  block_run(L, blockIdx.x, j, (uint32_t*)block_lds);
+}
+
+// The same for a table of lattices; tasks are (lattice, strip).
+__global__ __launch_bounds__(1024) void k_block_many(
+    const BlockLattice* tab, const BlockTask* tasks, int j) {
+  extern __shared__ uint64_t block_lds[];
+  const BlockTask task = ((const BlockTask ISING_CONSTANT_AS*)tasks)[blockIdx.x];
+  block_run(((const BlockLattice ISING_CONSTANT_AS*)tab)[task.lattice], task.strip, j,
+            (uint32_t*)block_lds);
+}
+
+// (E, M) of every lattice's last launch.
+__global__ __launch_bounds__(64) void k_block_finalize(BlockLattice L) {
+  reduce_last(L, blockIdx.x, gridDim.x);
+}
+
+__global__ __launch_bounds__(64) void k_block_finalize_many(const BlockLattice* tab) {
+  const auto& L = ((const BlockLattice ISING_CONSTANT_AS*)tab)[blockIdx.x];
+  if (L.EM != nullptr && L.strips > 1) reduce_last(L, 0, 1);
+}
+
+}  // namespace
+
+// ---------------------------------------------------------------------
+// Host side
+// ---------------------------------------------------------------------
+
+// Measured costs of the model below, in cycles and seconds.
+constexpr double kClock = 2.4e9;
+constexpr double kLaunch = 5e-6;   // a launch: gap, loads, stores
+constexpr double kBarrier = 1e-7;  // of a colour step
+
+// Instructions of one wave's pass with ls lanes per half.
+static double pass_instructions(int ls) {
+  return ls == 8 ? 115 : ls == 4 ? 180 : ls == 2 ? 290 : 460;
+}
+
+static double waves_of(double halves, int ls) { return std::ceil(halves * ls / 64); }
+
+// Seconds of one colour step of a workgroup that updates `halves` halves with
+// the compute unit to itself: the busiest SIMD issues its waves' instructions
+// one per four cycles, and a lone wave no more than one per six.
+static double step_seconds(double halves, int ls) {
+  const double issue = std::ceil(waves_of(halves, ls) / 4) * 4, alone = 6;
+  return std::max(issue, alone) * pass_instructions(ls) / kClock + kBarrier;
+}
+
+// Strips of `rows` rows with K sweeps per launch.
+static BlockShape shape_of(int64_t L, int64_t rows, int K) {
+  BlockShape s;
+  const int64_t W = words_per_row(L), nh = (L / 2 + 31) / 32;
+  const bool single = rows >= L;
+  s.rows = (int32_t)std::min(rows, L);
+  s.strips = single ? 1 : (int32_t)((L + rows - 1) / rows);
+  s.sweeps = K;
+  const int64_t R = single ? L : s.rows + 4 * (int64_t)K;       // rows in LDS
+  const int64_t mean = single ? L : s.rows + 2 * (int64_t)K;    // rows of a mean step
+  // More lanes per half make more waves of fewer instructions, but more
+  // instructions in all (115 / 256, 290 / 1024, 460 / 2048 sites): as many
+  // lanes as shorten the step.  Measured, us per sweep with 1, 2, 4, 8 lanes:
+  // 64^2 1.71, 1.09, 0.92, 0.93; 128^2 1.90, 1.92, 2.17, 3.69; 512^2 in strips
+  // of 2 rows, 8 sweeps 2.84, 2.66, 2.79, 3.07; 2048^2 in strips of 8 rows, 4
+  // sweeps 5.34, 5.57, 6.23, 7.96.
+  s.ls = 1;
+  for (int ls = 2; ls <= 8; ls *= 2)
+    if (nh * ls <= 1024 && step_seconds((double)(mean * nh), ls) <
+                               step_seconds((double)(mean * nh), s.ls))
+      s.ls = ls;
+  const int64_t per = nh * s.ls;
+  s.pass = (int32_t)std::max<int64_t>(1, std::min<int64_t>(R, 1024 / per));
+  s.threads = (int32_t)((s.pass * per + 63) / 64 * 64);
+  s.lds = (size_t)(2 * R * W) * sizeof(uint64_t);
+  s.step_s = step_seconds((double)(mean * nh), s.ls);
+  s.issue_s = waves_of((double)(mean * nh), s.ls) * pass_instructions(s.ls) / kClock;
+  return s;
+}
+
+// Measured: 3.5 us per launch (gap, ramp and drain), at least 2 us for one
+// word's uniforms, and beyond that the updates at the tiles' rate (2900
+// updates/ns); 4096^2 11.7 us per sweep, the 56-lattice grid 82 us.
+double launch_per_step_seconds(double sites) {
+  return 2 * (3.5e-6 + std::max(2e-6, 0.5 * sites / 2.9e12));
+}
+
+BlockShape block_shape_single(int64_t L) { return shape_of(L, L, 1); }
+
+// Both planes of a single strip fit one workgroup's LDS.
+bool block_fits_single(int64_t L) {
+  return L <= kBlockMaxL && 2 * (int64_t)plane_bytes(L) <= kBlockMaxLds;
+}
+
+// The cheapest cut of a set of lattices by the model: sweeps per launch K,
+// and strips of about `target` halves per mean colour step, so that the
+// strips of all lattices are about equal.  A lattice that fits one workgroup
+// takes a single strip where a strip would be as large.
+BlockPlan plan_blocks(const std::vector<int64_t>& Ls, int64_t n, int cus) {
+  BlockPlan best;
+  bool all_single = true;
+  for (int64_t L : Ls) all_single = all_single && block_fits_single(L);
+  auto consider = [&](int K, int64_t target, bool singles) {
+    BlockPlan p;
+    double longest = 0, issue = 0;
+    int64_t strips = 0;
+    for (int64_t L : Ls) {
+      const int64_t nh = (L / 2 + 31) / 32;
+      // L rows at most in LDS, kBlockMaxStrips strips at most
+      int64_t rows = std::max<int64_t>(target / nh - 2 * (int64_t)K, 1);
+      rows = std::max(rows, (L + kBlockMaxStrips - 1) / kBlockMaxStrips);
+      const bool single = block_fits_single(L) && (singles || rows + 2 * K >= L);
+      if (single)
+        rows = L;
+      else if (rows + 4 * (int64_t)K > L)
+        return;
+      const BlockShape s = shape_of(L, rows, K);
+      if (s.lds > (size_t)kBlockMaxLds || (!single && K > s.strips)) return;
+      p.shapes.push_back(s);
+      longest = std::max(longest, s.step_s);
+      issue += s.issue_s * s.strips;
+      strips += s.strips;
+    }
+    if (strips > kBlockMaxTasks + (int64_t)Ls.size()) return;
+    p.sweeps = K;
+    p.tasks = strips;
+    const double step = std::max(longest, issue / cus);
+    p.sweep_s = 2 * step + (singles ? 0.0 : kLaunch / K);
+    if (best.shapes.empty() || p.sweep_s < best.sweep_s) best = p;
+  };
+  if (all_single) consider(1, 0, true);
+  if (n >= 2)
+    for (int K : {1, 2, 3, 4, 6, 8, 12})
+      if (K <= (n + 1) / 2)
+        for (int64_t target = 32; target <= 4096; target += target / 4)
+          consider(K, target, false);
+  best.all_single = !best.shapes.empty();
+  for (const BlockShape& s : best.shapes) best.all_single = best.all_single && s.strips == 1;
+  return best;
+}
+
+BlockLattice block_lattice(const ising_lattice* h, const BlockShape& s, int64_t n,
+                           bool one_launch, int64_t* EM) {
+  BlockLattice b;
+  std::memset(&b, 0, sizeof(b));
+  b.buf[0] = h->planes;
+  b.buf[1] = h->spare;
+  b.L = (int32_t)h->L;
+  b.W = h->g.W;
+  b.half = (int32_t)h->g.half;
+  b.nh = (b.half + 31) / 32;
+  b.nbl = b.half - 32 * (b.nh - 1);
+  b.rows = s.rows;
+  b.strips = s.strips;
+  b.ls = s.ls;
+  b.pass = s.pass;
+  b.threads = s.threads;
+  if (s.strips == 1) {
+    const int64_t per = one_launch ? (int64_t)1 << 20 : s.sweeps;
+    b.launches = (int32_t)std::max<int64_t>((n + per - 1) / per, 1);
+  } else {
+    // an even number of launches leaves the result in the lattice's own planes
+    b.launches = (int32_t)(2 * ((n + 2 * s.sweeps - 1) / (2 * s.sweeps)));
+  }
+  b.k0 = (uint32_t)h->seed;
+  b.k1 = (uint32_t)(h->seed >> 32);
+  b.sid4 = h->stream_id << 2;
+  b.t = (uint32_t)h->sweep;
+  b.t4 = h->t4;
+  b.t8 = h->t8;
+  b.cut = h->cut;
+  b.n = n;
+  b.EM = EM;
+  b.part = (uint32_t*)h->part[0];
+  b.perturb = debug_perturb_seed();
+  return b;
+}
+
+ising_status enqueue_block_sweeps(ising_lattice* h, const BlockShape& s, int64_t n,
+                                  int64_t* dev_EM) {
+  const BlockLattice b = block_lattice(h, s, n, true, dev_EM);
+  for (int32_t j = 0; j < b.launches; ++j) {
+    hipLaunchKernelGGL(k_block, dim3(s.strips), dim3(s.threads), s.lds, h->stream, b, j);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "block sweep launch");
+  }
+  if (s.strips > 1 && dev_EM) {
+    hipLaunchKernelGGL(k_block_finalize, dim3(s.sweeps), dim3(64), 0, h->stream, b);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "block E/M finalisation launch");
+  }
+  return ISING_OK;
+}
+
+hipError_t launch_block_many(hipStream_t st, const BlockLattice* tab, const BlockTask* tasks,
+                             int ntasks, int threads, size_t lds, int j) {
+  hipLaunchKernelGGL(k_block_many, dim3(ntasks), dim3(threads), lds, st, tab, tasks, j);
+  return hipGetLastError();
+}
+
+hipError_t launch_block_finalize_many(hipStream_t st, const BlockLattice* tab, int nlat) {
+  hipLaunchKernelGGL(k_block_finalize_many, dim3(nlat), dim3(64), 0, st, tab);
+  return hipGetLastError();
+}
+
+}  // namespace ising

@@ -26,12 +26,9 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
 
 // One Philox4x32-10 block.  Each round is two 32x32->64 multiplies
 // (v_mad_u64_u32, full rate on gfx950) and two three-input XORs; the key
-// schedule is wave-uniform.  With BUMP_SALU the round keys are bumped by a
-// scalar add in every round instead of being precomputed, which keeps 18
-// SGPRs free (the scalar adds issue beside the vector work).  philox_from
-// takes the first round's product kM0 * x0 from the caller, who gets the
-// products of consecutive blocks from one another without forming x0.
-template <bool BUMP_SALU = false>
+// schedule is wave-uniform.  philox_from takes the first round's product
+// kM0 * x0 from the caller, who gets the products of consecutive blocks from
+// one another without forming x0.
 __device__ __forceinline__ void philox_from(uint64_t p0, uint32_t& x0, uint32_t& x1,
                                             uint32_t& x2, uint32_t& x3, uint32_t k0,
                                             uint32_t k1) {
@@ -45,22 +42,14 @@ __device__ __forceinline__ void philox_from(uint64_t p0, uint32_t& x0, uint32_t&
     x3 = (uint32_t)p0;
     x0 = y0;
     x2 = y2;
-    if (BUMP_SALU) {
-      if (r < 9) {
-        asm("s_add_u32 %0, %0, %1" : "+s"(k0) : "i"(kW0) : "scc");
-        asm("s_add_u32 %0, %0, %1" : "+s"(k1) : "i"(kW1) : "scc");
-      }
-    } else {
-      k0 += kW0;
-      k1 += kW1;
-    }
+    k0 += kW0;
+    k1 += kW1;
   }
 }
 
-template <bool BUMP_SALU = false>
 __device__ __forceinline__ void philox4x32_10(uint32_t& x0, uint32_t& x1, uint32_t& x2,
                                               uint32_t& x3, uint32_t k0, uint32_t k1) {
-  philox_from<BUMP_SALU>((uint64_t)kM0 * x0, x0, x1, x2, x3, k0, k1);
+  philox_from((uint64_t)kM0 * x0, x0, x1, x2, x3, k0, k1);
 }
 
 // Geometry of one lattice as the kernels see it.
@@ -290,7 +279,7 @@ __device__ __forceinline__ void shift_in4(uint32_t& a4, uint32_t& a8, uint32_t x
 // 4q..4q+3.  Blocks are visited from q = 15 down to 0 so that the shift-in
 // order leaves block 0 in the lowest bits; with FULL every word has 16
 // blocks, otherwise blocks q >= nq are skipped and their bits stay zero.
-template <bool FULL, bool BUMP_SALU = false>
+template <bool FULL>
 __device__ __forceinline__ void masks_shift(uint32_t lo, uint32_t hi, int nq, uint32_t k0,
                                             uint32_t k1, uint32_t t, uint32_t ctr3, uint32_t t4,
                                             uint32_t t8, uint64_t& r4, uint64_t& r8) {
@@ -299,7 +288,7 @@ __device__ __forceinline__ void masks_shift(uint32_t lo, uint32_t hi, int nq, ui
   for (int q = 15; q >= 0; --q) {
     if (FULL || q < nq) {
       uint32_t x0 = lo + (uint32_t)q, x1 = hi, x2 = t, x3 = ctr3;
-      philox4x32_10<BUMP_SALU>(x0, x1, x2, x3, k0, k1);
+      philox4x32_10(x0, x1, x2, x3, k0, k1);
       if (q >= 8)
         shift_in4(a4_hi, a8_hi, x0, x1, x2, x3, t4, t8);
       else
@@ -348,37 +337,44 @@ __device__ __forceinline__ void cut_planes(const uint32_t (&acc)[4], uint32_t& u
 
 // first + kM0 Q for a block number Q of a word: one multiply-add with an
 // inline constant (written out: the compiler would keep the sixteen 64-bit
-// constants kM0 Q in VGPRs, which spill).  `after`, the accumulators of the
-// block before, are operands so that the blocks stay one after the other: the
-// other resident waves hide a block's latency, and interleaved blocks would
-// need more than the 64 VGPRs of 8 waves per SIMD.
-template <int Q>
+// constants kM0 Q in VGPRs, which spill).  With SERIAL, `after`, the
+// accumulators of the block before, are operands, so that the blocks stay one
+// after the other: where 8 waves per SIMD hide a block's latency, interleaved
+// blocks would only need more than their 64 VGPRs.
+template <int Q, bool SERIAL>
 __device__ __forceinline__ uint64_t block_product(uint64_t first, uint32_t (&after)[4]) {
   uint64_t p = first, carry;
-  if (Q == 0)
-    asm("" : "+v"(p), "+v"(after[0]), "+v"(after[1]), "+v"(after[2]), "+v"(after[3]));
-  else
-    asm("v_mad_u64_u32 %0, %1, %6, %7, %8"
-        : "=v"(p), "=s"(carry), "+v"(after[0]), "+v"(after[1]), "+v"(after[2]), "+v"(after[3])
+  if (SERIAL) {
+    if (Q == 0)
+      asm("" : "+v"(p), "+v"(after[0]), "+v"(after[1]), "+v"(after[2]), "+v"(after[3]));
+    else
+      asm("v_mad_u64_u32 %0, %1, %6, %7, %8"
+          : "=v"(p), "=s"(carry), "+v"(after[0]), "+v"(after[1]), "+v"(after[2]), "+v"(after[3])
+          : "n"(Q), "s"(kM0), "v"(first));
+  } else if (Q > 0) {
+    asm("v_mad_u64_u32 %0, %1, %2, %3, %4"
+        : "=v"(p), "=s"(carry)
         : "n"(Q), "s"(kM0), "v"(first));
+  }
   return p;
 }
 
 // Codes of blocks 8 H + B .. 8 H of a word, shifted into acc in that order.
-template <bool FULL, int H, int B>
+template <bool FULL, int H, int B, bool SERIAL>
 __device__ __forceinline__ void cut_blocks(uint32_t (&acc)[4], uint64_t first, uint32_t hi,
                                            int nq, uint32_t k0, uint32_t k1, uint32_t t,
                                            uint32_t ctr3, uint32_t X, uint64_t C) {
   constexpr int Q = 8 * H + B;
   if (FULL || Q < nq) {
     uint32_t x0 = 0, x1 = hi, x2 = t, x3 = ctr3;
-    philox_from(block_product<Q>(first, acc), x0, x1, x2, x3, k0, k1);
+    philox_from(block_product<Q, SERIAL>(first, acc), x0, x1, x2, x3, k0, k1);
     cut_in(acc[0], x0, X, C);
     cut_in(acc[1], x1, X, C);
     cut_in(acc[2], x2, X, C);
     cut_in(acc[3], x3, X, C);
   }
-  if constexpr (B > 0) cut_blocks<FULL, H, B - 1>(acc, first, hi, nq, k0, k1, t, ctr3, X, C);
+  if constexpr (B > 0)
+    cut_blocks<FULL, H, B - 1, SERIAL>(acc, first, hi, nq, k0, k1, t, ctr3, X, C);
 }
 
 // Cut planes of one word (64 sites) whose blocks are lo + q, as masks_shift.
@@ -392,12 +388,12 @@ __device__ __forceinline__ void masks_cut(uint32_t lo, uint32_t hi, int nq, uint
   uint32_t u[2], l[2];
   {
     uint32_t acc[4] = {0, 0, 0, 0};
-    cut_blocks<FULL, 1, 7>(acc, first, hi, nq, k0, k1, t, ctr3, X, C);
+    cut_blocks<FULL, 1, 7, true>(acc, first, hi, nq, k0, k1, t, ctr3, X, C);
     cut_planes(acc, u[1], l[1]);
   }
   {
     uint32_t acc[4] = {0, 0, 0, 0};
-    cut_blocks<FULL, 0, 7>(acc, first, hi, nq, k0, k1, t, ctr3, X, C);
+    cut_blocks<FULL, 0, 7, true>(acc, first, hi, nq, k0, k1, t, ctr3, X, C);
     cut_planes(acc, u[0], l[0]);
   }
   up = ((uint64_t)u[1] << 32) | u[0];
@@ -499,6 +495,22 @@ __device__ __forceinline__ void masks_lcg(uint32_t& z, uint32_t c, uint32_t e, u
   }
   r4 = ((uint64_t)a4_hi << 32) | a4_lo;
   r8 = ((uint64_t)a8_hi << 32) | a8_lo;
+}
+
+// Test hook: with a nonzero seed, this wave pauses for a pseudo-random
+// 0 .. 31 short sleeps (hash of seed, call site, block and wave) before a
+// block barrier.  Waves then reach the barrier in a shuffled order; a
+// result that depends on that order (a missing barrier or fence) changes.
+__device__ __forceinline__ void perturb_wave(uint32_t seed, uint32_t site) {
+  if (seed == 0) return;
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t h = seed ^ (site * 0x9E3779B9u) ^ (blockIdx.x * 0x85EBCA77u) ^ (wave * 0xC2B2AE3Du);
+  h ^= h >> 16;
+  h *= 0x7FEB352Du;
+  h ^= h >> 15;
+  h *= 0x846CA68Bu;
+  h ^= h >> 16;
+  for (uint32_t i = 0, n = h & 31u; i < n; ++i) __builtin_amdgcn_s_sleep(8);
 }
 
 }  // namespace ising

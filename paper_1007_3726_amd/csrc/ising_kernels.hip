@@ -1,8 +1,7 @@
 // HIP kernels (gfx950) of the checkerboard Metropolis sweep on
 // colour-packed uint64 words: initialisation, half-sweeps with the energy
-// and magnetisation reduction fused into the colour-1 pass, a measurement
-// pass, and a single-workgroup LDS-resident multi-sweep kernel for small
-// lattices.
+// and magnetisation reduction fused into the colour-1 pass, and a measurement
+// pass.  (Several sweeps per launch: ising_block.hip.)
 #include <algorithm>
 
 #include "ising_kernels.hpp"
@@ -56,22 +55,6 @@ __device__ __forceinline__ void block_sum2(uint32_t a32, uint32_t p32, uint64_t*
     a = sa;
     p = sp;
   }
-}
-
-// Test hook: with a nonzero seed, this wave pauses for a pseudo-random
-// 0 .. 31 short sleeps (hash of seed, call site, block and wave) before a
-// block barrier.  Waves then reach the barrier in a shuffled order; a
-// result that depends on that order (a missing barrier or fence) changes.
-__device__ __forceinline__ void perturb_wave(uint32_t seed, uint32_t site) {
-  if (seed == 0) return;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  uint32_t h = seed ^ (site * 0x9E3779B9u) ^ (blockIdx.x * 0x85EBCA77u) ^ (wave * 0xC2B2AE3Du);
-  h ^= h >> 16;
-  h *= 0x7FEB352Du;
-  h ^= h >> 15;
-  h *= 0x846CA68Bu;
-  h ^= h >> 16;
-  for (uint32_t i = 0, n = h & 31u; i < n; ++i) __builtin_amdgcn_s_sleep(8);
 }
 
 // Contribution of one updated colour-1 word to the bond and spin counts:
@@ -199,158 +182,18 @@ __global__ void k_set_em(int64_t* EM, int64_t e, int64_t m) {
 }
 
 // ---------------------------------------------------------------------
-// Small lattices: one workgroup keeps both planes in LDS and runs all n
-// sweeps, with a block barrier between the colour steps (the barrier plays
-// the role of the paper's second kernel launch, section 5.2).
-// ---------------------------------------------------------------------
-template <bool ALIGNED>
-__global__ __launch_bounds__(1024) void k_small_sweeps(SmallArgs a) {
-  extern __shared__ uint64_t lds[];
-  __shared__ uint64_t red[2 * 16];
-  const Geom g = a.g;
-  const int64_t pw = a.plane_words;
-  for (int64_t i = threadIdx.x; i < 2 * pw; i += blockDim.x) lds[i] = a.planes[i];
-  __syncthreads();
-  for (int64_t k = 0; k < a.n; ++k) {
-    const uint32_t t = a.t0 + (uint32_t)k;
-    uint32_t anti = 0, up = 0;
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      uint64_t* self = lds + (c ? pw : 0);
-      const uint64_t* other = lds + (c ? 0 : pw);
-      for (int64_t idx = threadIdx.x; idx < pw; idx += blockDim.x) {
-        const int64_t y = idx / g.W;
-        const int32_t w = (int32_t)(idx - y * g.W);
-        const uint64_t valid = (w == g.W - 1) ? low_mask(g.nb_last) : ~0ull;
-        const uint64_t s = self[idx];
-        const Nbr n = gather(other, g, c, y, w);
-        uint64_t r4, r8;
-        if (ALIGNED)
-          masks_aligned(g, y, w, a.k0, a.k1, t, a.sid4 | c, a.t4, a.t8, r4, r8);
-        else
-          masks_generic(g, y, w, a.k0, a.k1, t, a.sid4 | c, a.t4, a.t8, r4, r8);
-        const uint64_t s_new = s ^ (flip_mask(s, n, r4, r8) & valid);
-        self[idx] = s_new;
-        if (c == 1) count_word(s_new, n, valid, anti, up);
-      }
-      perturb_wave(a.perturb, (uint32_t)(2 * k + c));
-      __syncthreads();
-    }
-    if (a.EM) {
-      uint64_t sa, sp;
-      block_sum2(anti, up, red, sa, sp);
-      if (threadIdx.x == 0) {
-        a.EM[2 * k] = 2 * (int64_t)sa - 2 * g.L * g.L;
-        a.EM[2 * k + 1] = 2 * (int64_t)sp - g.L * g.L;
-      }
-      __syncthreads();
-    }
-  }
-  for (int64_t i = threadIdx.x; i < 2 * pw; i += blockDim.x) a.planes[i] = lds[i];
-}
-
-// Masks of one word split over LPW lanes (L % 8 == 0): lane `sub` of the
-// word computes Philox blocks q = sub*NQ .. sub*NQ + NQ - 1 (NQ = 16 / LPW)
-// of the word's 16 (blocks past a partial last word are computed too and
-// later masked by `valid`), shifts their decisions into one 32-bit pair of
-// accumulators and places them at bit 4*NQ*sub; the OR over the word's
-// lanes (adjacent lanes, one DPP row) gives every lane the full masks.
-template <int LPW>
-__device__ __forceinline__ void masks_split(uint32_t lo, int sub, uint32_t k0, uint32_t k1,
-                                            uint32_t t, uint32_t ctr3, uint32_t t4, uint32_t t8,
-                                            uint64_t& r4, uint64_t& r8) {
-  constexpr int NQ = 16 / LPW;
-  uint32_t a4 = 0, a8 = 0;
-  const uint32_t q0 = (uint32_t)(sub * NQ);
-#pragma unroll
-  for (int k = NQ - 1; k >= 0; --k) {
-    uint32_t x0 = lo + q0 + (uint32_t)k, x1 = 0, x2 = t, x3 = ctr3;
-    philox4x32_10<false>(x0, x1, x2, x3, k0, k1);
-    shift_in4(a4, a8, x0, x1, x2, x3, t4, t8);
-  }
-  const int sh = 4 * NQ * sub;
-  r4 = (uint64_t)a4 << sh;
-  r8 = (uint64_t)a8 << sh;
-#pragma unroll
-  for (int off = 1; off < LPW; off <<= 1) {
-    r4 |= __shfl_xor(r4, off, 64);
-    r8 |= __shfl_xor(r8, off, 64);
-  }
-}
-
-// All n sweeps of one lattice resident in LDS (one workgroup, L % 8 == 0,
-// every Philox block index below 2^32), LPW lanes per word: for the
-// smallest lattices the per-colour-step latency is the cost, and spreading
-// a word's 16 Philox blocks over 2-16 lanes divides it.  Lane 0 of a word
-// stores the update and counts E/M.
-template <int LPW>
-__global__ __launch_bounds__(1024) void k_small_sweeps_split(SmallArgs a) {
-  extern __shared__ uint64_t lds[];
-  __shared__ uint64_t red[32];
-  const Geom g = a.g;
-  const int64_t pw = a.plane_words;
-  for (int64_t i = threadIdx.x; i < 2 * pw; i += blockDim.x) lds[i] = a.planes[i];
-  __syncthreads();
-  const int sub = threadIdx.x % LPW;
-  for (int64_t k = 0; k < a.n; ++k) {
-    const uint32_t t = a.t0 + (uint32_t)k;
-    uint32_t anti = 0, up = 0;
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      uint64_t* self = lds + (c ? pw : 0);
-      const uint64_t* other = lds + (c ? 0 : pw);
-      // the loop bound is uniform per word group, so the shuffles see
-      // every lane of a word
-      for (int64_t base = 0; base < pw * LPW; base += blockDim.x) {
-        const int64_t idx = (base + threadIdx.x) / LPW;
-        const bool ok = idx < pw;
-        const int64_t ic = ok ? idx : pw - 1;
-        const int64_t y = ic / g.W;
-        const int32_t w = (int32_t)(ic - y * g.W);
-        const uint32_t lo = (uint32_t)y * (uint32_t)g.L8 + 16u * (uint32_t)w;
-        uint64_t r4, r8;
-        masks_split<LPW>(lo, sub, a.k0, a.k1, t, a.sid4 | c, a.t4, a.t8, r4, r8);
-        if (ok && sub == 0) {
-          const uint64_t valid = (w == g.W - 1) ? low_mask(g.nb_last) : ~0ull;
-          const uint64_t s = self[ic];
-          const Nbr n = gather(other, g, c, y, w);
-          const uint64_t s_new = s ^ (flip_mask(s, n, r4, r8) & valid);
-          self[ic] = s_new;
-          if (c == 1) count_word(s_new, n, valid, anti, up);
-        }
-      }
-      perturb_wave(a.perturb, (uint32_t)(2 * k + c));
-      __syncthreads();
-    }
-    if (a.EM) {
-      uint64_t sa, sp;
-      block_sum2(anti, up, red, sa, sp);
-      if (threadIdx.x == 0) {
-        a.EM[2 * k] = 2 * (int64_t)sa - 2 * g.L * g.L;
-        a.EM[2 * k + 1] = 2 * (int64_t)sp - g.L * g.L;
-      }
-      __syncthreads();
-    }
-  }
-  for (int64_t i = threadIdx.x; i < 2 * pw; i += blockDim.x) a.planes[i] = lds[i];
-}
-
-// ---------------------------------------------------------------------
 // Tiled half-sweep for L % 8 == 0.
 //
 // Work unit: a tile of TR = 4*R*RPW rows x TW words of colour C.  A wave
 // processes RPW row groups of the tile one after the other, one word per
 // lane per group (W >= kWideMinWords: a row group is one row of a 64-word segment;
-// W < 64: a row group is R = floor(64/W) whole rows).  The plain and fused
-// kernels read each word's four neighbour words directly
-// (process_tile_direct: the rows that neighbouring lanes and tiles share
-// hit in L1/L2, the loads are issued before the Philox stretch and used
-// after it, and the waves of a workgroup never wait for each other).  The
-// packed persistent kernel stages the other colour's rows y0-1 .. y0+TR
-// and words w0-1 .. w0+TW (periodic) in LDS instead (process_tile), since
-// it needs block barriers between colour steps anyway.  The Philox block index of word
-// (y, w) is y*L/8 + 16*w + q; its high word is 0 (hi_mode 0) or uniform
-// over the wave's row (hi_mode 1), so only the low word varies per lane.
+// W < 64: a row group is R = floor(64/W) whole rows).  Each lane reads its
+// word's four neighbour words directly (the rows that neighbouring lanes and
+// tiles share hit in L1/L2, the loads are issued before the Philox stretch
+// and used after it, and the waves of a workgroup never wait for each other).
+// The Philox block index of word (y, w) is y*L/8 + 16*w + q; its high word is
+// 0 (hi_mode 0) or uniform over the wave's row (hi_mode 1), so only the low
+// word varies per lane.
 //
 // Workgroups walk the tiles with a grid stride; logical block numbers are
 // grouped by XCD (hardware dispatches block b to XCD b mod 8), so that
@@ -394,13 +237,12 @@ __device__ __forceinline__ int64_t wrap_row(int64_t y, int64_t L) {
   return y < 0 ? y + L : (y >= L ? y - L : y);
 }
 
-// Lane-to-word and lane-to-staging maps of one lattice's tile shape.
+// Lane-to-word map of one lattice's tile shape.
 struct TileLane {
   bool wide;
-  int TR, SW, SR;    // rows per tile, staged row width, staged rows
-  int r_off, w_l;    // position of this lane inside a row group
+  int TR;          // rows per tile
+  int r_off, w_l;  // position of this lane inside a row group
   bool lane_ok;
-  int st_r, st_c, P; // staging: row/column of this lane within a pass of P rows
 };
 
 template <int WIDEM>
@@ -408,114 +250,23 @@ __device__ __forceinline__ TileLane tile_lane(const TileArgs& a) {
   TileLane t;
   // WIDEM: 0 / 1 fixes the row-group shape at compile time, 2 reads it from
   // the arguments (W >= kWideMinWords).
-  const bool WIDE = WIDEM == 2 ? (a.g.W >= kWideMinWords) : (WIDEM == 1);
-  t.wide = WIDE;
+  t.wide = WIDEM == 2 ? (a.g.W >= kWideMinWords) : (WIDEM == 1);
   const int lane = threadIdx.x & 63;
-  const int TW = a.TW, R = a.R;
-  t.TR = 4 * R * a.RPW;
-  t.SW = TW + 2;
-  t.SR = t.TR + 2;
-  if (WIDE) {
+  t.TR = 4 * a.R * a.RPW;
+  if (t.wide) {
     t.r_off = 0;
     t.w_l = lane;
     t.lane_ok = true;
-    // a wave pass loads one staged row of 66 words (lanes 0 and 1 also
-    // load words 64 and 65)
-    t.P = 1;
-    t.st_r = 0;
-    t.st_c = lane;
   } else {
-    t.r_off = lane / TW;
-    t.w_l = lane - t.r_off * TW;
-    t.lane_ok = t.r_off < R;
-    t.P = 64 / t.SW;
-    t.st_r = lane / t.SW;
-    t.st_c = lane - t.st_r * t.SW;
-    if (t.st_r >= t.P) t.st_r = -1;
-    // hosts only build narrow shapes with SW <= 64; never let a pass be empty
-    if (t.P < 1) t.P = 1;
+    t.r_off = lane / a.TW;
+    t.w_l = lane - t.r_off * a.TW;
+    t.lane_ok = t.r_off < a.R;
   }
   return t;
 }
 
-// One tile of one colour step: stage the other colour's rows in LDS, then
-// update this tile's words (RPW row groups per wave).  `colour` and `em`
-// are uniform.  Contains two block barriers.
-template <bool FULL, int WIDEM, bool BUMP_SALU = false>
-__device__ __forceinline__ void process_tile(const TileArgs& a, const TileLane& tl, int colour,
-                                             bool em, int64_t tidx, uint64_t* tile,
-                                             uint32_t& anti, uint32_t& up) {
-  const Geom& g = a.g;
-  const bool WIDE = WIDEM == 2 ? tl.wide : (WIDEM == 1);
-  uint64_t* __restrict__ self = a.planes + (colour ? a.plane_words : 0);
-  const uint64_t* __restrict__ other = a.planes + (colour ? 0 : a.plane_words);
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int R = a.R, RPW = a.RPW, TR = tl.TR, SW = tl.SW, SR = tl.SR;
-  const int r_off = tl.r_off, w_l = tl.w_l, st_r = tl.st_r, st_c = tl.st_c, P = tl.P;
-  const bool lane_ok = tl.lane_ok;
-  const uint32_t ctr3 = a.sid4 | (uint32_t)colour;
-  const int64_t y0 = (tidx / a.segs) * TR;
-  const int32_t w0 = WIDE ? (int32_t)(tidx % a.segs) * 64 : 0;
-  for (int rr0 = wave * P; rr0 < SR; rr0 += 4 * P) {
-    const int rr = rr0 + st_r;
-    if (st_r >= 0 && rr < SR) {
-      // a tile may span more than L rows when L is small: full modulo
-      int64_t yy = (y0 - 1 + rr) % g.L;
-      yy = yy < 0 ? yy + g.L : yy;
-      const int32_t ww = (int32_t)wrap_row(w0 - 1 + st_c, g.W);
-      tile[rr * SW + st_c] = other[yy * g.W + ww];
-      if (WIDE && lane < 2) {
-        const int32_t w2 = (int32_t)wrap_row(w0 + 63 + lane, g.W);
-        tile[rr * SW + 64 + lane] = other[yy * g.W + w2];
-      }
-    }
-  }
-  perturb_wave(a.perturb, (uint32_t)(4 * tidx + 2 * colour));
-  __syncthreads();
-  for (int j = 0; j < RPW; ++j) {
-    const int r_l = (wave * RPW + j) * R + r_off;
-    const int64_t y = y0 + r_l;
-    const int32_t w = w0 + w_l;
-    if (!(lane_ok && y < g.L && w < g.W)) continue;
-    const uint64_t s = self[y * g.W + w];
-    const int base = (r_l + 1) * SW + (w_l + 1);
-    Nbr n;
-    n.n0 = tile[base];
-    n.n2 = tile[base - SW];
-    n.n3 = tile[base + SW];
-    if (((y + colour) & 1) == 0) {
-      const uint64_t left = tile[base - 1];
-      n.n1 = (n.n0 << 1) | ((w > 0) ? (left >> 63) : ((left >> (g.nb_last - 1)) & 1ull));
-    } else {
-      const uint64_t right = tile[base + 1];
-      n.n1 = (w < g.W - 1) ? ((n.n0 >> 1) | (right << 63))
-                           : ((n.n0 >> 1) | ((right & 1ull) << (g.nb_last - 1)));
-    }
-    uint32_t lo, hi;
-    if (a.hi_mode == 0) {
-      lo = (uint32_t)y * (uint32_t)g.L8 + 16u * (uint32_t)w;
-      hi = 0;
-    } else {
-      const uint64_t gy =
-          (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)y) * (uint64_t)g.L8;
-      hi = (uint32_t)(gy >> 32);
-      lo = (uint32_t)gy + 16u * (uint32_t)w;
-    }
-    const int nq = (FULL || w < g.W - 1) ? 16 : (g.nb_last >> 2);
-    uint64_t r4, r8;
-    masks_shift<FULL, BUMP_SALU>(lo, hi, nq, a.k0, a.k1, a.t, ctr3, a.t4, a.t8, r4, r8);
-    const uint64_t valid = (FULL || w < g.W - 1) ? ~0ull : low_mask(g.nb_last);
-    const uint64_t s_new = s ^ (flip_mask(s, n, r4, r8) & valid);
-    self[y * g.W + w] = s_new;
-    if (colour == 1 && em) count_word(s_new, n, valid, anti, up);
-  }
-  perturb_wave(a.perturb, (uint32_t)(4 * tidx + 2 * colour + 1));
-  __syncthreads();
-}
-
-// The same tile of one colour step without LDS staging: each lane loads its
-// own word and its four neighbour words straight from memory (the rows
+// One tile of one colour step: each lane loads its own word and its four
+// neighbour words straight from memory (the rows
 // shared by neighbouring lanes hit in L1/L2), issues the loads before the
 // Philox stretch and uses them after it.  No block barrier: the four waves
 // of a workgroup work independently.  Spin words are stored write-through.
@@ -1127,10 +878,6 @@ __global__ __launch_bounds__(256) void k_finalize_em(const uint64_t* part, int n
 // bond, up spin) counts to part[(k & 1)][tile]; colour 0 of the next sweep
 // (or k_fused_finalize after the last one) reduces them per lattice into
 // (E, M) = (2A - 2N, 2P - N).
-//
-// k_batch: a persistent kernel for batches of small lattices that each fit
-// one workgroup: every workgroup runs its packed list of lattices for all
-// n sweeps with block barriers only (one launch in total).
 // ---------------------------------------------------------------------
 __device__ __forceinline__ void finalize_tiles(const FusedArgs& f, uint32_t k, uint64_t* red64) {
   // per-wave partials: 4 slots of (anti, up) per tile; lattice totals need
@@ -1223,48 +970,6 @@ __global__ __launch_bounds__(256) void k_fused_finalize(FusedArgs f) {
 
 __global__ void k_advance(uint32_t* kbase, uint32_t by) {
   if (blockIdx.x == 0 && threadIdx.x == 0) *kbase += by;
-}
-
-__device__ __forceinline__ void run_packed_lattice(const BatchLattice& Lt, int64_t n,
-                                                   uint64_t* tile, uint64_t* red) {
-  TileArgs a = Lt.ta;
-  const uint32_t t0 = Lt.ta.t;
-  const bool em = Lt.EM != nullptr;
-  const TileLane tl = tile_lane<2>(a);
-  const int64_t nk = Lt.nsweeps < n ? Lt.nsweeps : n;
-  for (int64_t k = 0; k < nk; ++k) {
-    a.t = t0 + (uint32_t)k;
-    uint32_t anti = 0, up = 0;
-    for (int64_t tidx = 0; tidx < a.tiles; ++tidx)
-      process_tile<false, 2, true>(a, tl, 0, false, tidx, tile, anti, up);
-    for (int64_t tidx = 0; tidx < a.tiles; ++tidx)
-      process_tile<false, 2, true>(a, tl, 1, em, tidx, tile, anti, up);
-    if (em) {
-      uint64_t sa, sp;
-      block_sum2(anti, up, red, sa, sp);
-      if (threadIdx.x == 0) {
-        Lt.EM[2 * k] = 2 * (int64_t)sa - 2 * a.g.L * a.g.L;
-        Lt.EM[2 * k + 1] = 2 * (int64_t)sp - a.g.L * a.g.L;
-      }
-      __syncthreads();
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) void k_batch(BatchArgs b) {
-  __shared__ uint64_t tile[kTileLdsMaxWords];
-  __shared__ uint64_t red[8];
-  // The tables are read-only for the whole launch: read them through the
-  // constant address space so that they land in SGPRs (scalar loads).
-  typedef const BatchWG ISING_CONSTANT_AS* WgPtr;
-  typedef const BatchItem ISING_CONSTANT_AS* ItemPtr;
-  typedef const BatchLattice ISING_CONSTANT_AS* LatPtr;
-  const BatchWG wg = ((WgPtr)b.wgs)[blockIdx.x];
-  for (int it = 0; it < wg.n_items; ++it) {
-    const BatchItem item = ((ItemPtr)b.items)[wg.first_item + it];
-    const BatchLattice Lt = ((LatPtr)b.lat)[item.lattice];
-    run_packed_lattice(Lt, b.n, tile, red);
-  }
 }
 
 hipError_t launch_fused(hipStream_t st, int colour, const FusedArgs& f, int blocks) {
@@ -1418,10 +1123,6 @@ hipError_t launch_finalize_em(hipStream_t st, const uint64_t* part, int blocks, 
   hipLaunchKernelGGL(k_finalize_em, dim3(1), dim3(256), 0, st, part, blocks, L, EM);
   return hipGetLastError();
 }
-hipError_t launch_batch(hipStream_t st, const BatchArgs& a, int blocks) {
-  hipLaunchKernelGGL(k_batch, dim3(blocks), dim3(256), 0, st, a);
-  return hipGetLastError();
-}
 
 hipError_t launch_init(hipStream_t st, uint64_t* planes, const Geom& g, uint32_t k0, uint32_t k1,
                        uint32_t sid4, int init, int blocks) {
@@ -1461,34 +1162,6 @@ hipError_t launch_measure(hipStream_t st, const uint64_t* planes, const Geom& g,
                           int64_t plane_words, int64_t* EM, int blocks) {
   hipLaunchKernelGGL(k_set_em, dim3(1), dim3(64), 0, st, EM, -2 * g.L * g.L, -g.L * g.L);
   hipLaunchKernelGGL(k_measure, dim3(blocks), dim3(256), 0, st, planes, g, plane_words, EM);
-  return hipGetLastError();
-}
-
-hipError_t launch_small_sweeps(hipStream_t st, const SmallArgs& a, int threads) {
-  const size_t lds = (size_t)(2 * a.plane_words) * sizeof(uint64_t);
-  const int64_t pw = a.plane_words;
-  if ((a.g.L % 8) == 0 && pw >= 128 && pw <= 512) {
-    // as many lanes per word as one workgroup of <= 1024 threads allows
-    // (measured per sweep: 128^2 6.5 -> 5.2 us, 256^2 9.8 -> 9.3 us; at 64^2,
-    // 16 lanes per word were slower than one, 4.5 against 4.1 us: there the
-    // barriers and the per-sweep E/M reduction cost more than the Philox
-    // stretch)
-    int lpw = 16;
-    while (lpw > 2 && pw * lpw > 1024) lpw >>= 1;
-    const int th = (int)std::min<int64_t>(1024, (pw * lpw + 63) / 64 * 64);
-#define ISING_SPLIT(N) hipLaunchKernelGGL(k_small_sweeps_split<N>, dim3(1), dim3(th), lds, st, a)
-    switch (lpw) {
-      case 16: ISING_SPLIT(16); break;
-      case 8: ISING_SPLIT(8); break;
-      case 4: ISING_SPLIT(4); break;
-      default: ISING_SPLIT(2); break;
-    }
-#undef ISING_SPLIT
-  } else if ((a.g.L % 8) == 0) {
-    hipLaunchKernelGGL(k_small_sweeps<true>, dim3(1), dim3(threads), lds, st, a);
-  } else {
-    hipLaunchKernelGGL(k_small_sweeps<false>, dim3(1), dim3(threads), lds, st, a);
-  }
   return hipGetLastError();
 }
 

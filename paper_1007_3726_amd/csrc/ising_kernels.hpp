@@ -19,24 +19,13 @@ struct SweepArgs {
   int64_t* EM;          // (E, M) of this sweep, or null
 };
 
-struct SmallArgs {
-  uint64_t* planes;
-  int64_t plane_words;
-  Geom g;
-  uint32_t k0, k1, sid4, t0, t4, t8;
-  int64_t n;            // sweeps
-  int64_t* EM;          // n x 2, or null
-  uint32_t perturb;     // test hook: nonzero seeds pauses before block barriers
-};
-
 // Tiled half-sweep (L % 8 == 0): a workgroup of four waves handles a tile
-// of 4*R*RPW rows x TW words of one colour (the packed persistent kernel
-// stages the neighbour rows of the other colour in LDS once per tile, and
-// the tile shape is bounded by that staging area).
-constexpr int kTileLdsMaxWords = 2048;
+// of 4*R*RPW rows x TW words of one colour.  A tile with its neighbour words
+// is bounded by kTileMaxWords, which keeps installed shapes within reach of
+// one workgroup's share of a small grid.
+constexpr int kTileMaxWords = 2048;
 // Rows of at least this many words use the wide tile shape (64-word row
-// segments).  A narrow tile stages whole rows of W + 2 words, and each such
-// row must fit one 64-lane wave pass, so narrow tiles need W <= 62.
+// segments); narrow tiles take whole rows.
 constexpr int kWideMinWords = 63;
 constexpr int kMaxSweepBlocks = 2048;
 
@@ -76,10 +65,6 @@ struct TileArgs {
   const uint64_t* pool;
   uint32_t pool_shift, pool_mask;
   int32_t pool_linear;
-  // test hook of the LDS-staged tiles (packed persistent kernel): a nonzero
-  // seed makes every wave pause a pseudo-random time before each block
-  // barrier, so that a missing barrier shows up as a different result
-  uint32_t perturb;
 };
 
 // Switch tile arguments of a lattice to the flat mapping (see
@@ -125,30 +110,9 @@ struct FusedArgs {
   uint32_t* part;       // 2 slots x ntiles x (anti, up)
 };
 
-struct BatchLattice {
-  TileArgs ta;          // tile shape, key, thresholds; ta.t is the first sweep counter
-  int64_t* EM;          // nsweeps x 2 per-sweep (E, M), or null
-  int64_t nsweeps;      // sweeps this lattice takes in the launch
-};
-struct BatchItem {
-  int32_t lattice;
-  int32_t rank;
-};
-struct BatchWG {
-  int32_t first_item;
-  int32_t n_items;
-};
-struct BatchArgs {
-  const BatchLattice* lat;
-  const BatchItem* items;
-  const BatchWG* wgs;
-  int64_t n;            // sweeps
-};
-
 hipError_t launch_fused(hipStream_t st, int colour, const FusedArgs& f, int blocks);
 hipError_t launch_fused_finalize(hipStream_t st, const FusedArgs& f, int blocks);
 hipError_t launch_advance(hipStream_t st, uint32_t* kbase, uint32_t by);
-hipError_t launch_batch(hipStream_t st, const BatchArgs& a, int blocks);
 
 // One GPU's share of a lattice split into row strips (the per-GPU part of
 // a multi-GPU decomposition): global rows y0 .. y0 + rows - 1 of an L x L
@@ -180,6 +144,5 @@ hipError_t launch_init(hipStream_t st, uint64_t* planes, const Geom& g, uint32_t
 hipError_t launch_half_sweep(hipStream_t st, int colour, const SweepArgs& a, int blocks);
 hipError_t launch_measure(hipStream_t st, const uint64_t* planes, const Geom& g,
                           int64_t plane_words, int64_t* EM, int blocks);
-hipError_t launch_small_sweeps(hipStream_t st, const SmallArgs& a, int threads);
 
 }  // namespace ising

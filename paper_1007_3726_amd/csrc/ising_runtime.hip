@@ -4,6 +4,7 @@
 #include <atomic>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -11,6 +12,7 @@
 #include <vector>
 
 #include "ising.h"
+#include "ising_batch.hpp"
 #include "ising_kernels.hpp"
 #include "ising_runtime.hpp"
 
@@ -111,11 +113,11 @@ int tile_rpw(int64_t L, int want) {
   const int64_t W = words_per_row(L);
   const bool wide = W >= kWideMinWords;
   const int64_t TW = wide ? 64 : W, R = wide ? 1 : 64 / W, segs = wide ? (W + 63) / 64 : 1;
-  if (want > 0 && (4 * R * want + 2) * (TW + 2) <= kTileLdsMaxWords) return want;
+  if (want > 0 && (4 * R * want + 2) * (TW + 2) <= kTileMaxWords) return want;
   for (int rpw = 4; rpw > 1; rpw >>= 1) {
     const int64_t TR = 4 * R * rpw;
     const int64_t tiles = ((L + TR - 1) / TR) * segs;
-    if (tiles >= 2048 && (TR + 2) * (TW + 2) <= kTileLdsMaxWords) return rpw;
+    if (tiles >= 2048 && (TR + 2) * (TW + 2) <= kTileMaxWords) return rpw;
   }
   return 1;
 }
@@ -132,7 +134,7 @@ bool tile_args(const ising_lattice* h, TileArgs* out) {
   a.RPW = tile_rpw(L, h->tune.rpw);
   const int64_t TR = 4 * (int64_t)a.R * a.RPW;
   a.tiles = ((L + TR - 1) / TR) * a.segs;
-  if ((TR + 2) * (a.TW + 2) > kTileLdsMaxWords) return false;
+  if ((TR + 2) * (a.TW + 2) > kTileMaxWords) return false;
   // a narrow staged row (W + 2 words) must fit one 64-lane wave pass
   if (!wide && a.TW + 2 > 64) return false;
   const bool pow2 = (L & (L - 1)) == 0;
@@ -176,6 +178,14 @@ bool strip_args(const ising_lattice* h, TileArgs* out) {
 bool use_small_path(const ising_lattice* h) {
   return h->lcg == nullptr && h->pool == nullptr &&
          2 * h->plane_words * (int64_t)sizeof(uint64_t) <= h->tune.small_lds_bytes;
+}
+
+// Several sweeps per launch: a lattice of its own shape (no installed tile or
+// strip shape) with a spare copy of its planes.  One sweep takes two launches
+// either way.
+bool use_block_path(const ising_lattice* h, int64_t n) {
+  return h->lcg == nullptr && h->pool == nullptr && h->spare != nullptr && n >= 2 &&
+         h->L <= kBlockMaxL && h->tune.form == ISING_FORM_TILE && h->tune.rpw == 0;
 }
 
 // (d, m) of the LCG decision (x + d) < m for threshold t' (ising_device.hpp)
@@ -232,24 +242,18 @@ static ising_status fill_pool(ising_lattice* h) {
 
 ising_status enqueue_sweeps(ising_lattice* h, int64_t n, int64_t* dev_EM) {
   if (n == 0) return ISING_OK;
-  if (use_small_path(h)) {
-    SmallArgs a;
-    a.planes = h->planes;
-    a.plane_words = h->plane_words;
-    a.g = h->g;
-    a.k0 = (uint32_t)h->seed;
-    a.k1 = (uint32_t)(h->seed >> 32);
-    a.sid4 = h->stream_id << 2;
-    a.t0 = (uint32_t)h->sweep;
-    a.t4 = h->t4;
-    a.t8 = h->t8;
-    a.n = n;
-    a.EM = dev_EM;
-    a.perturb = debug_perturb_seed();
-    int threads = (int)std::min<int64_t>(1024, ((h->plane_words + 63) / 64) * 64);
-    hipError_t e = launch_small_sweeps(h->stream, a, threads);
-    if (e != hipSuccess) return hip_fail(e, "small-lattice sweep launch");
-    return ISING_OK;
+  if (use_small_path(h)) return enqueue_block_sweeps(h, block_shape_single(h->L), n, dev_EM);
+  if (use_block_path(h, n)) {
+    // the shape depends on n only below kBlockPlanN sweeps; kept with the handle
+    const int64_t key = std::min(n, kBlockPlanN);
+    if (h->block_n != key) {
+      const BlockPlan plan = plan_blocks({h->L}, key, device_cus(h->device));
+      h->block = plan.shapes.empty() || plan.sweep_s >= launch_per_step_seconds((double)h->L * h->L)
+                     ? BlockShape()
+                     : plan.shapes[0];
+      h->block_n = key;
+    }
+    if (h->block.strips > 0) return enqueue_block_sweeps(h, h->block, n, dev_EM);
   }
   TileArgs ta;
   if (h->pool) return enqueue_pool_sweeps(h, n, dev_EM);
@@ -363,6 +367,7 @@ ising_status ising_create(int64_t L, uint64_t seed, uint32_t stream_id, int32_t 
   h->init = init;
   h->stream = (hipStream_t)hip_stream;
   h->sweep = 0;
+  h->block_n = 0;
   h->beta_set = false;
   hipError_t e = hipGetDevice(&h->device);
   if (e != hipSuccess) {
@@ -383,6 +388,28 @@ ising_status ising_create(int64_t L, uint64_t seed, uint32_t stream_id, int32_t 
 ising_status ising_destroy(ising_t* h) {
   clear_error();
   delete h;
+  return ISING_OK;
+}
+
+size_t ising_spare_bytes(int64_t L) {
+  if (L < 4 || (L & 1) || L > kBlockMaxL) return 0;
+  return 2 * plane_bytes(L);
+}
+
+ising_status ising_set_spare(ising_t* h, void* dev_spare, size_t bytes) {
+  clear_error();
+  if (!h) return fail(ISING_EINVAL, "ising_set_spare: NULL handle");
+  if (!dev_spare) {
+    h->spare = nullptr;
+    return ISING_OK;
+  }
+  const size_t need = ising_spare_bytes(h->L);
+  if (need == 0) return fail(ISING_EINVAL, "ising_set_spare: L=%lld takes none", (long long)h->L);
+  if (((uintptr_t)dev_spare) & 7)
+    return fail(ISING_EINVAL, "ising_set_spare: buffer must be 8-byte aligned");
+  if (bytes < need)
+    return fail(ISING_ENOMEM, "ising_set_spare: %zu bytes < %zu needed", bytes, need);
+  h->spare = (uint64_t*)dev_spare;
   return ISING_OK;
 }
 

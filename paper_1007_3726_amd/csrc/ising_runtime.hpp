@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "ising.h"
+#include "ising_block.hpp"
 #include "ising_kernels.hpp"
 
 namespace ising {
@@ -35,6 +36,7 @@ ising_status fail(ising_status code, const char* fmt, ...);
 ising_status hip_fail(hipError_t e, const char* what);
 void clear_error();
 int64_t words_per_row(int64_t L);
+size_t plane_bytes(int64_t L);
 size_t lattice_bytes(int64_t L);
 Geom make_geom(int64_t L);
 uint32_t metropolis_threshold(double beta, int dE);
@@ -57,6 +59,7 @@ struct ising_lattice {
   uint32_t stream_id;
   int32_t init;
   double beta;
+  uint64_t* spare;      // device: a second copy of the planes (caller's), or null
   uint32_t t4, t8;
   ising::Cut cut;       // three-way cut of (t4, t8)
   uint32_t l4, l8;      // LCG thresholds min(floor(exp(-beta dE) 2^31), 2^31)
@@ -69,6 +72,8 @@ struct ising_lattice {
   hipStream_t stream;
   int device;
   ising::Tuning tune;
+  ising::BlockShape block;  // strips 0: colour steps are launches
+  int64_t block_n;          // the sweeps per call (at most kBlockPlanN) it is for, 0: none yet
 };
 
 namespace ising {

@@ -8,8 +8,8 @@
 //      whole arena is rejected at submission;
 //   2. one batched call advances every active lattice by up to
 //      quantum_sweeps sweeps (fewer for a request that has fewer left), all
-//      lattices together in fused launches or one packed launch, with the
-//      task tables in a region reserved at the end of the arena (1/32 of
+//      lattices together in fused launches, blocks of several sweeps per
+//      launch or one packed launch, with the task tables in a region reserved at the end of the arena (1/32 of
 //      it; every admitted lattice also reserves its share of that region,
 //      so the tables of any active set fit);
 //   3. retirement: finished requests copy their series/spins to the
@@ -96,6 +96,7 @@ struct Job {
   ising_request req;
   State state = State::Queued;
   size_t off = 0, bytes = 0;   // arena slice: lattice then series
+  size_t spare_off = 0, spare_bytes = 0;  // second copy of the planes, if it has one
   size_t share = 0;            // reserved bytes of the task-table region
   ising_lattice* h = nullptr;
   int64_t* dev_series = nullptr;
@@ -163,6 +164,14 @@ ising_status admit(ising_server* s) {
       return st;
     }
     j.h = h;
+    // the second copy of the planes (several sweeps per launch) only while
+    // half the arena stays free, so that it never holds a request back
+    const size_t sb = align256(ising_spare_bytes(j.req.L));
+    if (sb && s->arena.used() + sb <= s->arena_bytes / 2 && s->arena.alloc(sb, &j.spare_off)) {
+      j.spare_bytes = sb;
+      st = ising_set_spare(h, s->arena_base + j.spare_off, sb);
+      if (st != ISING_OK) return st;
+    }
     s->table_used += j.share;
     j.dev_series = (int64_t*)(s->arena_base + off + lb);
     j.state = State::Active;
@@ -275,6 +284,8 @@ ising_status begin_retire(ising_server* s, const std::vector<uint64_t>& done) {
     s->leaving.emplace_back(t, off);
     off += n;
     s->arena.release(j.off, j.bytes);
+    if (j.spare_bytes) s->arena.release(j.spare_off, j.spare_bytes);
+    j.spare_bytes = 0;
     s->table_used -= j.share;
   }
   hipError_t e = hipEventRecord(s->copied, s->stream);

@@ -106,7 +106,13 @@ ising_status ising_autotune(int64_t L, void* dev_buf, size_t dev_bytes, void* hi
   int64_t* dev_EM = nullptr;
   if (dev_bytes >= lat_bytes + 16 * (size_t)em_sweeps)
     dev_EM = (int64_t*)((char*)dev_buf + lat_bytes);
-  st = ising_set_beta(h, 1.0 / 2.269185);
+  // and the size rule's several sweeps per launch, when there is room for a
+  // second copy of the planes behind the series
+  const size_t spare_at = lat_bytes + (16 * (size_t)em_sweeps + 255) / 256 * 256;
+  const size_t spare_bytes = ising_spare_bytes(L);
+  if (spare_bytes && dev_EM && dev_bytes >= spare_at + spare_bytes)
+    st = ising_set_spare(h, (char*)dev_buf + spare_at, spare_bytes);
+  if (st == ISING_OK) st = ising_set_beta(h, 1.0 / 2.269185);
   struct Cand {
     Tuning t;
   };
@@ -114,6 +120,7 @@ ising_status ising_autotune(int64_t L, void* dev_buf, size_t dev_bytes, void* hi
   const int64_t plane_bytes = 2 * h->plane_words * (int64_t)sizeof(uint64_t);
   if (plane_bytes <= 65536)  // LDS-resident
     cands.push_back({Tuning{plane_bytes, 2048, 0, ISING_FORM_TILE}});
+  cands.push_back({Tuning{0, 2048, 0, ISING_FORM_TILE}});  // the size rule
   for (int rpw : {1, 2, 4})
     for (int mb : {512, 1024, 2048}) cands.push_back({Tuning{0, mb, rpw, ISING_FORM_TILE}});
   if (h->g.W >= kWideMinWords)
@@ -129,8 +136,8 @@ ising_status ising_autotune(int64_t L, void* dev_buf, size_t dev_bytes, void* hi
     h->tune = cands[i].t;
     TileArgs ta;
     // skip shapes the tiled layout would not honour
-    if (h->tune.small_lds_bytes == 0 && h->tune.form == ISING_FORM_TILE && tile_args(h, &ta) &&
-        ta.RPW != h->tune.rpw)
+    if (h->tune.small_lds_bytes == 0 && h->tune.form == ISING_FORM_TILE && h->tune.rpw > 0 &&
+        tile_args(h, &ta) && ta.RPW != h->tune.rpw)
       continue;
     h->sweep = 0;
     st = enqueue_sweeps(h, 2, dev_EM);  // warm-up

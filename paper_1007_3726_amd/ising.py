@@ -92,6 +92,8 @@ def lib():
         "ising_version": ([], ctypes.c_char_p),
         "ising_lattice_bytes": ([i64], ctypes.c_size_t),
         "ising_create": ([i64, u64, u32, i32, vp, ctypes.c_size_t, vp, P(vp)], i32),
+        "ising_spare_bytes": ([i64], ctypes.c_size_t),
+        "ising_set_spare": ([vp, vp, ctypes.c_size_t], i32),
         "ising_destroy": ([vp], i32),
         "ising_set_beta": ([vp, ctypes.c_double], i32),
         "ising_get_thresholds": ([vp, P(u32)], i32),
@@ -301,11 +303,16 @@ class Lattice:
         self.L = int(L)
         self.device = torch.device(device)
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
-        self.buf = _dev_alloc(nbytes, self.device)
+        # behind the lattice, a second copy of the planes (several sweeps per launch)
+        nspare = int(lib().ising_spare_bytes(self.L))
+        at = (nbytes + 255) // 256 * 256
+        self.buf = _dev_alloc(at + nspare if nspare else nbytes, self.device)
         h = ctypes.c_void_p()
         check(lib().ising_create(self.L, seed & (2 ** 64 - 1), stream_id, init, self.buf.data_ptr(),
                                  nbytes, _stream_ptr(self.stream), ctypes.byref(h)))
         self.h = h
+        if nspare:
+            check(lib().ising_set_spare(self.h, self.buf.data_ptr() + at, nspare))
         if beta is not None:
             self.set_beta(beta)
 
@@ -420,8 +427,10 @@ def autotune(L: int, trial_sweeps: int = 10, device="cuda", stream=None) -> dict
     import torch
     dev = torch.device(device)
     st = stream if stream is not None else torch.cuda.current_stream(dev)
-    # the lattice, then room for the trials' per-sweep (E, M)
+    # the lattice, then room for the trials' per-sweep (E, M) and a second
+    # copy of the planes
     nbytes = (ising_lattice_bytes(L) + 255) // 256 * 256 + 16 * max(int(trial_sweeps), 2)
+    nbytes = (nbytes + 255) // 256 * 256 + int(lib().ising_spare_bytes(L))
     buf = _dev_alloc(nbytes, dev)
     out = ising_tuning()
     check(lib().ising_autotune(int(L), buf.data_ptr(), nbytes, _stream_ptr(st), int(trial_sweeps),

@@ -1,0 +1,143 @@
+"""Several sweeps per launch on rows held in LDS (csrc/ising_block.hip)
+against the oracle, bit for bit: strips at sides where rows, halves, lanes per
+half and the last strip come out uneven, sweep counts that the launches share
+unevenly, temperatures with and without the cut, lattices with and without the
+spare copy of the planes, and batches whose lattices run different numbers of
+strips, sweeps and launches."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def I():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1007_3726_amd import ising
+    ising.lib()
+    yield ising
+    ising.tuning_clear()
+
+
+def _check(I, L, T, n, seed=9, sid=3, init=workloads.INIT_HOT):
+    print("case L=%d T=%g n=%d" % (L, T, n), flush=True)
+    lat = I.Lattice(L, seed=seed, stream_id=sid, init=init, beta=1 / T)
+    em = lat.sweep_em(n).cpu().numpy()
+    s, oem = oracle.run(L, 1 / T, seed, sid, init, n)
+    assert np.array_equal(em, oem)
+    assert np.array_equal(lat.get_spins(), s)
+    # without a series, and from a counter that is not 0: the same lattice
+    again = I.Lattice(L, seed=seed, stream_id=sid, init=init, beta=1 / T)
+    again.sweep(1)
+    again.sweep(n - 1)
+    assert np.array_equal(again.get_spins(), s)
+    assert again.measure() == tuple(oem[-1])
+
+
+@pytest.mark.parametrize("n", [2, 3, 25, 61])
+@pytest.mark.parametrize("T", [1.4, 2.25])
+@pytest.mark.parametrize("L", [4, 10, 64, 66, 100, 128, 130, 136, 200, 258, 264, 384, 520])
+def test_small_sides(I, L, T, n):
+    _check(I, L, T, n)
+
+
+@pytest.mark.parametrize("n", [2, 9, 26])
+@pytest.mark.parametrize("T", [1.4, 2.25, 6.5])
+@pytest.mark.parametrize("L", [1000, 1002, 1022, 1024, 1538, 2048, 2050])
+def test_middle_sides(I, L, T, n):
+    _check(I, L, T, n, init=workloads.INIT_COLD_DOWN)
+
+
+@pytest.mark.parametrize("T", [1.4, 2.25])
+@pytest.mark.parametrize("L", [3000, 4094, 4096, 4098])
+def test_largest_sides(I, L, T):
+    _check(I, L, T, 7)
+
+
+@pytest.mark.parametrize("L", [300, 640, 682])
+def test_one_workgroup_up_to_its_lds(I, L):
+    """682^2: 65472 bytes of planes, the most that one workgroup takes."""
+    I.tuning_set([{"L_min": L, "L_max": L, "form": I.ISING_FORM_TILE, "rpw": 0,
+                   "max_blocks": 2048, "small_lds_bytes": 65536, "updates_per_ns": 0.0}])
+    try:
+        for T in (1.4, 2.25):
+            _check(I, L, T, 35)
+    finally:
+        I.tuning_clear()
+
+
+@pytest.mark.parametrize("L", [136, 514, 1024, 3000])
+def test_spare_copy_changes_nothing(I, L):
+    n = 11
+    a = I.Lattice(L, seed=2, init=workloads.INIT_HOT, beta=1 / 2.3)
+    b = I.Lattice(L, seed=2, init=workloads.INIT_HOT, beta=1 / 2.3)
+    I.check(I.lib().ising_set_spare(b.h, None, 0))
+    for k in (n, 1, 4):
+        assert np.array_equal(a.sweep_em(k).cpu().numpy(), b.sweep_em(k).cpu().numpy()), k
+        assert np.array_equal(a.get_spins(), b.get_spins()), k
+    # taken away between calls, and a buffer that is too small or misaligned
+    I.check(I.lib().ising_set_spare(a.h, None, 0))
+    assert np.array_equal(a.sweep_em(3).cpu().numpy(), b.sweep_em(3).cpu().numpy())
+    need = int(I.lib().ising_spare_bytes(L))
+    assert I.lib().ising_set_spare(a.h, a.buf.data_ptr(), need - 1) == I.ISING_ENOMEM
+    assert I.lib().ising_set_spare(a.h, a.buf.data_ptr() + 4, need) == I.ISING_EINVAL
+
+
+@pytest.mark.parametrize("spec", [
+    [(8, 2.2), (30, 1.4), (64, 2.3), (66, 2.1), (128, 5.0)],         # one workgroup each
+    [(64, 2.2), (512, 1.4), (258, 2.3), (100, 2.1), (32, 9.0)],      # strips beside singles
+    [(1024, 2.2), (34, 1.4), (2048, 2.3), (130, 2.1), (1000, 2.4)],
+])
+def test_batches(I, spec):
+    import torch
+    n = 27
+    lats = [I.Lattice(L, seed=6, stream_id=i, init=workloads.INIT_HOT, beta=1 / T)
+            for i, (L, T) in enumerate(spec)]
+    # one lattice without a series
+    EMs = [torch.empty((n, 2), dtype=torch.int64, device="cuda") for _ in spec]
+    EMs[1] = None
+    I.multi_sweep(lats, n, EMs)
+    for i, (L, T) in enumerate(spec):
+        s, oem = oracle.run(L, 1 / T, 6, i, workloads.INIT_HOT, n)
+        if EMs[i] is not None:
+            assert np.array_equal(EMs[i].cpu().numpy(), oem), (L, T)
+        assert np.array_equal(lats[i].get_spins(), s), (L, T)
+
+
+def test_served_requests_of_uneven_length(I):
+    reqs = [{"L": L, "beta": 1 / T, "seed": 40 + i, "stream_id": i, "init": workloads.INIT_HOT,
+             "n_sweeps": n, "record_series": True, "return_spins": True}
+            for i, (L, T, n) in enumerate([(32, 2.0, 70), (256, 2.2, 9), (512, 1.45, 41),
+                                           (1024, 2.3, 1), (96, 3.0, 33), (34, 2.5, 17),
+                                           (1002, 2.2, 12)])]
+    for arena in (4 << 20, 64 << 20):  # without and with room for spare copies
+        srv = I.Server(arena, quantum_sweeps=16)
+        tickets = srv.submit(reqs)
+        srv.run_until_idle()
+        for r, t in zip(reqs, tickets):
+            got = srv.poll(t)
+            s, oem = oracle.run(r["L"], r["beta"], r["seed"], r["stream_id"], r["init"],
+                                r["n_sweeps"])
+            assert np.array_equal(got["series"], oem), (arena, r["L"])
+            assert np.array_equal(got["spins"], s), (arena, r["L"])
+        srv.close()
+
+
+@pytest.mark.parametrize("seed", [5, 0xABCDE])
+@pytest.mark.parametrize("L", [200, 512, 1002])
+def test_shuffled_barriers(I, L, seed):
+    n = 6
+    I.debug_perturb(seed)
+    try:
+        lat = I.Lattice(L, seed=3, init=workloads.INIT_HOT, beta=1 / 2.269185)
+        em = lat.sweep_em(n).cpu().numpy()
+    finally:
+        I.debug_perturb(0)
+    s, oem = oracle.run(L, 1 / 2.269185, 3, 0, workloads.INIT_HOT, n)
+    assert np.array_equal(em, oem)
+    assert np.array_equal(lat.get_spins(), s)
