@@ -342,9 +342,13 @@ __device__ __forceinline__ void process_tile_direct(const TileArgs& a, const Til
     if (LCG) {
       // this word's generator: thread (colour L + y) W + w
       uint32_t* xs = a.lcg + (colour ? a.plane_words : 0) + off;
-      uint32_t z = *xs + a.l4d;
-      masks_lcg(z, a.lc, a.le, a.l4m, a.l8m, r4, r8);
-      *xs = z - a.l4d;
+      const uint32_t shift = CUT ? 0x80000000u : a.l4d;
+      uint32_t z = *xs + shift;
+      if (CUT)
+        masks_lcg_cut(z, a.lcut.x, a.lcut.c, r4, r8);
+      else
+        masks_lcg(z, a.lc, a.le, a.l4m, a.l8m, r4, r8);
+      *xs = z - shift;
     } else {
       uint32_t lo, hi;
       if (a.hi_mode == 0) {
@@ -1024,7 +1028,9 @@ static void launch_tile_sweep_rng(hipStream_t st, int colour, const TileArgs& a,
 }
 
 hipError_t launch_tile_sweep(hipStream_t st, int colour, const TileArgs& a, int blocks) {
-  if (a.lcg)
+  if (a.lcg && a.lcut.x)
+    launch_tile_sweep_rng<true, true>(st, colour, a, blocks);
+  else if (a.lcg)
     launch_tile_sweep_rng<true, false>(st, colour, a, blocks);
   else if (a.cut.x)
     launch_tile_sweep_rng<false, true>(st, colour, a, blocks);

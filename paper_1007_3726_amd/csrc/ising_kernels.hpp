@@ -46,10 +46,12 @@ struct TileArgs {
   const uint64_t* prev_part;  // partials of the previous sweep
   int32_t prev_blocks;
   // per-thread LCG dynamics (plain tiles only): states [2][L][W], or null
-  // for Philox; the chain runs on z = x + l4d with addend lc, the tests are
-  // z < l4m and z + le < l8m (see ising_device.hpp)
+  // for Philox; without a cut of its thresholds (lcut.x = 0) the chain runs on
+  // z = x + l4d with addend lc, the tests are z < l4m and z + le < l8m (see
+  // ising_device.hpp)
   uint32_t* lcg;
   uint32_t l4d, lc, le, l4m, l8m;
+  Cut lcut;
   // flat lane mapping of the direct-load kernels (rows whose width W neither
   // divides 64 nor is a multiple of it): wave task k covers words
   // 64 k .. 64 k + 63 of the colour plane in row-major order, so every lane

@@ -270,6 +270,7 @@ ising_status enqueue_sweeps(ising_lattice* h, int64_t n, int64_t* dev_EM) {
     lcg_decision(h->l8, &l8d, &ta.l8m);
     ta.lc = kLcgC + ta.l4d - kLcgA * ta.l4d;  // addend of the chain on z = x + l4d
     ta.le = l8d - ta.l4d;
+    ta.lcut = h->lcut;
     for (int64_t k = 0; k < n; ++k) {
       ta.t = (uint32_t)(h->sweep + (uint64_t)k);
       ta.prev_EM = (dev_EM && k > 0) ? dev_EM + 2 * (k - 1) : nullptr;
@@ -424,6 +425,7 @@ ising_status ising_set_beta(ising_t* h, double beta) {
   h->cut = make_cut(h->t4, h->t8);
   h->l4 = lcg_threshold(beta, 4);
   h->l8 = lcg_threshold(beta, 8);
+  h->lcut = make_cut(h->l4 + 1u, h->l8 + 1u, 0x80000001u);
   h->beta_set = true;
   if (h->pool) return fill_pool(h);  // the patterns encode this temperature
   return ISING_OK;

@@ -63,6 +63,7 @@ struct ising_lattice {
   uint32_t t4, t8;
   ising::Cut cut;       // three-way cut of (t4, t8)
   uint32_t l4, l8;      // LCG thresholds min(floor(exp(-beta dE) 2^31), 2^31)
+  ising::Cut lcut;      // three-way cut of (l4 + 1, l8 + 1), for |int32(x)| + 1
   bool beta_set;
   uint32_t* lcg;        // device: per-thread LCG states [2][L][W] (caller's), or null
   uint64_t* pool;       // device: Boltzmann-pattern pool, 2^pool_m (r4, r8) pairs (caller's), or null

@@ -27,28 +27,29 @@ def probe():
         subprocess.run(["g++", "-O1", "-std=c++17", "-I" + inc, "-o", out, src], check=True)
 
         def run(cases):
-            r = subprocess.run([out], input="\n".join("%d %d %d" % c for c in cases) + "\n",
+            r = subprocess.run([out], input="\n".join("%d %d %d %d" % c for c in cases) + "\n",
                                capture_output=True, text=True, check=True)
             return [tuple(int(v) for v in ln.split()) for ln in r.stdout.splitlines()]
         yield run
 
 
-def _uniforms(t4, t8, rng):
-    u = {0, TOP, t4, t8}
-    u |= {int(v) for v in rng.integers(0, 2 ** 32, 60)}
+def _uniforms(t4, t8, top, rng):
+    u = {0, top, t4, t8}
+    u |= {int(v) for v in rng.integers(0, top, 60)}
     d = max(t4 - t8, 1)
     for k in range(-2, 18):  # every place where the code steps
         u |= {t8 + k * d + e for e in (-2, -1, 0, 1, 2)}
     for t in (t4, t8):
         u |= {t + e for e in (-2, -1, 0, 1, 2)}
-    return sorted(v for v in u if 0 <= v <= TOP)
+    return sorted(v for v in u if 0 <= v <= top)
 
 
-def _check(probe, pairs):
+def _check(probe, pairs, top=TOP):
+    """Compares all pairs on the uniforms 0 .. top; says which have a cut."""
     rng = np.random.default_rng(8)
-    cases = [(t4, t8, u) for t4, t8 in pairs for u in _uniforms(t4, t8, rng)]
+    cases = [(t4, t8, top, u) for t4, t8 in pairs for u in _uniforms(t4, t8, top, rng)]
     has = {}
-    for (t4, t8, u), (x, code) in zip(cases, probe(cases)):
+    for (t4, t8, _, u), (x, code) in zip(cases, probe(cases)):
         has[(t4, t8)] = x != 0
         if x:
             assert min(code, 2) == (0 if u < t8 else 1 if u < t4 else 2), (t4, t8, u, code)
@@ -77,3 +78,20 @@ def test_code_at_the_limits_of_the_thresholds(probe):
             if t8 + d <= TOP:
                 pairs.append((t8 + d, t8))
     _check(probe, pairs)
+
+
+def test_code_of_the_lcg_range(probe):
+    """|int32| + 1, 1 .. 2^31 + 1, against thresholds of that scale plus one."""
+    def t(T, dE):
+        return min(int(math.floor(math.ldexp(math.exp(-dE / T), 31))), 2 ** 31) + 1
+    Ts = [float(v) for v in np.linspace(0.3, 8.0, 400)] + [2.269185, 1e9]
+    pairs = {T: (t(T, 4), t(T, 8)) for T in Ts}
+    has = _check(probe, sorted(set(pairs.values())), 2 ** 31 + 1)
+    for T, p in pairs.items():
+        if 2.1 <= T <= 5.7:
+            assert has[p], T
+        if T < 2.05 or T > 5.8:
+            assert not has[p], T
+    d = 2 ** 28
+    _check(probe, [(0, 0), (2 ** 31, 0), (2 ** 31, 2 ** 31), (d, 0), (d + 1, 0), (2 * d + 1, d),
+                   (2 * d + 3, d + 1)], 2 ** 31 + 1)

@@ -74,3 +74,19 @@ def test_shares(I, T):
     s, oem = oracle.run(L, 1 / T, 5, 0, workloads.INIT_HOT, n)
     assert np.array_equal(em, oem)
     assert np.array_equal(st.get_spins(), s)
+
+
+@pytest.mark.parametrize("T", [1.5, 2.07, 2.09, 3.5, 5.7, 5.8, 9.0])
+@pytest.mark.parametrize("L", [24, 520, 1024, 8072])
+def test_lcg(I, L, T):
+    # the generators' cut reaches from 2.08 to 5.77
+    n = 3
+    lat = I.Lattice(L, seed=77, init=workloads.INIT_HOT, beta=1 / T)
+    lat.use_lcg()
+    em = lat.sweep_em(n).cpu().numpy()
+    s = oracle.init(L, 77, 0, workloads.INIT_HOT)
+    st = oracle.lcg_seed(L, 77)
+    oem = oracle.lcg_sweeps(s, 1 / T, st, n)
+    assert np.array_equal(em, oem)
+    assert np.array_equal(lat.get_spins(), s)
+    assert np.array_equal(lat.lcg_states(), st)
