@@ -572,11 +572,20 @@ def reweight(EMs, betas0, discards, task_lattice, task_beta, nblocks: int, strea
     n = (ctypes.c_int64 * max(nl, 1))(*[int(e.shape[0]) for e in EMs])
     d = (ctypes.c_int64 * max(nl, 1))(*[int(v) for v in discards])
     b0 = (ctypes.c_double * max(nl, 1))(*[float(v) for v in betas0])
-    tl = (ctypes.c_int32 * max(nt, 1))(*[int(v) for v in task_lattice])
-    tb = (ctypes.c_double * max(nt, 1))(*[float(v) for v in task_beta])
-    check(lib().ising_reweight(nl, ptrs, n, d, b0, nt, tl, tb, int(nblocks), sums.data_ptr(),
-                               shift.data_ptr(), work.data_ptr(), int(work.numel()),
-                               _stream_ptr(st)))
+    # a task list has thousands of entries: numpy converts it at once
+    tl = np.zeros(max(nt, 1), dtype=np.int32)
+    tb = np.zeros(max(nt, 1), dtype=np.float64)
+    betas = np.asarray(task_beta, dtype=np.float64).reshape(-1)
+    if betas.size > nt:
+        raise IndexError("reweight: more task betas than tasks")
+    if nt:
+        tl[:] = np.asarray(task_lattice)
+        tb[:betas.size] = betas
+    check(lib().ising_reweight(nl, ptrs, n, d, b0, nt,
+                               tl.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)),
+                               tb.ctypes.data_as(ctypes.POINTER(ctypes.c_double)), int(nblocks),
+                               sums.data_ptr(), shift.data_ptr(), work.data_ptr(),
+                               int(work.numel()), _stream_ptr(st)))
     return sums, shift
 
 
@@ -630,19 +639,18 @@ def binder_curves(EMs, Ls, temps, discard: int, T_grid, nblocks: int = 20, strea
     """U4 curves on T_grid for every lattice size among Ls: each grid point is
     reweighted from the run of that size whose temperature is nearest.
     Returns {L: (est (K, 3), err (K, 3), u4_rep (nblocks, K))}."""
-    import numpy as np
-    Ls = [int(v) for v in Ls]
+    Ls = np.asarray([int(v) for v in Ls], dtype=np.int64)
     temps = np.asarray(temps, dtype=np.float64)
     T_grid = np.asarray(T_grid, dtype=np.float64)
-    sizes = sorted(set(Ls))
-    tl, tb, tsite = [], [], []
+    sizes = [int(L) for L in np.unique(Ls)]
+    nearest = []
     for L in sizes:
-        runs = [i for i, v in enumerate(Ls) if v == L]
-        for T in T_grid:
-            i = runs[int(np.argmin(np.abs(temps[runs] - T)))]
-            tl.append(i)
-            tb.append(1.0 / T)
-            tsite.append(L * L)
+        runs = np.flatnonzero(Ls == L)
+        # the first of the nearest, as for one grid point at a time
+        nearest.append(runs[np.argmin(np.abs(temps[runs][None, :] - T_grid[:, None]), axis=1)])
+    tl = np.concatenate(nearest)
+    tb = np.tile(1.0 / T_grid, len(sizes))
+    tsite = np.repeat(np.asarray(sizes, dtype=np.int64) ** 2, len(T_grid))
     sums, _ = reweight(EMs, [1.0 / t for t in temps], [discard] * len(EMs), tl, tb, nblocks,
                        stream)
     est, err, rep = fss_moments(sums.cpu().numpy(), tsite)
