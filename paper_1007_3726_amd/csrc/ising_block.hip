@@ -97,7 +97,7 @@ __device__ __forceinline__ void half_planes(uint32_t at, int sub, uint32_t k0, u
   a = b = 0;
   if (MODE == kCut) {
     uint32_t acc[4] = {0, 0, 0, 0};
-    cut_blocks<true, 0, NB - 1, false>(acc, (uint64_t)kM0 * at, 0, 16, k0, k1, t, ctr3, cut_x, cut_c);
+    cut_blocks<0, NB - 1, false>(acc, (uint64_t)kM0 * at, 0, k0, k1, t, ctr3, cut_x, cut_c);
     cut_planes(acc, a, b);
   } else if (MODE == kCompare) {
 #pragma unroll

@@ -274,26 +274,25 @@ __device__ __forceinline__ void shift_in4(uint32_t& a4, uint32_t& a8, uint32_t x
       : [x0] "v"(x0), [x1] "v"(x1), [x2] "v"(x2), [x3] "v"(x3), [t4] "s"(t4), [t8] "s"(t8));
 }
 
-// Masks for one word whose Philox blocks are lo + q, q < nq, all with the
+// Masks for one word whose Philox blocks are lo + q, q < 16, all with the
 // same high counter word `hi` (no carry out of lo + q): block q covers bits
 // 4q..4q+3.  Blocks are visited from q = 15 down to 0 so that the shift-in
-// order leaves block 0 in the lowest bits; with FULL every word has 16
-// blocks, otherwise blocks q >= nq are skipped and their bits stay zero.
-template <bool FULL>
-__device__ __forceinline__ void masks_shift(uint32_t lo, uint32_t hi, int nq, uint32_t k0,
-                                            uint32_t k1, uint32_t t, uint32_t ctr3, uint32_t t4,
-                                            uint32_t t8, uint64_t& r4, uint64_t& r8) {
+// order leaves block 0 in the lowest bits.  A partial last word's blocks past
+// the row are drawn too (the caller masks them): its lane would wait for the
+// others anyway, and a branch per block cost every lane (40000^2: 2414
+// updates/ns with it, 2802 without).
+__device__ __forceinline__ void masks_shift(uint32_t lo, uint32_t hi, uint32_t k0, uint32_t k1,
+                                            uint32_t t, uint32_t ctr3, uint32_t t4, uint32_t t8,
+                                            uint64_t& r4, uint64_t& r8) {
   uint32_t a4_hi = 0, a8_hi = 0, a4_lo = 0, a8_lo = 0;
 #pragma unroll
   for (int q = 15; q >= 0; --q) {
-    if (FULL || q < nq) {
-      uint32_t x0 = lo + (uint32_t)q, x1 = hi, x2 = t, x3 = ctr3;
-      philox4x32_10(x0, x1, x2, x3, k0, k1);
-      if (q >= 8)
-        shift_in4(a4_hi, a8_hi, x0, x1, x2, x3, t4, t8);
-      else
-        shift_in4(a4_lo, a8_lo, x0, x1, x2, x3, t4, t8);
-    }
+    uint32_t x0 = lo + (uint32_t)q, x1 = hi, x2 = t, x3 = ctr3;
+    philox4x32_10(x0, x1, x2, x3, k0, k1);
+    if (q >= 8)
+      shift_in4(a4_hi, a8_hi, x0, x1, x2, x3, t4, t8);
+    else
+      shift_in4(a4_lo, a8_lo, x0, x1, x2, x3, t4, t8);
   }
   r4 = ((uint64_t)a4_hi << 32) | a4_lo;
   r8 = ((uint64_t)a8_hi << 32) | a8_lo;
@@ -359,41 +358,34 @@ __device__ __forceinline__ uint64_t block_product(uint64_t first, uint32_t (&aft
   return p;
 }
 
-// Codes of blocks 8 H + B .. 8 H of a word, shifted into acc in that order.
-template <bool FULL, int H, int B, bool SERIAL>
+// Codes of blocks Q0 + B .. Q0 of a word, shifted into acc in that order.
+template <int Q0, int B, bool SERIAL>
 __device__ __forceinline__ void cut_blocks(uint32_t (&acc)[4], uint64_t first, uint32_t hi,
-                                           int nq, uint32_t k0, uint32_t k1, uint32_t t,
-                                           uint32_t ctr3, uint32_t X, uint64_t C) {
-  constexpr int Q = 8 * H + B;
-  if (FULL || Q < nq) {
-    uint32_t x0 = 0, x1 = hi, x2 = t, x3 = ctr3;
-    philox_from(block_product<Q, SERIAL>(first, acc), x0, x1, x2, x3, k0, k1);
-    cut_in(acc[0], x0, X, C);
-    cut_in(acc[1], x1, X, C);
-    cut_in(acc[2], x2, X, C);
-    cut_in(acc[3], x3, X, C);
-  }
-  if constexpr (B > 0)
-    cut_blocks<FULL, H, B - 1, SERIAL>(acc, first, hi, nq, k0, k1, t, ctr3, X, C);
+                                           uint32_t k0, uint32_t k1, uint32_t t, uint32_t ctr3,
+                                           uint32_t X, uint64_t C) {
+  uint32_t x0 = 0, x1 = hi, x2 = t, x3 = ctr3;
+  philox_from(block_product<Q0 + B, SERIAL>(first, acc), x0, x1, x2, x3, k0, k1);
+  cut_in(acc[0], x0, X, C);
+  cut_in(acc[1], x1, X, C);
+  cut_in(acc[2], x2, X, C);
+  cut_in(acc[3], x3, X, C);
+  if constexpr (B > 0) cut_blocks<Q0, B - 1, SERIAL>(acc, first, hi, k0, k1, t, ctr3, X, C);
 }
 
 // Cut planes of one word (64 sites) whose blocks are lo + q, as masks_shift.
-// Blocks q >= nq are skipped; their sites' planes mean nothing (the caller
-// masks them).
-template <bool FULL>
-__device__ __forceinline__ void masks_cut(uint32_t lo, uint32_t hi, int nq, uint32_t k0,
-                                          uint32_t k1, uint32_t t, uint32_t ctr3, uint32_t X,
-                                          uint64_t C, uint64_t& up, uint64_t& low) {
+__device__ __forceinline__ void masks_cut(uint32_t lo, uint32_t hi, uint32_t k0, uint32_t k1,
+                                          uint32_t t, uint32_t ctr3, uint32_t X, uint64_t C,
+                                          uint64_t& up, uint64_t& low) {
   const uint64_t first = (uint64_t)kM0 * lo;  // kM0 (lo + q) = first + kM0 q: no carry out of lo + q
   uint32_t u[2], l[2];
   {
     uint32_t acc[4] = {0, 0, 0, 0};
-    cut_blocks<FULL, 1, 7, true>(acc, first, hi, nq, k0, k1, t, ctr3, X, C);
+    cut_blocks<8, 7, true>(acc, first, hi, k0, k1, t, ctr3, X, C);
     cut_planes(acc, u[1], l[1]);
   }
   {
     uint32_t acc[4] = {0, 0, 0, 0};
-    cut_blocks<FULL, 0, 7, true>(acc, first, hi, nq, k0, k1, t, ctr3, X, C);
+    cut_blocks<0, 7, true>(acc, first, hi, k0, k1, t, ctr3, X, C);
     cut_planes(acc, u[0], l[0]);
   }
   up = ((uint64_t)u[1] << 32) | u[0];
@@ -401,15 +393,71 @@ __device__ __forceinline__ void masks_cut(uint32_t lo, uint32_t hi, int nq, uint
 }
 
 // Random planes of one word: cut planes with CUT, else (r4, r8).
-template <bool FULL, bool CUT>
-__device__ __forceinline__ void word_planes(uint32_t lo, uint32_t hi, int nq, uint32_t k0,
-                                            uint32_t k1, uint32_t t, uint32_t ctr3, uint32_t t4,
-                                            uint32_t t8, const Cut& cut, uint64_t& a,
-                                            uint64_t& b) {
+template <bool CUT>
+__device__ __forceinline__ void word_planes(uint32_t lo, uint32_t hi, uint32_t k0, uint32_t k1,
+                                            uint32_t t, uint32_t ctr3, uint32_t t4, uint32_t t8,
+                                            const Cut& cut, uint64_t& a, uint64_t& b) {
   if (CUT)
-    masks_cut<FULL>(lo, hi, nq, k0, k1, t, ctr3, cut.x, cut.c, a, b);
+    masks_cut(lo, hi, k0, k1, t, ctr3, cut.x, cut.c, a, b);
   else
-    masks_shift<FULL>(lo, hi, nq, k0, k1, t, ctr3, t4, t8, a, b);
+    masks_shift(lo, hi, k0, k1, t, ctr3, t4, t8, a, b);
+}
+
+// Random planes of one word whose first site has any colour-local index i0
+// (rows that start inside a Philox block): 17 blocks from i0 / 4 on, whose
+// bits are shifted down by i0 mod 4.  HI: the lattice has block indices of
+// 2^32 and more, so that every block has a high counter word of its own.
+template <bool CUT, bool HI>
+__device__ __forceinline__ void word_planes_any(uint64_t i0, uint32_t k0, uint32_t k1, uint32_t t,
+                                                uint32_t ctr3, uint32_t t4, uint32_t t8,
+                                                const Cut& cut, uint64_t& a, uint64_t& b) {
+  const uint32_t r = (uint32_t)i0 & 3u;
+  const uint64_t g = i0 >> 2;
+  uint32_t u[3], l[3];  // planes of blocks 9 .. 16, 1 .. 8 and 0
+  if (CUT && !HI) {
+    const uint64_t first = (uint64_t)kM0 * (uint32_t)g;  // (a carry out of g + q is past the lattice)
+    uint32_t x[4] = {0, 0, 0, 0}, y[4] = {0, 0, 0, 0}, z[4] = {0, 0, 0, 0};
+    cut_blocks<9, 7, true>(x, first, 0, k0, k1, t, ctr3, cut.x, cut.c);
+    cut_planes(x, u[0], l[0]);
+    cut_blocks<1, 7, true>(y, first, 0, k0, k1, t, ctr3, cut.x, cut.c);
+    cut_planes(y, u[1], l[1]);
+    cut_blocks<0, 0, true>(z, first, 0, k0, k1, t, ctr3, cut.x, cut.c);
+    cut_planes(z, u[2], l[2]);
+  } else {
+#pragma unroll
+    for (int part = 0; part < 3; ++part) {
+      uint32_t acc[4] = {0, 0, 0, 0};
+      const int q0 = part == 0 ? 9 : part == 1 ? 1 : 0;
+#pragma unroll
+      for (int q = q0 + (part == 2 ? 0 : 7); q >= q0; --q) {
+        const uint64_t gq = HI ? g + (uint64_t)q : (uint64_t)((uint32_t)g + (uint32_t)q);
+        uint32_t x0 = (uint32_t)gq, x1 = (uint32_t)(gq >> 32), x2 = t, x3 = ctr3;
+        // one block at a time, as in block_product
+        asm("" : "+v"(x0), "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
+        philox4x32_10(x0, x1, x2, x3, k0, k1);
+        if (CUT) {
+          cut_in(acc[0], x0, cut.x, cut.c);
+          cut_in(acc[1], x1, cut.x, cut.c);
+          cut_in(acc[2], x2, cut.x, cut.c);
+          cut_in(acc[3], x3, cut.x, cut.c);
+        } else {
+          shift_in4(acc[0], acc[1], x0, x1, x2, x3, t4, t8);
+        }
+      }
+      if (CUT) {
+        cut_planes(acc, u[part], l[part]);
+      } else {
+        u[part] = acc[0];
+        l[part] = acc[1];
+      }
+    }
+  }
+  // (blocks 1 .. 16 << 4 | block 0) >> r, 64 bits of it
+  const uint32_t s = 28u + r;
+  const uint32_t a_lo = __builtin_amdgcn_alignbit(u[1], u[2] << 28, s);
+  const uint32_t b_lo = __builtin_amdgcn_alignbit(l[1], l[2] << 28, s);
+  a = ((uint64_t)__builtin_amdgcn_alignbit(u[0], u[1], s) << 32) | a_lo;
+  b = ((uint64_t)__builtin_amdgcn_alignbit(l[0], l[1], s) << 32) | b_lo;
 }
 
 // ---------------------------------------------------------------------

@@ -196,8 +196,7 @@ __global__ void k_set_em(int64_t* EM, int64_t e, int64_t m) {
 // word varies per lane.
 //
 // Workgroups walk the tiles with a grid stride; logical block numbers are
-// grouped by XCD (hardware dispatches block b to XCD b mod 8), so that
-// vertically adjacent tiles share one L2.
+// grouped by XCD (logical_block).
 //
 // E/M (colour 1): each block writes its (anti-aligned bond, up spin) counts
 // to part[block]; block 0 of the next colour-0 pass (or launch_finalize_em)
@@ -231,6 +230,24 @@ __device__ __forceinline__ void finalize_partials(const uint64_t* part, int nblo
     EM[1] = 2 * (int64_t)sp - L * L;
   }
   __syncthreads();
+}
+
+// Logical number of block b of G.  Hardware dispatches block b to XCD b mod 8;
+// runs of consecutive tiles stay on one XCD, so that vertically adjacent
+// tiles share its L2.  One run of G / 8 per XCD shares most (262144^2 92.6
+// against 95.0 ms per 4 sweeps in runs of 64), but gives a last round's tiles
+// to the first few XCDs while the others' compute units wait: `spread` (set by
+// spread_runs) has runs of 64.
+__device__ __forceinline__ int logical_block(int b, int G, bool spread) {
+  if (spread) return (b & ~511) + (b & 7) * 64 + ((b >> 3) & 63);
+  return G % 8 == 0 ? (b % 8) * (G / 8) + b / 8 : b;
+}
+
+// Runs of 64 for a grid of G blocks: few rounds, the last of them short.
+// 20000^2 (1.5 rounds) 2197 -> 2739 updates/ns, 24576^2 (2.25) 2203 -> 2889,
+// the 56-lattice grid (1.7) 7.92 -> 7.08 ms per 96 sweeps.
+static int32_t spread_runs(int64_t tiles, int G) {
+  return G % 512 == 0 && tiles % G != 0 && tiles < 16 * (int64_t)G;
 }
 
 __device__ __forceinline__ int64_t wrap_row(int64_t y, int64_t L) {
@@ -270,7 +287,9 @@ __device__ __forceinline__ TileLane tile_lane(const TileArgs& a) {
 // shared by neighbouring lanes hit in L1/L2), issues the loads before the
 // Philox stretch and uses them after it.  No block barrier: the four waves
 // of a workgroup work independently.  Spin words are stored write-through.
-template <bool FULL, int WIDEM, bool CUT, bool LCG = false, bool FLAT = false>
+// ANY: 0, or rows that start anywhere in a Philox block, with block indices
+// below 2^32 (1) or not (2).
+template <bool FULL, int WIDEM, bool CUT, bool LCG = false, bool FLAT = false, int ANY = 0>
 __device__ __forceinline__ void process_tile_direct(const TileArgs& a, const TileLane& tl,
                                                     int colour, bool em, int64_t tidx,
                                                     uint32_t& anti, uint32_t& up) {
@@ -349,6 +368,9 @@ __device__ __forceinline__ void process_tile_direct(const TileArgs& a, const Til
       else
         masks_lcg(z, a.lc, a.le, a.l4m, a.l8m, r4, r8);
       *xs = z - shift;
+    } else if (ANY) {
+      const uint64_t i0 = (uint64_t)(uint32_t)y * (uint32_t)g.half + 64u * (uint32_t)w;
+      word_planes_any<CUT, ANY == 2>(i0, a.k0, a.k1, a.t, ctr3, a.t4, a.t8, a.cut, r4, r8);
     } else {
       uint32_t lo, hi;
       if (a.hi_mode == 0) {
@@ -360,8 +382,7 @@ __device__ __forceinline__ void process_tile_direct(const TileArgs& a, const Til
         hi = (uint32_t)(gy >> 32);
         lo = (uint32_t)gy + 16u * (uint32_t)w;
       }
-      const int nq = (FULL || w < W - 1) ? 16 : (g.nb_last >> 2);
-      word_planes<FULL, CUT>(lo, hi, nq, a.k0, a.k1, a.t, ctr3, a.t4, a.t8, a.cut, r4, r8);
+      word_planes<CUT>(lo, hi, a.k0, a.k1, a.t, ctr3, a.t4, a.t8, a.cut, r4, r8);
     }
     __builtin_amdgcn_sched_barrier(0);
     Nbr n;
@@ -386,7 +407,7 @@ __device__ __forceinline__ void process_tile_direct(const TileArgs& a, const Til
 
 // Tiles read their neighbour words directly (process_tile_direct): no LDS
 // staging and no barrier until the E/M reduction at the end.
-template <int C, bool EM, bool FULL, bool WIDE, bool LCG, bool FLAT, bool CUT>
+template <int C, bool EM, bool FULL, bool WIDE, bool LCG, bool FLAT, bool CUT, int ANY = 0>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k_tile_sweep(
     TileArgs a) {
   __shared__ uint64_t red64[8];
@@ -396,11 +417,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
   // logical block number grouped by XCD
   const int G = gridDim.x;
   const int b = blockIdx.x;
-  const int lb = (G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b;
+  const int lb = logical_block(b, G, a.spread != 0);
   uint32_t anti = 0, up = 0;
   const TileLane tl = tile_lane<WIDE ? 1 : 0>(a);
   for (int64_t tidx = lb; tidx < a.tiles; tidx += G)
-    process_tile_direct<FULL, WIDE ? 1 : 0, CUT, LCG, FLAT>(a, tl, C, EM, tidx, anti, up);
+    process_tile_direct<FULL, WIDE ? 1 : 0, CUT, LCG, FLAT, ANY>(a, tl, C, EM, tidx, anti, up);
   if (C == 1 && EM) {
     uint64_t sa, sp;
     block_sum2(anti, up, red, sa, sp);
@@ -431,7 +452,7 @@ __global__ __launch_bounds__(256) void k_pool_fill(uint64_t* pool, int64_t P, ui
   for (int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; p < P;
        p += (int64_t)gridDim.x * blockDim.x) {
     uint64_t r4, r8;
-    masks_shift<true>(16u * (uint32_t)p, 0u, 16, k0, k1, 0xFFFFFFFFu, sid4 | 2u, t4, t8, r4,
+    masks_shift(16u * (uint32_t)p, 0u, k0, k1, 0xFFFFFFFFu, sid4 | 2u, t4, t8, r4,
                       r8);
     pool[2 * p] = r4;
     pool[2 * p + 1] = r8;
@@ -547,7 +568,7 @@ __global__ __launch_bounds__(256) void k_pool_sweep(TileArgs a) {
     finalize_partials(a.prev_part, a.prev_blocks, a.g.L, a.prev_EM, red64);
   const int G = gridDim.x;
   const int b = blockIdx.x;
-  const int lb = (G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b;
+  const int lb = logical_block(b, G, a.spread != 0);
   uint32_t anti = 0, up = 0;
   for (int64_t tidx = lb; tidx < a.tiles; tidx += G) pool_tile<C, EM, FULL, LINEAR>(a, tidx, anti, up);
   if (C == 1 && EM) {
@@ -601,7 +622,7 @@ __global__ __launch_bounds__(256) void k_share_init(ShareArgs a, int init) {
     } else {
       const uint64_t g = (uint64_t)(a.y0 + r) * a.L8 + 16u * w;
       uint64_t m, unused;
-      masks_shift<true>((uint32_t)g, (uint32_t)(g >> 32), 16, a.k0, a.k1, 0u,
+      masks_shift((uint32_t)g, (uint32_t)(g >> 32), a.k0, a.k1, 0u,
                         a.sid4 | (2u + (uint32_t)c), 0x80000000u, 0x80000000u, m, unused);
       word = m;
     }
@@ -634,7 +655,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
     const uint64_t sd = other[row * W + ws];
     const uint64_t g = (uint64_t)y * a.L8 + 16u * w;
     uint64_t r4, r8;
-    word_planes<true, CUT>((uint32_t)g, (uint32_t)(g >> 32), 16, a.k0, a.k1, a.t, ctr3, a.t4, a.t8,
+    word_planes<CUT>((uint32_t)g, (uint32_t)(g >> 32), a.k0, a.k1, a.t, ctr3, a.t4, a.t8,
                            a.cut, r4, r8);
     __builtin_amdgcn_sched_barrier(0);
     Nbr n;
@@ -768,7 +789,6 @@ __device__ __forceinline__ void strip_task(const TileArgs& a, int64_t task, uint
   const int64_t y1 = (y0 + a.RPW < L) ? y0 + a.RPW : L;
   const uint32_t ctr3 = a.sid4 | (uint32_t)C;
   const uint64_t valid = (FULL || w < W - 1) ? ~0ull : low_mask(g.nb_last);
-  const int nq = (FULL || w < W - 1) ? 16 : (g.nb_last >> 2);
   // Row y: the other colour's rows y-1, y, y+1 are in (om, oc, op), the
   // horizontal partner word in sd and the own word in s.  Before computing
   // it, the step loads row y+2 into `nx` and the partner and own words of
@@ -797,7 +817,7 @@ __device__ __forceinline__ void strip_task(const TileArgs& a, int64_t task, uint
       lo = (uint32_t)gy + 16u * (uint32_t)w;
     }
     uint64_t r4, r8;
-    word_planes<FULL, CUT>(lo, hi, nq, a.k0, a.k1, a.t, ctr3, a.t4, a.t8, a.cut, r4, r8);
+    word_planes<CUT>(lo, hi, a.k0, a.k1, a.t, ctr3, a.t4, a.t8, a.cut, r4, r8);
     // the uniforms need no lattice data: keep the gather below them so that
     // the row's loads have the whole Philox stretch to arrive
     __builtin_amdgcn_sched_barrier(0);
@@ -846,7 +866,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
   // logical block number grouped by XCD, so that neighbouring tasks share an L2
   const int G = gridDim.x;
   const int b = blockIdx.x;
-  const int lb = (G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b;
+  const int lb = logical_block(b, G, a.spread != 0);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t anti = 0, up = 0;
   for (int64_t task = (int64_t)lb * 4 + wave; task < a.tiles; task += (int64_t)G * 4)
@@ -929,7 +949,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8))) void k
   if (C == 0 && k > 0) finalize_tiles(f, k - 1, red64);
   const int G = gridDim.x;
   const int b = blockIdx.x;
-  const int lb = (G % 8 == 0) ? (b % 8) * (G / 8) + b / 8 : b;
+  const int lb = logical_block(b, G, f.spread != 0);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t* part = f.part + (size_t)(k & 1u) * 8 * f.ntiles;
   for (int64_t tidx = lb; tidx < f.ntiles; tidx += G) {
@@ -976,7 +996,8 @@ __global__ void k_advance(uint32_t* kbase, uint32_t by) {
   if (blockIdx.x == 0 && threadIdx.x == 0) *kbase += by;
 }
 
-hipError_t launch_fused(hipStream_t st, int colour, const FusedArgs& f, int blocks) {
+hipError_t launch_fused(hipStream_t st, int colour, FusedArgs f, int blocks) {
+  f.spread = spread_runs(f.ntiles, blocks);
   if (colour == 0)
     hipLaunchKernelGGL(k_fused<0>, dim3(blocks), dim3(256), 0, st, f);
   else
@@ -1027,7 +1048,31 @@ static void launch_tile_sweep_rng(hipStream_t st, int colour, const TileArgs& a,
     launch_tile_sweep_v<LCG, false, CUT, false>(st, colour, a, blocks);
 }
 
-hipError_t launch_tile_sweep(hipStream_t st, int colour, const TileArgs& a, int blocks) {
+template <bool CUT, int ANY>
+static void launch_tile_sweep_any(hipStream_t st, int colour, const TileArgs& a, int blocks) {
+#define ISING_TILE(C, E)                                                             \
+  hipLaunchKernelGGL((k_tile_sweep<C, E, false, false, false, true, CUT, ANY>), dim3(blocks), \
+                     dim3(256), 0, st, a)
+  if (colour == 0)
+    ISING_TILE(0, false);
+  else if (a.part != nullptr)
+    ISING_TILE(1, true);
+  else
+    ISING_TILE(1, false);
+#undef ISING_TILE
+}
+
+hipError_t launch_tile_sweep(hipStream_t st, int colour, TileArgs a, int blocks) {
+  a.spread = spread_runs(a.tiles, blocks);
+  if (a.any) {
+    if (a.hi_mode == 0)
+      a.cut.x ? launch_tile_sweep_any<true, 1>(st, colour, a, blocks)
+              : launch_tile_sweep_any<false, 1>(st, colour, a, blocks);
+    else
+      a.cut.x ? launch_tile_sweep_any<true, 2>(st, colour, a, blocks)
+              : launch_tile_sweep_any<false, 2>(st, colour, a, blocks);
+    return hipGetLastError();
+  }
   if (a.lcg && a.lcut.x)
     launch_tile_sweep_rng<true, true>(st, colour, a, blocks);
   else if (a.lcg)
@@ -1089,7 +1134,8 @@ static void launch_pool_sweep_v(hipStream_t st, int colour, const TileArgs& a, i
 #undef ISING_POOL
 }
 
-hipError_t launch_pool_sweep(hipStream_t st, int colour, const TileArgs& a, int blocks) {
+hipError_t launch_pool_sweep(hipStream_t st, int colour, TileArgs a, int blocks) {
+  a.spread = spread_runs(a.tiles, blocks);
   if (a.pool_linear)
     launch_pool_sweep_v<true>(st, colour, a, blocks);
   else
@@ -1116,7 +1162,8 @@ static void launch_strip_sweep_v(hipStream_t st, int colour, const TileArgs& a, 
 #undef ISING_STRIP
 }
 
-hipError_t launch_strip_sweep(hipStream_t st, int colour, const TileArgs& a, int blocks) {
+hipError_t launch_strip_sweep(hipStream_t st, int colour, TileArgs a, int blocks) {
+  a.spread = spread_runs((a.tiles + 3) / 4, blocks);
   if (a.cut.x)
     launch_strip_sweep_v<true>(st, colour, a, blocks);
   else

@@ -40,7 +40,10 @@ struct TileArgs {
   int32_t RPW;      // row groups per wave in one tile
   int32_t segs;     // 64-word segments per row (1 when W < 64)
   int64_t tiles;    // ceil(L / (4 R RPW)) * segs
-  int32_t hi_mode;  // 0: every Philox block index < 2^32; 1: high word uniform per row
+  // 0: every Philox block index < 2^32; 1: high word uniform per row; 2: any
+  // (tiles of any row start only)
+  int32_t hi_mode;
+  int32_t any;      // rows start anywhere in a Philox block (flat mapping)
   uint64_t* part;   // colour 1 with E/M: per-block (anti-aligned bonds, up spins)
   int64_t* prev_EM;           // colour 0: (E, M) slot of the previous sweep to finalise
   const uint64_t* prev_part;  // partials of the previous sweep
@@ -60,6 +63,7 @@ struct TileArgs {
   // q W > i.
   int32_t flat;
   uint32_t wdiv_m;
+  int32_t spread;   // how block numbers are dealt to XCDs (set at the launch)
   // Boltzmann-pattern-pool dynamics (plain tiles, flat mapping, RPW = 4):
   // 2^m patterns of (r4, r8) word pairs, or null; a word reads pattern
   // v >> pool_shift (pool_shift = 32 - m) of its own Philox draw, or, with
@@ -75,10 +79,10 @@ struct TileArgs {
 // row-group mapping.
 void make_flat(TileArgs& a, bool always = false);
 
-hipError_t launch_tile_sweep(hipStream_t st, int colour, const TileArgs& a, int blocks);
+hipError_t launch_tile_sweep(hipStream_t st, int colour, TileArgs a, int blocks);
 // Strip form (W >= kWideMinWords): TileArgs with TW = 64, R = 1, RPW = rows
 // per wave task, tiles = number of wave tasks (segs x ceil(L / RPW)).
-hipError_t launch_strip_sweep(hipStream_t st, int colour, const TileArgs& a, int blocks);
+hipError_t launch_strip_sweep(hipStream_t st, int colour, TileArgs a, int blocks);
 hipError_t launch_finalize_em(hipStream_t st, const uint64_t* part, int blocks, int64_t L,
                               int64_t* EM);
 // Thread seeds of the LCG dynamics: state[j] = s0 * 16807^j mod 2^32.
@@ -87,7 +91,7 @@ hipError_t launch_lcg_seed(hipStream_t st, uint32_t* state, int64_t n, uint32_t 
 hipError_t launch_pool_fill(hipStream_t st, uint64_t* pool, int m, uint32_t k0, uint32_t k1,
                             uint32_t sid4, uint32_t t4, uint32_t t8);
 // Colour step of the pool dynamics (TileArgs with flat = 1, RPW = 4, pool set).
-hipError_t launch_pool_sweep(hipStream_t st, int colour, const TileArgs& a, int blocks);
+hipError_t launch_pool_sweep(hipStream_t st, int colour, TileArgs a, int blocks);
 
 // Batched sweeps (see ising_kernels.hip).
 struct FusedLattice {
@@ -110,9 +114,10 @@ struct FusedArgs {
   int64_t ntiles;
   const uint32_t* kbase;  // device word: sweep index of the chunk's first sweep
   uint32_t* part;       // 2 slots x ntiles x (anti, up)
+  int32_t spread;       // how block numbers are dealt to XCDs (set at the launch)
 };
 
-hipError_t launch_fused(hipStream_t st, int colour, const FusedArgs& f, int blocks);
+hipError_t launch_fused(hipStream_t st, int colour, FusedArgs f, int blocks);
 hipError_t launch_fused_finalize(hipStream_t st, const FusedArgs& f, int blocks);
 hipError_t launch_advance(hipStream_t st, uint32_t* kbase, uint32_t by);
 

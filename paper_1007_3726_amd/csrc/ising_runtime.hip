@@ -157,6 +157,70 @@ bool tile_args(const ising_lattice* h, TileArgs* out) {
   return true;
 }
 
+// Word-steps that the busiest SIMD takes for `tiles` workgroups of `rpw` words
+// per lane, 8 resident per compute unit.  Workgroups beyond the resident ones
+// follow in rounds; a last round of few leaves its waves alone on their SIMDs,
+// where a word takes about twice as long.
+static int64_t word_steps(int64_t tiles, int64_t rpw, int64_t cus) {
+  if (tiles <= 8 * cus) return rpw * ((tiles + cus - 1) / cus);
+  const int64_t rounds = tiles / (8 * cus), rest = tiles - rounds * 8 * cus;
+  return 8 * rounds * rpw + (rest ? std::max(2 * rpw, rpw * ((rest + cus - 1) / cus)) : 0);
+}
+
+// Words per lane of the flat mapping that fill the compute units most evenly,
+// where the shape at hand leaves some of them waiting.  Measured, updates/ns:
+// 10000^2 (one round of 2 words on six of eight places) 2097 -> 2278, 12000^2
+// (1.1 rounds of 2) 1783 -> 2400; 16384^2 (one round of 4) stays.
+static void balance_tiles(TileArgs& a, int64_t cus) {
+  if (a.plane_words >= (1ll << 32) || a.hi_mode == 1 || cus <= 0) return;
+  const int64_t units = (a.plane_words + 255) / 256;  // workgroups of one word per lane
+  if (units > 16 * 8 * cus) return;  // many rounds: the last one hardly counts
+  int64_t best = 0;
+  double steps = 0.97 * (double)word_steps(a.tiles, a.RPW, cus);
+  for (int64_t rpw = 1; rpw <= 16; ++rpw) {
+    const double s = (double)word_steps((units + rpw - 1) / rpw, rpw, cus);
+    if (s < steps) {  // of equals the one with the most waves
+      best = rpw;
+      steps = s;
+    }
+  }
+  if (!best) return;
+  a.RPW = (int32_t)best;
+  make_flat(a, true);
+}
+
+// Tiles of a lattice that tile_args does not take (L % 8 != 0: rows start
+// inside a Philox block; or block indices of 2^32 and more whose high word is
+// not uniform over a row): flat mapping, 17 blocks per word.  False for
+// planes of 2^32 words or more.  Measured against the one-word-per-lane
+// kernel with 64-bit shifts that such lattices took before, updates/ns:
+// 4098^2 492 -> 1060, 16386^2 1280 -> 2290, 200000^2 2111 -> 2504.
+static bool any_tile_args(const ising_lattice* h, TileArgs* out) {
+  if (h->plane_words >= (1ll << 32)) return false;
+  TileArgs a;
+  std::memset(&a, 0, sizeof(a));
+  a.any = 1;
+  a.hi_mode = (uint64_t)h->L * (uint64_t)h->L / 8 < (1ull << 32) - 32 ? 0 : 2;
+  a.TW = 64;
+  a.R = 1;
+  a.segs = 1;
+  // as many words per lane (up to 4) as keep 2048 workgroups
+  a.RPW = 4;
+  while (a.RPW > 1 && (h->plane_words + 256 * a.RPW - 1) / (256 * a.RPW) < 2048) a.RPW >>= 1;
+  a.planes = h->planes;
+  a.plane_words = h->plane_words;
+  a.g = h->g;
+  a.k0 = (uint32_t)h->seed;
+  a.k1 = (uint32_t)(h->seed >> 32);
+  a.sid4 = h->stream_id << 2;
+  a.t4 = h->t4;
+  a.t8 = h->t8;
+  a.cut = h->cut;
+  make_flat(a, true);
+  *out = a;
+  return true;
+}
+
 // Strip form of the same lattice (wide rows only): RPW = rows per wave
 // task, tiles = number of wave tasks.
 bool strip_args(const ising_lattice* h, TileArgs* out) {
@@ -258,8 +322,10 @@ ising_status enqueue_sweeps(ising_lattice* h, int64_t n, int64_t* dev_EM) {
   TileArgs ta;
   if (h->pool) return enqueue_pool_sweeps(h, n, dev_EM);
   const bool strip = strip_args(h, &ta);
-  if (strip || tile_args(h, &ta)) {
-    if (!strip) make_flat(ta);  // direct-load tiles: every lane busy at any W
+  const bool tile = !strip && tile_args(h, &ta);
+  if (tile) make_flat(ta);  // direct-load tiles: every lane busy at any W
+  if (strip || tile || (h->lcg == nullptr && any_tile_args(h, &ta))) {
+    if (!strip && h->tune.rpw == 0) balance_tiles(ta, device_cus(h->device));
     const int64_t units = strip ? (ta.tiles + 3) / 4 : ta.tiles;  // 4 wave tasks per block
     const int blocks = (int)std::min<int64_t>(units, std::min(h->tune.max_blocks,
                                                               kMaxSweepBlocks));
