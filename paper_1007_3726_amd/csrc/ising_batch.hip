@@ -404,15 +404,17 @@ ising_status batch_sweeps(ising_lattice* const* hs, int32_t count, int64_t n,
     std::vector<int> all(count);
     std::iota(all.begin(), all.end(), 0);
     std::vector<int64_t> Ls;
-    double sites = 0;
+    double sites = 0, words = 0;
     for (int i = 0; i < count; ++i) {
       if (!(hs[i]->L <= kBlockMaxL && (hs[i]->spare || block_fits_single(hs[i]->L)))) break;
       Ls.push_back(hs[i]->L);
       sites += (double)hs[i]->L * hs[i]->L;
+      words += (double)hs[i]->plane_words;
     }
     if ((int)Ls.size() == count && sites <= kBlockMaxSites) {
-      const BlockPlan plan = plan_blocks(Ls, std::min(n, kBlockPlanN), device_cus(device));
-      bool ok = !plan.shapes.empty() && plan.sweep_s < launch_per_step_seconds(sites) &&
+      const int cus = device_cus(device);
+      const BlockPlan plan = plan_blocks(Ls, std::min(n, kBlockPlanN), cus);
+      bool ok = !plan.shapes.empty() && plan.sweep_s < launch_per_step_seconds(words, cus) &&
                 block_layout(count, plan.tasks).bytes <= work_bytes;
       for (int i = 0; i < count && ok; ++i) ok = plan.shapes[i].strips == 1 || hs[i]->spare;
       if (ok) {

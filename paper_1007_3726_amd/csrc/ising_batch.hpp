@@ -68,9 +68,9 @@ ising_status batch_sweeps(ising_lattice* const* hs, int32_t count, int64_t n,
 // Several sweeps per launch (ising_block.hip).
 BlockShape block_shape_single(int64_t L);
 bool block_fits_single(int64_t L);
-// Model: seconds per sweep of lattices with `sites` sites in all when every
-// colour step is a launch.
-double launch_per_step_seconds(double sites);
+// Model: seconds per sweep of lattices with `words` words per colour in all
+// when every colour step is a launch.
+double launch_per_step_seconds(double words, int cus);
 BlockPlan plan_blocks(const std::vector<int64_t>& Ls, int64_t n, int cus);
 // One lattice's entry for n sweeps; one_launch: a single strip runs them all
 // in its first launch, else as many per launch as the shape's.

@@ -84,11 +84,11 @@ __device__ __forceinline__ uint32_t wave_total(uint32_t v) {
 
 // How a half's uniforms are drawn: rows of whole Philox blocks (L % 8 == 0)
 // with the plain compares or the cut, or rows that start anywhere in a block.
-enum { kCompare = 0, kCut = 1, kAnyRow = 2 };
+enum { kCompare = 0, kCut = 1, kAnyRow = 2, kAnyRowCut = 3 };
 
 // Random planes of this lane's 32 / LS sites of a half, at their places in
 // the half (bits of other lanes' sites mean nothing).  `at`: colour-local
-// index of the lane's first site, over 4 unless MODE is kAnyRow.
+// index of the lane's first site, over 4 where rows are whole blocks.
 template <int LS, int MODE>
 __device__ __forceinline__ void half_planes(uint32_t at, int sub, uint32_t k0, uint32_t k1,
                                             uint32_t t, uint32_t ctr3, uint32_t t4, uint32_t t8,
@@ -110,14 +110,24 @@ __device__ __forceinline__ void half_planes(uint32_t at, int sub, uint32_t k0, u
     // NB + 1 blocks cover the sites; the first block's r lowest outputs
     // belong to the sites before
     const uint32_t g = at >> 2, r = at & 3u;
-    for (int q = NB; q >= 1; --q) {
-      uint32_t x0 = g + (uint32_t)q, x1 = 0, x2 = t, x3 = ctr3;
-      philox4x32_10(x0, x1, x2, x3, k0, k1);
-      shift_in4(a, b, x0, x1, x2, x3, t4, t8);
+    if (MODE == kAnyRowCut) {
+      uint32_t acc[4] = {0, 0, 0, 0};
+      cut_blocks<1, NB - 1, false>(acc, (uint64_t)kM0 * g, 0, k0, k1, t, ctr3, cut_x, cut_c);
+      cut_planes(acc, a, b);
+    } else {
+      for (int q = NB; q >= 1; --q) {
+        uint32_t x0 = g + (uint32_t)q, x1 = 0, x2 = t, x3 = ctr3;
+        philox4x32_10(x0, x1, x2, x3, k0, k1);
+        shift_in4(a, b, x0, x1, x2, x3, t4, t8);
+      }
     }
     uint32_t x0 = g, x1 = 0, x2 = t, x3 = ctr3, a0 = 0, b0 = 0;
     philox4x32_10(x0, x1, x2, x3, k0, k1);
     shift_in4(a0, b0, x0, x1, x2, x3, t4, t8);
+    if (MODE == kAnyRowCut) {  // (r4, r8) -> (up, low)
+      a0 ^= 15u;
+      b0 ^= 15u;
+    }
     a = (a << (4u - r)) | (a0 >> r);
     b = (b << (4u - r)) | (b0 >> r);
   }
@@ -189,8 +199,8 @@ __device__ __forceinline__ void block_steps(const Lat& L, uint32_t* lds, uint2* 
   // of the row for the first half), bit 0 of the half to the right
   const int hl = hw > 0 ? hw - 1 : L.nh - 1, hr = last ? 0 : hw + 1;
   const int shl = hw > 0 ? 31 : L.nbl - 1, shr = last ? L.nbl - 1 : 31;
-  const uint32_t rowlen = MODE == kAnyRow ? (uint32_t)L.half : (uint32_t)L.half >> 2;
-  const uint32_t col = MODE == kAnyRow ? 32u * hw + 4u * NB * sub : 8u * hw + NB * (uint32_t)sub;
+  const uint32_t rowlen = MODE >= kAnyRow ? (uint32_t)L.half : (uint32_t)L.half >> 2;
+  const uint32_t col = MODE >= kAnyRow ? 32u * hw + 4u * NB * sub : 8u * hw + NB * (uint32_t)sub;
   const uint32_t k0 = L.k0, k1 = L.k1, sid4 = L.sid4, t4 = L.t4, t8 = L.t8, cut_x = L.cut.x;
   const uint64_t cut_c = L.cut.c;
   const int side = L.L, wave = (int)threadIdx.x >> 6;
@@ -220,7 +230,7 @@ __device__ __forceinline__ void block_steps(const Lat& L, uint32_t* lds, uint2* 
         half_planes<LS, MODE>((uint32_t)y * rowlen + col, sub, k0, k1, t, sid4 | (uint32_t)c, t4,
                               t8, cut_x, cut_c, a, b);
         const uint32_t n1 = bfi(left, (n0 << 1) | (sd >> shl), (n0 >> 1) | (sd << shr));
-        uint32_t f = MODE == kCut ? flip_half_cut(s_old, n0, n1, n2, n3, a, b)
+        uint32_t f = MODE == kCut || MODE == kAnyRowCut ? flip_half_cut(s_old, n0, n1, n2, n3, a, b)
                                   : flip_half(s_old, n0, n1, n2, n3, a, b);
         f = lanes_or<LS>(f & mine);
         const uint32_t s_new = s_old ^ f;
@@ -347,12 +357,18 @@ __device__ __forceinline__ void block_run(const Lat& L, int strip, int j, uint32
       block_steps<LS, MODE, false>(L, lds, counts, strip, j, R, H, own, y0, s0, K);     \
   } while (0)
   if ((L.half & 3) != 0) {
-    switch (L.ls) {
-      case 8: ISING_BLOCK(8, kAnyRow); break;
-      case 4: ISING_BLOCK(4, kAnyRow); break;
-      case 2: ISING_BLOCK(2, kAnyRow); break;
-      default: ISING_BLOCK(1, kAnyRow); break;
-    }
+    if (L.ls == 8)
+      ISING_BLOCK(8, kAnyRow);
+    else if (L.ls == 4)
+      ISING_BLOCK(4, kAnyRow);
+    else if (L.cut.x != 0 && L.ls == 2)
+      ISING_BLOCK(2, kAnyRowCut);
+    else if (L.cut.x != 0)
+      ISING_BLOCK(1, kAnyRowCut);
+    else if (L.ls == 2)
+      ISING_BLOCK(2, kAnyRow);
+    else
+      ISING_BLOCK(1, kAnyRow);
   } else if (L.ls >= 4) {
     // one or two blocks per lane: the transpose of the cut costs as much as
     // the compares it saves
@@ -416,8 +432,10 @@ constexpr double kClock = 2.4e9;
 constexpr double kLaunch = 5e-6;   // a launch: gap, loads, stores
 constexpr double kBarrier = 1e-7;  // of a colour step
 
-// Instructions of one wave's pass with ls lanes per half.
-static double pass_instructions(int ls) {
+// Instructions of one wave's pass with ls lanes per half; `any`: rows that
+// start anywhere in a Philox block.
+static double pass_instructions(int ls, bool any) {
+  if (any) return ls == 8 ? 155 : ls == 4 ? 220 : ls == 2 ? 335 : 515;
   return ls == 8 ? 115 : ls == 4 ? 180 : ls == 2 ? 290 : 460;
 }
 
@@ -426,16 +444,16 @@ static double waves_of(double halves, int ls) { return std::ceil(halves * ls / 6
 // Seconds of one colour step of a workgroup that updates `halves` halves with
 // the compute unit to itself: the busiest SIMD issues its waves' instructions
 // one per four cycles, and a lone wave no more than one per six.
-static double step_seconds(double halves, int ls) {
+static double step_seconds(double halves, int ls, bool any) {
   const double issue = std::ceil(waves_of(halves, ls) / 4) * 4, alone = 6;
-  return std::max(issue, alone) * pass_instructions(ls) / kClock + kBarrier;
+  return std::max(issue, alone) * pass_instructions(ls, any) / kClock + kBarrier;
 }
 
 // Strips of `rows` rows with K sweeps per launch.
 static BlockShape shape_of(int64_t L, int64_t rows, int K) {
   BlockShape s;
   const int64_t W = words_per_row(L), nh = (L / 2 + 31) / 32;
-  const bool single = rows >= L;
+  const bool single = rows >= L, any = L % 8 != 0;
   s.rows = (int32_t)std::min(rows, L);
   s.strips = single ? 1 : (int32_t)((L + rows - 1) / rows);
   s.sweeps = K;
@@ -449,23 +467,23 @@ static BlockShape shape_of(int64_t L, int64_t rows, int K) {
   // sweeps 5.34, 5.57, 6.23, 7.96.
   s.ls = 1;
   for (int ls = 2; ls <= 8; ls *= 2)
-    if (nh * ls <= 1024 && step_seconds((double)(mean * nh), ls) <
-                               step_seconds((double)(mean * nh), s.ls))
+    if (nh * ls <= 1024 && step_seconds((double)(mean * nh), ls, any) <
+                               step_seconds((double)(mean * nh), s.ls, any))
       s.ls = ls;
   const int64_t per = nh * s.ls;
   s.pass = (int32_t)std::max<int64_t>(1, std::min<int64_t>(R, 1024 / per));
   s.threads = (int32_t)((s.pass * per + 63) / 64 * 64);
   s.lds = (size_t)(2 * R * W) * sizeof(uint64_t);
-  s.step_s = step_seconds((double)(mean * nh), s.ls);
-  s.issue_s = waves_of((double)(mean * nh), s.ls) * pass_instructions(s.ls) / kClock;
+  s.step_s = step_seconds((double)(mean * nh), s.ls, any);
+  s.issue_s = waves_of((double)(mean * nh), s.ls) * pass_instructions(s.ls, any) / kClock;
   return s;
 }
 
-// Measured: 3.5 us per launch (gap, ramp and drain), at least 2 us for one
-// word's uniforms, and beyond that the updates at the tiles' rate (2900
-// updates/ns); 4096^2 11.7 us per sweep, the 56-lattice grid 82 us.
-double launch_per_step_seconds(double sites) {
-  return 2 * (3.5e-6 + std::max(2e-6, 0.5 * sites / 2.9e12));
+// Measured: 3 us per launch (gap, ramp and drain) and 1.45 us per word of the
+// busiest SIMD's waves, at least 2.2 us for a word alone: us per sweep 15.3 at
+// 4104^2, 20.7 at 6000^2, 29.3 at 8192^2, 74 for the 56-lattice grid.
+double launch_per_step_seconds(double words, int cus) {
+  return 2 * (3e-6 + std::max(2.2e-6, 1.45e-6 * std::ceil(words / 256 / std::max(cus, 1))));
 }
 
 BlockShape block_shape_single(int64_t L) { return shape_of(L, L, 1); }

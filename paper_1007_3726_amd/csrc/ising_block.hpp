@@ -17,7 +17,7 @@ constexpr int kBlockMaxStrips = 256;
 // Strips of a batch (beyond one per lattice).
 constexpr int64_t kBlockMaxTasks = 1024;
 // Largest side whose sweeps may take this form with several strips.
-constexpr int64_t kBlockMaxL = 4096;
+constexpr int64_t kBlockMaxL = 8704;
 // LDS of one workgroup: two planes of the strip's rows and its halos.
 constexpr int64_t kBlockMaxLds = 65536;
 

@@ -311,8 +311,10 @@ ising_status enqueue_sweeps(ising_lattice* h, int64_t n, int64_t* dev_EM) {
     // the shape depends on n only below kBlockPlanN sweeps; kept with the handle
     const int64_t key = std::min(n, kBlockPlanN);
     if (h->block_n != key) {
-      const BlockPlan plan = plan_blocks({h->L}, key, device_cus(h->device));
-      h->block = plan.shapes.empty() || plan.sweep_s >= launch_per_step_seconds((double)h->L * h->L)
+      const int cus = device_cus(h->device);
+      const BlockPlan plan = plan_blocks({h->L}, key, cus);
+      h->block = plan.shapes.empty() ||
+                         plan.sweep_s >= launch_per_step_seconds((double)h->plane_words, cus)
                      ? BlockShape()
                      : plan.shapes[0];
       h->block_n = key;

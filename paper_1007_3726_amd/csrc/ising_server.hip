@@ -165,9 +165,10 @@ ising_status admit(ising_server* s) {
     }
     j.h = h;
     // the second copy of the planes (several sweeps per launch) only while
-    // half the arena stays free, so that it never holds a request back
+    // half the arena stays free, so that it never holds a request back, and
+    // for sides that a batch may take blocks with
     const size_t sb = align256(ising_spare_bytes(j.req.L));
-    if (sb && s->arena.used() + sb <= s->arena_bytes / 2 && s->arena.alloc(sb, &j.spare_off)) {
+    if (sb && (double)j.req.L * (double)j.req.L <= kBlockMaxSites && s->arena.used() + sb <= s->arena_bytes / 2 && s->arena.alloc(sb, &j.spare_off)) {
       j.spare_bytes = sb;
       st = ising_set_spare(h, s->arena_base + j.spare_off, sb);
       if (st != ISING_OK) return st;

@@ -54,7 +54,7 @@ def test_middle_sides(I, L, T, n):
 
 
 @pytest.mark.parametrize("T", [1.4, 2.25])
-@pytest.mark.parametrize("L", [3000, 4094, 4096, 4098])
+@pytest.mark.parametrize("L", [3000, 4094, 4096, 4098, 5000, 8200, 8702, 8704])
 def test_largest_sides(I, L, T):
     _check(I, L, T, 7)
 
