@@ -413,8 +413,8 @@ ising_status batch_sweeps(ising_lattice* const* hs, int32_t count, int64_t n,
     }
     if ((int)Ls.size() == count && sites <= kBlockMaxSites) {
       const int cus = device_cus(device);
-      const BlockPlan plan = plan_blocks(Ls, std::min(n, kBlockPlanN), cus);
-      bool ok = !plan.shapes.empty() && plan.sweep_s < launch_per_step_seconds(words, cus) &&
+      const BlockPlan plan = plan_blocks(kBlockPhilox, Ls, std::min(n, kBlockPlanN), cus);
+      bool ok = !plan.shapes.empty() && plan.sweep_s < launch_per_step_seconds(kBlockPhilox, words, cus) &&
                 block_layout(count, plan.tasks).bytes <= work_bytes;
       for (int i = 0; i < count && ok; ++i) ok = plan.shapes[i].strips == 1 || hs[i]->spare;
       if (ok) {
@@ -456,7 +456,7 @@ ising_status batch_sweeps(ising_lattice* const* hs, int32_t count, int64_t n,
   if (packed) {
     BlockPlan singles;
     singles.all_single = true;
-    for (int i : tiled) singles.shapes.push_back(block_shape_single(hs[i]->L));
+    for (int i : tiled) singles.shapes.push_back(block_shape_single(kBlockPhilox, hs[i]->L));
     return run_blocks(hs, tiled, n, nsw, dev_EM, singles, (char*)work, opt.keep_image);
   }
   // the fused grid walks actual tiles; size it for them

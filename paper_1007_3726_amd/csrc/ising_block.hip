@@ -31,6 +31,15 @@
 // (E, M) series, a launch per colour step (or the LDS kernel that this one
 // replaced) before: 64^2 4.29 -> 0.95, 512^2 10.3 -> 2.5, 1002^2 16.6 -> 4.2,
 // 4096^2 11.7 -> 10.4; 24 lattices of 8^2 to 64^2 8.95 -> 1.12.
+//
+// The paper's generators and pools run in the same blocks.  A word's
+// generator is affine in its steps, so every lane of a half jumps to its own
+// values, and the halo rows' generators need no second copy: a strip advances
+// them from the states before the call, and one last kernel advances the
+// caller's.  A pool's patterns are read from memory, several rows ahead.
+// us per sweep before -> after, LCG / linear pool / random pool: 64^2 9.0 / 8.4
+// / 8.6 -> 0.73 / 0.99 / 1.0; 1024^2 9.7 / 9.7 / 10.9 -> 2.9 / 2.8 / 3.7;
+// 4096^2 10.6 / 9.7 / 12.2 -> 6.7 / 4.4 / 9.3; 16384^2 linear 28.3 -> 22.6.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -84,7 +93,8 @@ __device__ __forceinline__ uint32_t wave_total(uint32_t v) {
 
 // How a half's uniforms are drawn: rows of whole Philox blocks (L % 8 == 0)
 // with the plain compares or the cut, or rows that start anywhere in a block.
-enum { kCompare = 0, kCut = 1, kAnyRow = 2, kAnyRowCut = 3 };
+// kLcg: the word's generator; kPool, kPoolLinear: patterns.
+enum { kCompare = 0, kCut = 1, kAnyRow = 2, kAnyRowCut = 3, kLcg = 4, kPool = 5, kPoolLinear = 6 };
 
 // Random planes of this lane's 32 / LS sites of a half, at their places in
 // the half (bits of other lanes' sites mean nothing).  `at`: colour-local
@@ -137,6 +147,22 @@ __device__ __forceinline__ void half_planes(uint32_t at, int sub, uint32_t k0, u
   }
 }
 
+// Cut planes of this lane's sites of a half from its word's generator, whose
+// state x comes before the value of the lane's highest site (masks_lcg_cut).
+template <int LS>
+__device__ __forceinline__ void lcg_half(uint32_t x, int sub, uint32_t cut_x, uint64_t cut_c,
+                                         uint32_t& a, uint32_t& b) {
+  constexpr int NB = 8 / LS;
+  uint32_t acc[4] = {0, 0, 0, 0};
+  uint32_t y = x + 0x80000000u;
+  lcg_codes<NB>(acc, y, cut_x, cut_c);
+  cut_planes(acc, a, b);
+  if (LS > 1) {
+    a <<= 4 * NB * sub;
+    b <<= 4 * NB * sub;
+  }
+}
+
 // The counts of `cnt` sweeps leave the LDS slots (one (anti, up) pair per
 // wave and sweep): the first of them is sweep k0 of the launch (first sweep
 // s0 of the lattice's series).
@@ -171,6 +197,45 @@ __device__ __forceinline__ void lds_add(uint2* slot, uint32_t anti, uint32_t up)
   asm volatile("ds_add_u64 %0, %1\n\ts_waitcnt lgkmcnt(0)" : : "v"(addr), "v"(v) : "memory");
 }
 
+// x -> a x + b (mod 2^32): one or several steps of the generator at once.
+struct Affine {
+  uint32_t a, b;
+};
+
+__host__ __device__ inline Affine lcg_skip(uint64_t steps) {
+  Affine r = {1u, 0u}, p = {kLcgA, kLcgC};
+  for (; steps; steps >>= 1) {
+    if (steps & 1) r = Affine{p.a * r.a, p.a * r.b + p.b};
+    p = Affine{p.a * p.a, p.a * p.b + p.b};
+  }
+  return r;
+}
+
+// What the alternative dynamics keep beside the planes of a strip.
+struct AltStrip {
+  const uint32_t* lcg;   // LDS: the strip's generators as they were before the call
+  Affine sweep;          // their advance to the current sweep (64 steps each)
+  const uint32_t* pool;  // patterns (device memory)
+  uint32_t shift, mask;
+  uint32_t* starts;      // LDS: [2][kMaxGroups] start of every 256-word group, by step parity
+  uint32_t first;        // global index of the strip's first word
+  uint32_t group0;       // its group
+  int groups;            // groups of the strip's words
+  int wrapped;           // groups before the lattice's first word comes round again
+};
+constexpr int kMaxGroups = 64;
+
+// Starts of step s of the strip's groups for linear reads, by the first wave.
+template <typename Lat>
+__device__ __forceinline__ void pool_starts(const Lat& L, const AltStrip& x, int64_t s0, int s) {
+  const int i = (int)threadIdx.x;
+  if (i >= x.groups) return;
+  uint32_t x0 = i < x.wrapped ? x.group0 + (uint32_t)i : (uint32_t)(i - x.wrapped);
+  uint32_t x1 = 0, x2 = L.t + (uint32_t)(s0 + (s >> 1)), x3 = L.sid4 | (uint32_t)(s & 1);
+  philox4x32_10(x0, x1, x2, x3, L.k0, L.k1);
+  x.starts[(s & 1) * kMaxGroups + i] = x0 >> x.shift;
+}
+
 // K sweeps of the strip's R rows in LDS: local row r is global row y0 + r
 // (mod L); rows H .. H + own - 1 are the strip's own.  A colour step's time
 // is mostly a wave's chain of instructions, so lanes without work take the
@@ -180,8 +245,14 @@ __device__ __forceinline__ void lds_add(uint2* slot, uint32_t anti, uint32_t up)
 template <int LS, int MODE, bool ONE, typename Lat>
 __device__ __forceinline__ void block_steps(const Lat& L, uint32_t* lds, uint2* counts, int strip,
                                             int j, int R, int H, int own, int y0, int64_t s0,
-                                            int K) {
+                                            int K, AltStrip alt) {
   constexpr int NB = 8 / LS;
+  constexpr bool kAny = MODE == kAnyRow || MODE == kAnyRowCut;
+  constexpr bool kPooled = MODE == kPool || MODE == kPoolLinear;
+  constexpr bool kCutPlanes = MODE == kCut || MODE == kAnyRowCut || MODE == kLcg;
+  // patterns come from memory: several rows' loads go out before the first is
+  // used
+  constexpr int kAhead = kPooled && !ONE ? 4 : 1;
   // few lanes count: they add in LDS; many: the wave sums first
   constexpr bool kAddCounts = LS >= 4;
   const bool wrap = ONE || L.strips == 1;
@@ -199,12 +270,18 @@ __device__ __forceinline__ void block_steps(const Lat& L, uint32_t* lds, uint2* 
   // of the row for the first half), bit 0 of the half to the right
   const int hl = hw > 0 ? hw - 1 : L.nh - 1, hr = last ? 0 : hw + 1;
   const int shl = hw > 0 ? 31 : L.nbl - 1, shr = last ? L.nbl - 1 : 31;
-  const uint32_t rowlen = MODE >= kAnyRow ? (uint32_t)L.half : (uint32_t)L.half >> 2;
-  const uint32_t col = MODE >= kAnyRow ? 32u * hw + 4u * NB * sub : 8u * hw + NB * (uint32_t)sub;
+  const uint32_t rowlen = kAny ? (uint32_t)L.half : (uint32_t)L.half >> 2;
+  const uint32_t col = kAny ? 32u * hw + 4u * NB * sub : 8u * hw + NB * (uint32_t)sub;
   const uint32_t k0 = L.k0, k1 = L.k1, sid4 = L.sid4, t4 = L.t4, t8 = L.t8, cut_x = L.cut.x;
   const uint64_t cut_c = L.cut.c;
   const int side = L.L, wave = (int)threadIdx.x >> 6;
   const int plane = R * stride, lastrow = plane - stride;
+  const int words = R * L.W;
+  // the generator's values of this lane's sites follow this many others of
+  // the word (site 63 takes the first)
+  const Affine own_skip =
+      MODE == kLcg ? lcg_skip((uint32_t)(64 - 32 * (hw & 1) - 4 * NB * (sub + 1))) : Affine{1u, 0u};
+  const Affine sweep_skip = MODE == kLcg ? lcg_skip(64) : Affine{1u, 0u};
   for (int k = 0; k < K; ++k) {
     const uint32_t t = L.t + (uint32_t)(s0 + k);
     uint2* const slot = &counts[(k & (kEmSlots - 1)) * kMaxWaves + wave];
@@ -215,10 +292,32 @@ __device__ __forceinline__ void block_steps(const Lat& L, uint32_t* lds, uint2* 
       const int ra = wrap ? 0 : 1 + s, rb = wrap ? R - 1 : R - 2 - s;
       uint32_t* const self = lds + (c ? plane : 0);
       const uint32_t* const other = lds + (c ? 0 : plane);
-      auto rows = [&](int want) {
+      auto global_row = [&](int r) {
+        const int y = y0 + r;
+        return y >= side ? y - side : y;
+      };
+      // the two pattern halves of row `want` (or the last)
+      auto pattern = [&](int want, uint32_t& a, uint32_t& b) {
         const int r = want < rb ? want : rb;
-        int y = y0 + r;
-        y = y >= side ? y - side : y;
+        const uint32_t iu = (uint32_t)(global_row(r) * L.W + (hw >> 1));
+        uint32_t addr;
+        if (MODE == kPoolLinear) {
+          int g = (int)((iu >> 8) - alt.group0);
+          if (iu < alt.first) g = (int)(iu >> 8) + alt.wrapped;
+          addr = (alt.starts[c * kMaxGroups + g] + (iu & 255u)) & alt.mask;
+        } else {
+          uint32_t x0 = iu, x1 = 0, x2 = t, x3 = sid4 | (uint32_t)c;
+          philox4x32_10(x0, x1, x2, x3, k0, k1);
+          addr = x0 >> alt.shift;
+        }
+        const uint32_t* p = alt.pool + 4 * (size_t)addr + (hw & 1);
+        a = p[0];
+        b = p[2];
+      };
+      // one row of the step; pools: (a, b) are given
+      auto row = [&](int want, uint32_t a, uint32_t b) {
+        const int r = want < rb ? want : rb;
+        const int y = global_row(r);
         const int at = (int)__umul24((uint32_t)r, (uint32_t)stride);
         const int am = wrap && r == 0 ? lastrow : at - stride;
         const int ap = wrap && at == lastrow ? 0 : at + stride;
@@ -226,12 +325,17 @@ __device__ __forceinline__ void block_steps(const Lat& L, uint32_t* lds, uint2* 
         const uint32_t s_old = self[at + hw], n0 = other[at + hw];
         const uint32_t n2 = other[am + hw], n3 = other[ap + hw];
         const uint32_t sd = other[at + (left ? hl : hr)];
-        uint32_t a, b;
-        half_planes<LS, MODE>((uint32_t)y * rowlen + col, sub, k0, k1, t, sid4 | (uint32_t)c, t4,
-                              t8, cut_x, cut_c, a, b);
+        if (MODE == kLcg) {
+          uint32_t x = alt.lcg[(c ? words : 0) + (at >> 1) + (hw >> 1)];
+          x = alt.sweep.a * x + alt.sweep.b;
+          lcg_half<LS>(own_skip.a * x + own_skip.b, sub, cut_x, cut_c, a, b);
+        } else if (!kPooled) {
+          half_planes<LS, MODE>((uint32_t)y * rowlen + col, sub, k0, k1, t, sid4 | (uint32_t)c, t4,
+                                t8, cut_x, cut_c, a, b);
+        }
         const uint32_t n1 = bfi(left, (n0 << 1) | (sd >> shl), (n0 >> 1) | (sd << shr));
-        uint32_t f = MODE == kCut || MODE == kAnyRowCut ? flip_half_cut(s_old, n0, n1, n2, n3, a, b)
-                                  : flip_half(s_old, n0, n1, n2, n3, a, b);
+        uint32_t f = kCutPlanes ? flip_half_cut(s_old, n0, n1, n2, n3, a, b)
+                                : flip_half(s_old, n0, n1, n2, n3, a, b);
         f = lanes_or<LS>(f & mine);
         const uint32_t s_new = s_old ^ f;
         const bool store = first_lane && want <= rb;
@@ -246,11 +350,22 @@ __device__ __forceinline__ void block_steps(const Lat& L, uint32_t* lds, uint2* 
         }
       };
       if (ONE) {
-        rows(r0);
+        uint32_t a = 0, b = 0;
+        if (kPooled) pattern(r0, a, b);
+        row(r0, a, b);
       } else {
-        for (int base = ra; base <= rb; base += pass) {
+        for (int base = ra; base <= rb; base += pass * kAhead) {
+          uint32_t a[kAhead], b[kAhead];
           // the wave's first lane has its smallest row
-          if (__builtin_amdgcn_readfirstlane(base + r0) <= rb) rows(base + r0);
+          if (__builtin_amdgcn_readfirstlane(base + r0) > rb) continue;
+          if (kPooled) {
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) pattern(base + r0 + i * pass, a[i], b[i]);
+          }
+#pragma unroll
+          for (int i = 0; i < kAhead; ++i)
+            if (i == 0 || __builtin_amdgcn_readfirstlane(base + r0 + i * pass) <= rb)
+              row(base + r0 + i * pass, a[i], b[i]);
         }
       }
       if (c == 1 && em) {
@@ -261,9 +376,12 @@ __device__ __forceinline__ void block_steps(const Lat& L, uint32_t* lds, uint2* 
           if ((threadIdx.x & 63) == 63) *slot = make_uint2(wa, wu);
         }
       }
+      if (MODE == kPoolLinear) pool_starts(L, alt, s0, s + 1);
       perturb_wave(L.perturb, (uint32_t)s);
       __syncthreads();
     }
+    if (MODE == kLcg)
+      alt.sweep = Affine{sweep_skip.a * alt.sweep.a, sweep_skip.a * alt.sweep.b + sweep_skip.b};
     // the slots are written again only after the next colour-0 barrier
     if (em && ((k & (kEmSlots - 1)) == kEmSlots - 1 || k == K - 1))
       drain_counts(L, counts, strip, j, s0, k & ~(kEmSlots - 1), (k & (kEmSlots - 1)) + 1);
@@ -317,9 +435,12 @@ __device__ __forceinline__ void reduce_last(const Lat& L, int first, int step) {
 }
 
 // Lat: BlockLattice, as a kernel argument or in a table (constant memory).
-template <typename Lat>
-__device__ __forceinline__ void block_run(const Lat& L, int strip, int j, uint32_t* lds) {
+// ALT: the alternative dynamics x of a lone lattice instead of Philox.
+template <bool ALT, typename Lat>
+__device__ __forceinline__ void block_run(const Lat& L, const BlockAlt* x, int strip, int j,
+                                          uint32_t* lds) {
   __shared__ uint2 counts[kEmSlots * kMaxWaves];
+  __shared__ uint32_t starts[ALT ? 2 * kMaxGroups : 1];
   // waves beyond this lattice's share of the workgroup leave at once
   if ((int)(threadIdx.x & ~63u) >= L.threads || j >= L.launches) return;
   const bool wrap = L.strips == 1;
@@ -341,6 +462,25 @@ __device__ __forceinline__ void block_run(const Lat& L, int strip, int j, uint32
     p = p >= all ? p - all : p;
     lds64[i] = src[p];
     lds64[R * W + i] = src[all + p];
+    if (ALT && x->kind == kBlockLcg) {
+      lds[4 * R * W + i] = x->lcg[p];
+      lds[5 * R * W + i] = x->lcg[all + p];
+    }
+  }
+  AltStrip alt = {};
+  if (ALT) {
+    alt.lcg = lds + 4 * R * W;
+    alt.sweep = lcg_skip(64 * (uint64_t)s0);
+    alt.pool = (const uint32_t*)x->pool;
+    alt.shift = x->pool_shift;
+    alt.mask = x->pool_mask;
+    alt.starts = starts;
+    alt.first = (uint32_t)(y0 * W);
+    alt.group0 = alt.first >> 8;
+    const int end = y0 * W + R * W;  // past `all` when the strip's rows wrap
+    alt.wrapped = (((end < all ? end : all) - 1) >> 8) - (int)alt.group0 + 1;
+    alt.groups = alt.wrapped + (end > all ? ((end - all - 1) >> 8) + 1 : 0);
+    if (x->kind == kBlockPoolLinear) pool_starts(L, alt, s0, 0);
   }
   // the first strips reduce the E/M partials of the launch before, one sweep
   // each (a launch has fewer sweeps than strips); loaded now, summed at the end
@@ -352,11 +492,24 @@ __device__ __forceinline__ void block_run(const Lat& L, int strip, int j, uint32
 #define ISING_BLOCK(LS, MODE)                                                           \
   do {                                                                                  \
     if (wrap && R <= L.pass)                                                            \
-      block_steps<LS, MODE, true>(L, lds, counts, strip, j, R, H, own, y0, s0, K);      \
+      block_steps<LS, MODE, true>(L, lds, counts, strip, j, R, H, own, y0, s0, K, alt); \
     else                                                                                \
-      block_steps<LS, MODE, false>(L, lds, counts, strip, j, R, H, own, y0, s0, K);     \
+      block_steps<LS, MODE, false>(L, lds, counts, strip, j, R, H, own, y0, s0, K, alt); \
   } while (0)
-  if ((L.half & 3) != 0) {
+  if constexpr (ALT) {
+    if (x->kind == kBlockPool) {
+      ISING_BLOCK(1, kPool);
+    } else if (x->kind == kBlockPoolLinear) {
+      ISING_BLOCK(1, kPoolLinear);
+    } else {
+      switch (L.ls) {
+        case 8: ISING_BLOCK(8, kLcg); break;
+        case 4: ISING_BLOCK(4, kLcg); break;
+        case 2: ISING_BLOCK(2, kLcg); break;
+        default: ISING_BLOCK(1, kLcg); break;
+      }
+    }
+  } else if ((L.half & 3) != 0) {
     if (L.ls == 8)
       ISING_BLOCK(8, kAnyRow);
     else if (L.ls == 4)
@@ -399,16 +552,30 @@ __device__ __forceinline__ void block_run(const Lat& L, int strip, int j, uint32
 
 __global__ __launch_bounds__(1024) void k_block(BlockLattice L, int j) {
   extern __shared__ uint64_t block_lds[];
-  block_run(L, blockIdx.x, j, (uint32_t*)block_lds);
+  block_run<false>(L, nullptr, blockIdx.x, j, (uint32_t*)block_lds);
+}
+
+// The paper's generators and pools.
+__global__ __launch_bounds__(1024) void k_block_alt(BlockLattice L, BlockAlt x, int j) {
+  extern __shared__ uint64_t block_lds[];
+  block_run<true>(L, &x, blockIdx.x, j, (uint32_t*)block_lds);
+}
+
+// All generators `skip` steps on (the strips of a call derive their states
+// from those before it, so the caller's buffer changes once).
+__global__ __launch_bounds__(256) void k_lcg_advance(uint32_t* state, int64_t n, Affine skip) {
+  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * blockDim.x)
+    state[i] = skip.a * state[i] + skip.b;
 }
 
 // The same for a table of lattices; tasks are (lattice, strip).
-__global__ __launch_bounds__(1024) void k_block_many(
-    const BlockLattice* tab, const BlockTask* tasks, int j) {
+__global__ __launch_bounds__(1024) void k_block_many(const BlockLattice* tab,
+                                                     const BlockTask* tasks, int j) {
   extern __shared__ uint64_t block_lds[];
   const BlockTask task = ((const BlockTask ISING_CONSTANT_AS*)tasks)[blockIdx.x];
-  block_run(((const BlockLattice ISING_CONSTANT_AS*)tab)[task.lattice], task.strip, j,
-            (uint32_t*)block_lds);
+  block_run<false>(((const BlockLattice ISING_CONSTANT_AS*)tab)[task.lattice], nullptr, task.strip,
+                   j, (uint32_t*)block_lds);
 }
 
 // (E, M) of every lattice's last launch.
@@ -431,10 +598,15 @@ __global__ __launch_bounds__(64) void k_block_finalize_many(const BlockLattice* 
 constexpr double kClock = 2.4e9;
 constexpr double kLaunch = 5e-6;   // a launch: gap, loads, stores
 constexpr double kBarrier = 1e-7;  // of a colour step
+constexpr double kCuBytes = 2.5e10;  // bytes per second of one compute unit's share
+constexpr double kPatternLatency = 1e-6;
 
 // Instructions of one wave's pass with ls lanes per half; `any`: rows that
 // start anywhere in a Philox block.
-static double pass_instructions(int ls, bool any) {
+static double pass_instructions(int kind, int ls, bool any) {
+  if (kind == kBlockLcg) return ls == 8 ? 85 : ls == 4 ? 105 : ls == 2 ? 140 : 210;
+  if (kind == kBlockPool) return 115;
+  if (kind == kBlockPoolLinear) return 75;
   if (any) return ls == 8 ? 155 : ls == 4 ? 220 : ls == 2 ? 335 : 515;
   return ls == 8 ? 115 : ls == 4 ? 180 : ls == 2 ? 290 : 460;
 }
@@ -444,13 +616,18 @@ static double waves_of(double halves, int ls) { return std::ceil(halves * ls / 6
 // Seconds of one colour step of a workgroup that updates `halves` halves with
 // the compute unit to itself: the busiest SIMD issues its waves' instructions
 // one per four cycles, and a lone wave no more than one per six.
-static double step_seconds(double halves, int ls, bool any) {
+static double step_seconds(int kind, double halves, int ls, bool any) {
   const double issue = std::ceil(waves_of(halves, ls) / 4) * 4, alone = 6;
-  return std::max(issue, alone) * pass_instructions(ls, any) / kClock + kBarrier;
+  double s = std::max(issue, alone) * pass_instructions(kind, ls, any) / kClock + kBarrier;
+  // patterns: one load's latency, and 8 bytes per half at a CU's share of the
+  // memory's rate (a 128-byte line per random pattern)
+  if (kind == kBlockPoolLinear) s = std::max(s, halves * 8 / kCuBytes) + kPatternLatency;
+  if (kind == kBlockPool) s = std::max(s, halves * 64 / kCuBytes) + kPatternLatency;
+  return s;
 }
 
 // Strips of `rows` rows with K sweeps per launch.
-static BlockShape shape_of(int64_t L, int64_t rows, int K) {
+static BlockShape shape_of(int kind, int64_t L, int64_t rows, int K) {
   BlockShape s;
   const int64_t W = words_per_row(L), nh = (L / 2 + 31) / 32;
   const bool single = rows >= L, any = L % 8 != 0;
@@ -466,27 +643,33 @@ static BlockShape shape_of(int64_t L, int64_t rows, int K) {
   // of 2 rows, 8 sweeps 2.84, 2.66, 2.79, 3.07; 2048^2 in strips of 8 rows, 4
   // sweeps 5.34, 5.57, 6.23, 7.96.
   s.ls = 1;
-  for (int ls = 2; ls <= 8; ls *= 2)
-    if (nh * ls <= 1024 && step_seconds((double)(mean * nh), ls, any) <
-                               step_seconds((double)(mean * nh), s.ls, any))
+  const double halves = (double)(mean * nh);
+  for (int ls = 2; ls <= 8 && kind <= kBlockLcg; ls *= 2)
+    if (nh * ls <= 1024 &&
+        step_seconds(kind, halves, ls, any) < step_seconds(kind, halves, s.ls, any))
       s.ls = ls;
   const int64_t per = nh * s.ls;
   s.pass = (int32_t)std::max<int64_t>(1, std::min<int64_t>(R, 1024 / per));
   s.threads = (int32_t)((s.pass * per + 63) / 64 * 64);
-  s.lds = (size_t)(2 * R * W) * sizeof(uint64_t);
-  s.step_s = step_seconds((double)(mean * nh), s.ls, any);
-  s.issue_s = waves_of((double)(mean * nh), s.ls) * pass_instructions(s.ls, any) / kClock;
+  s.lds = (size_t)(R * W) * (kind == kBlockLcg ? 24 : 16);
+  s.step_s = step_seconds(kind, halves, s.ls, any);
+  s.issue_s = waves_of(halves, s.ls) * pass_instructions(kind, s.ls, any) / kClock;
+  s.move_s = (double)(s.lds + 16 * s.rows * W) / kCuBytes;
   return s;
 }
 
 // Measured: 3 us per launch (gap, ramp and drain) and 1.45 us per word of the
 // busiest SIMD's waves, at least 2.2 us for a word alone: us per sweep 15.3 at
 // 4104^2, 20.7 at 6000^2, 29.3 at 8192^2, 74 for the 56-lattice grid.
-double launch_per_step_seconds(double words, int cus) {
-  return 2 * (3e-6 + std::max(2.2e-6, 1.45e-6 * std::ceil(words / 256 / std::max(cus, 1))));
+// Generators 0.58 us and 1.5 us (their chain is serial), patterns 0.35 us
+// (random 1.4 us) and 1 us: 16384^2 24.0, 14.2 and 45.7 us per colour step.
+double launch_per_step_seconds(int kind, double words, int cus) {
+  static const double word[] = {1.45e-6, 0.65e-6, 1.35e-6, 0.35e-6};
+  static const double alone[] = {2.2e-6, 1.5e-6, 1.0e-6, 1.0e-6};
+  return 2 * (3e-6 + std::max(alone[kind], word[kind] * std::ceil(words / 256 / std::max(cus, 1))));
 }
 
-BlockShape block_shape_single(int64_t L) { return shape_of(L, L, 1); }
+BlockShape block_shape_single(int kind, int64_t L) { return shape_of(kind, L, L, 1); }
 
 // Both planes of a single strip fit one workgroup's LDS.
 bool block_fits_single(int64_t L) {
@@ -497,13 +680,15 @@ bool block_fits_single(int64_t L) {
 // and strips of about `target` halves per mean colour step, so that the
 // strips of all lattices are about equal.  A lattice that fits one workgroup
 // takes a single strip where a strip would be as large.
-BlockPlan plan_blocks(const std::vector<int64_t>& Ls, int64_t n, int cus) {
+BlockPlan plan_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int cus) {
   BlockPlan best;
   bool all_single = true;
   for (int64_t L : Ls) all_single = all_single && block_fits_single(L);
+  // a lone lattice's strips have a compute unit each
+  const int64_t lds = Ls.size() == 1 ? kBlockLoneLds : kBlockMaxLds;
   auto consider = [&](int K, int64_t target, bool singles) {
     BlockPlan p;
-    double longest = 0, issue = 0;
+    double longest = 0, issue = 0, move = 0;
     int64_t strips = 0;
     for (int64_t L : Ls) {
       const int64_t nh = (L / 2 + 31) / 32;
@@ -515,25 +700,27 @@ BlockPlan plan_blocks(const std::vector<int64_t>& Ls, int64_t n, int cus) {
         rows = L;
       else if (rows + 4 * (int64_t)K > L)
         return;
-      const BlockShape s = shape_of(L, rows, K);
-      if (s.lds > (size_t)kBlockMaxLds || (!single && K > s.strips)) return;
+      const BlockShape s = shape_of(kind, L, rows, K);
+      if (s.lds > (size_t)lds || (!single && K > s.strips)) return;
+      if (kind == kBlockPoolLinear && (int64_t)(s.lds / 16) / 256 + 3 > kMaxGroups) return;
       p.shapes.push_back(s);
       longest = std::max(longest, s.step_s);
       issue += s.issue_s * s.strips;
+      move = std::max(move, s.move_s);
       strips += s.strips;
     }
     if (strips > kBlockMaxTasks + (int64_t)Ls.size()) return;
     p.sweeps = K;
     p.tasks = strips;
     const double step = std::max(longest, issue / cus);
-    p.sweep_s = 2 * step + (singles ? 0.0 : kLaunch / K);
+    p.sweep_s = 2 * step + (singles ? 0.0 : (kLaunch + move) / K);
     if (best.shapes.empty() || p.sweep_s < best.sweep_s) best = p;
   };
   if (all_single) consider(1, 0, true);
   if (n >= 2)
     for (int K : {1, 2, 3, 4, 6, 8, 12})
       if (K <= (n + 1) / 2)
-        for (int64_t target = 32; target <= 4096; target += target / 4)
+        for (int64_t target = 32; target <= 20000; target += target / 4)
           consider(K, target, false);
   best.all_single = !best.shapes.empty();
   for (const BlockShape& s : best.shapes) best.all_single = best.all_single && s.strips == 1;
@@ -577,11 +764,32 @@ BlockLattice block_lattice(const ising_lattice* h, const BlockShape& s, int64_t 
   return b;
 }
 
+// Dynamics of a handle as the block kernels know them, or -1 where they have
+// none (generators without a cut of their thresholds).
+int block_kind(const ising_lattice* h) {
+  if (h->pool) return h->pool_linear ? kBlockPoolLinear : kBlockPool;
+  if (h->lcg) return h->lcut.x ? kBlockLcg : -1;
+  return kBlockPhilox;
+}
+
 ising_status enqueue_block_sweeps(ising_lattice* h, const BlockShape& s, int64_t n,
                                   int64_t* dev_EM) {
-  const BlockLattice b = block_lattice(h, s, n, true, dev_EM);
+  BlockLattice b = block_lattice(h, s, n, true, dev_EM);
+  BlockAlt x = {};
+  x.kind = block_kind(h);
+  if (x.kind == kBlockLcg) {
+    b.cut = h->lcut;
+    x.lcg = h->lcg;
+  } else if (x.kind != kBlockPhilox) {
+    x.pool = h->pool;
+    x.pool_shift = (uint32_t)(32 - h->pool_m);
+    x.pool_mask = (uint32_t)((1ull << h->pool_m) - 1);
+  }
   for (int32_t j = 0; j < b.launches; ++j) {
-    hipLaunchKernelGGL(k_block, dim3(s.strips), dim3(s.threads), s.lds, h->stream, b, j);
+    if (x.kind == kBlockPhilox)
+      hipLaunchKernelGGL(k_block, dim3(s.strips), dim3(s.threads), s.lds, h->stream, b, j);
+    else
+      hipLaunchKernelGGL(k_block_alt, dim3(s.strips), dim3(s.threads), s.lds, h->stream, b, x, j);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "block sweep launch");
   }
@@ -589,6 +797,13 @@ ising_status enqueue_block_sweeps(ising_lattice* h, const BlockShape& s, int64_t
     hipLaunchKernelGGL(k_block_finalize, dim3(s.sweeps), dim3(64), 0, h->stream, b);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "block E/M finalisation launch");
+  }
+  if (x.kind == kBlockLcg) {
+    const int64_t words = 2 * h->plane_words;
+    hipLaunchKernelGGL(k_lcg_advance, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 2048)),
+                       dim3(256), 0, h->stream, h->lcg, words, lcg_skip(64 * (uint64_t)n));
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "generator advance launch");
   }
   return ISING_OK;
 }

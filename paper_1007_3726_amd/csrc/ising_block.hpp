@@ -17,9 +17,21 @@ constexpr int kBlockMaxStrips = 256;
 // Strips of a batch (beyond one per lattice).
 constexpr int64_t kBlockMaxTasks = 1024;
 // Largest side whose sweeps may take this form with several strips.
-constexpr int64_t kBlockMaxL = 8704;
-// LDS of one workgroup: two planes of the strip's rows and its halos.
+constexpr int64_t kBlockMaxL = 16384;
+// LDS of one workgroup (two planes of the strip's rows and its halos): half
+// of a compute unit's, and where each has a strip of its own nearly all.
 constexpr int64_t kBlockMaxLds = 65536;
+constexpr int64_t kBlockLoneLds = 156 * 1024;
+
+// Dynamics of a block.
+enum { kBlockPhilox = 0, kBlockLcg = 1, kBlockPool = 2, kBlockPoolLinear = 3 };
+
+struct BlockAlt {
+  int32_t kind;
+  uint32_t* lcg;         // generators [2][L][W]
+  const uint64_t* pool;  // (r4, r8) pairs
+  uint32_t pool_shift, pool_mask;
+};
 
 struct BlockLattice {
   uint64_t* buf[2];    // planes; several strips: launch j reads buf[j & 1], writes the other
@@ -49,6 +61,7 @@ struct BlockShape {
   size_t lds = 0;
   double step_s = 0.0;   // model: seconds of a mean colour step of one strip alone on a CU
   double issue_s = 0.0;  // of which its CU's SIMDs issue for it
+  double move_s = 0.0;   // seconds to load and store one strip
 };
 
 // Sites of a batch above which it is not worth planning: its colour steps

@@ -550,25 +550,31 @@ __device__ __forceinline__ void masks_lcg(uint32_t& z, uint32_t c, uint32_t e, u
 // |int32(x)| + 1 = |y - 2^31| + 1 is one v_sad_u32, to which the three-way cut
 // of the thresholds + 1 applies: 4.5 lane-operations per site against 6
 // (16384^2, 100 sweeps: 5.77 -> 4.77 ms).
+template <int NB>
+__device__ __forceinline__ void lcg_codes(uint32_t (&acc)[4], uint32_t& y, uint32_t X,
+                                          uint64_t C) {
+#pragma unroll
+  for (int b = NB - 1; b >= 0; --b) {
+#pragma unroll
+    for (int j = 3; j >= 0; --j) {
+      y = lcg_next(y, kLcgC);
+      const uint32_t mid = 0x80000000u;
+      const uint32_t v = (y > mid ? y : mid) - (y > mid ? mid : y) + 1u;
+      cut_in(acc[j], v, X, C);
+    }
+    // four values at a time: without this the whole chain would run first
+    // and its values spill
+    asm("" : "+v"(y), "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
+  }
+}
+
 __device__ __forceinline__ void masks_lcg_cut(uint32_t& y, uint32_t X, uint64_t C, uint64_t& up,
                                               uint64_t& low) {
   uint32_t u[2], l[2];
 #pragma unroll
   for (int h = 1; h >= 0; --h) {
     uint32_t acc[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int b = 7; b >= 0; --b) {
-#pragma unroll
-      for (int j = 3; j >= 0; --j) {
-        y = lcg_next(y, kLcgC);
-        const uint32_t mid = 0x80000000u;
-        const uint32_t v = (y > mid ? y : mid) - (y > mid ? mid : y) + 1u;
-        cut_in(acc[j], v, X, C);
-      }
-      // four values at a time: without this the whole chain would run first
-      // and its values spill
-      asm("" : "+v"(y), "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]));
-    }
+    lcg_codes<8>(acc, y, X, C);
     cut_planes(acc, u[h], l[h]);
   }
   up = ((uint64_t)u[1] << 32) | u[0];

@@ -240,7 +240,7 @@ bool strip_args(const ising_lattice* h, TileArgs* out) {
 }
 
 bool use_small_path(const ising_lattice* h) {
-  return h->lcg == nullptr && h->pool == nullptr &&
+  return block_kind(h) >= 0 &&
          2 * h->plane_words * (int64_t)sizeof(uint64_t) <= h->tune.small_lds_bytes;
 }
 
@@ -248,8 +248,8 @@ bool use_small_path(const ising_lattice* h) {
 // strip shape) with a spare copy of its planes.  One sweep takes two launches
 // either way.
 bool use_block_path(const ising_lattice* h, int64_t n) {
-  return h->lcg == nullptr && h->pool == nullptr && h->spare != nullptr && n >= 2 &&
-         h->L <= kBlockMaxL && h->tune.form == ISING_FORM_TILE && h->tune.rpw == 0;
+  return block_kind(h) >= 0 && h->spare != nullptr && n >= 2 && h->L <= kBlockMaxL &&
+         h->tune.form == ISING_FORM_TILE && h->tune.rpw == 0;
 }
 
 // (d, m) of the LCG decision (x + d) < m for threshold t' (ising_device.hpp)
@@ -306,15 +306,18 @@ static ising_status fill_pool(ising_lattice* h) {
 
 ising_status enqueue_sweeps(ising_lattice* h, int64_t n, int64_t* dev_EM) {
   if (n == 0) return ISING_OK;
-  if (use_small_path(h)) return enqueue_block_sweeps(h, block_shape_single(h->L), n, dev_EM);
+  if (use_small_path(h))
+    return enqueue_block_sweeps(h, block_shape_single(block_kind(h), h->L), n, dev_EM);
   if (use_block_path(h, n)) {
-    // the shape depends on n only below kBlockPlanN sweeps; kept with the handle
-    const int64_t key = std::min(n, kBlockPlanN);
+    // the shape depends on the dynamics, and on n only below kBlockPlanN
+    // sweeps; kept with the handle
+    const int kind = block_kind(h);
+    const int64_t key = std::min(n, kBlockPlanN) + (kBlockPlanN + 1) * kind;
     if (h->block_n != key) {
       const int cus = device_cus(h->device);
-      const BlockPlan plan = plan_blocks({h->L}, key, cus);
+      const BlockPlan plan = plan_blocks(kind, {h->L}, std::min(n, kBlockPlanN), cus);
       h->block = plan.shapes.empty() ||
-                         plan.sweep_s >= launch_per_step_seconds((double)h->plane_words, cus)
+                         plan.sweep_s >= launch_per_step_seconds(kind, (double)h->plane_words, cus)
                      ? BlockShape()
                      : plan.shapes[0];
       h->block_n = key;

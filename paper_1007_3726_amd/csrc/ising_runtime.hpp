@@ -74,7 +74,7 @@ struct ising_lattice {
   int device;
   ising::Tuning tune;
   ising::BlockShape block;  // strips 0: colour steps are launches
-  int64_t block_n;          // the sweeps per call (at most kBlockPlanN) it is for, 0: none yet
+  int64_t block_n;          // the sweeps per call and dynamics it is for, 0: none yet
 };
 
 namespace ising {

@@ -141,3 +141,65 @@ def test_shuffled_barriers(I, L, seed):
     s, oem = oracle.run(L, 1 / 2.269185, 3, 0, workloads.INIT_HOT, n)
     assert np.array_equal(em, oem)
     assert np.array_equal(lat.get_spins(), s)
+
+
+@pytest.mark.parametrize("n", [2, 7, 26])
+@pytest.mark.parametrize("L", [8, 64, 72, 128, 136, 200, 264, 520, 1000, 2056])
+def test_generators(I, L, n):
+    """The paper's generators: lattice, series and generator states, over two
+    calls (the second from advanced states)."""
+    T = 2.3
+    print("case lcg L=%d n=%d" % (L, n), flush=True)
+    lat = I.Lattice(L, seed=7, init=workloads.INIT_HOT, beta=1 / T)
+    lat.use_lcg()
+    s = oracle.init(L, 7, 0, workloads.INIT_HOT)
+    st = oracle.lcg_seed(L, 7)
+    for k in (n, 3):
+        em = lat.sweep_em(k).cpu().numpy()
+        assert np.array_equal(em, oracle.lcg_sweeps(s, 1 / T, st, k))
+        assert np.array_equal(lat.get_spins(), s)
+        assert np.array_equal(lat.lcg_states(), st)
+
+
+@pytest.mark.parametrize("linear", [False, True])
+@pytest.mark.parametrize("L,m,n", [(8, 10, 5), (64, 10, 40), (72, 11, 9), (128, 12, 26),
+                                   (136, 10, 26), (264, 10, 9), (1000, 12, 9), (1024, 10, 26),
+                                   (4096, 14, 5), (9000, 16, 5)])
+def test_pools(I, L, m, n, linear):
+    T = 2.2
+    print("case pool L=%d m=%d n=%d linear=%d" % (L, m, n, linear), flush=True)
+    lat = I.Lattice(L, seed=5, stream_id=3, init=workloads.INIT_HOT, beta=1 / T)
+    lat.use_pool(m, linear=linear)
+    s = oracle.init(L, 5, 3, workloads.INIT_HOT)
+    t = 0
+    for k in (n, 3):
+        em = lat.sweep_em(k).cpu().numpy()
+        assert np.array_equal(em, oracle.pool_sweeps(s, 1 / T, 5, 3, t, k, m, linear))
+        assert np.array_equal(lat.get_spins(), s)
+        t += k
+
+
+def test_largest_pool_block(I):
+    """16384^2, linear reads: strips of 64 rows that fill a compute unit's LDS."""
+    L, m, n, T = 16384, 12, 4, 2.2
+    lat = I.Lattice(L, seed=5, stream_id=3, init=workloads.INIT_COLD_UP, beta=1 / T)
+    lat.use_pool(m, linear=True)
+    em = lat.sweep_em(n).cpu().numpy()
+    s = oracle.init(L, 5, 3, workloads.INIT_COLD_UP)
+    assert np.array_equal(em, oracle.pool_sweeps(s, 1 / T, 5, 3, 0, n, m, True))
+    assert np.array_equal(lat.get_spins(), s)
+
+
+@pytest.mark.parametrize("kind", ["lcg", "pool", "linear"])
+def test_shuffled_barriers_of_the_alternative_dynamics(I, kind):
+    L, n, T = 520, 9, 2.25
+    ems = []
+    for seed in (0, 77):
+        I.debug_perturb(seed)
+        try:
+            lat = I.Lattice(L, seed=3, init=workloads.INIT_HOT, beta=1 / T)
+            lat.use_lcg() if kind == "lcg" else lat.use_pool(12, linear=kind == "linear")
+            ems.append(lat.sweep_em(n).cpu().numpy())
+        finally:
+            I.debug_perturb(0)
+    assert np.array_equal(ems[0], ems[1])
