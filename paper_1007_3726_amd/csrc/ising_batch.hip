@@ -307,7 +307,7 @@ static ising_status run_blocks(ising_lattice* const* hs, const std::vector<int>&
   const BlockLattice* tab = (const BlockLattice*)work;
   for (int j = 0; j < launches && e == hipSuccess; ++j)
     e = launch_block_many(stream, tab, (const BlockTask*)(work + bl.off_tasks), (int)tasks.size(),
-                          threads, lds, j);
+                          device_cus(hs[idx[0]]->device), threads, lds, j);
   if (e == hipSuccess && finalize) e = launch_block_finalize_many(stream, tab, nl);
   // the host image must outlive the upload: wait before it goes, unless the
   // caller keeps it

@@ -80,7 +80,7 @@ BlockLattice block_lattice(const ising_lattice* h, const BlockShape& s, int64_t 
 ising_status enqueue_block_sweeps(ising_lattice* h, const BlockShape& s, int64_t n,
                                   int64_t* dev_EM);
 hipError_t launch_block_many(hipStream_t st, const BlockLattice* tab, const BlockTask* tasks,
-                             int ntasks, int threads, size_t lds, int j);
+                             int ntasks, int cus, int threads, size_t lds, int j);
 hipError_t launch_block_finalize_many(hipStream_t st, const BlockLattice* tab, int nlat);
 // Compute units of a device (cached), 0 if it has no properties.
 int device_cus(int device);

@@ -29,8 +29,8 @@
 // Bound by the instructions of one workgroup's steps (halves computed in
 // halos included) plus 5 us per launch.  Measured, us per sweep with the
 // (E, M) series, a launch per colour step (or the LDS kernel that this one
-// replaced) before: 64^2 4.29 -> 0.95, 512^2 10.3 -> 2.5, 1002^2 16.6 -> 4.2,
-// 4096^2 11.7 -> 10.4; 24 lattices of 8^2 to 64^2 8.95 -> 1.12.
+// replaced) before: 64^2 4.29 -> 0.90, 512^2 10.3 -> 2.5, 1002^2 16.6 -> 3.9,
+// 4096^2 11.7 -> 10.3; 24 lattices of 8^2 to 64^2 8.95 -> 1.15.
 //
 // The paper's generators and pools run in the same blocks.  A word's
 // generator is affine in its steps, so every lane of a half jumps to its own
@@ -99,7 +99,7 @@ enum { kCompare = 0, kCut = 1, kAnyRow = 2, kAnyRowCut = 3, kLcg = 4, kPool = 5,
 // Random planes of this lane's 32 / LS sites of a half, at their places in
 // the half (bits of other lanes' sites mean nothing).  `at`: colour-local
 // index of the lane's first site, over 4 where rows are whole blocks.
-template <int LS, int MODE>
+template <int LS, int MODE, bool SERIAL>
 __device__ __forceinline__ void half_planes(uint32_t at, int sub, uint32_t k0, uint32_t k1,
                                             uint32_t t, uint32_t ctr3, uint32_t t4, uint32_t t8,
                                             uint32_t cut_x, uint64_t cut_c, uint32_t& a, uint32_t& b) {
@@ -107,12 +107,13 @@ __device__ __forceinline__ void half_planes(uint32_t at, int sub, uint32_t k0, u
   a = b = 0;
   if (MODE == kCut) {
     uint32_t acc[4] = {0, 0, 0, 0};
-    cut_blocks<0, NB - 1, false>(acc, (uint64_t)kM0 * at, 0, k0, k1, t, ctr3, cut_x, cut_c);
+    cut_blocks<0, NB - 1, SERIAL>(acc, (uint64_t)kM0 * at, 0, k0, k1, t, ctr3, cut_x, cut_c);
     cut_planes(acc, a, b);
   } else if (MODE == kCompare) {
 #pragma unroll
     for (int q = NB - 1; q >= 0; --q) {
       uint32_t x0 = at + (uint32_t)q, x1 = 0, x2 = t, x3 = ctr3;
+      if (SERIAL) asm("" : "+v"(x0), "+v"(a), "+v"(b));
       philox4x32_10(x0, x1, x2, x3, k0, k1);
       shift_in4(a, b, x0, x1, x2, x3, t4, t8);
     }
@@ -122,16 +123,18 @@ __device__ __forceinline__ void half_planes(uint32_t at, int sub, uint32_t k0, u
     const uint32_t g = at >> 2, r = at & 3u;
     if (MODE == kAnyRowCut) {
       uint32_t acc[4] = {0, 0, 0, 0};
-      cut_blocks<1, NB - 1, false>(acc, (uint64_t)kM0 * g, 0, k0, k1, t, ctr3, cut_x, cut_c);
+      cut_blocks<1, NB - 1, SERIAL>(acc, (uint64_t)kM0 * g, 0, k0, k1, t, ctr3, cut_x, cut_c);
       cut_planes(acc, a, b);
     } else {
       for (int q = NB; q >= 1; --q) {
         uint32_t x0 = g + (uint32_t)q, x1 = 0, x2 = t, x3 = ctr3;
+        if (SERIAL) asm("" : "+v"(x0), "+v"(a), "+v"(b));
         philox4x32_10(x0, x1, x2, x3, k0, k1);
         shift_in4(a, b, x0, x1, x2, x3, t4, t8);
       }
     }
     uint32_t x0 = g, x1 = 0, x2 = t, x3 = ctr3, a0 = 0, b0 = 0;
+    if (SERIAL) asm("" : "+v"(x0), "+v"(a), "+v"(b));
     philox4x32_10(x0, x1, x2, x3, k0, k1);
     shift_in4(a0, b0, x0, x1, x2, x3, t4, t8);
     if (MODE == kAnyRowCut) {  // (r4, r8) -> (up, low)
@@ -242,7 +245,7 @@ __device__ __forceinline__ void pool_starts(const Lat& L, const AltStrip& x, int
 // last row's and only their stores are left out (whole waves without work
 // skip it), and with ONE (a single strip, one row per lane) everything but
 // the uniforms and the spins is loop-invariant.
-template <int LS, int MODE, bool ONE, typename Lat>
+template <int LS, int MODE, bool ONE, bool SERIAL, typename Lat>
 __device__ __forceinline__ void block_steps(const Lat& L, uint32_t* lds, uint2* counts, int strip,
                                             int j, int R, int H, int own, int y0, int64_t s0,
                                             int K, AltStrip alt) {
@@ -256,7 +259,7 @@ __device__ __forceinline__ void block_steps(const Lat& L, uint32_t* lds, uint2* 
   // few lanes count: they add in LDS; many: the wave sums first
   constexpr bool kAddCounts = LS >= 4;
   const bool wrap = ONE || L.strips == 1;
-  const bool em = L.EM != nullptr;
+  const bool em = L.EM != nullptr, perturbed = L.perturb != 0;
   const int per = L.nh * LS, stride = 2 * L.W, pass = L.pass;
   int r0 = (int)threadIdx.x / per;
   const int hw = ((int)threadIdx.x - r0 * per) / LS, sub = (int)threadIdx.x % LS;
@@ -282,6 +285,11 @@ __device__ __forceinline__ void block_steps(const Lat& L, uint32_t* lds, uint2* 
   const Affine own_skip =
       MODE == kLcg ? lcg_skip((uint32_t)(64 - 32 * (hw & 1) - 4 * NB * (sub + 1))) : Affine{1u, 0u};
   const Affine sweep_skip = MODE == kLcg ? lcg_skip(64) : Affine{1u, 0u};
+  // With two waves on a SIMD the loop is bound by instruction fetch as much as
+  // by issue: its rare parts stand out of line (one taken branch per sweep),
+  // and it is placed the same whatever code precedes it.  1000 sweeps of 64^2:
+  // 0.89 ms; with the branches 0.90 to 1.01, by its place.
+  asm volatile(".p2align 8");
   for (int k = 0; k < K; ++k) {
     const uint32_t t = L.t + (uint32_t)(s0 + k);
     uint2* const slot = &counts[(k & (kEmSlots - 1)) * kMaxWaves + wave];
@@ -330,8 +338,8 @@ __device__ __forceinline__ void block_steps(const Lat& L, uint32_t* lds, uint2* 
           x = alt.sweep.a * x + alt.sweep.b;
           lcg_half<LS>(own_skip.a * x + own_skip.b, sub, cut_x, cut_c, a, b);
         } else if (!kPooled) {
-          half_planes<LS, MODE>((uint32_t)y * rowlen + col, sub, k0, k1, t, sid4 | (uint32_t)c, t4,
-                                t8, cut_x, cut_c, a, b);
+          half_planes<LS, MODE, SERIAL>((uint32_t)y * rowlen + col, sub, k0, k1, t,
+                                        sid4 | (uint32_t)c, t4, t8, cut_x, cut_c, a, b);
         }
         const uint32_t n1 = bfi(left, (n0 << 1) | (sd >> shl), (n0 >> 1) | (sd << shr));
         uint32_t f = kCutPlanes ? flip_half_cut(s_old, n0, n1, n2, n3, a, b)
@@ -377,13 +385,13 @@ __device__ __forceinline__ void block_steps(const Lat& L, uint32_t* lds, uint2* 
         }
       }
       if (MODE == kPoolLinear) pool_starts(L, alt, s0, s + 1);
-      perturb_wave(L.perturb, (uint32_t)s);
+      if (__builtin_expect(perturbed, 0)) perturb_wave(L.perturb, (uint32_t)s);
       __syncthreads();
     }
     if (MODE == kLcg)
       alt.sweep = Affine{sweep_skip.a * alt.sweep.a, sweep_skip.a * alt.sweep.b + sweep_skip.b};
     // the slots are written again only after the next colour-0 barrier
-    if (em && ((k & (kEmSlots - 1)) == kEmSlots - 1 || k == K - 1))
+    if (__builtin_expect(em && ((k & (kEmSlots - 1)) == kEmSlots - 1 || k == K - 1), 0))
       drain_counts(L, counts, strip, j, s0, k & ~(kEmSlots - 1), (k & (kEmSlots - 1)) + 1);
   }
 }
@@ -436,7 +444,7 @@ __device__ __forceinline__ void reduce_last(const Lat& L, int first, int step) {
 
 // Lat: BlockLattice, as a kernel argument or in a table (constant memory).
 // ALT: the alternative dynamics x of a lone lattice instead of Philox.
-template <bool ALT, typename Lat>
+template <bool ALT, bool SERIAL, typename Lat>
 __device__ __forceinline__ void block_run(const Lat& L, const BlockAlt* x, int strip, int j,
                                           uint32_t* lds) {
   __shared__ uint2 counts[kEmSlots * kMaxWaves];
@@ -492,9 +500,11 @@ __device__ __forceinline__ void block_run(const Lat& L, const BlockAlt* x, int s
 #define ISING_BLOCK(LS, MODE)                                                           \
   do {                                                                                  \
     if (wrap && R <= L.pass)                                                            \
-      block_steps<LS, MODE, true>(L, lds, counts, strip, j, R, H, own, y0, s0, K, alt); \
+      block_steps<LS, MODE, true, SERIAL>(L, lds, counts, strip, j, R, H, own, y0, s0,  \
+                                          K, alt);                                      \
     else                                                                                \
-      block_steps<LS, MODE, false>(L, lds, counts, strip, j, R, H, own, y0, s0, K, alt); \
+      block_steps<LS, MODE, false, SERIAL>(L, lds, counts, strip, j, R, H, own, y0, s0, \
+                                           K, alt);                                     \
   } while (0)
   if constexpr (ALT) {
     if (x->kind == kBlockPool) {
@@ -552,13 +562,13 @@ __device__ __forceinline__ void block_run(const Lat& L, const BlockAlt* x, int s
 
 __global__ __launch_bounds__(1024) void k_block(BlockLattice L, int j) {
   extern __shared__ uint64_t block_lds[];
-  block_run<false>(L, nullptr, blockIdx.x, j, (uint32_t*)block_lds);
+  block_run<false, false>(L, nullptr, blockIdx.x, j, (uint32_t*)block_lds);
 }
 
 // The paper's generators and pools.
 __global__ __launch_bounds__(1024) void k_block_alt(BlockLattice L, BlockAlt x, int j) {
   extern __shared__ uint64_t block_lds[];
-  block_run<true>(L, &x, blockIdx.x, j, (uint32_t*)block_lds);
+  block_run<true, false>(L, &x, blockIdx.x, j, (uint32_t*)block_lds);
 }
 
 // All generators `skip` steps on (the strips of a call derive their states
@@ -569,13 +579,29 @@ __global__ __launch_bounds__(256) void k_lcg_advance(uint32_t* state, int64_t n,
     state[i] = skip.a * state[i] + skip.b;
 }
 
-// The same for a table of lattices; tasks are (lattice, strip).
-__global__ __launch_bounds__(1024) void k_block_many(const BlockLattice* tab,
-                                                     const BlockTask* tasks, int j) {
+// The same for a table of lattices; tasks are (lattice, strip).  Up to one
+// task per compute unit, a task has its SIMDs to itself and its blocks
+// interleave (SERIAL: no, 113 VGPRs); more tasks share them, two workgroups of
+// 16 waves at a time (63 VGPRs).  1000 sweeps of 24 lattices of 8^2 to 64^2:
+// 1.15 ms against 1.20 with SERIAL; a queue of 24 requests up to 2048^2: 29.65
+// ms all interleaved, 28.9 all SERIAL, 28.75 by this rule.
+template <bool SERIAL>
+__device__ __forceinline__ void block_many(const BlockLattice* tab, const BlockTask* tasks,
+                                           int j) {
   extern __shared__ uint64_t block_lds[];
   const BlockTask task = ((const BlockTask ISING_CONSTANT_AS*)tasks)[blockIdx.x];
-  block_run<false>(((const BlockLattice ISING_CONSTANT_AS*)tab)[task.lattice], nullptr, task.strip,
-                   j, (uint32_t*)block_lds);
+  block_run<false, SERIAL>(((const BlockLattice ISING_CONSTANT_AS*)tab)[task.lattice], nullptr,
+                           task.strip, j, (uint32_t*)block_lds);
+}
+
+__global__ __launch_bounds__(1024) void k_block_few(const BlockLattice* tab,
+                                                    const BlockTask* tasks, int j) {
+  block_many<false>(tab, tasks, j);
+}
+
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void k_block_many(
+    const BlockLattice* tab, const BlockTask* tasks, int j) {
+  block_many<true>(tab, tasks, j);
 }
 
 // (E, M) of every lattice's last launch.
@@ -809,8 +835,11 @@ ising_status enqueue_block_sweeps(ising_lattice* h, const BlockShape& s, int64_t
 }
 
 hipError_t launch_block_many(hipStream_t st, const BlockLattice* tab, const BlockTask* tasks,
-                             int ntasks, int threads, size_t lds, int j) {
-  hipLaunchKernelGGL(k_block_many, dim3(ntasks), dim3(threads), lds, st, tab, tasks, j);
+                             int ntasks, int cus, int threads, size_t lds, int j) {
+  if (ntasks <= cus)
+    hipLaunchKernelGGL(k_block_few, dim3(ntasks), dim3(threads), lds, st, tab, tasks, j);
+  else
+    hipLaunchKernelGGL(k_block_many, dim3(ntasks), dim3(threads), lds, st, tab, tasks, j);
   return hipGetLastError();
 }
 

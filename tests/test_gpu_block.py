@@ -109,6 +109,14 @@ def test_batches(I, spec):
         assert np.array_equal(lats[i].get_spins(), s), (L, T)
 
 
+# more strips than compute units: two workgroups share one
+@pytest.mark.parametrize("spec", [
+    [(L, T) for T in (1.4, 2.25, 6.5) for L in (4, 8, 10, 32, 64, 66, 100, 128, 130, 136, 200)] * 8,
+    [(2048, 2.25), (2050, 2.25), (2048, 1.4), (2050, 1.4), (512, 2.25), (1002, 2.0), (64, 2.0)]])
+def test_batches_of_many_strips(I, spec):
+    test_batches(I, spec)
+
+
 def test_served_requests_of_uneven_length(I):
     reqs = [{"L": L, "beta": 1 / T, "seed": 40 + i, "stream_id": i, "init": workloads.INIT_HOT,
              "n_sweeps": n, "record_series": True, "return_spins": True}
