@@ -30,7 +30,7 @@
 // halos included) plus 5 us per launch.  Measured, us per sweep with the
 // (E, M) series, a launch per colour step (or the LDS kernel that this one
 // replaced) before: 64^2 4.29 -> 0.90, 512^2 10.3 -> 2.5, 1002^2 16.6 -> 3.9,
-// 4096^2 11.7 -> 10.3; 24 lattices of 8^2 to 64^2 8.95 -> 1.15.
+// 4096^2 11.7 -> 10.3; 24 lattices of 8^2 to 64^2 8.95 -> 1.01.
 //
 // The paper's generators and pools run in the same blocks.  A word's
 // generator is affine in its steps, so every lane of a half jumps to its own
@@ -583,7 +583,7 @@ __global__ __launch_bounds__(256) void k_lcg_advance(uint32_t* state, int64_t n,
 // task per compute unit, a task has its SIMDs to itself and its blocks
 // interleave (SERIAL: no, 113 VGPRs); more tasks share them, two workgroups of
 // 16 waves at a time (63 VGPRs).  1000 sweeps of 24 lattices of 8^2 to 64^2:
-// 1.15 ms against 1.20 with SERIAL; a queue of 24 requests up to 2048^2: 29.65
+// 1.15 ms against 1.20 with SERIAL (0.15 of both on the host); a queue of 24 requests up to 2048^2: 29.65
 // ms all interleaved, 28.9 all SERIAL, 28.75 by this rule.
 template <bool SERIAL>
 __device__ __forceinline__ void block_many(const BlockLattice* tab, const BlockTask* tasks,
@@ -702,6 +702,21 @@ bool block_fits_single(int64_t L) {
   return L <= kBlockMaxL && 2 * (int64_t)plane_bytes(L) <= kBlockMaxLds;
 }
 
+// Issue time of a colour step on the busiest compute unit: the strips go out
+// from the largest down, so that it has the first, the first after all units
+// have one, and so on.  A queue of 24 requests up to 2048^2: 28.9 ms with 379
+// strips, the best if they spread evenly over 256 units, 25.7 ms this way.
+static double busiest_issue(const std::vector<BlockShape>& shapes, int cus) {
+  std::vector<std::pair<double, int64_t>> of;
+  for (const BlockShape& s : shapes) of.push_back({s.issue_s, s.strips});
+  std::sort(of.rbegin(), of.rend());
+  double sum = 0;
+  int64_t seen = 0, next = 0;  // strips so far; the unit's next strip
+  for (const auto& o : of)
+    for (seen += o.second; next < seen; next += std::max(cus, 1)) sum += o.first;
+  return sum;
+}
+
 // The cheapest cut of a set of lattices by the model: sweeps per launch K,
 // and strips of about `target` halves per mean colour step, so that the
 // strips of all lattices are about equal.  A lattice that fits one workgroup
@@ -714,7 +729,7 @@ BlockPlan plan_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int c
   const int64_t lds = Ls.size() == 1 ? kBlockLoneLds : kBlockMaxLds;
   auto consider = [&](int K, int64_t target, bool singles) {
     BlockPlan p;
-    double longest = 0, issue = 0, move = 0;
+    double longest = 0, move = 0;
     int64_t strips = 0;
     for (int64_t L : Ls) {
       const int64_t nh = (L / 2 + 31) / 32;
@@ -729,16 +744,19 @@ BlockPlan plan_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int c
       const BlockShape s = shape_of(kind, L, rows, K);
       if (s.lds > (size_t)lds || (!single && K > s.strips)) return;
       if (kind == kBlockPoolLinear && (int64_t)(s.lds / 16) / 256 + 3 > kMaxGroups) return;
+      // no cheaper than the best even if this strip is the longest (planning
+      // 24 lattices took 0.15 ms of the host without this line)
+      if (!best.shapes.empty() && 2 * s.step_s + (singles ? 0.0 : kLaunch / K) >= best.sweep_s)
+        return;
       p.shapes.push_back(s);
       longest = std::max(longest, s.step_s);
-      issue += s.issue_s * s.strips;
       move = std::max(move, s.move_s);
       strips += s.strips;
     }
     if (strips > kBlockMaxTasks + (int64_t)Ls.size()) return;
     p.sweeps = K;
     p.tasks = strips;
-    const double step = std::max(longest, issue / cus);
+    const double step = std::max(longest, busiest_issue(p.shapes, cus));
     p.sweep_s = 2 * step + (singles ? 0.0 : (kLaunch + move) / K);
     if (best.shapes.empty() || p.sweep_s < best.sweep_s) best = p;
   };
