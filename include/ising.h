@@ -165,6 +165,8 @@ ISING_API ising_status ising_get_info(const ising_t *h, int64_t *L, int64_t *wor
  * ising_multi_sweep_form, whatever form it forces) needs for these handles
  * (same conditions on the handles as there; 0 when no lattice can take the
  * batched kernels).  The bytes depend only on the lattice sides.  Host only.
+ * Where some side is no multiple of 8 this includes tables without which the
+ * call still runs, those lattices one after another.
  */
 ISING_API ising_status ising_multi_sweep_work_bytes(ising_t *const *hs, int32_t count,
                                                     size_t *bytes);

@@ -364,11 +364,31 @@ static size_t work_bytes_for(ising_lattice* const* hs, const std::vector<int>& t
   return std::max(fused_layout(nl, ntiles).bytes, block_layout(nl, nl).bytes);
 }
 
+// Whether the sides let a whole batch run in blocks (a lattice of several
+// strips also needs its spare copy); fills the sides and the words of a plane.
+static bool blocks_allowed(ising_lattice* const* hs, int32_t count, std::vector<int64_t>* Ls,
+                           double* words) {
+  double sites = 0;
+  for (int i = 0; i < count; ++i) {
+    if (hs[i]->L > kBlockMaxL) return false;
+    sites += (double)hs[i]->L * hs[i]->L;
+    if (Ls) Ls->push_back(hs[i]->L);
+    if (words) *words += (double)hs[i]->plane_words;
+  }
+  return sites <= kBlockMaxSites;
+}
+
 size_t batch_work_bytes(ising_lattice* const* hs, int32_t count, const BatchOptions& opt) {
   std::vector<int> tiled, other;
   std::vector<TileArgs> targs;
   classify(hs, count, opt, tiled, other, targs);
-  return work_bytes_for(hs, tiled, targs);
+  size_t bytes = work_bytes_for(hs, tiled, targs);
+  // lattices that the tiles leave to the plain path, one after another, can
+  // advance together in blocks: 200 sweeps of 16 x 1002^2 12.3 -> 2.5 ms.
+  // (Without this much of a buffer they still run.)
+  if (count > 1 && !other.empty() && blocks_allowed(hs, count, nullptr, nullptr))
+    bytes = std::max(bytes, block_layout(count, count + kBlockMaxTasks).bytes);
+  return bytes;
 }
 
 size_t batch_work_share(int64_t L) {
@@ -404,17 +424,14 @@ ising_status batch_sweeps(ising_lattice* const* hs, int32_t count, int64_t n,
     std::vector<int> all(count);
     std::iota(all.begin(), all.end(), 0);
     std::vector<int64_t> Ls;
-    double sites = 0, words = 0;
-    for (int i = 0; i < count; ++i) {
-      if (!(hs[i]->L <= kBlockMaxL && (hs[i]->spare || block_fits_single(hs[i]->L)))) break;
-      Ls.push_back(hs[i]->L);
-      sites += (double)hs[i]->L * hs[i]->L;
-      words += (double)hs[i]->plane_words;
-    }
-    if ((int)Ls.size() == count && sites <= kBlockMaxSites) {
+    double words = 0;
+    bool spares = true;
+    for (int i = 0; i < count; ++i) spares = spares && (hs[i]->spare || block_fits_single(hs[i]->L));
+    if (spares && blocks_allowed(hs, count, &Ls, &words)) {
       const int cus = device_cus(device);
       const BlockPlan plan = plan_blocks(kBlockPhilox, Ls, std::min(n, kBlockPlanN), cus);
-      bool ok = !plan.shapes.empty() && plan.sweep_s < launch_per_step_seconds(kBlockPhilox, words, cus) &&
+      bool ok = !plan.shapes.empty() &&
+                plan.sweep_s < launch_per_step_seconds(kBlockPhilox, words, cus) &&
                 block_layout(count, plan.tasks).bytes <= work_bytes;
       for (int i = 0; i < count && ok; ++i) ok = plan.shapes[i].strips == 1 || hs[i]->spare;
       if (ok) {

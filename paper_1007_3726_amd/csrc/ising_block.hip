@@ -43,6 +43,9 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
+#include <iterator>
+#include <map>
 
 #include "ising_batch.hpp"
 #include "ising_block.hpp"
@@ -583,8 +586,9 @@ __global__ __launch_bounds__(256) void k_lcg_advance(uint32_t* state, int64_t n,
 // task per compute unit, a task has its SIMDs to itself and its blocks
 // interleave (SERIAL: no, 113 VGPRs); more tasks share them, two workgroups of
 // 16 waves at a time (63 VGPRs).  1000 sweeps of 24 lattices of 8^2 to 64^2:
-// 1.15 ms against 1.20 with SERIAL (0.15 of both on the host); a queue of 24 requests up to 2048^2: 29.65
-// ms all interleaved, 28.9 all SERIAL, 28.75 by this rule.
+// 1.15 ms against 1.20 with SERIAL (0.15 of both on the host); a queue of 24
+// requests up to 2048^2: 27.0 ms all interleaved, 25.8 all SERIAL, 25.4 by this
+// rule.
 template <bool SERIAL>
 __device__ __forceinline__ void block_many(const BlockLattice* tab, const BlockTask* tasks,
                                            int j) {
@@ -653,7 +657,7 @@ static double step_seconds(int kind, double halves, int ls, bool any) {
 }
 
 // Strips of `rows` rows with K sweeps per launch.
-static BlockShape shape_of(int kind, int64_t L, int64_t rows, int K) {
+static BlockShape shape_of(int kind, int64_t L, int64_t rows, int K, int max_ls = 8) {
   BlockShape s;
   const int64_t W = words_per_row(L), nh = (L / 2 + 31) / 32;
   const bool single = rows >= L, any = L % 8 != 0;
@@ -670,7 +674,7 @@ static BlockShape shape_of(int kind, int64_t L, int64_t rows, int K) {
   // sweeps 5.34, 5.57, 6.23, 7.96.
   s.ls = 1;
   const double halves = (double)(mean * nh);
-  for (int ls = 2; ls <= 8 && kind <= kBlockLcg; ls *= 2)
+  for (int ls = 2; ls <= max_ls && kind <= kBlockLcg; ls *= 2)
     if (nh * ls <= 1024 &&
         step_seconds(kind, halves, ls, any) < step_seconds(kind, halves, s.ls, any))
       s.ls = ls;
@@ -706,9 +710,11 @@ bool block_fits_single(int64_t L) {
 // from the largest down, so that it has the first, the first after all units
 // have one, and so on.  A queue of 24 requests up to 2048^2: 28.9 ms with 379
 // strips, the best if they spread evenly over 256 units, 25.7 ms this way.
-static double busiest_issue(const std::vector<BlockShape>& shapes, int cus) {
+static double busiest_issue(const std::vector<BlockShape>& shapes,
+                            const std::vector<std::pair<int64_t, int64_t>>& sides, int cus) {
   std::vector<std::pair<double, int64_t>> of;
-  for (const BlockShape& s : shapes) of.push_back({s.issue_s, s.strips});
+  for (size_t i = 0; i < shapes.size(); ++i)
+    of.push_back({shapes[i].issue_s, shapes[i].strips * sides[i].second});
   std::sort(of.rbegin(), of.rend());
   double sum = 0;
   int64_t seen = 0, next = 0;  // strips so far; the unit's next strip
@@ -720,19 +726,25 @@ static double busiest_issue(const std::vector<BlockShape>& shapes, int cus) {
 // The cheapest cut of a set of lattices by the model: sweeps per launch K,
 // and strips of about `target` halves per mean colour step, so that the
 // strips of all lattices are about equal.  A lattice that fits one workgroup
-// takes a single strip where a strip would be as large.
+// takes a single strip where a strip would be as large.  With more lattices
+// than compute units a lattice's own step counts for less than the
+// instructions in all, so that fewer lanes per half can win: 300 sweeps of 600
+// lattices of 64^2 3.3 -> 1.1 ms, of 128^2 5.3 -> 1.95.
 BlockPlan plan_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int cus) {
-  BlockPlan best;
+  BlockPlan best;  // a shape per distinct side
   bool all_single = true;
   for (int64_t L : Ls) all_single = all_single && block_fits_single(L);
+  std::map<int64_t, int64_t, std::greater<int64_t>> of;
+  for (int64_t L : Ls) ++of[L];
+  const std::vector<std::pair<int64_t, int64_t>> sides(of.begin(), of.end());
   // a lone lattice's strips have a compute unit each
   const int64_t lds = Ls.size() == 1 ? kBlockLoneLds : kBlockMaxLds;
-  auto consider = [&](int K, int64_t target, bool singles) {
+  auto consider = [&](int K, int64_t target, bool singles, int max_ls) {
     BlockPlan p;
     double longest = 0, move = 0;
     int64_t strips = 0;
-    for (int64_t L : Ls) {
-      const int64_t nh = (L / 2 + 31) / 32;
+    for (const auto& side : sides) {
+      const int64_t L = side.first, nh = (L / 2 + 31) / 32;
       // L rows at most in LDS, kBlockMaxStrips strips at most
       int64_t rows = std::max<int64_t>(target / nh - 2 * (int64_t)K, 1);
       rows = std::max(rows, (L + kBlockMaxStrips - 1) / kBlockMaxStrips);
@@ -741,7 +753,7 @@ BlockPlan plan_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int c
         rows = L;
       else if (rows + 4 * (int64_t)K > L)
         return;
-      const BlockShape s = shape_of(kind, L, rows, K);
+      const BlockShape s = shape_of(kind, L, rows, K, max_ls);
       if (s.lds > (size_t)lds || (!single && K > s.strips)) return;
       if (kind == kBlockPoolLinear && (int64_t)(s.lds / 16) / 256 + 3 > kMaxGroups) return;
       // no cheaper than the best even if this strip is the longest (planning
@@ -751,23 +763,31 @@ BlockPlan plan_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int c
       p.shapes.push_back(s);
       longest = std::max(longest, s.step_s);
       move = std::max(move, s.move_s);
-      strips += s.strips;
+      strips += s.strips * side.second;
     }
     if (strips > kBlockMaxTasks + (int64_t)Ls.size()) return;
     p.sweeps = K;
     p.tasks = strips;
-    const double step = std::max(longest, busiest_issue(p.shapes, cus));
+    const double step = std::max(longest, busiest_issue(p.shapes, sides, cus));
     p.sweep_s = 2 * step + (singles ? 0.0 : (kLaunch + move) / K);
     if (best.shapes.empty() || p.sweep_s < best.sweep_s) best = p;
   };
-  if (all_single) consider(1, 0, true);
-  if (n >= 2)
-    for (int K : {1, 2, 3, 4, 6, 8, 12})
-      if (K <= (n + 1) / 2)
-        for (int64_t target = 32; target <= 20000; target += target / 4)
-          consider(K, target, false);
-  best.all_single = !best.shapes.empty();
-  for (const BlockShape& s : best.shapes) best.all_single = best.all_single && s.strips == 1;
+  for (int max_ls = 8; max_ls >= ((int64_t)Ls.size() > cus ? 1 : 8); max_ls /= 2) {
+    if (all_single) consider(1, 0, true, max_ls);
+    if (n >= 2)
+      for (int K : {1, 2, 3, 4, 6, 8, 12})
+        if (K <= (n + 1) / 2)
+          for (int64_t target = 32; target <= 20000; target += target / 4)
+            consider(K, target, false, max_ls);
+  }
+  if (best.shapes.empty()) return best;
+  std::vector<BlockShape> shapes;
+  best.all_single = true;
+  for (int64_t L : Ls) {
+    shapes.push_back(best.shapes[std::distance(of.begin(), of.find(L))]);
+    best.all_single = best.all_single && shapes.back().strips == 1;
+  }
+  best.shapes = shapes;
   return best;
 }
 

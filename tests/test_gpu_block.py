@@ -109,10 +109,13 @@ def test_batches(I, spec):
         assert np.array_equal(lats[i].get_spins(), s), (L, T)
 
 
-# more strips than compute units: two workgroups share one
+# more strips than compute units, two workgroups share one; more lattices than
+# compute units
 @pytest.mark.parametrize("spec", [
     [(L, T) for T in (1.4, 2.25, 6.5) for L in (4, 8, 10, 32, 64, 66, 100, 128, 130, 136, 200)] * 8,
-    [(2048, 2.25), (2050, 2.25), (2048, 1.4), (2050, 1.4), (512, 2.25), (1002, 2.0), (64, 2.0)]])
+    [(2048, 2.25), (2050, 2.25), (2048, 1.4), (2050, 1.4), (512, 2.25), (1002, 2.0), (64, 2.0)],
+    # no side a multiple of 8: together all the same
+    [(1002, 2.2), (10, 2.3), (66, 1.4), (258, 6.5), (1002, 1.4), (514, 2.0)]])
 def test_batches_of_many_strips(I, spec):
     test_batches(I, spec)
 
