@@ -54,8 +54,10 @@ import workloads  # noqa: E402
 VALU_PEAK_LANE_OPS = 256 * 4 * 16 * 2.4e9
 # Algorithmic lane-operations per spin update:
 # a quarter of a Philox4x32-10 block (10 rounds x (2 wide multiplies + 2
-# three-input XORs) / 4 = 10), two threshold compares and two bit inserts.
-ALU_OPS_PER_UPDATE = 14.0
+# three-input XORs) / 4 = 10), one multiply-add and one funnel shift that put
+# a uniform into one of the three classes of the two thresholds, and half an
+# operation that unpacks the classes (four sites per lane operation).
+ALU_OPS_PER_UPDATE = 12.5
 
 
 def parse():
@@ -241,7 +243,7 @@ def bench_served(torch, ising, dev, n_req, arena_gib, quantum, plain_n, plain_ra
 def kernel_sources_sha():
     import hashlib
     h = hashlib.sha256()
-    for f in ("ising_device.hpp", "ising_kernels.hpp", "ising_kernels.hip"):
+    for f in ("ising_cut.hpp", "ising_device.hpp", "ising_kernels.hpp", "ising_kernels.hip"):
         with open(os.path.join(ROOT, "paper_1007_3726_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
@@ -250,8 +252,8 @@ def kernel_sources_sha():
 def plain_kernel(ising, L, tuned):
     """Name of the kernel that runs a colour step of the plain sweep for side L
     under the tuning entry `tuned`."""
-    if 2 * L * ((L // 2 + 63) // 64) * 8 <= tuned["small_lds_bytes"]:
-        return "k_small_sweeps"
+    if L <= 4096 and tuned["form"] != ising.ISING_FORM_STRIP:
+        return "k_block"
     if tuned["form"] == ising.ISING_FORM_STRIP and (L // 2 + 63) // 64 >= 63:
         return "k_strip_sweep"
     return "k_tile_sweep"
@@ -438,11 +440,10 @@ def bench_fss(torch, ising, dev, grid, EMs, discard, per_interval=8, nblocks=20)
             "tc_exact": round(2.0 / math.log(1.0 + math.sqrt(2.0)), 6)}
 
 
-# The paper's per-thread LCG dynamics: one v_mad_u64_u32 per uniform (the
-# chain runs on a shifted state so that the first range test is a bare
-# compare), one add for the second range test, two compares and two bit
-# inserts: 6 lane-operations per spin update.
-LCG_OPS_PER_UPDATE = 6.0
+# The paper's per-thread LCG dynamics: one v_mad_u64_u32 per value, one v_sad
+# for its distance from 0, and 2.5 operations that class it as above: 4.5
+# lane-operations per spin update.
+LCG_OPS_PER_UPDATE = 4.5
 
 
 def bench_lcg(torch, ising, dev, w, steps):

@@ -177,7 +177,8 @@ ISING_API ising_status ising_multi_sweep_work_bytes(ising_t *const *hs, int32_t 
  * equivalent bit for bit to calling ising_sweep(hs[i], n, dev_EM[i]) on
  * each (section 3's checkerboard sweep, Eqs. (1), (3)-(5), per lattice).
  * All lattices advance together in fused launches (or, for batches of small
- * lattices, one persistent launch); see ising_multi_sweep_form.  dev_EM may
+ * and medium lattices, in launches of several sweeps); see
+ * ising_multi_sweep_form.  dev_EM may
  * be NULL or hold NULL entries.  The task tables go to dev_work (device,
  * caller-owned, 256-byte aligned, at least ising_multi_sweep_work_bytes
  * bytes; may be NULL when that is 0); the library allocates no device
@@ -210,8 +211,8 @@ ISING_API ising_status ising_multi_sweep_static(ising_t *const *hs, int32_t coun
  * form -1 lets the cost model choose, 0 forces the fused form (two launches
  * per sweep over the flattened tiles of all lattices, replayed from captured
  * hipGraph chunks of graph_chunk sweeps; 0 disables graphs, -1 keeps the
- * default), 1 forces the packed persistent form (each lattice on one
- * workgroup, one launch for all n sweeps).  Results are bit-identical for
+ * default), 1 forces the packed form (each lattice on one workgroup, one
+ * launch for all n sweeps).  Results are bit-identical for
  * every form.  For tests and tuning.
  */
 ISING_API ising_status ising_multi_sweep_form(ising_t *const *hs, int32_t count, int64_t n,

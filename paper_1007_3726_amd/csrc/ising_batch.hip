@@ -328,8 +328,8 @@ static void classify(ising_lattice* const* hs, int32_t count, const BatchOptions
     // 2^32 words or more (L >= 741456) take the plain path
     if (tile_args(hs[i], &ta) && hs[i]->plane_words < (1ll << 32)) {
       // fine tiles balance best across the flat list; lattices with many
-      // tiles take up to rpw_max row groups per wave (the packed kernel's
-      // LDS staging bounds the shape)
+      // tiles take up to rpw_max row groups per wave (kTileMaxWords words of a
+      // tile at most)
       const int64_t TR1 = 4 * (int64_t)ta.R;
       const int64_t tiles1 = ((hs[i]->L + TR1 - 1) / TR1) * ta.segs;
       int rpw = 1;

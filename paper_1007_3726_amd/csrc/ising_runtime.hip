@@ -105,10 +105,9 @@ bool strip_form(const ising_lattice* h) {
   return h->tune.form == 1 && h->g.W >= kWideMinWords && h->lcg == nullptr && h->pool == nullptr;
 }
 
-// Shape of the tiled half-sweep for this lattice; false when it does not
-// apply (L % 8 != 0, or Philox block indices that cross 2^32 inside a row).
 // Row groups per wave of the tile form for side L: the tuned value `want`
-// if it fits in LDS, else as many as keep >= 2048 tiles (8 per CU) and fit.
+// if a tile stays within kTileMaxWords, else as many as keep >= 2048 tiles
+// (8 per CU) and do.
 int tile_rpw(int64_t L, int want) {
   const int64_t W = words_per_row(L);
   const bool wide = W >= kWideMinWords;
@@ -122,6 +121,8 @@ int tile_rpw(int64_t L, int want) {
   return 1;
 }
 
+// Shape of the tiled colour step for rows of whole Philox blocks; false when
+// it does not apply (L % 8 != 0, or block indices that cross 2^32 in a row).
 bool tile_args(const ising_lattice* h, TileArgs* out) {
   const int64_t L = h->L, W = h->g.W;
   if (L % 8 != 0) return false;
@@ -135,7 +136,7 @@ bool tile_args(const ising_lattice* h, TileArgs* out) {
   const int64_t TR = 4 * (int64_t)a.R * a.RPW;
   a.tiles = ((L + TR - 1) / TR) * a.segs;
   if ((TR + 2) * (a.TW + 2) > kTileMaxWords) return false;
-  // a narrow staged row (W + 2 words) must fit one 64-lane wave pass
+  // whole rows per wave up to 62 words
   if (!wide && a.TW + 2 > 64) return false;
   const bool pow2 = (L & (L - 1)) == 0;
   if ((uint64_t)L * (uint64_t)L / 8 <= (1ull << 32))
