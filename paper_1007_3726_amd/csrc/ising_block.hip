@@ -39,7 +39,7 @@
 // caller's.  A pool's patterns are read from memory, several rows ahead.
 // us per sweep before -> after, LCG / linear pool / random pool: 64^2 9.0 / 8.4
 // / 8.6 -> 0.73 / 0.99 / 1.0; 1024^2 9.7 / 9.7 / 10.9 -> 2.9 / 2.8 / 3.7;
-// 4096^2 10.6 / 9.7 / 12.2 -> 6.7 / 4.4 / 9.3; 16384^2 linear 28.3 -> 22.6.
+// 4096^2 10.6 / 9.7 / 12.2 -> 6.7 / 3.7 / 8.8; 16384^2 linear 28.3 -> 16.1.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -399,6 +399,108 @@ __device__ __forceinline__ void block_steps(const Lat& L, uint32_t* lds, uint2* 
   }
 }
 
+// The same for the pools with a whole word per lane: the VALU bounds a step
+// (75 instructions a half, of which the flip takes 18), and a word's address,
+// row and neighbours cost what a half's do.  us per sweep of a linear pool with
+// a half and a word per lane: 2048^2 3.5, 2.65; 8192^2 7.8, 5.6; 16384^2 22.4,
+// 16.1; random addresses are bound by memory either way.
+template <int MODE, typename Lat>
+__device__ __forceinline__ void pool_word_steps(const Lat& L, uint64_t* lds, uint2* counts,
+                                                int strip, int j, int R, int H, int own, int y0,
+                                                int64_t s0, int K, const AltStrip& alt) {
+  constexpr int kAhead = 4;  // rows whose patterns are on their way
+  const bool wrap = L.strips == 1, em = L.EM != nullptr, perturbed = L.perturb != 0;
+  const int W = L.W, pass = L.pass, side = L.L, wave = (int)threadIdx.x >> 6;
+  int r0 = (int)threadIdx.x / W;
+  const int w = (int)threadIdx.x - r0 * W;
+  if (r0 >= pass) r0 = 1 << 24;  // a lane of no row
+  const bool last = w == W - 1;
+  const int nb = L.half - 64 * (W - 1);  // sites of a row's last word
+  const uint64_t valid = last && nb < 64 ? (1ull << nb) - 1ull : ~0ull;
+  const int wl = w > 0 ? w - 1 : W - 1, wr = last ? 0 : w + 1;
+  const int shl = w > 0 ? 63 : nb - 1, shr = last ? nb - 1 : 63;
+  const int plane = R * W, lastrow = plane - W;
+  const ulonglong2* const pool = (const ulonglong2*)alt.pool;
+  asm volatile(".p2align 8");
+  for (int k = 0; k < K; ++k) {
+    uint2* const slot = &counts[(k & (kEmSlots - 1)) * kMaxWaves + wave];
+    uint32_t anti = 0, up = 0;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const int s = 2 * k + c;
+      const int ra = wrap ? 0 : 1 + s, rb = wrap ? R - 1 : R - 2 - s;
+      uint64_t* const self = lds + (c ? plane : 0);
+      const uint64_t* const other = lds + (c ? 0 : plane);
+      auto global_row = [&](int r) {
+        const int y = y0 + r;
+        return y >= side ? y - side : y;
+      };
+      auto pattern = [&](int want) {
+        const uint32_t iu = (uint32_t)(global_row(want < rb ? want : rb) * W + w);
+        uint32_t addr;
+        if (MODE == kPoolLinear) {
+          int g = (int)((iu >> 8) - alt.group0);
+          if (iu < alt.first) g = (int)(iu >> 8) + alt.wrapped;
+          addr = (alt.starts[c * kMaxGroups + g] + (iu & 255u)) & alt.mask;
+        } else {
+          uint32_t x0 = iu, x1 = 0, x2 = L.t + (uint32_t)(s0 + k), x3 = L.sid4 | (uint32_t)c;
+          philox4x32_10(x0, x1, x2, x3, L.k0, L.k1);
+          addr = x0 >> alt.shift;
+        }
+        return pool[addr];
+      };
+      auto row = [&](int want, ulonglong2 ab) {
+        const int r = want < rb ? want : rb;
+        const int at = (int)__umul24((uint32_t)r, (uint32_t)W);
+        const int am = wrap && r == 0 ? lastrow : at - W;
+        const int ap = wrap && at == lastrow ? 0 : at + W;
+        const bool left = ((global_row(r) + c) & 1) == 0;
+        const uint64_t s_old = self[at + w], n0 = other[at + w];
+        const uint64_t n2 = other[am + w], n3 = other[ap + w];
+        const uint64_t sd = other[at + (left ? wl : wr)];
+        const uint64_t n1 = left ? (n0 << 1) | (sd >> shl) : (n0 >> 1) | (sd << shr);
+        const uint32_t lo = flip_half((uint32_t)s_old, (uint32_t)n0, (uint32_t)n1, (uint32_t)n2,
+                                      (uint32_t)n3, (uint32_t)ab.x, (uint32_t)ab.y);
+        const uint32_t hi = flip_half((uint32_t)(s_old >> 32), (uint32_t)(n0 >> 32),
+                                      (uint32_t)(n1 >> 32), (uint32_t)(n2 >> 32),
+                                      (uint32_t)(n3 >> 32), (uint32_t)(ab.x >> 32),
+                                      (uint32_t)(ab.y >> 32));
+        const uint64_t s_new = s_old ^ ((((uint64_t)hi << 32) | lo) & valid);
+        const bool store = want <= rb;
+        if (store) self[at + w] = s_new;
+        if (c == 1 && em) {
+          const bool on = store && (uint32_t)(r - H) < (uint32_t)own;
+          const uint32_t da = __popcll(s_new ^ n0) + __popcll((s_new ^ n1) & valid) +
+                              __popcll(s_new ^ n2) + __popcll(s_new ^ n3);
+          const uint32_t du = __popcll(s_new) + __popcll(n0);
+          anti += on ? da : 0u;
+          up += on ? du : 0u;
+        }
+      };
+      for (int base = ra; base <= rb; base += pass * kAhead) {
+        ulonglong2 ab[kAhead];
+        // the wave's first lane has its smallest row
+        if (__builtin_amdgcn_readfirstlane(base + r0) > rb) continue;
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) ab[i] = pattern(base + r0 + i * pass);
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i)
+          if (i == 0 || __builtin_amdgcn_readfirstlane(base + r0 + i * pass) <= rb)
+            row(base + r0 + i * pass, ab[i]);
+      }
+      if (c == 1 && em) {
+        const uint32_t wa = wave_total(anti), wu = wave_total(up);
+        if ((threadIdx.x & 63) == 63) *slot = make_uint2(wa, wu);
+      }
+      if (MODE == kPoolLinear) pool_starts(L, alt, s0, s + 1);
+      if (__builtin_expect(perturbed, 0)) perturb_wave(L.perturb, (uint32_t)s);
+      __syncthreads();
+    }
+    if (__builtin_expect(em && ((k & (kEmSlots - 1)) == kEmSlots - 1 || k == K - 1), 0))
+      drain_counts(L, counts, strip, j, s0, k & ~(kEmSlots - 1), (k & (kEmSlots - 1)) + 1);
+  }
+}
+
 // One wave's share of the partials of one sweep (kBlockMaxStrips / 64 strips
 // per lane).
 struct Parts {
@@ -510,7 +612,11 @@ __device__ __forceinline__ void block_run(const Lat& L, const BlockAlt* x, int s
                                            K, alt);                                     \
   } while (0)
   if constexpr (ALT) {
-    if (x->kind == kBlockPool) {
+    if (L.ls == 0 && x->kind == kBlockPool) {
+      pool_word_steps<kPool>(L, lds64, counts, strip, j, R, H, own, y0, s0, K, alt);
+    } else if (L.ls == 0) {
+      pool_word_steps<kPoolLinear>(L, lds64, counts, strip, j, R, H, own, y0, s0, K, alt);
+    } else if (x->kind == kBlockPool) {
       ISING_BLOCK(1, kPool);
     } else if (x->kind == kBlockPoolLinear) {
       ISING_BLOCK(1, kPoolLinear);
@@ -635,13 +741,13 @@ constexpr double kPatternLatency = 1e-6;
 // start anywhere in a Philox block.
 static double pass_instructions(int kind, int ls, bool any) {
   if (kind == kBlockLcg) return ls == 8 ? 85 : ls == 4 ? 105 : ls == 2 ? 140 : 210;
-  if (kind == kBlockPool) return 115;
-  if (kind == kBlockPoolLinear) return 75;
+  if (kind == kBlockPool) return ls == 0 ? 165 : 115;
+  if (kind == kBlockPoolLinear) return ls == 0 ? 105 : 75;
   if (any) return ls == 8 ? 155 : ls == 4 ? 220 : ls == 2 ? 335 : 515;
   return ls == 8 ? 115 : ls == 4 ? 180 : ls == 2 ? 290 : 460;
 }
 
-static double waves_of(double halves, int ls) { return std::ceil(halves * ls / 64); }
+static double waves_of(double halves, int ls) { return std::ceil(halves * (ls ? ls : 0.5) / 64); }
 
 // Seconds of one colour step of a workgroup that updates `halves` halves with
 // the compute unit to itself: the busiest SIMD issues its waves' instructions
@@ -678,7 +784,11 @@ static BlockShape shape_of(int kind, int64_t L, int64_t rows, int K, int max_ls 
     if (nh * ls <= 1024 &&
         step_seconds(kind, halves, ls, any) < step_seconds(kind, halves, s.ls, any))
       s.ls = ls;
-  const int64_t per = nh * s.ls;
+  // pools: a whole word per lane (ls 0) where that leaves enough waves: a lone
+  // wave's step is longer with it (64^2, 128^2 stay with halves)
+  if (kind >= kBlockPool && step_seconds(kind, halves, 0, any) < step_seconds(kind, halves, 1, any))
+    s.ls = 0;
+  const int64_t per = s.ls ? nh * s.ls : W;
   s.pass = (int32_t)std::max<int64_t>(1, std::min<int64_t>(R, 1024 / per));
   s.threads = (int32_t)((s.pass * per + 63) / 64 * 64);
   s.lds = (size_t)(R * W) * (kind == kBlockLcg ? 24 : 16);

@@ -190,6 +190,13 @@ def test_pools(I, L, m, n, linear):
         t += k
 
 
+# a word per lane: last words of 4, 44 and 64 sites, rows of odd and even words
+@pytest.mark.parametrize("linear", [False, True])
+@pytest.mark.parametrize("L,n", [(1032, 27), (2056, 9), (2136, 8), (2048, 11), (3072, 5)])
+def test_pools_of_whole_words(I, L, n, linear):
+    test_pools(I, L, 12, n, linear)
+
+
 def test_largest_pool_block(I):
     """16384^2, linear reads: strips of 64 rows that fill a compute unit's LDS."""
     L, m, n, T = 16384, 12, 4, 2.2
