@@ -477,8 +477,10 @@ def bench_lcg(torch, ising, dev, w, steps):
 
 # Algorithmic HBM bytes per update of the pattern-pool dynamics: the two
 # colour planes (3 bits: read both colours once, write one) plus one
-# 16-byte (r4, r8) pattern pair per 64-site word.
+# 16-byte (r4, r8) pattern pair per 64-site word.  Linear reads up to 16384^2
+# run several sweeps per launch with the planes in LDS: the patterns alone.
 POOL_BYTES_PER_UPDATE = 3 / 8 + 16 / 64
+PATTERN_BYTES_PER_UPDATE = 16 / 64
 HBM_PEAK_BYTES = 8.0e12
 
 
@@ -509,9 +511,11 @@ def bench_pool(torch, ising, dev, w, steps, log2_patterns=22):
         ms = a.elapsed_time(b)
         assert tuple(EM[-1].cpu().tolist()) == lat.measure(), "E/M disagrees with a recount"
         ups = N * w.sweeps * steps / (ms * 1e6)
+        per = PATTERN_BYTES_PER_UPDATE if linear and w.L <= 16384 else POOL_BYTES_PER_UPDATE
         out[name] = {"value": round(ups, 2), "unit": "spin updates/ns",
                      "avg_launch_us": round(ms * 1e3 / (2 * w.sweeps * steps), 3),
-                     "hbm_frac": round(ups * 1e9 * POOL_BYTES_PER_UPDATE / HBM_PEAK_BYTES, 4)}
+                     "bytes_per_update": per,
+                     "hbm_frac": round(ups * 1e9 * per / HBM_PEAK_BYTES, 4)}
         del lat, EM
         torch.cuda.empty_cache()
     return out
