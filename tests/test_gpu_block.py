@@ -221,3 +221,26 @@ def test_shuffled_barriers_of_the_alternative_dynamics(I, kind):
         finally:
             I.debug_perturb(0)
     assert np.array_equal(ems[0], ems[1])
+
+
+# a batch of odd sides runs, to the same result, in a work buffer of any size
+@pytest.mark.parametrize("share", [0.0, 0.5, 1.0])
+def test_odd_batch_with_less_than_its_tables(I, share):
+    import ctypes
+
+    import torch
+    spec = [(258, 2.2), (66, 1.4), (10, 2.3), (1002, 2.2)]
+    lats = [I.Lattice(L, seed=6, stream_id=i, init=workloads.INIT_HOT, beta=1 / T)
+            for i, (L, T) in enumerate(spec)]
+    hs = (ctypes.c_void_p * len(lats))(*[lat.h.value for lat in lats])
+    need = ctypes.c_size_t()
+    I.check(I.lib().ising_multi_sweep_work_bytes(hs, len(lats), ctypes.byref(need)))
+    assert need.value > 0
+    size = int(need.value * share)
+    buf = torch.empty(max(size, 1), dtype=torch.uint8, device="cuda")
+    I.check(I.lib().ising_multi_sweep(hs, len(lats), 12, None, buf.data_ptr() if size else None,
+                                      size))
+    I.check(I.lib().ising_multi_sweep_static(hs, len(lats), 5, None))
+    for i, (L, T) in enumerate(spec):
+        s, _ = oracle.run(L, 1 / T, 6, i, workloads.INIT_HOT, 17)
+        assert np.array_equal(lats[i].get_spins(), s), (L, T)
