@@ -39,7 +39,7 @@ struct BlockLattice {
   int32_t nh, nbl;     // 32-bit halves per row, valid bits of the last one
   int32_t rows;        // rows per strip (L for a single strip)
   int32_t strips;
-  int32_t ls;          // lanes per half: 1, 2, 4 or 8
+  int32_t ls;          // lanes per half: 1, 2, 4 or 8; 0: a lane per word (pools)
   int32_t pass;        // rows per pass of the workgroup
   int32_t threads;     // pass * nh * ls, rounded up to whole waves
   int32_t launches;    // launches that this lattice's n sweeps are dealt over
