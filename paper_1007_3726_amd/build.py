@@ -18,11 +18,11 @@ ARCH = "gfx950"
 
 
 def sources():
-    return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
+    return sorted(glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "*.cpp")))
 
 
 def build(verbose: bool = False) -> str:
-    """Compile every HIP source into paper_1007_3726_amd/libising.so."""
+    """Compile every HIP and C++ source into paper_1007_3726_amd/libising.so."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tmp = LIB + ".tmp"
     cmd = [hipcc, "-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=" + ARCH,

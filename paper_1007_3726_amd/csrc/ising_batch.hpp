@@ -66,13 +66,7 @@ ising_status batch_sweeps(ising_lattice* const* hs, int32_t count, int64_t n,
                           void* work, size_t work_bytes, int* form_out);
 
 // Several sweeps per launch (ising_block.hip).
-BlockShape block_shape_single(int kind, int64_t L);
 int block_kind(const ising_lattice* h);
-bool block_fits_single(int64_t L);
-// Model: seconds per sweep of lattices with `words` words per colour in all
-// when every colour step is a launch.
-double launch_per_step_seconds(int kind, double words, int cus);
-BlockPlan plan_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int cus);
 // One lattice's entry for n sweeps; one_launch: a single strip runs them all
 // in its first launch, else as many per launch as the shape's.
 BlockLattice block_lattice(const ising_lattice* h, const BlockShape& s, int64_t n,

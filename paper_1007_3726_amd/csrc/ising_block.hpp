@@ -4,27 +4,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <vector>
-
 #include "ising_device.hpp"
+#include "ising_plan.hpp"
 
 namespace ising {
-
-// Sweeps of one launch are bounded by the E/M partials of the scratch area:
-// 2 slots x kBlockMaxK sweeps x strips x 8 bytes, strips <= kBlockMaxStrips.
-constexpr int kBlockMaxK = 16;
-constexpr int kBlockMaxStrips = 256;
-// Strips of a batch (beyond one per lattice).
-constexpr int64_t kBlockMaxTasks = 1024;
-// Largest side whose sweeps may take this form with several strips.
-constexpr int64_t kBlockMaxL = 16384;
-// LDS of one workgroup (two planes of the strip's rows and its halos): half
-// of a compute unit's, and where each has a strip of its own nearly all.
-constexpr int64_t kBlockMaxLds = 65536;
-constexpr int64_t kBlockLoneLds = 156 * 1024;
-
-// Dynamics of a block.
-enum { kBlockPhilox = 0, kBlockLcg = 1, kBlockPool = 2, kBlockPoolLinear = 3 };
 
 struct BlockAlt {
   int32_t kind;
@@ -53,30 +36,6 @@ struct BlockLattice {
 
 struct BlockTask {
   int32_t lattice, strip;
-};
-
-// How one lattice is cut: rows per strip, strips and sweeps per launch.
-struct BlockShape {
-  int32_t rows = 0, strips = 0, ls = 1, pass = 0, threads = 0, sweeps = 0;
-  size_t lds = 0;
-  double step_s = 0.0;   // model: seconds of a mean colour step of one strip alone on a CU
-  double issue_s = 0.0;  // of which its CU's SIMDs issue for it
-  double move_s = 0.0;   // seconds to load and store one strip
-};
-
-// Sites of a batch above which it is not worth planning: its colour steps
-// take several launches' time.
-constexpr double kBlockMaxSites = 6.4e7;
-// Calls of at least this many sweeps are all cut alike.
-constexpr int64_t kBlockPlanN = 24;
-
-// The cut of a set of lattices (one shape each, in order).
-struct BlockPlan {
-  std::vector<BlockShape> shapes;  // empty: the set has none
-  int32_t sweeps = 0;              // per launch
-  int64_t tasks = 0;               // strips in all
-  bool all_single = false;         // every lattice in one strip: all sweeps in one launch
-  double sweep_s = 0.0;            // model: seconds per sweep of the set
 };
 
 }  // namespace ising

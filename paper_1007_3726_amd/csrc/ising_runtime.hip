@@ -36,10 +36,6 @@ ising_status hip_fail(hipError_t e, const char* what) {
 
 void clear_error() { g_last_error.clear(); }
 
-int64_t words_per_row(int64_t L) { return ((L / 2) + 63) / 64; }
-
-size_t plane_bytes(int64_t L) { return (size_t)L * (size_t)words_per_row(L) * sizeof(uint64_t); }
-
 size_t lattice_bytes(int64_t L) {
   if (L < 4 || L > kMaxL || (L & 1)) return 0;
   size_t b = 2 * plane_bytes(L);

@@ -35,8 +35,6 @@ int tile_rpw(int64_t L, int want);
 ising_status fail(ising_status code, const char* fmt, ...);
 ising_status hip_fail(hipError_t e, const char* what);
 void clear_error();
-int64_t words_per_row(int64_t L);
-size_t plane_bytes(int64_t L);
 size_t lattice_bytes(int64_t L);
 Geom make_geom(int64_t L);
 uint32_t metropolis_threshold(double beta, int dE);
