@@ -56,9 +56,6 @@
 namespace ising {
 namespace {
 
-constexpr int kMaxWaves = 16;  // of one workgroup
-constexpr int kEmSlots = 32;   // sweeps whose counts are kept in LDS at a time
-
 // Sweeps done before launch j of m that share n sweeps.
 __device__ __forceinline__ int64_t sweeps_before(int64_t n, int64_t j, int64_t m) {
   const int64_t each = n / m, more = n - each * m;  // the first `more` launches take one more
@@ -549,6 +546,10 @@ __device__ __forceinline__ void block_run(const Lat& L, const BlockAlt* x, int s
                                           uint32_t* lds) {
   __shared__ uint2 counts[kEmSlots * kMaxWaves];
   __shared__ uint32_t starts[ALT ? 2 * kMaxGroups : 1];
+  // what the plans leave for them (an unused array takes none)
+  static_assert(sizeof(counts) + (ALT ? sizeof(starts) : 0) ==
+                    (size_t)block_static_lds(ALT ? kBlockLcg : kBlockPhilox),
+                "block_static_lds");
   // waves beyond this lattice's share of the workgroup leave at once
   if ((int)(threadIdx.x & ~63u) >= L.threads || j >= L.launches) return;
   const bool wrap = L.strips == 1;

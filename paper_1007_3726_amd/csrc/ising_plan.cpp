@@ -128,7 +128,7 @@ BlockPlan plan_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int c
   for (int64_t L : Ls) ++of[L];
   const std::vector<std::pair<int64_t, int64_t>> sides(of.begin(), of.end());
   // a lone lattice's strips have a compute unit each
-  const int64_t lds = Ls.size() == 1 ? kBlockLoneLds : kBlockMaxLds;
+  const int64_t lds = Ls.size() == 1 ? block_lone_lds(kind) : kBlockMaxLds;
   auto consider = [&](int K, int64_t target, bool singles, int max_ls) {
     BlockPlan p;
     double longest = 0, move = 0;

@@ -24,15 +24,24 @@ constexpr int kBlockMaxStrips = 256;
 constexpr int64_t kBlockMaxTasks = 1024;
 // Largest side whose sweeps may take this form with several strips.
 constexpr int64_t kBlockMaxL = 16384;
-// LDS of one workgroup (two planes of the strip's rows and its halos): half
-// of a compute unit's, and where each has a strip of its own nearly all.
+// LDS of one workgroup (two planes of the strip's rows and its halos) where
+// two share a compute unit.
 constexpr int64_t kBlockMaxLds = 65536;
-constexpr int64_t kBlockLoneLds = 156 * 1024;
 
 // Dynamics of a block.
 enum { kBlockPhilox = 0, kBlockLcg = 1, kBlockPool = 2, kBlockPoolLinear = 3 };
+
+constexpr int kMaxWaves = 16;  // of one workgroup
+constexpr int kEmSlots = 32;   // sweeps whose counts are kept in LDS at a time
 // 256-word groups of a linear pool that one strip may span.
 constexpr int kMaxGroups = 64;
+// LDS that the kernels take beside the rows: a pair of counts per sweep and
+// wave, and for generators and pools (one kernel) two starts per group.
+constexpr int64_t block_static_lds(int kind) {
+  return 8 * kEmSlots * kMaxWaves + (kind == kBlockPhilox ? 0 : 2 * 4 * kMaxGroups);
+}
+// Rows of a strip that has a compute unit of its own: all that is left.
+constexpr int64_t block_lone_lds(int kind) { return 160 * 1024 - block_static_lds(kind); }
 
 // How one lattice is cut: rows per strip, strips and sweeps per launch.
 struct BlockShape {

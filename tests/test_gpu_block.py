@@ -244,3 +244,20 @@ def test_odd_batch_with_less_than_its_tables(I, share):
     for i, (L, T) in enumerate(spec):
         s, _ = oracle.run(L, 1 / T, 6, i, workloads.INIT_HOT, 17)
         assert np.array_equal(lats[i].get_spins(), s), (L, T)
+
+
+def test_pool_block_that_fills_the_lds(I):
+    """16064^2, linear reads, 9 sweeps: the plan nearest to a compute unit's
+    LDS (rows and the kernel's own part together)."""
+    L, m, n, T = 16064, 12, 9, 2.2
+    lat = I.Lattice(L, seed=5, stream_id=3, init=workloads.INIT_HOT, beta=1 / T)
+    lat.use_pool(m, linear=True)
+    em = lat.sweep_em(n).cpu().numpy()
+    assert tuple(em[-1]) == lat.measure()
+    pool = oracle.pool_fill(1 / T, 5, 3, m)
+    for (x0, y0) in [(0, 0), (L - 20, L - 5), (L // 2, 8037)]:
+        want = oracle.pool_window(L, 1 / T, 5, 3, workloads.INIT_HOT, 0, n, m, True, x0, y0, 40,
+                                  12, pool)
+        rows = [lat.get_window(0, (y0 + i) % L, L, 1)[0] for i in range(12)]
+        xs = (x0 + np.arange(40)) % L
+        assert np.array_equal(np.stack([r[xs] for r in rows]), want), (x0, y0)

@@ -1,0 +1,70 @@
+"""Plans of the block form (csrc/ising_plan.cpp, host only): what every plan
+has to keep to, whatever the sides, dynamics, sweeps per call and compute
+units."""
+import os
+import subprocess
+import tempfile
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+PHILOX, LCG, POOL, POOL_LINEAR = range(4)
+# 160 KiB of LDS per compute unit; the kernels' own: 32 sweeps' counts of 16
+# waves, and where generators or pools are compiled in the starts of 64 groups
+CU_LDS = 160 * 1024
+STATIC_LDS = {PHILOX: 32 * 16 * 8, LCG: 32 * 16 * 8 + 2 * 64 * 4}
+STATIC_LDS[POOL] = STATIC_LDS[POOL_LINEAR] = STATIC_LDS[LCG]
+# calls whose sweeps allow other launches: K <= (n + 1) / 2 of 1, 2, 3, 4, 6, 8, 12
+SWEEPS = [2, 3, 5, 7, 11, 15, 24]
+
+
+@pytest.fixture(scope="module")
+def plans():
+    src = os.path.join(HERE, "xref", "plan_probe.cpp")
+    csrc = os.path.join(os.path.dirname(HERE), "paper_1007_3726_amd", "csrc")
+    with tempfile.TemporaryDirectory() as d:
+        out = os.path.join(d, "plan_probe")
+        subprocess.run(["g++", "-O2", "-std=c++17", "-I" + csrc, "-o", out, src,
+                        os.path.join(csrc, "ising_plan.cpp")], check=True)
+
+        def run(cases):
+            """cases: (kind, n, cus, Ls); (microseconds per sweep, strips, shapes) of each."""
+            text = "".join("%d %d %d %d %s\n" % (k, n, c, len(Ls), " ".join(map(str, Ls)))
+                           for k, n, c, Ls in cases)
+            r = subprocess.run([out], input=text, capture_output=True, text=True, check=True)
+            res = []
+            for ln in r.stdout.splitlines():
+                f = ln.split()
+                v = [int(x) for x in f[3:]]
+                shapes = [dict(zip(("rows", "strips", "ls", "pass", "threads", "sweeps", "lds"),
+                                   v[7 * i:7 * i + 7])) for i in range(int(f[2]))]
+                res.append((float(f[0]), int(f[1]), shapes))
+            assert len(res) == len(cases)
+            return res
+        yield run
+
+
+def _sides(kind):
+    # generators and pools need sides that are multiples of 8
+    return range(4, 16385, 2) if kind == PHILOX else range(8, 16385, 8)
+
+
+@pytest.mark.parametrize("kind", [PHILOX, LCG, POOL, POOL_LINEAR])
+def test_every_lone_plan_can_be_launched(plans, kind):
+    """Side by side over all sides: the strips fit a compute unit's LDS with
+    the kernel's own part of it, and the halos stay inside the lattice."""
+    for cus in (256, 64):
+        cases = [(kind, n, cus, [L]) for n in SWEEPS for L in _sides(kind)]
+        for (_, n, _, Ls), (_, _, shapes) in zip(cases, plans(cases)):
+            L, W = Ls[0], (Ls[0] // 2 + 63) // 64
+            for s in shapes:
+                where = (L, n, cus, s)
+                R = L if s["strips"] == 1 else s["rows"] + 4 * s["sweeps"]
+                assert s["lds"] == R * W * (24 if kind == LCG else 16), where
+                assert s["lds"] + STATIC_LDS[kind] <= CU_LDS, where
+                assert s["threads"] <= 1024 and s["threads"] % 64 == 0, where
+                assert R <= L and s["strips"] <= 256 and s["sweeps"] <= 12, where
+                if s["strips"] > 1:  # the first strips reduce a launch's sweeps, one each
+                    assert s["sweeps"] <= s["strips"] and (s["strips"] - 1) * s["rows"] < L, where
+                if kind == POOL_LINEAR:  # groups of 256 words, the lattice's first ones again
+                    assert R * W // 256 + 3 <= 64, where
