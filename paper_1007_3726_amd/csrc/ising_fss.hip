@@ -41,7 +41,8 @@ struct RwLattice {
   int64_t n;
   int64_t discard;
   double beta0;
-  int64_t E_min, E_max;  // over the kept sweeps (written by k_series_range)
+  int64_t used;          // some task reweights it
+  int64_t E_min, E_max;  // over the kept sweeps (written by k_series_range where used)
 };
 struct RwTask {
   int32_t lattice;
@@ -55,10 +56,12 @@ __device__ __forceinline__ double wave_add(double v) {
   return v;
 }
 
-// One workgroup per series: the least and the greatest E of its kept sweeps.
+// One workgroup per series: the least and the greatest E of its kept sweeps
+// (a series that no task uses is not read).
 __global__ __launch_bounds__(kRwThreads) void k_series_range(RwLattice* lat) {
   __shared__ int64_t red[2][kRwThreads / 64];
   RwLattice* lt = &lat[blockIdx.x];
+  if (!lt->used) return;
   const int64_t* EM = lt->EM;
   int64_t lo = std::numeric_limits<int64_t>::max(), hi = std::numeric_limits<int64_t>::min();
   for (int64_t t = lt->discard + threadIdx.x; t < lt->n; t += kRwThreads) {
@@ -232,13 +235,14 @@ ising_status ising_reweight(int32_t nlat, const int64_t* const* dev_EM, const in
                   "ising_reweight: series %d needs a device pointer, 0 <= discard and at least "
                   "nblocks kept sweeps, and a finite beta0 >= 0",
                   i);
-    lat[i] = RwLattice{dev_EM[i], n_sweeps[i], discard[i], beta0[i], 0, 0};
+    lat[i] = RwLattice{dev_EM[i], n_sweeps[i], discard[i], beta0[i], 0, 0, 0};
   }
   std::vector<RwTask> tasks((size_t)ntask);
   for (int32_t k = 0; k < ntask; ++k) {
     if (task_lattice[k] < 0 || task_lattice[k] >= nlat || !finite_nonneg(task_beta[k]))
       return fail(ISING_EINVAL, "ising_reweight: task %d has a bad series index or beta", k);
     tasks[k] = RwTask{task_lattice[k], 0, task_beta[k]};
+    lat[task_lattice[k]].used = 1;
   }
   const size_t off_task = rw_task_offset(nlat);
   const size_t bytes = rw_work_bytes(nlat, ntask);

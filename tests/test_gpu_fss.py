@@ -182,3 +182,33 @@ def test_batched_gpu_run_puts_the_binder_crossing_near_tc(I):
         assert not math.isnan(t) and not math.isnan(et)
         assert abs(t - physics.TC_EXACT) < 0.03 + 4 * et
         assert 0.55 < u < 0.68
+
+
+def test_reweight_leaves_unused_series_unread(I):
+    """The ranges of the energies, kept in the work buffer, are taken of the
+    series that some task names, and of no other."""
+    import ctypes
+
+    import torch
+    rng = np.random.default_rng(3)
+    host = [_series(rng, 64, 300) for _ in range(3)]
+    EMs = [torch.tensor(h, device="cuda") for h in host]
+    n = (ctypes.c_int64 * 3)(300, 300, 300)
+    zero = (ctypes.c_int64 * 3)(0, 0, 0)
+    b0 = (ctypes.c_double * 3)(0.4, 0.4, 0.4)
+    work = torch.zeros(int(I.lib().ising_reweight_work_bytes(3, 2)), dtype=torch.uint8,
+                       device="cuda")
+    sums = torch.empty((2, 5, 5), dtype=torch.float64, device="cuda")
+    I.check(I.lib().ising_reweight(
+        3, (ctypes.c_void_p * 3)(*[e.data_ptr() for e in EMs]), n, zero, b0, 2,
+        (ctypes.c_int32 * 2)(0, 2), (ctypes.c_double * 2)(0.41, 0.39), 5, sums.data_ptr(), None,
+        work.data_ptr(), work.numel(), int(torch.cuda.current_stream().cuda_stream)))
+    torch.cuda.synchronize()
+    # a series' record: pointer, sweeps, discard, beta0, used, least and greatest E
+    rec = work.view(torch.int64).cpu().numpy()[:21].reshape(3, 7)
+    for i in range(3):
+        want = [0, 0, 0] if i == 1 else [1, host[i][:, 0].min(), host[i][:, 0].max()]
+        assert list(rec[i, 4:]) == want, i
+    for k, (i, b) in enumerate([(0, 0.41), (2, 0.39)]):
+        want, _ = fss.reweight_sums(host[i][:, 0], host[i][:, 1], 0, 0.4, b, 5)
+        _check_sums(sums[k].cpu().numpy(), want, host[i][:, 0])
