@@ -35,6 +35,9 @@ namespace {
 
 constexpr int kRwThreads = 256;
 constexpr int kRwMaxBlocks = 4096;
+// Blocks of a call up to which each has a workgroup of its own (k_reweight):
+// sixteen per compute unit.
+constexpr int64_t kRwFewBlocks = 4096;
 
 struct RwLattice {
   const int64_t* EM;  // n x (E, M)
@@ -90,15 +93,26 @@ __global__ __launch_bounds__(kRwThreads) void k_series_range(RwLattice* lat) {
   }
 }
 
-// One workgroup per task (lattice, target beta), one wave per block of
-// sweeps: the five sums of every block.  The maximum exponent needs no pass
-// of its own: -db (E - E_ref) is monotone in E (E is exact in binary64, and
-// rounding a product is monotone), so it is the exponent of E_min or E_max.
+// The five sums of every block of sweeps of a task (lattice, target beta).
+// The maximum exponent needs no pass of its own: -db (E - E_ref) is monotone
+// in E (E is exact in binary64, and rounding a product is monotone), so it is
+// the exponent of E_min or E_max.
+//
+// Many blocks in all (SHARED false): a workgroup per task, a wave per block.
 // A wave reduces its own block, so there is no block barrier, and the
 // shuffles are paid once per block of sweeps (a workgroup per block of 400
 // sweeps paid them in each of its four waves, after two steps of 256 lanes of
 // which the second was nearly half idle).  1743 tasks of 8000 sweeps in 20
 // blocks: 148 us -> 51 us, plus 16 us for the series' ranges.
+//
+// Few blocks (SHARED): a workgroup per task and block, whose waves share it.
+// A wave per block would leave most of the chip, and with fewer than four
+// blocks per task waves of its own workgroup, without work.  Calls of 10^6
+// sweeps with a wave and a workgroup per block: 1 task, 1 block 6.3 -> 2.4 ms
+// (half of it the range); 8 tasks, 5 blocks 3.3 -> 1.3; 64 tasks of 10^5
+// sweeps, 1 block 0.40 -> 0.18.  At the limit both take the same: 200 and 210
+// tasks of 8000 sweeps in 20 blocks 70 and 72 us either way.
+template <bool SHARED>
 __global__ __launch_bounds__(kRwThreads) void k_reweight(const RwLattice* lat, const RwTask* task,
                                                          int nblocks, double* sums,
                                                          double* shift) {
@@ -106,6 +120,8 @@ __global__ __launch_bounds__(kRwThreads) void k_reweight(const RwLattice* lat, c
   // fused multiply-add would move the exponent by an ulp of |x|, which is
   // then amplified by exp)
 #pragma clang fp contract(off)
+  constexpr int kWaves = kRwThreads / 64;
+  __shared__ double red[SHARED ? kWaves : 1][5];
   const RwTask tk = task[blockIdx.x];
   const RwLattice lt = lat[tk.lattice];
   const int64_t* EM = lt.EM;
@@ -116,11 +132,12 @@ __global__ __launch_bounds__(kRwThreads) void k_reweight(const RwLattice* lat, c
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const double xm = fmax(-db * (double)(lt.E_min - E_ref), -db * (double)(lt.E_max - E_ref));
 
-  for (int b = wave; b < nblocks; b += kRwThreads / 64) {
+  for (int b = SHARED ? (int)blockIdx.y : wave; b < nblocks; b += SHARED ? nblocks : kWaves) {
     const int64_t j0 = ((int64_t)b * count + nblocks - 1) / nblocks;
     const int64_t j1 = ((int64_t)(b + 1) * count + nblocks - 1) / nblocks;
     double s[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int64_t j = j0 + lane; j < j1; j += 64) {
+    for (int64_t j = j0 + (SHARED ? (int)threadIdx.x : lane); j < j1;
+         j += SHARED ? kRwThreads : 64) {
       const int64_t E = EM[2 * (t0 + j)];
       const double m = (double)EM[2 * (t0 + j) + 1];
       const double x = -db * (double)(E - E_ref);
@@ -134,10 +151,21 @@ __global__ __launch_bounds__(kRwThreads) void k_reweight(const RwLattice* lat, c
     }
 #pragma unroll
     for (int i = 0; i < 5; ++i) s[i] = wave_add(s[i]);
-    if (lane == 0)
-      for (int i = 0; i < 5; ++i) sums[((int64_t)blockIdx.x * nblocks + b) * 5 + i] = s[i];
+    double* out = sums + ((int64_t)blockIdx.x * nblocks + b) * 5;
+    if (SHARED) {
+      if (lane == 0)
+        for (int i = 0; i < 5; ++i) red[wave][i] = s[i];
+      __syncthreads();
+      if (threadIdx.x < 5) {
+        double v = 0.0;
+        for (int k = 0; k < kWaves; ++k) v += red[k][threadIdx.x];
+        out[threadIdx.x] = v;
+      }
+    } else if (lane == 0) {
+      for (int i = 0; i < 5; ++i) out[i] = s[i];
+    }
   }
-  if (threadIdx.x == 0 && shift) shift[blockIdx.x] = xm;
+  if (threadIdx.x == 0 && shift && (!SHARED || blockIdx.y == 0)) shift[blockIdx.x] = xm;
 }
 
 // Layout of the task tables in the caller's work buffer: the series
@@ -258,8 +286,14 @@ ising_status ising_reweight(int32_t nlat, const int64_t* const* dev_EM, const in
   hipLaunchKernelGGL(k_series_range, dim3(nlat), dim3(kRwThreads), 0, st, (RwLattice*)dev_work);
   e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "ising_reweight: launch");
-  hipLaunchKernelGGL(k_reweight, dim3(ntask), dim3(kRwThreads), 0, st, (const RwLattice*)dev_work,
-                     (const RwTask*)((char*)dev_work + off_task), nblocks, dev_sums, dev_shift);
+  const RwLattice* dl = (const RwLattice*)dev_work;
+  const RwTask* dt = (const RwTask*)((char*)dev_work + off_task);
+  if (nblocks < 4 || (int64_t)ntask * nblocks <= kRwFewBlocks)
+    hipLaunchKernelGGL(k_reweight<true>, dim3(ntask, nblocks), dim3(kRwThreads), 0, st, dl, dt,
+                       nblocks, dev_sums, dev_shift);
+  else
+    hipLaunchKernelGGL(k_reweight<false>, dim3(ntask), dim3(kRwThreads), 0, st, dl, dt, nblocks,
+                       dev_sums, dev_shift);
   e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(e, "ising_reweight: launch");
   return ISING_OK;

@@ -212,3 +212,21 @@ def test_reweight_leaves_unused_series_unread(I):
     for k, (i, b) in enumerate([(0, 0.41), (2, 0.39)]):
         want, _ = fss.reweight_sums(host[i][:, 0], host[i][:, 1], 0, 0.4, b, 5)
         _check_sums(sums[k].cpu().numpy(), want, host[i][:, 0])
+
+
+# fewer blocks than a workgroup has waves, one block, and both sides of the
+# rule that gives each block a workgroup or a wave (4096 blocks in a call)
+@pytest.mark.parametrize("ntask,nb", [(1, 1), (1, 2), (3, 3), (5, 4), (8, 512), (9, 512),
+                                      (1500, 3), (1024, 4), (1100, 4)])
+def test_reweight_of_few_and_of_many_blocks(I, ntask, nb):
+    import torch
+    rng = np.random.default_rng(5)
+    host = _series(rng, 96, 1029)
+    EM = torch.tensor(host, device="cuda")
+    betas = [0.42 + 1e-5 * k for k in range(ntask)]
+    sums, shift = I.reweight([EM], [0.44], [3], [0] * ntask, betas, nb)
+    sums, shift = sums.cpu().numpy(), shift.cpu().numpy()
+    for k in range(0, ntask, max(1, ntask // 20)):
+        want, wshift = fss.reweight_sums(host[:, 0], host[:, 1], 3, 0.44, betas[k], nb)
+        assert shift[k] == wshift, k
+        _check_sums(sums[k], want, host[3:, 0])
