@@ -548,6 +548,19 @@ def batch_tuning_clear():
     check(lib().ising_batch_tuning_clear())
 
 
+def _numbers(v, kind):
+    """kind(x) of every x of v as an array: a list, a tensor on any device or
+    an iterator.  A task list has thousands of entries, so numpy converts what
+    it can at once."""
+    try:
+        a = np.asarray(v)
+        if a.ndim == 1 and a.dtype.kind in "biuf" and (kind is float or a.dtype.kind != "f"):
+            return a.astype(kind)
+    except (TypeError, ValueError, RuntimeError):
+        pass
+    return np.asarray([kind(x) for x in v], dtype=kind)
+
+
 def reweight(EMs, betas0, discards, task_lattice, task_beta, nblocks: int, stream=None):
     """Per-block reweighted sums of device series (ising_reweight).
 
@@ -572,14 +585,13 @@ def reweight(EMs, betas0, discards, task_lattice, task_beta, nblocks: int, strea
     n = (ctypes.c_int64 * max(nl, 1))(*[int(e.shape[0]) for e in EMs])
     d = (ctypes.c_int64 * max(nl, 1))(*[int(v) for v in discards])
     b0 = (ctypes.c_double * max(nl, 1))(*[float(v) for v in betas0])
-    # a task list has thousands of entries: numpy converts it at once
     tl = np.zeros(max(nt, 1), dtype=np.int32)
     tb = np.zeros(max(nt, 1), dtype=np.float64)
-    betas = np.asarray(task_beta, dtype=np.float64).reshape(-1)
+    betas = _numbers(task_beta, float)
     if betas.size > nt:
         raise IndexError("reweight: more task betas than tasks")
     if nt:
-        tl[:] = np.asarray(task_lattice)
+        tl[:] = _numbers(task_lattice, int)
         tb[:betas.size] = betas
     check(lib().ising_reweight(nl, ptrs, n, d, b0, nt,
                                tl.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)),

@@ -112,3 +112,34 @@ def test_autocorr_time_argument_checks(I):
                 ([1.0, float("inf")], 5.0)):
         with pytest.raises(I.IsingError):
             I.autocorr_time(*bad)
+
+
+class _OnDevice:
+    """Numbers that numpy cannot read as an array, one by one only (as a
+    tensor on a GPU)."""
+
+    def __init__(self, v):
+        self.v = v
+
+    def __array__(self, *a, **k):
+        raise TypeError("not on the host")
+
+    def __iter__(self):
+        return iter(self.v)
+
+
+def test_task_lists_may_be_anything_that_yields_numbers(I):
+    import torch
+    b = [0.25, 0.5, 1.0]
+    for v in (b, tuple(b), np.array(b), torch.tensor(b), torch.tensor(b, requires_grad=True),
+              (x for x in b), [torch.tensor(x) for x in b], _OnDevice(b),
+              np.array(b, dtype=np.float32), [np.float64(x) for x in b]):
+        got = I._numbers(v, float)
+        assert got.dtype == np.float64 and list(got) == b
+    for v in ([2, 0, 1], np.array([2, 0, 1], dtype=np.uint8), (x for x in (2, 0, 1)),
+              torch.tensor([2, 0, 1]), _OnDevice([2, 0, 1]), [2.9, 0.0, 1.5]):
+        got = I._numbers(v, int)
+        assert got.dtype.kind == "i" and list(got) == [2, 0, 1]
+    assert I._numbers([], float).size == 0 and I._numbers([], int).size == 0
+    with pytest.raises(TypeError):
+        I._numbers([[0.1, 0.2], [0.3, 0.4]], float)

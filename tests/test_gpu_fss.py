@@ -230,3 +230,15 @@ def test_reweight_of_few_and_of_many_blocks(I, ntask, nb):
         want, wshift = fss.reweight_sums(host[:, 0], host[:, 1], 3, 0.44, betas[k], nb)
         assert shift[k] == wshift, k
         _check_sums(sums[k], want, host[3:, 0])
+
+
+def test_reweight_takes_device_tensors_and_iterators_as_task_lists(I):
+    import torch
+    host = _series(np.random.default_rng(8), 64, 400)
+    EM = torch.tensor(host, device="cuda")
+    tl, tb = [0, 0, 0], [0.43, 0.44, 0.45]
+    want = I.reweight([EM], [0.44], [0], tl, tb, 5)[0].cpu()
+    for a, b in ((torch.tensor(tl, device="cuda"), torch.tensor(tb, device="cuda",
+                                                                dtype=torch.float64)),
+                 (tuple(tl), (x for x in tb))):
+        assert torch.equal(I.reweight([EM], [0.44], [0], a, b, 5)[0].cpu(), want)
