@@ -19,6 +19,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -39,7 +40,7 @@ namespace {
 // be captured).  The mutex serialises captures on that stream.
 struct DeviceState {
   std::mutex m;
-  int cus = 0;
+  std::atomic<int> cus{0};
   hipStream_t capture = nullptr;
 };
 
@@ -49,15 +50,6 @@ DeviceState& state_for(int device) {
 }
 
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
-
-int cu_count(DeviceState& D, int device) {
-  std::lock_guard<std::mutex> lock(D.m);
-  if (D.cus == 0) {
-    hipDeviceProp_t p;
-    if (hipGetDeviceProperties(&p, device) == hipSuccess) D.cus = p.multiProcessorCount;
-  }
-  return D.cus;
-}
 
 // Byte offsets of the fused form's tables in the work buffer.
 struct FusedLayout {
@@ -93,7 +85,18 @@ int64_t fused_tiles(int64_t plane_words, int32_t rpw) {
 
 }  // namespace
 
-int device_cus(int device) { return cu_count(state_for(device), device); }
+// Without the mutex: a batch holds that until its captured sweeps are done, and
+// every sweep of a lone lattice comes here.
+int device_cus(int device) {
+  DeviceState& D = state_for(device);
+  int cus = D.cus.load(std::memory_order_relaxed);
+  if (cus == 0) {
+    hipDeviceProp_t p;
+    if (hipGetDeviceProperties(&p, device) == hipSuccess) cus = p.multiProcessorCount;
+    D.cus.store(cus, std::memory_order_relaxed);
+  }
+  return cus;
+}
 
 // Pack single-workgroup lattices onto `bins` workgroups, longest first.
 std::vector<std::vector<int>> pack_lpt(const std::vector<double>& cost, int bins) {
