@@ -211,9 +211,10 @@ ISING_API ising_status ising_multi_sweep_static(ising_t *const *hs, int32_t coun
  * form -1 lets the cost model choose, 0 forces the fused form (two launches
  * per sweep over the flattened tiles of all lattices, replayed from captured
  * hipGraph chunks of graph_chunk sweeps; 0 disables graphs, -1 keeps the
- * default), 1 forces the packed form (each lattice on one workgroup, one
- * launch for all n sweeps).  Results are bit-identical for
- * every form.  For tests and tuning.
+ * default), 1 forces the packed form (each lattice whose planes fit 64 KiB
+ * on one workgroup, one launch for all n sweeps; larger ones together in the
+ * fused form).  Results are bit-identical for every form.  For tests and
+ * tuning.
  */
 ISING_API ising_status ising_multi_sweep_form(ising_t *const *hs, int32_t count, int64_t n,
                                               int64_t *const *dev_EM, int32_t form,
@@ -222,10 +223,10 @@ ISING_API ising_status ising_multi_sweep_form(ising_t *const *hs, int32_t count,
 
 /*
  * Launch form the batched path would choose for lattices of sides Ls[i]
- * (each a multiple of 8) on a device with `cus` compute units: *form_out
- * 0 (fused) or 1 (packed), *blocks_out its grid size, *est_seconds_out
- * (may be NULL) the cost model's seconds per sweep.  Host-only; for
- * inspection and tests.
+ * (each a multiple of 8, each with a spare copy) on a device with `cus`
+ * compute units: *form_out 0 (fused, or several sweeps per launch in strips)
+ * or 1 (packed), *blocks_out its grid size, *est_seconds_out (may be NULL)
+ * the cost model's seconds per sweep.  Host-only; for inspection and tests.
  */
 ISING_API ising_status ising_batch_plan(const int64_t *Ls, int32_t count, int32_t cus,
                                         int32_t *form_out, int32_t *blocks_out,

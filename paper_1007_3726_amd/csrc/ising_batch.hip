@@ -1,7 +1,7 @@
 // Batched sweeps: many lattices of uneven size and temperature.
 //
-// Two launch forms, chosen per call by the cost model of the autotuner
-// (ising_tune.hip):
+// Two launch forms, chosen per call by the cost model of the blocks
+// (ising_plan.cpp):
 //   * fused: the tiles of all lattices form one flat list; each sweep is
 //     two launches of k_fused (colour 0, colour 1) that walk the whole list,
 //     so every colour step is balanced over the whole GPU.  Long runs are
@@ -9,8 +9,8 @@
 //     sweep counter advanced by the last node keeps the chunk reusable);
 //   * blocks (ising_block.hip): several sweeps per launch on rows held in LDS,
 //     for batches whose colour steps would not fill the GPU for longer than a
-//     launch takes; a batch of small lattices ("packed") gives each one
-//     workgroup and runs all n sweeps in one launch.
+//     launch takes; a batch of lattices that each fit one workgroup ("packed")
+//     runs all n sweeps in one launch.
 // Lattices the tiled layout does not cover (L % 8 != 0, or Philox block
 // indices crossing 2^32 inside a row) are advanced with the plain path unless
 // the whole batch takes blocks.
@@ -83,6 +83,10 @@ int64_t fused_tiles(int64_t plane_words, int32_t rpw) {
   return (plane_words + per_tile - 1) / per_tile;
 }
 
+int fused_grid(int64_t tiles, int wg_per_cu, int cus) {
+  return (int)std::min<int64_t>(std::max<int64_t>(tiles, 1), (int64_t)wg_per_cu * cus);
+}
+
 }  // namespace
 
 // Without the mutex: a batch holds that until its captured sweeps are done, and
@@ -98,46 +102,24 @@ int device_cus(int device) {
   return cus;
 }
 
-// Pack single-workgroup lattices onto `bins` workgroups, longest first.
-std::vector<std::vector<int>> pack_lpt(const std::vector<double>& cost, int bins) {
-  std::vector<int> order(cost.size());
-  std::iota(order.begin(), order.end(), 0);
-  std::sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
-  bins = std::max(1, std::min<int>(bins, (int)cost.size()));
-  std::vector<std::vector<int>> packs(bins);
-  std::vector<double> load(bins, 0.0);
-  for (int i : order) {
-    const int b = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-    load[b] += cost[i];
-    packs[b].push_back(i);
+// A batch of more sites than kBlockMaxSites fills the chip in every colour
+// step: only single strips, which have no halo rows, can still be cheaper.
+bool choose_blocks(const std::vector<int64_t>& Ls, int64_t n, int cus, BlockPlan* plan) {
+  double sites = 0, words = 0;
+  bool all_single = true;
+  for (int64_t L : Ls) {
+    if (L > kBlockMaxL) return false;
+    sites += (double)L * L;
+    words += (double)(L * words_per_row(L));
+    all_single = all_single && block_fits_single(L);
   }
-  return packs;
-}
-
-BatchPlan plan_batch(const std::vector<int64_t>& tiles, int cus, const PlanModel& m) {
-  BatchPlan p;
-  const int count = (int)tiles.size();
-  const int64_t total = std::accumulate(tiles.begin(), tiles.end(), (int64_t)0);
-  // fused: two launches per sweep, each walking all tiles with the full grid
-  p.fused_blocks = (int)std::min<int64_t>(std::max<int64_t>(total, 1), (int64_t)m.wg_per_cu * cus);
-  const double rounds = std::ceil((double)total / p.fused_blocks);
-  p.fused_s = 2.0 * (m.launch_gap_s + rounds * m.tile_s_full);
-  // packed: one workgroup per bin, all sweeps in one launch
-  const int bins = std::min<int>(count, m.wg_per_cu * cus);
-  std::vector<double> cost(count);
-  for (int i = 0; i < count; ++i) cost[i] = (double)tiles[i];
-  p.packs = pack_lpt(cost, bins);
-  double worst = 0.0;
-  for (const auto& pk : p.packs) {
-    double s = 0.0;
-    for (int i : pk) s += cost[i];
-    worst = std::max(worst, s);
+  if (sites > kBlockMaxSites) {
+    if (!all_single) return false;
+    n = 1;
   }
-  const double per_cu = std::ceil((double)p.packs.size() / std::max(cus, 1));
-  const double tile_s = std::max(m.tile_s_alone, m.tile_s_full * per_cu / m.wg_per_cu);
-  p.packed_s = 2.0 * worst * tile_s;
-  p.packed = p.packed_s < p.fused_s;
-  return p;
+  *plan = plan_blocks(kBlockPhilox, Ls, std::min(n, kBlockPlanN), cus);
+  return !plan->shapes.empty() &&
+         plan->sweep_s < launch_per_step_seconds(kBlockPhilox, words, cus);
 }
 
 static ising_status run_fused(ising_lattice* const* hs, const std::vector<int>& idx,
@@ -367,20 +349,6 @@ static size_t work_bytes_for(ising_lattice* const* hs, const std::vector<int>& t
   return std::max(fused_layout(nl, ntiles).bytes, block_layout(nl, nl).bytes);
 }
 
-// Whether the sides let a whole batch run in blocks (a lattice of several
-// strips also needs its spare copy); fills the sides and the words of a plane.
-static bool blocks_allowed(ising_lattice* const* hs, int32_t count, std::vector<int64_t>* Ls,
-                           double* words) {
-  double sites = 0;
-  for (int i = 0; i < count; ++i) {
-    if (hs[i]->L > kBlockMaxL) return false;
-    sites += (double)hs[i]->L * hs[i]->L;
-    if (Ls) Ls->push_back(hs[i]->L);
-    if (words) *words += (double)hs[i]->plane_words;
-  }
-  return sites <= kBlockMaxSites;
-}
-
 size_t batch_work_bytes(ising_lattice* const* hs, int32_t count, const BatchOptions& opt) {
   std::vector<int> tiled, other;
   std::vector<TileArgs> targs;
@@ -392,9 +360,14 @@ size_t batch_work_bytes(ising_lattice* const* hs, int32_t count, const BatchOpti
 // tiles leave to the plain path (sides no multiple of 8), one after another,
 // can advance together in blocks.  200 sweeps of 16 x 1002^2 12.3 -> 2.5 ms.
 static size_t optional_work_bytes(ising_lattice* const* hs, int32_t count) {
-  bool odd = false;
-  for (int i = 0; i < count; ++i) odd = odd || hs[i]->L % 8 != 0;
-  return count > 1 && odd && blocks_allowed(hs, count, nullptr, nullptr)
+  bool odd = false, sides = true;
+  double sites = 0;
+  for (int i = 0; i < count; ++i) {
+    odd = odd || hs[i]->L % 8 != 0;
+    sides = sides && hs[i]->L <= kBlockMaxL;
+    sites += (double)hs[i]->L * hs[i]->L;
+  }
+  return count > 1 && odd && sides && sites <= kBlockMaxSites
              ? block_layout(count, count + kBlockMaxTasks).bytes
              : 0;
 }
@@ -428,19 +401,19 @@ ising_status batch_sweeps(ising_lattice* const* hs, int32_t count, int64_t n,
   // step.  (Beside a lattice that cannot, the small ones ride along in its
   // launches.)  Their tables may need more than the work buffer holds: then
   // the other forms run.
+  const int cus = device_cus(device);
   if (opt.force_form < 0 && work && ((uintptr_t)work & 255) == 0) {
     std::vector<int> all(count);
     std::iota(all.begin(), all.end(), 0);
     std::vector<int64_t> Ls;
-    double words = 0;
     bool spares = true;
-    for (int i = 0; i < count; ++i) spares = spares && (hs[i]->spare || block_fits_single(hs[i]->L));
-    if (spares && blocks_allowed(hs, count, &Ls, &words)) {
-      const int cus = device_cus(device);
-      const BlockPlan plan = plan_blocks(kBlockPhilox, Ls, std::min(n, kBlockPlanN), cus);
-      bool ok = !plan.shapes.empty() &&
-                plan.sweep_s < launch_per_step_seconds(kBlockPhilox, words, cus) &&
-                block_layout(count, plan.tasks).bytes <= work_bytes;
+    for (int i = 0; i < count; ++i) {
+      Ls.push_back(hs[i]->L);
+      spares = spares && (hs[i]->spare || block_fits_single(hs[i]->L));
+    }
+    BlockPlan plan;
+    if (spares && choose_blocks(Ls, n, cus, &plan)) {
+      bool ok = block_layout(count, plan.tasks).bytes <= work_bytes;
       for (int i = 0; i < count && ok; ++i) ok = plan.shapes[i].strips == 1 || hs[i]->spare;
       if (ok) {
         if (form_out) *form_out = plan.all_single ? 1 : 0;
@@ -448,24 +421,33 @@ ising_status batch_sweeps(ising_lattice* const* hs, int32_t count, int64_t n,
       }
     }
   }
-  const int cus = device_cus(device);
-  bool packed = false;
-  BatchPlan plan;
+  // Packed: tiled lattices that fit one workgroup run all their sweeps in one
+  // launch, where that is forced, or where all of them fit and it is cheaper;
+  // any others advance together in the fused form (2048 lattices of 1024^2, 10
+  // sweeps: 15.5 ms, one after another 84).
+  BlockPlan singles;
+  std::vector<int> fits;
   if (!tiled.empty()) {
     if (cus <= 0) return fail(ISING_EDEVICE, "batched sweeps: no device properties");
-    std::vector<int64_t> tiles;
-    for (int i : tiled) tiles.push_back(tile_cost(targs[i].tiles, targs[i].RPW));
-    plan = plan_batch(tiles, cus, opt.model);
-    packed = plan.packed;
-    if (opt.force_form == 0) packed = false;
-    if (opt.force_form == 1) packed = true;
+    std::vector<int> rest;
+    std::vector<int64_t> Ls;
+    for (int i : tiled) {
+      (block_fits_single(hs[i]->L) ? fits : rest).push_back(i);
+      Ls.push_back(hs[i]->L);
+    }
+    const bool packed = opt.force_form == 1 ||
+                        (opt.force_form < 0 && rest.empty() && choose_blocks(Ls, 1, cus, &singles));
     if (form_out) *form_out = packed ? 1 : 0;
-  }
-  if (packed) {
-    // one workgroup each; lattices that do not fit one run by themselves
-    std::vector<int> fits;
-    for (int i : tiled) (block_fits_single(hs[i]->L) ? fits : other).push_back(i);
-    tiled.swap(fits);
+    if (packed) {
+      tiled.swap(rest);
+      if (opt.force_form == 1) {
+        singles = BlockPlan();
+        for (int i : fits) singles.shapes.push_back(block_shape_single(kBlockPhilox, hs[i]->L));
+        singles.all_single = true;
+      }
+    } else {
+      fits.clear();
+    }
   }
   for (int i : other) {
     // the plain path reads the handle's counter: advance a copy of it
@@ -473,22 +455,20 @@ ising_status batch_sweeps(ising_lattice* const* hs, int32_t count, int64_t n,
     ising_status st = enqueue_sweeps(&tmp, nsw ? nsw[i] : n, dev_EM ? dev_EM[i] : nullptr);
     if (st != ISING_OK) return st;
   }
+  if (!fits.empty()) {
+    ising_status st = run_blocks(hs, fits, n, nsw, dev_EM, singles, (char*)work, opt.keep_image);
+    if (st != ISING_OK) return st;
+  }
   if (tiled.empty()) {
     if (opt.keep_image) return ISING_OK;
     hipError_t e = hipStreamSynchronize(hs[0]->stream);
     return e == hipSuccess ? ISING_OK : hip_fail(e, "batched sweeps: synchronize");
   }
-  if (packed) {
-    BlockPlan singles;
-    singles.all_single = true;
-    for (int i : tiled) singles.shapes.push_back(block_shape_single(kBlockPhilox, hs[i]->L));
-    return run_blocks(hs, tiled, n, nsw, dev_EM, singles, (char*)work, opt.keep_image);
-  }
   // the fused grid walks actual tiles; size it for them
   int64_t ntiles = 0;
   for (int i : tiled) ntiles += targs[i].tiles;
-  const int blocks = (int)std::min<int64_t>(std::max<int64_t>(ntiles, 1), plan.fused_blocks);
-  return run_fused(hs, tiled, targs, n, nsw, dev_EM, opt, (char*)work, work_bytes, blocks);
+  return run_fused(hs, tiled, targs, n, nsw, dev_EM, opt, (char*)work, work_bytes,
+                   fused_grid(ntiles, opt.wg_per_cu, cus));
 }
 
 }  // namespace ising
@@ -501,7 +481,8 @@ extern "C" ising_status ising_batch_plan(const int64_t* Ls, int32_t count, int32
   clear_error();
   if (!Ls || count < 1 || cus < 1 || !form_out || !blocks_out)
     return fail(ISING_EINVAL, "ising_batch_plan: bad arguments");
-  std::vector<int64_t> tiles(count);
+  int64_t tiles = 0;
+  double words = 0;
   for (int32_t i = 0; i < count; ++i) {
     const int64_t L = Ls[i];
     if (L < 8 || L % 8 || L > kMaxL)
@@ -509,12 +490,17 @@ extern "C" ising_status ising_batch_plan(const int64_t* Ls, int32_t count, int32
     const int64_t W = words_per_row(L);
     const int64_t R = W >= kWideMinWords ? 1 : 64 / W;
     const int64_t segs = W >= kWideMinWords ? (W + 63) / 64 : 1;
-    tiles[i] = ((L + 4 * R - 1) / (4 * R)) * segs;
+    tiles += ((L + 4 * R - 1) / (4 * R)) * segs;
+    words += (double)(L * W);
   }
-  const BatchPlan plan = plan_batch(tiles, cus, default_model());
-  *form_out = plan.packed ? 1 : 0;
-  *blocks_out = plan.packed ? (int32_t)plan.packs.size() : plan.fused_blocks;
-  if (est_seconds_out) *est_seconds_out = plan.packed ? plan.packed_s : plan.fused_s;
+  BlockPlan plan;
+  const bool blocks = choose_blocks(std::vector<int64_t>(Ls, Ls + count), kBlockPlanN, cus, &plan);
+  *form_out = blocks && plan.all_single ? 1 : 0;
+  *blocks_out = blocks ? (int32_t)plan.tasks
+                       : fused_grid(tiles, default_batch_options().wg_per_cu, cus);
+  if (est_seconds_out)
+    *est_seconds_out =
+        blocks ? plan.sweep_s : launch_per_step_seconds(kBlockPhilox, words, cus);
   return ISING_OK;
 }
 

@@ -1,4 +1,4 @@
-// Batched-sweep planning (internal).
+// Batched sweeps (internal).
 #pragma once
 
 #include <stdint.h>
@@ -9,32 +9,13 @@
 
 namespace ising {
 
-// Cost model of the batched launch forms (filled by the autotuner defaults).
-struct PlanModel {
-  int wg_per_cu;        // resident workgroups per CU for the tiled kernels
-  double tile_s_full;   // seconds per tile per workgroup with every CU fully occupied
-  double tile_s_alone;  // seconds per tile for a workgroup with its CU to itself
-  double launch_gap_s;  // gap between dependent launches
-};
-
-// tile-steps (one word per lane) a lattice with these tile arguments costs per colour
-inline int64_t tile_cost(int64_t tiles, int32_t rpw) { return tiles * (int64_t)rpw; }
-
-struct BatchPlan {
-  int fused_blocks = 0;                 // grid of the fused launches
-  double fused_s = 0.0;                 // model: seconds per sweep, fused form
-  std::vector<std::vector<int>> packs;  // packed form: lattices per workgroup
-  double packed_s = 0.0;                // model: seconds per sweep, packed form
-  bool packed = false;                  // the cheaper form
-};
-
 struct BatchOptions {
-  PlanModel model;
+  int wg_per_cu;    // workgroups per compute unit of the fused grid
   int force_form;   // -1: cost model, 0: fused, 1: packed
   int graph_chunk;  // sweeps per captured hipGraph chunk (0: no graph)
   // row groups per wave of a lattice's tiles: the largest r in {1, 2, 4},
   // r <= rpw_max, for which the lattice has at least 128 r tiles of one row
-  // group per wave and the packed kernel's LDS staging still fits
+  // group per wave, of at most kTileMaxWords words each
   int rpw_max = 2;
   // when set (with graph_chunk 0): the table image is kept here, since it
   // must outlive its asynchronous upload, and the call returns without
@@ -43,13 +24,14 @@ struct BatchOptions {
   std::vector<char>* keep_image = nullptr;
 };
 
-PlanModel default_model();
 // The built-in batched options, with the batched autotuner's installed
 // fused shape (rpw_max, workgroups per CU, graph chunk) if there is one.
 BatchOptions default_batch_options();
 // Argument checks shared by the batched entry points (n: sweeps to come).
 ising_status check_batch(ising_t* const* hs, int32_t count, int64_t n, const char* who);
-BatchPlan plan_batch(const std::vector<int64_t>& tiles, int cus, const PlanModel& model);
+// Whether these lattices together are cheaper in blocks than in a launch per
+// colour step, for n sweeps (the cut in *plan).
+bool choose_blocks(const std::vector<int64_t>& Ls, int64_t n, int cus, BlockPlan* plan);
 // Device bytes of the work buffer batch_sweeps needs for these handles
 // (0 when every lattice takes the plain path).
 size_t batch_work_bytes(ising_lattice* const* hs, int32_t count, const BatchOptions& opt);

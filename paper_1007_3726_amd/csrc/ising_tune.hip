@@ -52,25 +52,16 @@ Tuning default_tuning(int64_t L) {
   return t;
 }
 
-PlanModel default_model() {
-  PlanModel m;
-  m.wg_per_cu = 8;          // 16.4 KB LDS and <= 64 VGPRs per lane allow 8 per CU
-  m.tile_s_full = 13e-6;    // ~1000 VALU instructions per lane, 8 waves per SIMD
-  m.tile_s_alone = 4.5e-6;  // one wave per SIMD: issue plus memory latency (measured)
-  m.launch_gap_s = 5e-6;    // dependent launches replayed from a graph (measured)
-  return m;
-}
-
 BatchOptions default_batch_options() {
   BatchOptions o;
-  o.model = default_model();
+  o.wg_per_cu = 8;  // resident at <= 64 VGPRs per lane
   o.force_form = -1;
   o.graph_chunk = 32;
   o.rpw_max = 2;
   std::lock_guard<std::mutex> lock(g_tune_mutex);
   if (g_batch_set) {
     o.rpw_max = g_batch.rpw_max;
-    o.model.wg_per_cu = g_batch.wg_per_cu;
+    o.wg_per_cu = g_batch.wg_per_cu;
     o.graph_chunk = g_batch.graph_chunk;
   }
   return o;
@@ -342,8 +333,7 @@ ising_status ising_multi_autotune(ising_t* const* hs, int32_t count, int32_t tri
     BatchOptions o = default_batch_options();
     o.force_form = 0;
     o.rpw_max = rpw_max;
-    o.model = default_model();
-    o.model.wg_per_cu = wg;
+    o.wg_per_cu = wg;
     o.graph_chunk = chunk;
     return o;
   };
@@ -384,28 +374,26 @@ ising_status ising_multi_autotune(ising_t* const* hs, int32_t count, int32_t tri
     }
   }
   if (st == ISING_OK) {
-    // the packed form, unless the cost model puts it far behind (one
-    // workgroup per lattice: a large lattice alone would take seconds)
-    std::vector<int64_t> tiles;
+    // the packed form, unless the cost model puts it far behind
+    std::vector<int64_t> fits;
+    double words = 0;
     BatchOptions o = shape(best.rpw_max, best.wg_per_cu, best.graph_chunk);
     for (int32_t i = 0; i < count; ++i) {
       TileArgs ta;
-      if (tile_args(hs[i], &ta)) tiles.push_back(tile_cost(ta.tiles, ta.RPW));
+      if (!tile_args(hs[i], &ta) || !block_fits_single(hs[i]->L)) continue;
+      fits.push_back(hs[i]->L);
+      words += (double)hs[i]->plane_words;
     }
-    int dev_cus = 0;
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, hs[0]->device) == hipSuccess)
-      dev_cus = prop.multiProcessorCount;
-    if (!tiles.empty() && dev_cus > 0) {
-      const BatchPlan plan = plan_batch(tiles, dev_cus, o.model);
-      if (plan.packed_s <= 4.0 * plan.fused_s) {
-        o.force_form = 1;
-        double r = 0.0;
-        st = rate(o, &r);
-        if (st == ISING_OK) {
-          best.packed_updates_per_ns = r;
-          if (r > best.updates_per_ns) best.form = 1;
-        }
+    const int cus = device_cus(hs[0]->device);
+    if (!fits.empty() && cus > 0 &&
+        plan_blocks(kBlockPhilox, fits, 1, cus).sweep_s <=
+            4.0 * launch_per_step_seconds(kBlockPhilox, words, cus)) {
+      o.force_form = 1;
+      double r = 0.0;
+      st = rate(o, &r);
+      if (st == ISING_OK) {
+        best.packed_updates_per_ns = r;
+        if (r > best.updates_per_ns) best.form = 1;
       }
     }
   }
