@@ -117,9 +117,9 @@ bool choose_blocks(const std::vector<int64_t>& Ls, int64_t n, int cus, BlockPlan
     if (!all_single) return false;
     n = 1;
   }
-  *plan = plan_blocks(kBlockPhilox, Ls, std::min(n, kBlockPlanN), cus);
-  return !plan->shapes.empty() &&
-         plan->sweep_s < launch_per_step_seconds(kBlockPhilox, words, cus);
+  *plan = plan_blocks(kBlockPhilox, Ls, n, cus,
+                      launch_per_step_seconds(kBlockPhilox, words, cus));
+  return !plan->shapes.empty();
 }
 
 static ising_status run_fused(ising_lattice* const* hs, const std::vector<int>& idx,
@@ -450,9 +450,7 @@ ising_status batch_sweeps(ising_lattice* const* hs, int32_t count, int64_t n,
     }
   }
   for (int i : other) {
-    // the plain path reads the handle's counter: advance a copy of it
-    ising_lattice tmp = *hs[i];
-    ising_status st = enqueue_sweeps(&tmp, nsw ? nsw[i] : n, dev_EM ? dev_EM[i] : nullptr);
+    ising_status st = enqueue_sweeps(hs[i], nsw ? nsw[i] : n, dev_EM ? dev_EM[i] : nullptr);
     if (st != ISING_OK) return st;
   }
   if (!fits.empty()) {

@@ -4,8 +4,6 @@
 #include <algorithm>
 #include <cmath>
 #include <functional>
-#include <iterator>
-#include <map>
 #include <utility>
 
 namespace ising {
@@ -58,21 +56,24 @@ static BlockShape shape_of(int kind, int64_t L, int64_t rows, int K, int max_ls 
   // 64^2 1.71, 1.09, 0.92, 0.93; 128^2 1.90, 1.92, 2.17, 3.69; 512^2 in strips
   // of 2 rows, 8 sweeps 2.84, 2.66, 2.79, 3.07; 2048^2 in strips of 8 rows, 4
   // sweeps 5.34, 5.57, 6.23, 7.96.
-  s.ls = 1;
   const double halves = (double)(mean * nh);
-  for (int ls = 2; ls <= max_ls && kind <= kBlockLcg; ls *= 2)
-    if (nh * ls <= 1024 &&
-        step_seconds(kind, halves, ls, any) < step_seconds(kind, halves, s.ls, any))
+  s.ls = 1;
+  s.step_s = step_seconds(kind, halves, 1, any);
+  auto offer = [&](int ls) {
+    const double step = step_seconds(kind, halves, ls, any);
+    if (step < s.step_s) {
       s.ls = ls;
+      s.step_s = step;
+    }
+  };
+  for (int ls = 2; ls <= max_ls && kind <= kBlockLcg && nh * ls <= 1024; ls *= 2) offer(ls);
   // pools: a whole word per lane (ls 0) where that leaves enough waves: a lone
   // wave's step is longer with it (64^2, 128^2 stay with halves)
-  if (kind >= kBlockPool && step_seconds(kind, halves, 0, any) < step_seconds(kind, halves, 1, any))
-    s.ls = 0;
+  if (kind >= kBlockPool) offer(0);
   const int64_t per = s.ls ? nh * s.ls : W;
   s.pass = (int32_t)std::max<int64_t>(1, std::min<int64_t>(R, 1024 / per));
   s.threads = (int32_t)((s.pass * per + 63) / 64 * 64);
   s.lds = (size_t)(R * W) * (kind == kBlockLcg ? 24 : 16);
-  s.step_s = step_seconds(kind, halves, s.ls, any);
   s.issue_s = waves_of(halves, s.ls) * pass_instructions(kind, s.ls, any) / kClock;
   s.move_s = (double)(s.lds + 16 * s.rows * W) / kCuBytes;
   return s;
@@ -101,8 +102,9 @@ bool block_fits_single(int64_t L) {
 // have one, and so on.  A queue of 24 requests up to 2048^2: 28.9 ms with 379
 // strips, the best if they spread evenly over 256 units, 25.7 ms this way.
 static double busiest_issue(const std::vector<BlockShape>& shapes,
-                            const std::vector<std::pair<int64_t, int64_t>>& sides, int cus) {
-  std::vector<std::pair<double, int64_t>> of;
+                            const std::vector<std::pair<int64_t, int64_t>>& sides, int cus,
+                            std::vector<std::pair<double, int64_t>>& of) {
+  of.clear();
   for (size_t i = 0; i < shapes.size(); ++i)
     of.push_back({shapes[i].issue_s, shapes[i].strips * sides[i].second});
   std::sort(of.rbegin(), of.rend());
@@ -113,68 +115,152 @@ static double busiest_issue(const std::vector<BlockShape>& shapes,
   return sum;
 }
 
-// The cheapest cut of a set of lattices by the model: sweeps per launch K,
-// and strips of about `target` halves per mean colour step, so that the
-// strips of all lattices are about equal.  A lattice that fits one workgroup
-// takes a single strip where a strip would be as large.  With more lattices
-// than compute units a lattice's own step counts for less than the
-// instructions in all, so that fewer lanes per half can win: 300 sweeps of 600
-// lattices of 64^2 3.3 -> 1.1 ms, of 128^2 5.3 -> 1.95.
-BlockPlan plan_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int cus) {
-  BlockPlan best;  // a shape per distinct side
-  bool all_single = true;
-  for (int64_t L : Ls) all_single = all_single && block_fits_single(L);
-  std::map<int64_t, int64_t, std::greater<int64_t>> of;
-  for (int64_t L : Ls) ++of[L];
-  const std::vector<std::pair<int64_t, int64_t>> sides(of.begin(), of.end());
-  // a lone lattice's strips have a compute unit each
-  const int64_t lds = Ls.size() == 1 ? block_lone_lds(kind) : kBlockMaxLds;
-  auto consider = [&](int K, int64_t target, bool singles, int max_ls) {
-    BlockPlan p;
-    double longest = 0, move = 0;
+// A set of lattices to be cut, and the cheapest cut found so far.
+namespace {
+typedef std::vector<std::pair<int64_t, int64_t>> Sides;  // (side, lattices), largest first
+
+struct CutOf {  // sweeps per launch, halves per strip, lanes; target 0: one strip each
+  int K = 0;
+  int64_t target = 0;
+  int max_ls = 8;
+};
+
+struct Search {
+  int kind;
+  Sides sides;
+  int64_t lattices, lds;
+  int cus;
+  BlockPlan best, p;  // a shape per side
+  CutOf cut;           // best's
+  std::vector<std::pair<double, int64_t>> of;
+
+  Search(int kind_, const Sides& sides_, int64_t lattices_, int cus_, double limit)
+      : kind(kind_), sides(sides_), lattices(lattices_), cus(cus_) {
+    // a lone lattice's strips have a compute unit each
+    lds = lattices == 1 ? block_lone_lds(kind) : kBlockMaxLds;
+    best.sweep_s = limit;
+  }
+
+  void consider(const CutOf& c) {
+    const bool singles = c.target == 0;
+    const int K = c.K;
+    const double fixed = singles ? 0.0 : kLaunch / K, units = std::max(cus, 1);
+    double longest = 0, move = 0, issue = 0;
     int64_t strips = 0;
+    p.shapes.clear();
     for (const auto& side : sides) {
       const int64_t L = side.first, nh = (L / 2 + 31) / 32;
       // L rows at most in LDS, kBlockMaxStrips strips at most
-      int64_t rows = std::max<int64_t>(target / nh - 2 * (int64_t)K, 1);
+      int64_t rows = std::max<int64_t>(c.target / nh - 2 * (int64_t)K, 1);
       rows = std::max(rows, (L + kBlockMaxStrips - 1) / kBlockMaxStrips);
       const bool single = block_fits_single(L) && (singles || rows + 2 * K >= L);
+      // (with the largest side all others are single: one launch is cheaper)
+      if (single && !singles && p.shapes.empty()) return;
       if (single)
         rows = L;
-      else if (rows + 4 * (int64_t)K > L)
+      else if (singles || rows + 4 * (int64_t)K > L)
         return;
-      const BlockShape s = shape_of(kind, L, rows, K, max_ls);
+      const BlockShape s = shape_of(kind, L, rows, K, c.max_ls);
       if (s.lds > (size_t)lds || (!single && K > s.strips)) return;
       if (kind == kBlockPoolLinear && (int64_t)(s.lds / 16) / 256 + 3 > kMaxGroups) return;
-      // no cheaper than the best even if this strip is the longest (planning
-      // 24 lattices took 0.15 ms of the host without this line)
-      if (!best.shapes.empty() && 2 * s.step_s + (singles ? 0.0 : kLaunch / K) >= best.sweep_s)
-        return;
-      p.shapes.push_back(s);
-      longest = std::max(longest, s.step_s);
-      move = std::max(move, s.move_s);
       strips += s.strips * side.second;
+      if (strips > kBlockMaxTasks + lattices) return;
+      longest = std::max(longest, s.step_s);
+      issue += s.issue_s * (double)(s.strips * side.second);
+      // no cheaper than the best even if no other strip is longer and all of
+      // them spread evenly (the busiest unit has the mean at least)
+      if (2 * std::max(longest, issue / units) + fixed >= best.sweep_s) return;
+      p.shapes.push_back(s);
+      move = std::max(move, s.move_s);
     }
-    if (strips > kBlockMaxTasks + (int64_t)Ls.size()) return;
     p.sweeps = K;
     p.tasks = strips;
-    const double step = std::max(longest, busiest_issue(p.shapes, sides, cus));
+    const double step = std::max(longest, busiest_issue(p.shapes, sides, cus, of));
     p.sweep_s = 2 * step + (singles ? 0.0 : (kLaunch + move) / K);
-    if (best.shapes.empty() || p.sweep_s < best.sweep_s) best = p;
-  };
-  for (int max_ls = 8; max_ls >= ((int64_t)Ls.size() > cus ? 1 : 8); max_ls /= 2) {
-    if (all_single) consider(1, 0, true, max_ls);
-    if (n >= 2)
-      for (int K : {1, 2, 3, 4, 6, 8, 12})
-        if (K <= (n + 1) / 2)
-          for (int64_t target = 32; target <= 20000; target += target / 4)
-            consider(K, target, false, max_ls);
+    if (p.sweep_s < best.sweep_s) {
+      std::swap(best, p);
+      cut = c;
+    }
   }
-  if (best.shapes.empty()) return best;
+
+  // Calls of n sweeps.  With more lattices than compute units a lattice's own
+  // step counts for less than the instructions in all, so that fewer lanes per
+  // half can win: 300 sweeps of 600 lattices of 64^2 3.3 -> 1.1 ms, of 128^2
+  // 5.3 -> 1.95.
+  void all(int64_t n) {
+    const int least = lattices > cus ? 1 : 8;
+    for (int max_ls = 8; max_ls >= least; max_ls /= 2) consider(CutOf{1, 0, max_ls});
+    if (n < 2) return;
+    std::vector<int64_t> targets;
+    for (int64_t target = 32; target <= 20000; target += target / 4) targets.push_back(target);
+    // every fourth target first, so that the others are measured by a good cut
+    for (size_t step : {4, 1})
+      for (int max_ls = 8; max_ls >= least; max_ls /= 2)
+        for (int K : {1, 2, 3, 4, 6, 8, 12})
+          if (K <= (n + 1) / 2)
+            for (size_t i = 0; i < targets.size(); i += step)
+              if (step == 4 || i % 4) consider(CutOf{K, targets[i], max_ls});
+  }
+};
+
+// Runs of neighbouring sides as so many of their middle one: few enough to be
+// searched in the time of a few sweeps.
+Sides grouped(const Sides& sides) {
+  const size_t run = (sides.size() + kBlockPlanSides - 1) / kBlockPlanSides;
+  Sides g;
+  for (size_t at = 0; at < sides.size(); at += run) {
+    const size_t end = std::min(at + run, sides.size());
+    g.push_back({sides[(at + end) / 2].first, 0});
+    for (size_t i = at; i < end; ++i) g.back().second += sides[i].second;
+  }
+  return g;
+}
+}  // namespace
+
+// The cheapest cut of a set of lattices by the model: sweeps per launch K,
+// and strips of about `target` halves per mean colour step, so that the
+// strips of all lattices are about equal.  A lattice that fits one workgroup
+// takes a single strip where a strip would be as large.  The host waits for
+// this in every batched call, so a cut is given up as soon as it cannot win,
+// and with many sides and few sweeps near sides are searched as one.  A call
+// of 24 sweeps of 24, 87 or 120 distinct sides is planned in 0.06, 0.10 and
+// 0.14 ms, 0.34, 1.8 and 10.5 with every cut of every side.
+BlockPlan plan_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int cus,
+                      double limit) {
+  std::vector<int64_t> sorted(Ls);
+  std::sort(sorted.begin(), sorted.end(), std::greater<int64_t>());
+  Sides sides;
+  for (int64_t L : sorted) {
+    if (sides.empty() || sides.back().first != L) sides.push_back({L, 0});
+    ++sides.back().second;
+  }
+  const int64_t lattices = (int64_t)Ls.size();
+  Search s(kind, sides, lattices, cus, limit);
+  // (grouped, a cut is up to a tenth dearer: 87 sides 12.5 us per sweep, each
+  // by itself 11.6, in four times the planning)
+  if (sides.size() <= kBlockPlanSides || n >= 8 * (int64_t)sides.size()) {
+    s.all(n);
+  } else {
+    // the cut of the groups, with strips as long and around that
+    Search g(kind, grouped(sides), lattices, cus, 1.1 * limit);
+    g.all(n);
+    if (g.best.shapes.empty()) return BlockPlan();
+    s.consider(g.cut);
+    for (double f : {1.25, 0.8, 1.5, 0.65, 1.9})
+      if (g.cut.target)
+        s.consider(CutOf{g.cut.K, (int64_t)(f * (double)g.cut.target), g.cut.max_ls});
+    if (s.best.shapes.empty()) s.all(n);
+  }
+  BlockPlan best;
+  if (s.best.shapes.empty()) return best;
+  best = s.best;
   std::vector<BlockShape> shapes;
   best.all_single = true;
   for (int64_t L : Ls) {
-    shapes.push_back(best.shapes[std::distance(of.begin(), of.find(L))]);
+    const auto at = std::lower_bound(
+        sides.begin(), sides.end(), L,
+        [](const std::pair<int64_t, int64_t>& side, int64_t v) { return side.first > v; });
+    shapes.push_back(best.shapes[at - sides.begin()]);
     best.all_single = best.all_single && shapes.back().strips == 1;
   }
   best.shapes = shapes;

@@ -57,6 +57,8 @@ struct BlockShape {
 constexpr double kBlockMaxSites = 6.4e7;
 // Calls of at least this many sweeps are all cut alike.
 constexpr int64_t kBlockPlanN = 24;
+// Distinct sides up to which each is planned by itself, however few the sweeps.
+constexpr size_t kBlockPlanSides = 24;
 
 // The cut of a set of lattices (one shape each, in order).
 struct BlockPlan {
@@ -73,6 +75,9 @@ bool block_fits_single(int64_t L);
 // Model: seconds per sweep of lattices with `words` words per colour in all
 // when every colour step is a launch.
 double launch_per_step_seconds(int kind, double words, int cus);
-BlockPlan plan_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int cus);
+// The cheapest cut for calls of n sweeps; empty if none takes less than
+// `limit` seconds per sweep.
+BlockPlan plan_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int cus,
+                      double limit = 1e9);
 
 }  // namespace ising

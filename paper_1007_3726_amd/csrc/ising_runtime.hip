@@ -306,20 +306,20 @@ ising_status enqueue_sweeps(ising_lattice* h, int64_t n, int64_t* dev_EM) {
   if (use_small_path(h))
     return enqueue_block_sweeps(h, block_shape_single(block_kind(h), h->L), n, dev_EM);
   if (use_block_path(h, n)) {
-    // the shape depends on the dynamics, and on n only below kBlockPlanN
-    // sweeps; kept with the handle
     const int kind = block_kind(h);
-    const int64_t key = std::min(n, kBlockPlanN) + (kBlockPlanN + 1) * kind;
-    if (h->block_n != key) {
+    const int64_t per_call = std::min(n, kBlockPlanN);
+    if (h->block_of != kind) h->block_planned = 0;
+    h->block_of = kind;
+    BlockShape& shape = h->block[per_call];
+    if (!(h->block_planned >> per_call & 1)) {
       const int cus = device_cus(h->device);
-      const BlockPlan plan = plan_blocks(kind, {h->L}, std::min(n, kBlockPlanN), cus);
-      h->block = plan.shapes.empty() ||
-                         plan.sweep_s >= launch_per_step_seconds(kind, (double)h->plane_words, cus)
-                     ? BlockShape()
-                     : plan.shapes[0];
-      h->block_n = key;
+      const BlockPlan plan =
+          plan_blocks(kind, {h->L}, per_call, cus,
+                      launch_per_step_seconds(kind, (double)h->plane_words, cus));
+      shape = plan.shapes.empty() ? BlockShape() : plan.shapes[0];
+      h->block_planned |= 1u << per_call;
     }
-    if (h->block.strips > 0) return enqueue_block_sweeps(h, h->block, n, dev_EM);
+    if (shape.strips > 0) return enqueue_block_sweeps(h, shape, n, dev_EM);
   }
   TileArgs ta;
   if (h->pool) return enqueue_pool_sweeps(h, n, dev_EM);
@@ -436,7 +436,7 @@ ising_status ising_create(int64_t L, uint64_t seed, uint32_t stream_id, int32_t 
   h->init = init;
   h->stream = (hipStream_t)hip_stream;
   h->sweep = 0;
-  h->block_n = 0;
+  h->block_planned = 0;
   h->beta_set = false;
   hipError_t e = hipGetDevice(&h->device);
   if (e != hipSuccess) {

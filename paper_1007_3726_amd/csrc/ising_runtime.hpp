@@ -71,8 +71,11 @@ struct ising_lattice {
   hipStream_t stream;
   int device;
   ising::Tuning tune;
-  ising::BlockShape block;  // strips 0: colour steps are launches
-  int64_t block_n;          // the sweeps per call and dynamics it is for, 0: none yet
+  // Blocks by sweeps per call (kBlockPlanN and more alike); strips 0: colour
+  // steps are launches.  Planned so far: bit n of block_planned, for block_of.
+  ising::BlockShape block[ising::kBlockPlanN + 1];
+  uint32_t block_planned;
+  int32_t block_of;  // dynamics
 };
 
 namespace ising {

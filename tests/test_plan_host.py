@@ -28,17 +28,18 @@ def plans():
                         os.path.join(csrc, "ising_plan.cpp")], check=True)
 
         def run(cases):
-            """cases: (kind, n, cus, Ls); (microseconds per sweep, strips, shapes) of each."""
+            """cases: (kind, n, cus, Ls); (microseconds per sweep, strips, shapes,
+            microseconds of planning) of each."""
             text = "".join("%d %d %d %d %s\n" % (k, n, c, len(Ls), " ".join(map(str, Ls)))
                            for k, n, c, Ls in cases)
             r = subprocess.run([out], input=text, capture_output=True, text=True, check=True)
             res = []
             for ln in r.stdout.splitlines():
                 f = ln.split()
-                v = [int(x) for x in f[3:]]
+                v = [int(x) for x in f[4:]]
                 shapes = [dict(zip(("rows", "strips", "ls", "pass", "threads", "sweeps", "lds"),
-                                   v[7 * i:7 * i + 7])) for i in range(int(f[2]))]
-                res.append((float(f[0]), int(f[1]), shapes))
+                                   v[7 * i:7 * i + 7])) for i in range(int(f[3]))]
+                res.append((float(f[1]), int(f[2]), shapes, float(f[0])))
             assert len(res) == len(cases)
             return res
         yield run
@@ -55,7 +56,7 @@ def test_every_lone_plan_can_be_launched(plans, kind):
     the kernel's own part of it, and the halos stay inside the lattice."""
     for cus in (256, 64):
         cases = [(kind, n, cus, [L]) for n in SWEEPS for L in _sides(kind)]
-        for (_, n, _, Ls), (_, _, shapes) in zip(cases, plans(cases)):
+        for (_, n, _, Ls), (_, _, shapes, _) in zip(cases, plans(cases)):
             L, W = Ls[0], (Ls[0] // 2 + 63) // 64
             for s in shapes:
                 where = (L, n, cus, s)
@@ -68,3 +69,21 @@ def test_every_lone_plan_can_be_launched(plans, kind):
                     assert s["sweeps"] <= s["strips"] and (s["strips"] - 1) * s["rows"] < L, where
                 if kind == POOL_LINEAR:  # groups of 256 words, the lattice's first ones again
                     assert R * W // 256 + 3 <= 64, where
+
+
+SETS = [[64 + 16 * k for k in range(24)], [64 + 8 * k for k in range(87)],
+        [64 + 8 * k for k in range(279)], [8 + 2 * (k % 120) for k in range(600)],
+        [8 * (k + 1) for k in range(60)], [256] * 200, [6 + 2 * (k % 9) for k in range(900)]]
+
+
+@pytest.mark.parametrize("Ls", SETS)
+def test_planning_is_short_beside_the_sweeps(plans, Ls):
+    """Batches of many sides, 24 sweeps: planning is a fraction of the time
+    that the sweeps take (every cut of 279 sides took 21 ms, of 120 sides
+    10.5), and the cut nearly as good as that of a long call, for which every
+    side is searched."""
+    (short, _, shapes, us), (long_, _, best, _) = plans([(PHILOX, 24, 256, Ls),
+                                                        (PHILOX, 10 ** 6, 256, Ls)])
+    assert us < 1000
+    assert bool(shapes) == bool(best)
+    assert short <= 1.25 * long_
