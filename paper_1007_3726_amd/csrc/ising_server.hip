@@ -9,9 +9,11 @@
 //   2. one batched call advances every active lattice by up to
 //      quantum_sweeps sweeps (fewer for a request that has fewer left), all
 //      lattices together in fused launches, blocks of several sweeps per
-//      launch or one packed launch, with the task tables in a region reserved at the end of the arena (1/32 of
-//      it; every admitted lattice also reserves its share of that region,
-//      so the tables of any active set fit);
+//      launch or one packed launch, with the task tables in a region
+//      reserved at the end of the arena (1/32 of it; every admitted lattice
+//      also reserves its share of that region, so the tables of any active
+//      set fit).  Strips need a second copy of the planes, which lies in
+//      arena space that no request has: admission does not see the copies;
 //   3. retirement: finished requests copy their series/spins to the
 //      caller's host buffers, get exact moment sums, a completion time, and
 //      free their arena space, so the next step can admit more.
@@ -83,6 +85,7 @@ class Arena {
     }
   }
   size_t used() const { return used_; }
+  const std::map<size_t, size_t>& free_ranges() const { return free_; }
 
  private:
   std::map<size_t, size_t> free_;
@@ -96,7 +99,6 @@ struct Job {
   ising_request req;
   State state = State::Queued;
   size_t off = 0, bytes = 0;   // arena slice: lattice then series
-  size_t spare_off = 0, spare_bytes = 0;  // second copy of the planes, if it has one
   size_t share = 0;            // reserved bytes of the task-table region
   ising_lattice* h = nullptr;
   int64_t* dev_series = nullptr;
@@ -122,6 +124,11 @@ struct ising_server {
   hipStream_t stream;
   int32_t quantum;
   Arena arena;
+  // Second copies of the planes (several sweeps per launch): offset -> (bytes,
+  // ticket).  They lie in what the arena counts as free, from its end down, and
+  // go as soon as a request needs the place.
+  std::map<size_t, std::pair<size_t, uint64_t>> spares;
+  size_t spare_bytes = 0;
   uint64_t next_ticket = 1;
   std::map<uint64_t, Job> jobs;
   std::deque<uint64_t> queue;
@@ -145,6 +152,63 @@ struct ising_server {
 namespace ising {
 namespace {
 
+// Takes the second copies away that lie in [lo, hi) or belong to `ticket`
+// (nothing is in flight: a quantum leaves the result in the lattice's own
+// planes).
+void take_spares(ising_server* s, size_t lo, size_t hi, uint64_t ticket = 0) {
+  for (auto it = s->spares.begin(); it != s->spares.end();) {
+    if ((it->first < hi && it->first + it->second.first > lo) || it->second.second == ticket) {
+      Job& j = s->jobs.at(it->second.second);
+      (void)ising_set_spare(j.h, nullptr, 0);
+      s->spare_bytes -= it->second.first;
+      it = s->spares.erase(it);
+    } else {
+      ++it;
+    }
+  }
+}
+
+// The highest place for `bytes` that neither a request nor another copy has.
+bool spare_place(const ising_server* s, size_t bytes, size_t* off) {
+  const auto& ranges = s->arena.free_ranges();
+  for (auto r = ranges.rbegin(); r != ranges.rend(); ++r) {
+    const size_t lo = r->first;
+    size_t hi = lo + r->second;
+    auto it = s->spares.lower_bound(hi);
+    for (;;) {
+      const bool more = it != s->spares.begin() && std::prev(it)->first >= lo;
+      const size_t below = more ? std::prev(it)->first + std::prev(it)->second.first : lo;
+      if (hi - below >= bytes) {
+        *off = hi - bytes;
+        return true;
+      }
+      if (!more) break;
+      --it;
+      hi = it->first;
+    }
+  }
+  return false;
+}
+
+// Second copies for the active lattices without one, of sides that a batch may
+// cut into strips, while half the arena stays free.
+ising_status give_spares(ising_server* s) {
+  for (uint64_t t : s->active) {
+    Job& j = s->jobs.at(t);
+    const size_t bytes = align256(ising_spare_bytes(j.req.L));
+    size_t off;
+    if (j.h->spare || !bytes || (double)j.req.L * (double)j.req.L > kBlockMaxSites ||
+        s->arena.used() + s->spare_bytes + bytes > s->arena_bytes / 2 ||
+        !spare_place(s, bytes, &off))
+      continue;
+    const ising_status st = ising_set_spare(j.h, s->arena_base + off, bytes);
+    if (st != ISING_OK) return st;
+    s->spares[off] = {bytes, t};
+    s->spare_bytes += bytes;
+  }
+  return ISING_OK;
+}
+
 ising_status admit(ising_server* s) {
   while (!s->queue.empty()) {
     Job& j = s->jobs.at(s->queue.front());
@@ -153,6 +217,7 @@ ising_status admit(ising_server* s) {
     if (s->table_used + j.share > s->table_bytes) break;
     if (!s->arena.alloc(j.bytes, &off)) break;
     j.off = off;
+    take_spares(s, off, off + j.bytes);
     ising_t* h = nullptr;
     const size_t lb = align256(lattice_bytes(j.req.L));
     ising_status st = ising_create(j.req.L, j.req.seed, j.req.stream_id, j.req.init,
@@ -164,15 +229,6 @@ ising_status admit(ising_server* s) {
       return st;
     }
     j.h = h;
-    // the second copy of the planes (several sweeps per launch) only while
-    // half the arena stays free, so that it never holds a request back, and
-    // for sides that a batch may take blocks with
-    const size_t sb = align256(ising_spare_bytes(j.req.L));
-    if (sb && (double)j.req.L * (double)j.req.L <= kBlockMaxSites && s->arena.used() + sb <= s->arena_bytes / 2 && s->arena.alloc(sb, &j.spare_off)) {
-      j.spare_bytes = sb;
-      st = ising_set_spare(h, s->arena_base + j.spare_off, sb);
-      if (st != ISING_OK) return st;
-    }
     s->table_used += j.share;
     j.dev_series = (int64_t*)(s->arena_base + off + lb);
     j.state = State::Active;
@@ -182,7 +238,7 @@ ising_status admit(ising_server* s) {
     ++s->admitted;
     s->peak = std::max<int64_t>(s->peak, (int64_t)s->arena.used());
   }
-  return ISING_OK;
+  return give_spares(s);
 }
 
 }  // namespace
@@ -285,8 +341,7 @@ ising_status begin_retire(ising_server* s, const std::vector<uint64_t>& done) {
     s->leaving.emplace_back(t, off);
     off += n;
     s->arena.release(j.off, j.bytes);
-    if (j.spare_bytes) s->arena.release(j.spare_off, j.spare_bytes);
-    j.spare_bytes = 0;
+    take_spares(s, 0, 0, t);
     s->table_used -= j.share;
   }
   hipError_t e = hipEventRecord(s->copied, s->stream);

@@ -193,3 +193,65 @@ def test_schedule_never_changes_results(I):
         if r["L"] <= 256:
             assert np.array_equal(got["spins"], lat.get_spins()), r
         del lat
+
+
+def test_second_copies_never_hold_a_request_back(I):
+    """Two lattices whose second copies fill the arena to less than half, then
+    a request that fits beside the lattices but not beside the copies: it is
+    admitted in the next step, and everything's results are the plain path's.
+    Memory in use counts requests only."""
+    def req(L, n, i):
+        return {"L": L, "beta": 1 / 2.3, "seed": 60 + i, "stream_id": i,
+                "init": workloads.INIT_HOT, "n_sweeps": n, "record_series": True,
+                "return_spins": True}
+
+    reqs = [req(1024, 60, 0), req(1024, 45, 1), req(4608, 12, 2), req(1024, 20, 3)]
+    size = [(I.ising_lattice_bytes(r["L"]) + 255) // 256 * 256 +
+            (16 * r["n_sweeps"] + 255) // 256 * 256 for r in reqs]
+    arena = (sum(size[:3]) + (32 << 10)) * 32 // 31  # 1/32 holds the task tables
+    assert sum(size[:3]) + 2 * int(I.lib().ising_spare_bytes(1024)) > arena
+    srv = I.Server(arena, quantum_sweeps=10)
+    tickets = srv.submit(reqs[:2])
+    srv.step()
+    assert srv.stats()["admitted"] == 2 and srv.stats()["bytes_in_use"] == sum(size[:2])
+    tickets += srv.submit(reqs[2:])
+    srv.step()
+    assert srv.stats()["admitted"] >= 3
+    srv.run_until_idle()
+    assert srv.stats()["peak_bytes"] <= sum(size)
+    for r, t in zip(reqs, tickets):
+        got = srv.poll(t)
+        lat = I.Lattice(r["L"], seed=r["seed"], stream_id=r["stream_id"], init=r["init"],
+                        beta=r["beta"])
+        assert np.array_equal(got["series"], lat.sweep_em(r["n_sweeps"]).cpu().numpy()), r["L"]
+        assert np.array_equal(got["spins"], lat.get_spins()), r["L"]
+    srv.close()
+
+
+def test_requests_come_and_go_around_second_copies(I):
+    """Uneven sides and lengths in arenas where copies are given, moved over
+    and taken away: every result is the plain path's."""
+    rng = np.random.default_rng(17)
+    reqs = [{"L": int(L), "beta": 1 / float(rng.uniform(1.6, 3.0)), "seed": 90 + i,
+             "stream_id": i, "init": workloads.INIT_HOT, "n_sweeps": int(rng.integers(3, 60)),
+             "record_series": True, "return_spins": True}
+            for i, L in enumerate(8 * rng.integers(8, 200, 40))]
+    alone = []
+    for r in reqs:
+        lat = I.Lattice(r["L"], seed=r["seed"], stream_id=r["stream_id"], init=r["init"],
+                        beta=r["beta"])
+        alone.append((lat.sweep_em(r["n_sweeps"]).cpu().numpy(), lat.get_spins()))
+    for arena in (1 << 20, 3 << 20, 12 << 20):
+        srv = I.Server(arena, quantum_sweeps=7)
+        srv.inject_fault(3)
+        tickets = []
+        for at in range(0, len(reqs), 5):  # five more every other step
+            tickets += srv.submit(reqs[at:at + 5])
+            srv.step()
+            srv.step()
+        srv.run_until_idle()
+        for r, t, (em, s) in zip(reqs, tickets, alone):
+            got = srv.poll(t)
+            assert np.array_equal(got["series"], em), (arena, r["L"])
+            assert np.array_equal(got["spins"], s), (arena, r["L"])
+        srv.close()
