@@ -104,10 +104,14 @@ ISING_API ising_status ising_create(int64_t L, uint64_t seed, uint32_t stream_id
  * Without one (the default) every colour step is a launch.  dev_spare is the
  * caller's, 8-byte aligned, at least ising_spare_bytes(L) bytes, and stays
  * with the handle until it is replaced or the handle destroyed (NULL takes
- * it away); its contents mean nothing between calls.  ising_spare_bytes is 0
- * for sides that take none (invalid, or too large to gain by it).  Results
- * are the same with and without.
- * Errors: EINVAL (NULL handle, a side that takes none, alignment), ENOMEM.
+ * it away); its contents mean nothing between calls, but enqueued sweeps use
+ * it: it may be freed or reused once the handle's stream has passed them.
+ * Handles of one stream may share a copy (a batch of such handles runs without
+ * the copies), handles of different streams may not.  ising_spare_bytes is 0
+ * for sides that take none (invalid, or too large to gain by it).  Results are
+ * the same with and without.
+ * Errors: EINVAL (NULL handle, a side that takes none, alignment, an overlap
+ * with the lattice's own ising_lattice_bytes), ENOMEM.
  */
 ISING_API size_t ising_spare_bytes(int64_t L);
 ISING_API ising_status ising_set_spare(ising_t *h, void *dev_spare, size_t bytes);

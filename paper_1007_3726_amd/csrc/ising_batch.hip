@@ -349,6 +349,21 @@ static size_t work_bytes_for(ising_lattice* const* hs, const std::vector<int>& t
   return std::max(fused_layout(nl, ntiles).bytes, block_layout(nl, nl).bytes);
 }
 
+// Whether every lattice that the plan cuts into strips has a copy of its own:
+// strips of one launch write all of them.
+static bool own_spares(ising_lattice* const* hs, const BlockPlan& plan) {
+  std::vector<std::pair<uintptr_t, size_t>> at;
+  for (size_t i = 0; i < plan.shapes.size(); ++i) {
+    if (plan.shapes[i].strips == 1) continue;
+    if (!hs[i]->spare) return false;
+    at.push_back({(uintptr_t)hs[i]->spare, ising_spare_bytes(hs[i]->L)});
+  }
+  std::sort(at.begin(), at.end());
+  for (size_t i = 1; i < at.size(); ++i)
+    if (at[i - 1].first + at[i - 1].second > at[i].first) return false;
+  return true;
+}
+
 size_t batch_work_bytes(ising_lattice* const* hs, int32_t count, const BatchOptions& opt) {
   std::vector<int> tiled, other;
   std::vector<TileArgs> targs;
@@ -413,9 +428,7 @@ ising_status batch_sweeps(ising_lattice* const* hs, int32_t count, int64_t n,
     }
     BlockPlan plan;
     if (spares && choose_blocks(Ls, n, cus, &plan)) {
-      bool ok = block_layout(count, plan.tasks).bytes <= work_bytes;
-      for (int i = 0; i < count && ok; ++i) ok = plan.shapes[i].strips == 1 || hs[i]->spare;
-      if (ok) {
+      if (block_layout(count, plan.tasks).bytes <= work_bytes && own_spares(hs, plan)) {
         if (form_out) *form_out = plan.all_single ? 1 : 0;
         return run_blocks(hs, all, n, nsw, dev_EM, plan, (char*)work, opt.keep_image);
       }

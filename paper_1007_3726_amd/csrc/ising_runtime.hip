@@ -478,6 +478,9 @@ ising_status ising_set_spare(ising_t* h, void* dev_spare, size_t bytes) {
     return fail(ISING_EINVAL, "ising_set_spare: buffer must be 8-byte aligned");
   if (bytes < need)
     return fail(ISING_ENOMEM, "ising_set_spare: %zu bytes < %zu needed", bytes, need);
+  const uintptr_t at = (uintptr_t)dev_spare, own = (uintptr_t)h->planes;
+  if (at < own + lattice_bytes(h->L) && own < at + need)
+    return fail(ISING_EINVAL, "ising_set_spare: the buffer overlaps the lattice");
   h->spare = (uint64_t*)dev_spare;
   return ISING_OK;
 }

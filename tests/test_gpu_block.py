@@ -261,3 +261,33 @@ def test_pool_block_that_fills_the_lds(I):
         rows = [lat.get_window(0, (y0 + i) % L, L, 1)[0] for i in range(12)]
         xs = (x0 + np.arange(40)) % L
         assert np.array_equal(np.stack([r[xs] for r in rows]), want), (x0, y0)
+
+
+# one copy for all, and copies that overlap in part
+@pytest.mark.parametrize("shift", [0, 4096])
+def test_batch_of_lattices_that_share_a_spare_copy(I, shift):
+    import torch
+    n, spec = 14, [(1024, 2.2), (512, 1.4), (1002, 2.3), (1024, 2.0)]
+    lats = [I.Lattice(L, seed=6, stream_id=i, init=workloads.INIT_HOT, beta=1 / T)
+            for i, (L, T) in enumerate(spec)]
+    need = int(I.lib().ising_spare_bytes(1024))
+    buf = torch.empty(need + 8 * shift, dtype=torch.uint8, device="cuda")
+    for i, lat in enumerate(lats):
+        I.check(I.lib().ising_set_spare(lat.h, buf.data_ptr() + i * shift, need))
+    I.multi_sweep(lats, n)
+    for lat in lats:  # one after another
+        lat.sweep(5)
+    for i, (L, T) in enumerate(spec):
+        s, _ = oracle.run(L, 1 / T, 6, i, workloads.INIT_HOT, n + 5)
+        assert np.array_equal(lats[i].get_spins(), s), (L, T)
+
+
+def test_spare_copy_may_not_overlap_its_lattice(I):
+    L = 512
+    lat = I.Lattice(L, seed=2, init=workloads.INIT_HOT, beta=1 / 2.3)
+    need, size = int(I.lib().ising_spare_bytes(L)), I.ising_lattice_bytes(L)
+    for off in (0, 4096, size - 8):
+        assert I.lib().ising_set_spare(lat.h, lat.buf.data_ptr() + off, need) == I.ISING_EINVAL
+    lat.sweep(9)  # the copy is still the one behind the lattice
+    s, _ = oracle.run(L, 1 / 2.3, 2, 0, workloads.INIT_HOT, 9)
+    assert np.array_equal(lat.get_spins(), s)
