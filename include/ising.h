@@ -236,6 +236,15 @@ ISING_API ising_status ising_batch_plan(const int64_t *Ls, int32_t count, int32_
                                         int32_t *form_out, int32_t *blocks_out,
                                         double *est_seconds_out);
 
+/*
+ * The form that ising_sweep(h, n, ...) runs in now (*form_out, ISING_FORM_*
+ * below) and the launches of its sweep kernel (*launches_out; the few that
+ * finish a series or move generators on are not counted).  n >= 1.  Host-only;
+ * for inspection and tests.  Errors: EINVAL.
+ */
+ISING_API ising_status ising_sweep_plan(ising_t *h, int64_t n, int32_t *form_out,
+                                        int64_t *launches_out);
+
 /* ---------------------------------------------------------------- */
 /* Autotuner: launch shapes of the plain sweep per lattice size class. */
 /* ---------------------------------------------------------------- */
@@ -244,6 +253,10 @@ ISING_API ising_status ising_batch_plan(const int64_t *Ls, int32_t count, int32_
                               loaded directly (the default) */
 #define ISING_FORM_STRIP 1 /* one wave per 64-word x rpw-row strip, rows rolled in
                               registers (rows of >= 63 words only; others use tiles) */
+/* forms that no tuning entry installs */
+#define ISING_FORM_BLOCK 2 /* several sweeps per launch on rows held in LDS */
+#define ISING_FORM_WORD 3  /* one word per lane (planes of 2^32 words or more that
+                              have no tiles) */
 
 typedef struct {
     int64_t L_min, L_max;    /* size class the entry applies to */

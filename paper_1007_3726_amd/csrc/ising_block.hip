@@ -742,13 +742,7 @@ BlockLattice block_lattice(const ising_lattice* h, const BlockShape& s, int64_t 
   b.ls = s.ls;
   b.pass = s.pass;
   b.threads = s.threads;
-  if (s.strips == 1) {
-    const int64_t per = one_launch ? (int64_t)1 << 20 : s.sweeps;
-    b.launches = (int32_t)std::max<int64_t>((n + per - 1) / per, 1);
-  } else {
-    // an even number of launches leaves the result in the lattice's own planes
-    b.launches = (int32_t)(2 * ((n + 2 * s.sweeps - 1) / (2 * s.sweeps)));
-  }
+  b.launches = (int32_t)block_launches(s, n, one_launch);
   b.k0 = (uint32_t)h->seed;
   b.k1 = (uint32_t)(h->seed >> 32);
   b.sid4 = h->stream_id << 2;

@@ -92,6 +92,15 @@ double launch_per_step_seconds(int kind, double words, int cus) {
 
 BlockShape block_shape_single(int kind, int64_t L) { return shape_of(kind, L, L, 1); }
 
+int64_t block_launches(const BlockShape& s, int64_t n, bool one_launch) {
+  if (s.strips == 1) {
+    const int64_t per = one_launch ? (int64_t)1 << 20 : s.sweeps;
+    return std::max<int64_t>((n + per - 1) / per, 1);
+  }
+  // an even number of launches leaves the result in the lattice's own planes
+  return 2 * ((n + 2 * s.sweeps - 1) / (2 * s.sweeps));
+}
+
 // Both planes of a single strip fit one workgroup's LDS.
 bool block_fits_single(int64_t L) {
   return L <= kBlockMaxL && 2 * (int64_t)plane_bytes(L) <= kBlockMaxLds;

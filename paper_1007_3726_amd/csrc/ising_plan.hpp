@@ -70,6 +70,9 @@ struct BlockPlan {
 };
 
 BlockShape block_shape_single(int kind, int64_t L);
+// Launches of a lattice's n sweeps; one_launch: a single strip runs them all in
+// its first launch, else as many per launch as the shape's.
+int64_t block_launches(const BlockShape& s, int64_t n, bool one_launch);
 // Both planes of a single strip fit one workgroup's LDS.
 bool block_fits_single(int64_t L);
 // Model: seconds per sweep of lattices with `words` words per colour in all

@@ -265,15 +265,12 @@ static bool pool_tile_args(const ising_lattice* h, TileArgs* out) {
   return true;
 }
 
-static ising_status enqueue_pool_sweeps(ising_lattice* h, int64_t n, int64_t* dev_EM) {
-  TileArgs ta;
-  if (!pool_tile_args(h, &ta))
-    return fail(ISING_EINVAL, "pattern-pool dynamics need L %% 8 == 0 and < 2^32 words per plane");
+static ising_status enqueue_pool_sweeps(ising_lattice* h, TileArgs ta, int blocks, int64_t n,
+                                        int64_t* dev_EM) {
   ta.pool = h->pool;
   ta.pool_shift = (uint32_t)(32 - h->pool_m);
   ta.pool_mask = (uint32_t)((1ull << h->pool_m) - 1);
   ta.pool_linear = h->pool_linear ? 1 : 0;
-  const int blocks = (int)std::min<int64_t>(ta.tiles, kMaxSweepBlocks);
   for (int64_t k = 0; k < n; ++k) {
     ta.t = (uint32_t)(h->sweep + (uint64_t)k);
     ta.prev_EM = (dev_EM && k > 0) ? dev_EM + 2 * (k - 1) : nullptr;
@@ -301,12 +298,24 @@ static ising_status fill_pool(ising_lattice* h) {
   return e == hipSuccess ? ISING_OK : hip_fail(e, "pattern pool fill");
 }
 
-ising_status enqueue_sweeps(ising_lattice* h, int64_t n, int64_t* dev_EM) {
-  if (n == 0) return ISING_OK;
-  if (use_small_path(h))
-    return enqueue_block_sweeps(h, block_shape_single(block_kind(h), h->L), n, dev_EM);
+// The form of a call of n sweeps.
+struct SweepPlan {
+  int form;  // ISING_FORM_*, kFormNone: these dynamics do not run here
+  BlockShape shape;
+  TileArgs ta;
+  int blocks;  // grid of a colour step
+};
+constexpr int kFormNone = -1;
+
+static SweepPlan plan_sweeps(ising_lattice* h, int64_t n) {
+  SweepPlan p;
+  p.form = ISING_FORM_BLOCK;
+  const int kind = block_kind(h);
+  if (use_small_path(h)) {
+    p.shape = block_shape_single(kind, h->L);
+    return p;
+  }
   if (use_block_path(h, n)) {
-    const int kind = block_kind(h);
     const int64_t per_call = std::min(n, kBlockPlanN);
     if (h->block_of != kind) h->block_planned = 0;
     h->block_of = kind;
@@ -319,19 +328,43 @@ ising_status enqueue_sweeps(ising_lattice* h, int64_t n, int64_t* dev_EM) {
       shape = plan.shapes.empty() ? BlockShape() : plan.shapes[0];
       h->block_planned |= 1u << per_call;
     }
-    if (shape.strips > 0) return enqueue_block_sweeps(h, shape, n, dev_EM);
+    p.shape = shape;
+    if (shape.strips > 0) return p;
   }
-  TileArgs ta;
-  if (h->pool) return enqueue_pool_sweeps(h, n, dev_EM);
+  TileArgs& ta = p.ta;
+  if (h->pool) {
+    p.form = pool_tile_args(h, &ta) ? ISING_FORM_TILE : kFormNone;
+    p.blocks = (int)std::min<int64_t>(ta.tiles, kMaxSweepBlocks);
+    return p;
+  }
   const bool strip = strip_args(h, &ta);
   const bool tile = !strip && tile_args(h, &ta);
   if (tile) make_flat(ta);  // direct-load tiles: every lane busy at any W
   if (strip || tile || (h->lcg == nullptr && any_tile_args(h, &ta))) {
     if (!strip && h->tune.rpw == 0) balance_tiles(ta, device_cus(h->device));
     const int64_t units = strip ? (ta.tiles + 3) / 4 : ta.tiles;  // 4 wave tasks per block
-    const int blocks = (int)std::min<int64_t>(units, std::min(h->tune.max_blocks,
-                                                              kMaxSweepBlocks));
-    auto launch = strip ? launch_strip_sweep : launch_tile_sweep;
+    p.form = strip ? ISING_FORM_STRIP : ISING_FORM_TILE;
+    p.blocks = (int)std::min<int64_t>(units, std::min(h->tune.max_blocks, kMaxSweepBlocks));
+    return p;
+  }
+  p.form = h->lcg ? kFormNone : ISING_FORM_WORD;
+  p.blocks = grid_blocks(h->plane_words, 256, h->tune.max_blocks);
+  return p;
+}
+
+ising_status enqueue_sweeps(ising_lattice* h, int64_t n, int64_t* dev_EM) {
+  if (n == 0) return ISING_OK;
+  SweepPlan p = plan_sweeps(h, n);
+  if (p.form == ISING_FORM_BLOCK) return enqueue_block_sweeps(h, p.shape, n, dev_EM);
+  if (p.form == kFormNone && h->pool)
+    return fail(ISING_EINVAL, "pattern-pool dynamics need L %% 8 == 0 and < 2^32 words per plane");
+  if (p.form == kFormNone)
+    return fail(ISING_EINVAL, "LCG dynamics need the tiled layout (L %% 8 == 0)");
+  if (h->pool) return enqueue_pool_sweeps(h, p.ta, p.blocks, n, dev_EM);
+  const int blocks = p.blocks;
+  if (p.form != ISING_FORM_WORD) {
+    TileArgs& ta = p.ta;
+    auto launch = p.form == ISING_FORM_STRIP ? launch_strip_sweep : launch_tile_sweep;
     ta.lcg = h->lcg;
     uint32_t l8d = 0;
     lcg_decision(h->l4, &ta.l4d, &ta.l4m);
@@ -359,8 +392,6 @@ ising_status enqueue_sweeps(ising_lattice* h, int64_t n, int64_t* dev_EM) {
     }
     return ISING_OK;
   }
-  if (h->lcg) return fail(ISING_EINVAL, "LCG dynamics need the tiled layout (L %% 8 == 0)");
-  const int blocks = grid_blocks(h->plane_words, 256, h->tune.max_blocks);
   for (int64_t k = 0; k < n; ++k) {
     const uint32_t t = (uint32_t)(h->sweep + (uint64_t)k);
     SweepArgs a = sweep_args(h, t, dev_EM ? dev_EM + 2 * k : nullptr);
@@ -580,6 +611,17 @@ ising_status ising_sweep(ising_t* h, int64_t n, int64_t* dev_EM) {
   ising_status st = enqueue_sweeps(h, n, dev_EM);
   if (st != ISING_OK) return st;
   h->sweep += (uint64_t)n;
+  return ISING_OK;
+}
+
+ising_status ising_sweep_plan(ising_t* h, int64_t n, int32_t* form_out, int64_t* launches_out) {
+  clear_error();
+  if (!h || n < 1 || !form_out || !launches_out)
+    return fail(ISING_EINVAL, "ising_sweep_plan: bad arguments");
+  const SweepPlan p = plan_sweeps(h, n);
+  if (p.form == kFormNone) return fail(ISING_EINVAL, "ising_sweep_plan: no form for this side");
+  *form_out = p.form;
+  *launches_out = p.form == ISING_FORM_BLOCK ? block_launches(p.shape, n, true) : 2 * n;
   return ISING_OK;
 }
 

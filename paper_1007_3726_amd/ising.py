@@ -22,6 +22,8 @@ ISING_ENOTFOUND = -4
 ISING_ERANGE = -5
 ISING_FORM_TILE = 0
 ISING_FORM_STRIP = 1
+ISING_FORM_BLOCK = 2
+ISING_FORM_WORD = 3
 ISING_RNG_PHILOX = 0
 ISING_RNG_LCG = 1
 ISING_RNG_POOL = 2
@@ -98,6 +100,7 @@ def lib():
         "ising_set_beta": ([vp, ctypes.c_double], i32),
         "ising_get_thresholds": ([vp, P(u32)], i32),
         "ising_sweep": ([vp, i64, vp], i32),
+        "ising_sweep_plan": ([vp, i64, P(i32), P(i64)], i32),
         "ising_measure": ([vp, P(i64), P(i64)], i32),
         "ising_get_spins": ([vp, vp], i32),
         "ising_set_spins": ([vp, vp], i32),
@@ -379,6 +382,12 @@ class Lattice:
         EM = torch.empty((n, 2), dtype=torch.int64, device=self.device)
         self.sweep(n, EM)
         return EM
+
+    def sweep_plan(self, n: int):
+        """(ISING_FORM_*, launches of the sweep kernel) of a call of n sweeps."""
+        form, launches = ctypes.c_int32(), ctypes.c_int64()
+        check(lib().ising_sweep_plan(self.h, int(n), ctypes.byref(form), ctypes.byref(launches)))
+        return int(form.value), int(launches.value)
 
     def measure(self):
         E, M = ctypes.c_int64(), ctypes.c_int64()

@@ -1,0 +1,114 @@
+"""The form that a call runs in (ising_sweep_plan) is the one a test means:
+blocks at the largest sides that take them, and the tiled sweep of narrow and
+wide rows and of the flat mapping without a second copy of the planes, over
+several sweeps, at temperatures on both sides of the cut's range; against the
+oracle, bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def I():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1007_3726_amd import ising
+    ising.lib()
+    yield ising
+    ising.tuning_clear()
+
+
+def _no_copy(I, lat):
+    I.check(I.lib().ising_set_spare(lat.h, None, 0))
+
+
+# 130, 264: rows of 2 and 3 words; 520: 5 words, 4 sites in the last; 1024:
+# narrow rows; 4098: any row start; 8072: wide rows
+@pytest.mark.parametrize("T", [1.45, 2.0, 5.8])
+@pytest.mark.parametrize("L", [130, 264, 520, 1024, 4098, 8072])
+def test_tiles(I, L, T):
+    n = 3
+    lat = I.Lattice(L, seed=11, stream_id=2, init=workloads.INIT_HOT, beta=1 / T)
+    _no_copy(I, lat)
+    assert lat.sweep_plan(n) == (I.ISING_FORM_TILE, 2 * n)
+    em = lat.sweep_em(n).cpu().numpy()
+    s, oem = oracle.run(L, 1 / T, 11, 2, workloads.INIT_HOT, n)
+    assert np.array_equal(em, oem)
+    assert np.array_equal(lat.get_spins(), s)
+
+
+@pytest.mark.parametrize("T", [1.5, 2.0, 5.8])
+@pytest.mark.parametrize("L", [136, 520, 1024])
+def test_generators_in_tiles(I, L, T):
+    n = 3
+    lat = I.Lattice(L, seed=77, init=workloads.INIT_HOT, beta=1 / T)
+    lat.use_lcg()
+    _no_copy(I, lat)
+    assert lat.sweep_plan(n) == (I.ISING_FORM_TILE, 2 * n)
+    em = lat.sweep_em(n).cpu().numpy()
+    s = oracle.init(L, 77, 0, workloads.INIT_HOT)
+    st = oracle.lcg_seed(L, 77)
+    assert np.array_equal(em, oracle.lcg_sweeps(s, 1 / T, st, n))
+    assert np.array_equal(lat.get_spins(), s)
+    assert np.array_equal(lat.lcg_states(), st)
+
+
+@pytest.mark.parametrize("linear", [False, True])
+@pytest.mark.parametrize("L", [136, 520, 1024])
+def test_pools_in_tiles(I, L, linear):
+    n, m, T = 3, 11, 2.2
+    lat = I.Lattice(L, seed=5, stream_id=3, init=workloads.INIT_HOT, beta=1 / T)
+    lat.use_pool(m, linear=linear)
+    _no_copy(I, lat)
+    assert lat.sweep_plan(n) == (I.ISING_FORM_TILE, 2 * n)
+    em = lat.sweep_em(n).cpu().numpy()
+    s = oracle.init(L, 5, 3, workloads.INIT_HOT)
+    assert np.array_equal(em, oracle.pool_sweeps(s, 1 / T, 5, 3, 0, n, m, linear))
+    assert np.array_equal(lat.get_spins(), s)
+
+
+# one strip; strips of uneven sides; the largest sides that take blocks
+@pytest.mark.parametrize("T", [1.45, 2.25])
+@pytest.mark.parametrize("L,n", [(64, 5), (130, 5), (520, 7), (1002, 9), (4096, 8), (5000, 24),
+                                 (7680, 24)])
+def test_blocks(I, L, n, T):
+    lat = I.Lattice(L, seed=9, stream_id=3, init=workloads.INIT_COLD_UP, beta=1 / T)
+    form, launches = lat.sweep_plan(n)
+    assert form == I.ISING_FORM_BLOCK and launches < 2 * n
+    em = lat.sweep_em(n).cpu().numpy()
+    s, oem = oracle.run(L, 1 / T, 9, 3, workloads.INIT_COLD_UP, n)
+    assert np.array_equal(em, oem)
+    assert np.array_equal(lat.get_spins(), s)
+
+
+@pytest.mark.parametrize("kind,L,n", [("lcg", 9216, 24), ("pool", 9152, 24), ("linear", 9000, 9),
+                                      ("linear", 12008, 7)])
+def test_largest_blocks_of_the_alternative_dynamics(I, kind, L, n):
+    T, m = 2.3, 12
+    lat = I.Lattice(L, seed=7, init=workloads.INIT_COLD_UP, beta=1 / T)
+    lat.use_lcg() if kind == "lcg" else lat.use_pool(m, linear=kind == "linear")
+    assert lat.sweep_plan(n)[0] == I.ISING_FORM_BLOCK
+    em = lat.sweep_em(n).cpu().numpy()
+    s = oracle.init(L, 7, 0, workloads.INIT_COLD_UP)
+    if kind == "lcg":
+        st = oracle.lcg_seed(L, 7)
+        assert np.array_equal(em, oracle.lcg_sweeps(s, 1 / T, st, n))
+        assert np.array_equal(lat.lcg_states(), st)
+    else:
+        assert np.array_equal(em, oracle.pool_sweeps(s, 1 / T, 7, 0, 0, n, m, kind == "linear"))
+    assert np.array_equal(lat.get_spins(), s)
+
+
+def test_arguments(I):
+    import ctypes
+    lat = I.Lattice(64, seed=1, beta=0.4)
+    form, launches = ctypes.c_int32(), ctypes.c_int64()
+    f, k = ctypes.byref(form), ctypes.byref(launches)
+    for args in ((None, 1, f, k), (lat.h, 0, f, k), (lat.h, 1, None, k), (lat.h, 1, f, None)):
+        assert I.lib().ising_sweep_plan(*args) == I.ISING_EINVAL
+    assert lat.sweep_plan(1)[1] == 1 and lat.sweep_plan(10 ** 6) == (I.ISING_FORM_BLOCK, 1)
