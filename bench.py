@@ -240,23 +240,21 @@ def bench_served(torch, ising, dev, n_req, arena_gib, quantum, plain_n, plain_ra
     return out
 
 
-def kernel_sources_sha():
+KERNELS = {0: "k_tile_sweep", 1: "k_strip_sweep", 2: "k_block", 3: "k_half_sweep"}
+
+
+def kernel_sources_sha(kernel):
+    """Hash of the sources that a sweep kernel is compiled from."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("ising_cut.hpp", "ising_device.hpp", "ising_kernels.hpp", "ising_kernels.hip"):
+    files = ["ising_cut.hpp", "ising_device.hpp", "ising_kernels.hpp", "ising_kernels.hip"]
+    if kernel == "k_block":
+        files = ["ising_cut.hpp", "ising_device.hpp", "ising_plan.hpp", "ising_plan.cpp",
+                 "ising_block.hpp", "ising_block.hip"]
+    for f in files:
         with open(os.path.join(ROOT, "paper_1007_3726_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())
     return h.hexdigest()
-
-
-def plain_kernel(ising, L, tuned):
-    """Name of the kernel that runs a colour step of the plain sweep for side L
-    under the tuning entry `tuned`."""
-    if L <= 4096 and tuned["form"] != ising.ISING_FORM_STRIP:
-        return "k_block"
-    if tuned["form"] == ising.ISING_FORM_STRIP and (L // 2 + 63) // 64 >= 63:
-        return "k_strip_sweep"
-    return "k_tile_sweep"
 
 
 def profiled_traffic(kernel, L):
@@ -272,7 +270,7 @@ def profiled_traffic(kernel, L):
             if ": " in line and not line.startswith(("#", " ", "|")):
                 k, v = line.rstrip("\n").split(": ", 1)
                 kv[k.strip()] = v.strip()
-    if kv.get("kernel_source_sha256") != kernel_sources_sha():
+    if kv.get("kernel_source_sha256") != kernel_sources_sha(kernel):
         return None
     try:
         return int(kv["traffic_bytes_per_launch"])
@@ -464,21 +462,23 @@ def bench_lcg(torch, ising, dev, w, steps):
     b.synchronize()
     ms = a.elapsed_time(b)
     N = w.L * w.L
-    launch_us = ms * 1e3 / (2 * w.sweeps * steps)
-    achieved = LCG_OPS_PER_UPDATE * (N / 2) / (launch_us * 1e-6)
+    form, launches = lat.sweep_plan(w.sweeps)
+    launch_us = ms * 1e3 / (launches * steps)
+    achieved = LCG_OPS_PER_UPDATE * N * w.sweeps * steps / (ms * 1e-3)
     last = EM[-1].cpu().tolist()
     assert tuple(last) == lat.measure(), "fused E/M disagrees with a recount"
     return {"value": round(N * w.sweeps * steps / (ms * 1e6), 2), "unit": "spin updates/ns",
             "workload": "as the plain workload, per-thread LCG x <- 1664525 x + 1013904223 "
                         "mod 2^32 per 64-site word (Eqs. (6), (7))",
+            "kernel": KERNELS[form] + ("_alt" if form == ising.ISING_FORM_BLOCK else ""),
             "avg_launch_us": round(launch_us, 3), "ops_per_update": LCG_OPS_PER_UPDATE,
             "roofline_frac": round(achieved / VALU_PEAK_LANE_OPS, 4)}
 
 
 # Algorithmic HBM bytes per update of the pattern-pool dynamics: the two
 # colour planes (3 bits: read both colours once, write one) plus one
-# 16-byte (r4, r8) pattern pair per 64-site word.  Linear reads up to 16384^2
-# run several sweeps per launch with the planes in LDS: the patterns alone.
+# 16-byte (r4, r8) pattern pair per 64-site word.  Several sweeps per launch
+# keep the planes in LDS: the patterns alone.
 POOL_BYTES_PER_UPDATE = 3 / 8 + 16 / 64
 PATTERN_BYTES_PER_UPDATE = 16 / 64
 HBM_PEAK_BYTES = 8.0e12
@@ -511,9 +511,12 @@ def bench_pool(torch, ising, dev, w, steps, log2_patterns=22):
         ms = a.elapsed_time(b)
         assert tuple(EM[-1].cpu().tolist()) == lat.measure(), "E/M disagrees with a recount"
         ups = N * w.sweeps * steps / (ms * 1e6)
-        per = PATTERN_BYTES_PER_UPDATE if linear and w.L <= 16384 else POOL_BYTES_PER_UPDATE
+        form, launches = lat.sweep_plan(w.sweeps)
+        block = form == ising.ISING_FORM_BLOCK
+        per = PATTERN_BYTES_PER_UPDATE if block else POOL_BYTES_PER_UPDATE
         out[name] = {"value": round(ups, 2), "unit": "spin updates/ns",
-                     "avg_launch_us": round(ms * 1e3 / (2 * w.sweeps * steps), 3),
+                     "kernel": "k_block_alt" if block else "k_pool_sweep",
+                     "avg_launch_us": round(ms * 1e3 / (launches * steps), 3),
                      "bytes_per_update": per,
                      "hbm_frac": round(ups * 1e9 * per / HBM_PEAK_BYTES, 4)}
         del lat, EM
@@ -823,7 +826,7 @@ def bench_configs(torch, ising, dev, stream, head):
                                                   w.sweeps),
                        "ms_per_run": round(ms / steps, 3),
                        "us_per_sweep": round(ms * 1e3 / (steps * w.sweeps), 3),
-                       "form": plain_kernel(ising, w.L, ising.tuning_lookup(w.L))}
+                       "form": KERNELS[lat.sweep_plan(w.sweeps)[0]]}
         del lat, EM
         torch.cuda.empty_cache()
     return out
@@ -861,17 +864,19 @@ def main():
         ising.tuning_clear()
         torch.cuda.empty_cache()
     tuned = ising.tuning_lookup(w.L)
-    kernel = plain_kernel(ising, w.L, tuned)
     print("bench: %s L=%d T=%r sweeps/step=%d warmup=%d steps=%d"
           % (w.name, w.L, w.T, w.sweeps, args.warmup, args.steps), file=sys.stderr, flush=True)
     ms, wall, lat, EM = time_plain(torch, ising, dev, stream, w, args.steps, args.warmup)
     N = w.L * w.L
     updates = N * w.sweeps * args.steps
     value = updates / (ms * 1e6)
-    launches = 2 * w.sweeps * args.steps
-    launch_us = ms * 1e3 / launches
-    ops_per_launch = ALU_OPS_PER_UPDATE * N / 2
-    achieved = ops_per_launch / (launch_us * 1e-6)
+    form, launches = lat.sweep_plan(w.sweeps)
+    kernel = KERNELS[form]
+    launch_us = ms * 1e3 / (launches * args.steps)
+    achieved = ALU_OPS_PER_UPDATE * updates / (ms * 1e-3)
+    # a colour step reads both planes and writes one; several sweeps per launch
+    # read both and write both once
+    launch_bytes = N // 4 if form == ising.ISING_FORM_BLOCK else 3 * N // 16
     del lat, EM
     torch.cuda.empty_cache()
     start_kind = ["cold +1", "cold -1", "hot"][w.init]
@@ -897,7 +902,7 @@ def main():
                      "peak": round(VALU_PEAK_LANE_OPS / 1e12, 3), "unit": "Tops/s",
                      "frac": round(achieved / VALU_PEAK_LANE_OPS, 4),
                      "traffic": profiled_traffic(kernel, w.L),
-                     "algorithmic_bytes_per_launch": 3 * N // 16,
+                     "algorithmic_bytes_per_launch": launch_bytes,
                      "kernel": kernel, "avg_launch_us": round(launch_us, 3),
                      "ops_per_update": ALU_OPS_PER_UPDATE},
         "wall_s": round(wall, 3),
