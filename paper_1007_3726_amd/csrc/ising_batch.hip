@@ -104,6 +104,7 @@ int device_cus(int device) {
 
 // A batch of more sites than kBlockMaxSites fills the chip in every colour
 // step: only single strips, which have no halo rows, can still be cheaper.
+// (And only they run any number of sweeps.)
 bool choose_blocks(const std::vector<int64_t>& Ls, int64_t n, int cus, BlockPlan* plan) {
   double sites = 0, words = 0;
   bool all_single = true;
@@ -113,7 +114,7 @@ bool choose_blocks(const std::vector<int64_t>& Ls, int64_t n, int cus, BlockPlan
     words += (double)(L * words_per_row(L));
     all_single = all_single && block_fits_single(L);
   }
-  if (sites > kBlockMaxSites) {
+  if (sites > kBlockMaxSites || n > kBlockMaxSweeps) {
     if (!all_single) return false;
     n = 1;
   }

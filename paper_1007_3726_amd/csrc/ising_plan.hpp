@@ -55,6 +55,9 @@ struct BlockShape {
 // Sites of a batch above which it is not worth planning: its colour steps
 // take several launches' time.
 constexpr double kBlockMaxSites = 6.4e7;
+// Sweeps of a call beyond which strips are not taken: their launches are counted
+// in 32 bits, one per sweep at the least.
+constexpr int64_t kBlockMaxSweeps = int64_t(1) << 30;
 // Calls of at least this many sweeps are all cut alike.
 constexpr int64_t kBlockPlanN = 24;
 // Distinct sides up to which each is planned by itself, however few the sweeps.

@@ -245,8 +245,8 @@ bool use_small_path(const ising_lattice* h) {
 // strip shape) with a spare copy of its planes.  One sweep takes two launches
 // either way.
 bool use_block_path(const ising_lattice* h, int64_t n) {
-  return block_kind(h) >= 0 && h->spare != nullptr && n >= 2 && h->L <= kBlockMaxL &&
-         h->tune.form == ISING_FORM_TILE && h->tune.rpw == 0;
+  return block_kind(h) >= 0 && h->spare != nullptr && n >= 2 && n <= kBlockMaxSweeps &&
+         h->L <= kBlockMaxL && h->tune.form == ISING_FORM_TILE && h->tune.rpw == 0;
 }
 
 // (d, m) of the LCG decision (x + d) < m for threshold t' (ising_device.hpp)

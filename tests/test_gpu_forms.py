@@ -112,3 +112,14 @@ def test_arguments(I):
     for args in ((None, 1, f, k), (lat.h, 0, f, k), (lat.h, 1, None, k), (lat.h, 1, f, None)):
         assert I.lib().ising_sweep_plan(*args) == I.ISING_EINVAL
     assert lat.sweep_plan(1)[1] == 1 and lat.sweep_plan(10 ** 6) == (I.ISING_FORM_BLOCK, 1)
+
+
+def test_sweeps_beyond_what_launches_count(I):
+    """Strips take up to 2^30 sweeps in a call (32-bit launch numbers; planned
+    only, nothing runs), a single strip any number."""
+    lat = I.Lattice(4096, seed=1, beta=0.4)
+    assert lat.sweep_plan(2 ** 30)[0] == I.ISING_FORM_BLOCK
+    for n in (2 ** 30 + 1, 2 ** 32 - 1):
+        assert lat.sweep_plan(n) == (I.ISING_FORM_TILE, 2 * n)
+    small = I.Lattice(64, seed=1, beta=0.4)
+    assert small.sweep_plan(2 ** 32) == (I.ISING_FORM_BLOCK, 2 ** 12)
