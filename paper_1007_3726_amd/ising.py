@@ -294,6 +294,16 @@ def ising_version() -> str:
     return lib().ising_version().decode()
 
 
+# Largest side that takes several sweeps per launch, and so a second copy of
+# the planes, by dynamics (alone: 7680, 9216, 9152, 16384; in batches 8000)
+_SPARE_SIDES = {ISING_RNG_PHILOX: 8000, ISING_RNG_LCG: 9216, ISING_RNG_POOL: 9152,
+                ISING_RNG_POOL_LINEAR: 16384}
+
+
+def _spare_bytes(L: int, kind: int) -> int:
+    return int(lib().ising_spare_bytes(L)) if L <= _SPARE_SIDES[kind] else 0
+
+
 class Lattice:
     """One L x L lattice whose packed planes live in a torch uint8 tensor."""
 
@@ -307,13 +317,14 @@ class Lattice:
         self.device = torch.device(device)
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
         # behind the lattice, a second copy of the planes (several sweeps per launch)
-        nspare = int(lib().ising_spare_bytes(self.L))
+        nspare = _spare_bytes(self.L, ISING_RNG_PHILOX)
         at = (nbytes + 255) // 256 * 256
         self.buf = _dev_alloc(at + nspare if nspare else nbytes, self.device)
         h = ctypes.c_void_p()
         check(lib().ising_create(self.L, seed & (2 ** 64 - 1), stream_id, init, self.buf.data_ptr(),
                                  nbytes, _stream_ptr(self.stream), ctypes.byref(h)))
         self.h = h
+        self._has_spare = nspare > 0
         if nspare:
             check(lib().ising_set_spare(self.h, self.buf.data_ptr() + at, nspare))
         if beta is not None:
@@ -333,12 +344,22 @@ class Lattice:
     def set_beta(self, beta: float):
         check(lib().ising_set_beta(self.h, float(beta)))
 
+    def _want_spare(self, kind: int):
+        """A second copy of the planes for dynamics that use one where plain
+        sweeps of this side do not."""
+        nbytes = _spare_bytes(self.L, kind)
+        if nbytes and not self._has_spare:
+            self.spare_buf = _dev_alloc(nbytes, self.device)
+            check(lib().ising_set_spare(self.h, self.spare_buf.data_ptr(), nbytes))
+            self._has_spare = True
+
     def use_lcg(self):
         """Switch to the paper's per-thread LCG dynamics (ising_set_rng); the
         state buffer is allocated here and seeded on the lattice's stream."""
         nbytes = ising_lcg_bytes(self.L)
         self.lcg_buf = _dev_alloc(max(nbytes, 4), self.device)
         check(lib().ising_set_rng(self.h, ISING_RNG_LCG, self.lcg_buf.data_ptr(), nbytes))
+        self._want_spare(ISING_RNG_LCG)
 
     def use_pool(self, log2_patterns: int = 22, linear: bool = False):
         """Switch to the Boltzmann-pattern-pool dynamics (ising_set_rng): a
@@ -348,6 +369,7 @@ class Lattice:
         self.pool_buf = _dev_alloc(max(nbytes, 16), self.device)
         kind = ISING_RNG_POOL_LINEAR if linear else ISING_RNG_POOL
         check(lib().ising_set_rng(self.h, kind, self.pool_buf.data_ptr(), nbytes))
+        self._want_spare(kind)
         self.lcg_buf = None
 
     def use_philox(self):
@@ -439,7 +461,7 @@ def autotune(L: int, trial_sweeps: int = 10, device="cuda", stream=None) -> dict
     # the lattice, then room for the trials' per-sweep (E, M) and a second
     # copy of the planes
     nbytes = (ising_lattice_bytes(L) + 255) // 256 * 256 + 16 * max(int(trial_sweeps), 2)
-    nbytes = (nbytes + 255) // 256 * 256 + int(lib().ising_spare_bytes(L))
+    nbytes = (nbytes + 255) // 256 * 256 + _spare_bytes(L, ISING_RNG_PHILOX)
     buf = _dev_alloc(nbytes, dev)
     out = ising_tuning()
     check(lib().ising_autotune(int(L), buf.data_ptr(), nbytes, _stream_ptr(st), int(trial_sweeps),

@@ -123,3 +123,18 @@ def test_sweeps_beyond_what_launches_count(I):
         assert lat.sweep_plan(n) == (I.ISING_FORM_TILE, 2 * n)
     small = I.Lattice(64, seed=1, beta=0.4)
     assert small.sweep_plan(2 ** 32) == (I.ISING_FORM_BLOCK, 2 ** 12)
+
+
+def test_second_copy_is_allocated_for_dynamics_that_use_it(I):
+    """Plain lattices above 8000^2 hold one copy of the planes; linear pools
+    bring the second one with them."""
+    L = 12008
+    lat = I.Lattice(L, seed=1, beta=0.4)
+    assert lat.buf.numel() == I.ising_lattice_bytes(L)
+    assert lat.sweep_plan(24)[0] == I.ISING_FORM_TILE
+    lat.use_lcg()
+    assert lat.sweep_plan(24)[0] == I.ISING_FORM_TILE
+    lat.use_pool(10, linear=True)
+    assert lat.sweep_plan(24)[0] == I.ISING_FORM_BLOCK
+    small = I.Lattice(64, seed=1, beta=0.4)
+    assert small.buf.numel() >= I.ising_lattice_bytes(64) + int(I.lib().ising_spare_bytes(64))

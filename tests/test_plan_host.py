@@ -29,17 +29,18 @@ def plans():
 
         def run(cases):
             """cases: (kind, n, cus, Ls); (microseconds per sweep, strips, shapes,
-            microseconds of planning) of each."""
+            microseconds of planning, whether cheaper than a launch per colour step) of
+            each."""
             text = "".join("%d %d %d %d %s\n" % (k, n, c, len(Ls), " ".join(map(str, Ls)))
                            for k, n, c, Ls in cases)
             r = subprocess.run([out], input=text, capture_output=True, text=True, check=True)
             res = []
             for ln in r.stdout.splitlines():
                 f = ln.split()
-                v = [int(x) for x in f[4:]]
+                v = [int(x) for x in f[4:-1]]
                 shapes = [dict(zip(("rows", "strips", "ls", "pass", "threads", "sweeps", "lds"),
                                    v[7 * i:7 * i + 7])) for i in range(int(f[3]))]
-                res.append((float(f[1]), int(f[2]), shapes, float(f[0])))
+                res.append((float(f[1]), int(f[2]), shapes, float(f[0]), f[-1] == "1"))
             assert len(res) == len(cases)
             return res
         yield run
@@ -56,7 +57,7 @@ def test_every_lone_plan_can_be_launched(plans, kind):
     the kernel's own part of it, and the halos stay inside the lattice."""
     for cus in (256, 64):
         cases = [(kind, n, cus, [L]) for n in SWEEPS for L in _sides(kind)]
-        for (_, n, _, Ls), (_, _, shapes, _) in zip(cases, plans(cases)):
+        for (_, n, _, Ls), (_, _, shapes, _, _) in zip(cases, plans(cases)):
             L, W = Ls[0], (Ls[0] // 2 + 63) // 64
             for s in shapes:
                 where = (L, n, cus, s)
@@ -82,8 +83,24 @@ def test_planning_is_short_beside_the_sweeps(plans, Ls):
     that the sweeps take (every cut of 279 sides took 21 ms, of 120 sides
     10.5), and the cut nearly as good as that of a long call, for which every
     side is searched."""
-    (short, _, shapes, us), (long_, _, best, _) = plans([(PHILOX, 24, 256, Ls),
+    (short, _, shapes, us, _), (long_, _, best, _, _) = plans([(PHILOX, 24, 256, Ls),
                                                         (PHILOX, 10 ** 6, 256, Ls)])
     assert us < 1000
     assert bool(shapes) == bool(best)
     assert short <= 1.25 * long_
+
+
+def test_second_copies_are_for_sides_that_use_them(plans):
+    """The binding's limits: beyond them no lone lattice of the MI355X's 256
+    compute units takes strips, and each is within a twentieth of the last
+    side that does."""
+    from paper_1007_3726_amd import ising
+    limits = [ising._SPARE_SIDES[k] for k in (ising.ISING_RNG_PHILOX, ising.ISING_RNG_LCG,
+                                              ising.ISING_RNG_POOL,
+                                              ising.ISING_RNG_POOL_LINEAR)]
+    for kind, limit in enumerate(limits):
+        cases = [(kind, 24, 256, [L]) for L in _sides(kind) if L > 0.95 * limit]
+        used = [Ls[0] for (_, _, _, Ls), r in zip(cases, plans(cases)) if r[4]]
+        assert used and max(used) <= limit, kind
+    # no batch with a larger side is cut into strips
+    assert limits[0] ** 2 <= 6.4e7 < (limits[0] + 2) ** 2

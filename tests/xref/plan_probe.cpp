@@ -1,7 +1,8 @@
 // Prints the plans of ising_plan.cpp: reads lines "kind n cus count L...",
 // prints "plan_us sweep_us tasks count" and, per lattice, "rows strips ls pass
-// threads sweeps lds" (count 0: no plan).  plan_us: microseconds that the
-// planning takes beside a launch per colour step, the best of three.
+// threads sweeps lds" (count 0: no plan), and 1 if that is cheaper than a launch
+// per colour step.  plan_us: microseconds that the planning takes when it is
+// held to that, the best of three.
 #include <chrono>
 #include <cstdio>
 
@@ -30,7 +31,8 @@ int main() {
     for (const auto& s : p.shapes)
       std::printf(" %d %d %d %d %d %d %zu", s.rows, s.strips, s.ls, s.pass, s.threads, s.sweeps,
                   s.lds);
-    std::printf("\n");
+    std::printf(" %d\n", !p.shapes.empty() &&
+                              p.sweep_s < ising::launch_per_step_seconds(kind, words, cus));
   }
   return 0;
 }
