@@ -242,11 +242,13 @@ bool use_small_path(const ising_lattice* h) {
 }
 
 // Several sweeps per launch: a lattice of its own shape (no installed tile or
-// strip shape) with a spare copy of its planes.  One sweep takes two launches
-// either way.
+// strip shape, which is one timed for plain sweeps and binds only those) with
+// a spare copy of its planes.  One sweep takes two launches either way.
 bool use_block_path(const ising_lattice* h, int64_t n) {
-  return block_kind(h) >= 0 && h->spare != nullptr && n >= 2 && n <= kBlockMaxSweeps &&
-         h->L <= kBlockMaxL && h->tune.form == ISING_FORM_TILE && h->tune.rpw == 0;
+  const int kind = block_kind(h);
+  return kind >= 0 && h->spare != nullptr && n >= 2 && n <= kBlockMaxSweeps &&
+         h->L <= kBlockMaxL &&
+         (kind != kBlockPhilox || (h->tune.form == ISING_FORM_TILE && h->tune.rpw == 0));
 }
 
 // (d, m) of the LCG decision (x + d) < m for threshold t' (ising_device.hpp)

@@ -33,7 +33,8 @@ int64_t class_lo(int64_t L) {
 
 }  // namespace
 
-Tuning default_tuning(int64_t L) {
+// The size rule.
+static Tuning builtin_tuning() {
   Tuning t;
   t.small_lds_bytes = 4096;  // L <= 128 runs in one LDS-resident workgroup
   t.max_blocks = 2048;
@@ -41,6 +42,11 @@ Tuning default_tuning(int64_t L) {
   // tiles with direct neighbour loads: measured faster than strips at every
   // size from 1024^2 to 262144^2 (strips stay an autotuner candidate)
   t.form = ISING_FORM_TILE;
+  return t;
+}
+
+Tuning default_tuning(int64_t L) {
+  Tuning t = builtin_tuning();
   std::lock_guard<std::mutex> lock(g_tune_mutex);
   for (const ising_tuning& e : g_table)
     if (L >= e.L_min && L <= e.L_max) {
@@ -104,27 +110,32 @@ ising_status ising_autotune(int64_t L, void* dev_buf, size_t dev_bytes, void* hi
   if (spare_bytes && dev_EM && dev_bytes >= spare_at + spare_bytes)
     st = ising_set_spare(h, (char*)dev_buf + spare_at, spare_bytes);
   if (st == ISING_OK) st = ising_set_beta(h, 1.0 / 2.269185);
-  struct Cand {
-    Tuning t;
-  };
-  std::vector<Cand> cands;
+  std::vector<Tuning> cands;
   const int64_t plane_bytes = 2 * h->plane_words * (int64_t)sizeof(uint64_t);
-  if (plane_bytes <= 65536)  // LDS-resident
-    cands.push_back({Tuning{plane_bytes, 2048, 0, ISING_FORM_TILE}});
-  cands.push_back({Tuning{0, 2048, 0, ISING_FORM_TILE}});  // the size rule
+  const Tuning rule = builtin_tuning();
+  const Tuning resident{plane_bytes, 2048, 0, ISING_FORM_TILE};
+  // LDS-resident, where that is not the rule's choice already
+  const bool try_resident = plane_bytes > rule.small_lds_bytes && plane_bytes <= 65536;
+  cands.push_back(rule);
+  if (try_resident) cands.push_back(resident);
+  const size_t first_shape = cands.size();
   for (int rpw : {1, 2, 4})
-    for (int mb : {512, 1024, 2048}) cands.push_back({Tuning{0, mb, rpw, ISING_FORM_TILE}});
+    for (int mb : {512, 1024, 2048}) cands.push_back(Tuning{0, mb, rpw, ISING_FORM_TILE});
   if (h->g.W >= kWideMinWords)
     for (int rows : {0, 4, 8, 16, 32})
-      for (int mb : {1024, 2048}) cands.push_back({Tuning{0, mb, rows, ISING_FORM_STRIP}});
+      for (int mb : {1024, 2048}) cands.push_back(Tuning{0, mb, rows, ISING_FORM_STRIP});
+  // the first trials run while the clocks rise
+  const size_t end_shape = cands.size();
+  cands.push_back(rule);
+  if (try_resident) cands.push_back(resident);
   hipEvent_t a = nullptr, b = nullptr;
   hipError_t e = hipEventCreate(&a);
   if (e == hipSuccess) e = hipEventCreate(&b);
-  double best = -1.0;
-  Tuning best_t = default_tuning(L);
+  double best = -1.0, rule_rate = -1.0, resident_rate = -1.0;
+  Tuning best_t = rule;
   const hipStream_t stream = (hipStream_t)hip_stream;
   for (size_t i = 0; i < cands.size() && st == ISING_OK && e == hipSuccess; ++i) {
-    h->tune = cands[i].t;
+    h->tune = cands[i];
     TileArgs ta;
     // skip shapes the tiled layout would not honour
     if (h->tune.small_lds_bytes == 0 && h->tune.form == ISING_FORM_TILE && h->tune.rpw > 0 &&
@@ -141,10 +152,23 @@ ising_status ising_autotune(int64_t L, void* dev_buf, size_t dev_bytes, void* hi
     if (e == hipSuccess && st == ISING_OK) e = hipEventElapsedTime(&ms, a, b);
     if (e != hipSuccess || st != ISING_OK) break;
     const double rate = (double)L * (double)L * trial_sweeps / (ms * 1e6);
-    if (rate > best) {
-      best = rate;
-      best_t = cands[i].t;
+    if (i >= first_shape && i < end_shape) {
+      if (rate > best) {
+        best = rate;
+        best_t = cands[i];
+      }
+    } else {
+      double& r = i == 0 || i == end_shape ? rule_rate : resident_rate;
+      r = std::max(r, rate);
     }
+  }
+  // A tile or strip shape is installed for the whole size class, and turns the
+  // size rule's evenly dealt tiles and several sweeps per launch off there.  It
+  // has to beat the rule by more than two trials of one kernel differ (16384^2,
+  // where the rule's shape is also a candidate: 1 %).
+  if (std::max(1.03 * rule_rate, resident_rate) >= best) {
+    best = std::max(rule_rate, resident_rate);
+    best_t = 1.03 * resident_rate >= rule_rate ? resident : rule;
   }
   if (a) (void)hipEventDestroy(a);
   if (b) (void)hipEventDestroy(b);

@@ -138,3 +138,35 @@ def test_second_copy_is_allocated_for_dynamics_that_use_it(I):
     assert lat.sweep_plan(24)[0] == I.ISING_FORM_BLOCK
     small = I.Lattice(64, seed=1, beta=0.4)
     assert small.buf.numel() >= I.ising_lattice_bytes(64) + int(I.lib().ising_spare_bytes(64))
+
+
+def test_installed_tile_shapes_bind_plain_sweeps_only(I):
+    """A shape timed for plain sweeps leaves generators and pools their
+    blocks; the autotuner keeps the size rule where blocks are ahead."""
+    L, n, T = 1024, 9, 2.3
+    for form in (I.ISING_FORM_TILE, I.ISING_FORM_STRIP):
+        I.tuning_set([{"L_min": L, "L_max": L, "form": form, "rpw": 1, "max_blocks": 2048,
+                       "small_lds_bytes": 0, "updates_per_ns": 0.0}])
+        lats = [I.Lattice(L, seed=7, init=workloads.INIT_HOT, beta=1 / T) for _ in range(4)]
+        I.tuning_clear()
+        lats[1].use_lcg()
+        lats[2].use_pool(11)
+        lats[3].use_pool(11, linear=True)
+        forms = [lat.sweep_plan(n)[0] for lat in lats]
+        assert forms == [I.ISING_FORM_TILE] + 3 * [I.ISING_FORM_BLOCK]
+        ems = [lat.sweep_em(n).cpu().numpy() for lat in lats]
+        want = oracle.run(L, 1 / T, 7, 0, workloads.INIT_HOT, n)[1]
+        assert np.array_equal(ems[0], want)
+        st = oracle.lcg_seed(L, 7)
+        assert np.array_equal(ems[1], oracle.lcg_sweeps(oracle.init(L, 7, 0, workloads.INIT_HOT),
+                                                        1 / T, st, n))
+        assert np.array_equal(lats[1].lcg_states(), st)
+        for k, linear in ((2, False), (3, True)):
+            s = oracle.init(L, 7, 0, workloads.INIT_HOT)
+            assert np.array_equal(ems[k], oracle.pool_sweeps(s, 1 / T, 7, 0, 0, n, 11, linear))
+    try:
+        e = I.autotune(2048, trial_sweeps=20)
+        assert e["rpw"] == 0 and e["form"] == I.ISING_FORM_TILE
+        assert I.Lattice(2048, seed=1, beta=0.4).sweep_plan(24)[0] == I.ISING_FORM_BLOCK
+    finally:
+        I.tuning_clear()
