@@ -198,11 +198,11 @@ ISING_API ising_status ising_multi_sweep(ising_t *const *hs, int32_t count, int6
  * For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * batched sweeps as ising_multi_sweep, bit for bit, with no work buffer.
- * The task tables go to a static device array of 4 MiB inside the library
- * (one per GPU, held until the process ends); a batch whose tables need
- * more is rejected with ENOMEM before any device work.  No hipGraph is
- * built (instantiation allocates): two kernel launches per sweep, enqueued
- * directly on the handles' stream.  The call allocates no device memory,
+ * The task tables go to a static device array inside the library (one per
+ * GPU, held until the process ends); a batch whose tables need more than
+ * 4 MiB (at 240 bytes per lattice) is rejected with ENOMEM before any device
+ * work.  No hipGraph is built (instantiation allocates): launches are
+ * enqueued directly on the handles' stream.  The call allocates no device memory,
  * waits for the stream before it returns, and is serialised with other
  * calls on the same GPU in this process (they share the array).  Errors:
  * EINVAL, ERANGE, ENOMEM, EDEVICE.

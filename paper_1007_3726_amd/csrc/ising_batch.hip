@@ -56,9 +56,9 @@ struct FusedLayout {
   size_t off_k = 0, off_lat = 256, off_tiles = 0, off_part = 0, bytes = 0;
 };
 
-FusedLayout fused_layout(size_t nl, size_t ntiles) {
+FusedLayout fused_layout(size_t nl, size_t ntiles, size_t record = sizeof(FusedLattice)) {
   FusedLayout f;
-  f.off_tiles = align_up(f.off_lat + nl * sizeof(FusedLattice), 256);
+  f.off_tiles = align_up(f.off_lat + nl * record, 256);
   f.off_part = align_up(f.off_tiles + ntiles * sizeof(FusedTile), 256);
   // per-wave E/M partials: 2 sweep slots x 4 waves x (anti, up) per tile
   f.bytes = align_up(f.off_part + 2 * 4 * 2 * ntiles * sizeof(uint32_t), 256);
@@ -342,12 +342,13 @@ static void classify(ising_lattice* const* hs, int32_t count, const BatchOptions
 
 // Work-buffer bytes for the tiled lattices: the larger of the two forms.
 static size_t work_bytes_for(ising_lattice* const* hs, const std::vector<int>& tiled,
-                             const std::vector<TileArgs>& targs) {
+                             const std::vector<TileArgs>& targs,
+                             size_t record = sizeof(FusedLattice)) {
   if (tiled.empty()) return 0;
   size_t ntiles = 0;
   for (int i : tiled) ntiles += (size_t)fused_tiles(hs[i]->plane_words, targs[i].RPW);
   const size_t nl = tiled.size();
-  return std::max(fused_layout(nl, ntiles).bytes, block_layout(nl, nl).bytes);
+  return std::max(fused_layout(nl, ntiles, record).bytes, block_layout(nl, nl).bytes);
 }
 
 // Whether every lattice that the plan cuts into strips has a copy of its own:
@@ -365,11 +366,16 @@ static bool own_spares(ising_lattice* const* hs, const BlockPlan& plan) {
   return true;
 }
 
-size_t batch_work_bytes(ising_lattice* const* hs, int32_t count, const BatchOptions& opt) {
+static size_t work_bytes_of(ising_lattice* const* hs, int32_t count, const BatchOptions& opt,
+                            size_t record) {
   std::vector<int> tiled, other;
   std::vector<TileArgs> targs;
   classify(hs, count, opt, tiled, other, targs);
-  return work_bytes_for(hs, tiled, targs);
+  return work_bytes_for(hs, tiled, targs, record);
+}
+
+size_t batch_work_bytes(ising_lattice* const* hs, int32_t count, const BatchOptions& opt) {
+  return work_bytes_of(hs, count, opt, sizeof(FusedLattice));
 }
 
 // Block tables that a batch runs without, but faster with: lattices that the
@@ -547,7 +553,14 @@ ising_status check_batch(ising_t* const* hs, int32_t count, int64_t n, const cha
 // before it returns), so calls from several threads of a process do not
 // overlap on the array.
 // ---------------------------------------------------------------------
-constexpr size_t kStaticWorkBytes = size_t(4) << 20;
+// A batch is taken if its tables are within 4 MiB with 240 bytes per lattice.
+// The record has grown beyond that, and the array with it, by as many lattices
+// as fit: each has a tile and its partials too.
+constexpr size_t kStaticLimit = size_t(4) << 20, kStaticRecord = 240;
+static_assert(sizeof(FusedLattice) >= kStaticRecord, "kStaticRecord");
+constexpr size_t kStaticWorkBytes =
+    (kStaticLimit + kStaticLimit / (kStaticRecord + sizeof(FusedTile) + 64) *
+                        (sizeof(FusedLattice) - kStaticRecord) + 511) & ~size_t(255);
 static __device__ __align__(256) unsigned char scratch[kStaticWorkBytes];
 
 namespace {
@@ -569,12 +582,12 @@ extern "C" ising_status ising_multi_sweep_static(ising_t* const* hs, int32_t cou
   if (count == 0 || n == 0) return ISING_OK;
   BatchOptions opt = default_batch_options();
   opt.graph_chunk = 0;  // no hipGraph: instantiating one allocates
-  const size_t need = batch_work_bytes(hs, count, opt);
-  if (need > kStaticWorkBytes)
+  const size_t need = work_bytes_of(hs, count, opt, kStaticRecord);
+  if (need > kStaticLimit)
     return fail(ISING_ENOMEM,
                 "ising_multi_sweep_static: the batch needs %zu bytes of tables, more than the "
-                "%zu-byte static scratch",
-                need, kStaticWorkBytes);
+                "%zu bytes of the static scratch",
+                need, kStaticLimit);
   const int device = hs[0]->device;
   if (device < 0 || device >= 64) return fail(ISING_EINVAL, "ising_multi_sweep_static: device");
   StaticScratch& S = static_scratch(device);

@@ -60,3 +60,36 @@ def test_batches_beyond_the_sites_of_blocks(I, L, count):
         s, oem = oracle.run(L, 1 / T, 3, i, workloads.INIT_HOT, t)
         assert np.array_equal(EM[i].cpu().numpy(), oem[-n:])
         assert np.array_equal(lats[i].get_spins(), s)
+
+
+def test_static_tables_of_many_small_lattices(I):
+    """13400 lattices of 8^2 by the entry point that allocates nothing: within
+    its 4 MiB by the record of 240 bytes that its limit was set with."""
+    import ctypes
+
+    import torch
+    count, n, T = 13400, 3, 2.2
+    size = (I.ising_lattice_bytes(8) + 255) // 256 * 256
+    buf = torch.empty(count * size, dtype=torch.uint8, device="cuda")
+    stream = int(torch.cuda.current_stream().cuda_stream)
+    hs = (ctypes.c_void_p * (count + 200))()
+    for i in range(count + 200):  # the last ones share a place and are never swept
+        h = ctypes.c_void_p()
+        I.check(I.lib().ising_create(8, 5, i, workloads.INIT_HOT,
+                                     buf.data_ptr() + min(i, count - 1) * size, size, stream,
+                                     ctypes.byref(h)))
+        I.check(I.lib().ising_set_beta(h, 1 / T))
+        hs[i] = h.value
+    assert I.lib().ising_multi_sweep_static(hs, count + 200, n, None) == I.ISING_ENOMEM
+    # (the lattices that shared the place left it hot with another stream id)
+    h = ctypes.c_void_p(hs[count - 1])
+    host = oracle.init(8, 5, count - 1, workloads.INIT_HOT)
+    I.check(I.lib().ising_set_spins(h, host.ctypes.data))
+    I.check(I.lib().ising_multi_sweep_static(hs, count, n, None))
+    got = np.empty((8, 8), dtype=np.int8)
+    for i in (0, 1, 777, 11914, 11915, count - 1):
+        I.check(I.lib().ising_get_spins(ctypes.c_void_p(hs[i]), got.ctypes.data))
+        s, _ = oracle.run(8, 1 / T, 5, i, workloads.INIT_HOT, n)
+        assert np.array_equal(got, s), i
+    for v in hs:
+        I.lib().ising_destroy(ctypes.c_void_p(v))
