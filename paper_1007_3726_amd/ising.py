@@ -316,17 +316,13 @@ class Lattice:
         self.L = int(L)
         self.device = torch.device(device)
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
-        # behind the lattice, a second copy of the planes (several sweeps per launch)
-        nspare = _spare_bytes(self.L, ISING_RNG_PHILOX)
-        at = (nbytes + 255) // 256 * 256
-        self.buf = _dev_alloc(at + nspare if nspare else nbytes, self.device)
+        self.buf = _dev_alloc(nbytes, self.device)
+        self.spare_buf = None
         h = ctypes.c_void_p()
         check(lib().ising_create(self.L, seed & (2 ** 64 - 1), stream_id, init, self.buf.data_ptr(),
                                  nbytes, _stream_ptr(self.stream), ctypes.byref(h)))
         self.h = h
-        self._has_spare = nspare > 0
-        if nspare:
-            check(lib().ising_set_spare(self.h, self.buf.data_ptr() + at, nspare))
+        self._want_spare(ISING_RNG_PHILOX)
         if beta is not None:
             self.set_beta(beta)
 
@@ -345,13 +341,12 @@ class Lattice:
         check(lib().ising_set_beta(self.h, float(beta)))
 
     def _want_spare(self, kind: int):
-        """A second copy of the planes for dynamics that use one where plain
-        sweeps of this side do not."""
+        """A second copy of the planes (several sweeps per launch), if these
+        dynamics use one at this side."""
         nbytes = _spare_bytes(self.L, kind)
-        if nbytes and not self._has_spare:
+        if nbytes and self.spare_buf is None:
             self.spare_buf = _dev_alloc(nbytes, self.device)
             check(lib().ising_set_spare(self.h, self.spare_buf.data_ptr(), nbytes))
-            self._has_spare = True
 
     def use_lcg(self):
         """Switch to the paper's per-thread LCG dynamics (ising_set_rng); the

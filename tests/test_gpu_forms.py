@@ -136,8 +136,26 @@ def test_second_copy_is_allocated_for_dynamics_that_use_it(I):
     assert lat.sweep_plan(24)[0] == I.ISING_FORM_TILE
     lat.use_pool(10, linear=True)
     assert lat.sweep_plan(24)[0] == I.ISING_FORM_BLOCK
-    small = I.Lattice(64, seed=1, beta=0.4)
-    assert small.buf.numel() >= I.ising_lattice_bytes(64) + int(I.lib().ising_spare_bytes(64))
+    assert lat.buf.numel() == I.ising_lattice_bytes(L)
+
+
+def test_buffer_holds_the_lattice_alone(I):
+    """A lattice's tensor is ising_lattice_bytes long, with and without a
+    second copy, so that one saved on the device fits wherever it is put."""
+    import torch
+    n, T = 8, 2.3
+    for L in (64, 130, 1024):
+        lat = I.Lattice(L, seed=4, init=workloads.INIT_HOT, beta=1 / T)
+        assert lat.sweep_plan(n)[0] == I.ISING_FORM_BLOCK
+        saved = torch.empty(I.ising_lattice_bytes(L), dtype=torch.uint8, device="cuda")
+        lat.sweep(n)
+        saved.copy_(lat.buf)
+        lat.sweep(n)
+        back = I.Lattice(L, seed=4, beta=1 / T)
+        back.buf.copy_(saved)
+        back.sweep_count = n
+        back.sweep(n)
+        assert np.array_equal(back.get_spins(), lat.get_spins()), L
 
 
 def test_installed_tile_shapes_bind_plain_sweeps_only(I):
