@@ -236,9 +236,16 @@ bool strip_args(const ising_lattice* h, TileArgs* out) {
   return true;
 }
 
+// One workgroup for all sweeps.  An installed size was timed for plain sweeps:
+// generators and pools take it up to the built-in one only.  100 sweeps of 640^2
+// in one workgroup and in tiles: generators 1.94 and 0.78 ms, random patterns
+// 1.39 and 1.00.
 bool use_small_path(const ising_lattice* h) {
-  return block_kind(h) >= 0 &&
-         2 * h->plane_words * (int64_t)sizeof(uint64_t) <= h->tune.small_lds_bytes;
+  const int kind = block_kind(h);
+  const int64_t most = kind == kBlockPhilox
+                           ? h->tune.small_lds_bytes
+                           : std::min(h->tune.small_lds_bytes, kSmallLdsBytes);
+  return kind >= 0 && 2 * h->plane_words * (int64_t)sizeof(uint64_t) <= most;
 }
 
 // Several sweeps per launch: a lattice of its own shape (no installed tile or

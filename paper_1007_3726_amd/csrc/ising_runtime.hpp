@@ -16,6 +16,10 @@ constexpr int64_t kMaxL = int64_t(1) << 21;
 // per-block E/M partials (2 x kMaxSweepBlocks x 16 bytes)
 constexpr size_t kScratchBytes = 256 + 2 * (size_t)kMaxSweepBlocks * 16;
 
+// Both planes of a lattice that one LDS-resident workgroup runs unless another
+// size is installed: L <= 128.
+constexpr int64_t kSmallLdsBytes = 4096;
+
 // Launch-shape choices for one lattice size (filled by default_tuning and
 // refined by the autotuner).
 struct Tuning {

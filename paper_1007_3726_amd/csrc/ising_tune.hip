@@ -36,7 +36,7 @@ int64_t class_lo(int64_t L) {
 // The size rule.
 static Tuning builtin_tuning() {
   Tuning t;
-  t.small_lds_bytes = 4096;  // L <= 128 runs in one LDS-resident workgroup
+  t.small_lds_bytes = kSmallLdsBytes;
   t.max_blocks = 2048;
   t.rpw = 0;
   // tiles with direct neighbour loads: measured faster than strips at every

@@ -188,3 +188,30 @@ def test_installed_tile_shapes_bind_plain_sweeps_only(I):
         assert I.Lattice(2048, seed=1, beta=0.4).sweep_plan(24)[0] == I.ISING_FORM_BLOCK
     finally:
         I.tuning_clear()
+
+
+@pytest.mark.parametrize("kind", ["lcg", "pool", "linear"])
+def test_installed_workgroup_sizes_bind_plain_sweeps_only(I, kind):
+    """640^2 with 64 KiB of planes installed for one workgroup: plain sweeps
+    take one, generators and pools strips, or tiles without a second copy."""
+    L, n, T, m = 640, 6, 2.3, 11
+    I.tuning_set([{"L_min": L, "L_max": L, "form": I.ISING_FORM_TILE, "rpw": 0,
+                   "max_blocks": 2048, "small_lds_bytes": 65536, "updates_per_ns": 0.0}])
+    plain, strips, tiles = [I.Lattice(L, seed=7, init=workloads.INIT_HOT, beta=1 / T)
+                            for _ in range(3)]
+    I.tuning_clear()
+    assert plain.sweep_plan(n) == (I.ISING_FORM_BLOCK, 1)
+    for lat in (strips, tiles):
+        lat.use_lcg() if kind == "lcg" else lat.use_pool(m, linear=kind == "linear")
+    _no_copy(I, tiles)
+    form, launches = strips.sweep_plan(n)
+    assert form == I.ISING_FORM_BLOCK and launches > 1
+    assert tiles.sweep_plan(n) == (I.ISING_FORM_TILE, 2 * n)
+    s = oracle.init(L, 7, 0, workloads.INIT_HOT)
+    if kind == "lcg":
+        want = oracle.lcg_sweeps(s, 1 / T, oracle.lcg_seed(L, 7), n)
+    else:
+        want = oracle.pool_sweeps(s, 1 / T, 7, 0, 0, n, m, kind == "linear")
+    for lat in (strips, tiles):
+        assert np.array_equal(lat.sweep_em(n).cpu().numpy(), want)
+        assert np.array_equal(lat.get_spins(), s)
