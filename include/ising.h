@@ -108,8 +108,9 @@ ISING_API ising_status ising_create(int64_t L, uint64_t seed, uint32_t stream_id
  * it: it may be freed or reused once the handle's stream has passed them.
  * Handles of one stream may share a copy (a batch of such handles runs without
  * the copies), handles of different streams may not.  ising_spare_bytes is 0
- * for sides that take none (invalid, or too large to gain by it).  Results are
- * the same with and without.
+ * for sides that take none: invalid, or too large to gain by it under any
+ * dynamics (plain sweeps use a copy up to about 8000^2, linear pools up to
+ * 16384^2).  Results are the same with and without.
  * Errors: EINVAL (NULL handle, a side that takes none, alignment, an overlap
  * with the lattice's own ising_lattice_bytes), ENOMEM.
  */

@@ -581,7 +581,7 @@ def _numbers(v, kind):
     try:
         a = np.asarray(v)
         if a.ndim == 1 and a.dtype.kind in "biuf" and (kind is float or a.dtype.kind != "f"):
-            return a.astype(kind)
+            return a.astype(kind, copy=False)
     except (TypeError, ValueError, RuntimeError):
         pass
     return np.asarray([kind(x) for x in v], dtype=kind)
