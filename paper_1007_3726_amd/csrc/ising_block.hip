@@ -98,7 +98,8 @@ enum { kCompare = 0, kCut = 1, kAnyRow = 2, kAnyRowCut = 3, kLcg = 4, kPool = 5,
 template <int LS, int MODE, bool SERIAL>
 __device__ __forceinline__ void half_planes(uint32_t at, int sub, uint32_t k0, uint32_t k1,
                                             uint32_t t, uint32_t ctr3, uint32_t t4, uint32_t t8,
-                                            uint32_t cut_x, uint64_t cut_c, uint32_t& a, uint32_t& b) {
+                                            uint32_t cut_x, uint64_t cut_c, uint32_t& a,
+                                            uint32_t& b) {
   constexpr int NB = 8 / LS;
   a = b = 0;
   if (MODE == kCut) {

@@ -342,7 +342,9 @@ static SweepPlan plan_sweeps(ising_lattice* h, int64_t n) {
   }
   TileArgs& ta = p.ta;
   if (h->pool) {
-    p.form = pool_tile_args(h, &ta) ? ISING_FORM_TILE : kFormNone;
+    p.form = kFormNone;
+    if (!pool_tile_args(h, &ta)) return p;
+    p.form = ISING_FORM_TILE;
     p.blocks = (int)std::min<int64_t>(ta.tiles, kMaxSweepBlocks);
     return p;
   }
