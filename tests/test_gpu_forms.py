@@ -215,3 +215,23 @@ def test_installed_workgroup_sizes_bind_plain_sweeps_only(I, kind):
     for lat in (strips, tiles):
         assert np.array_equal(lat.sweep_em(n).cpu().numpy(), want)
         assert np.array_equal(lat.get_spins(), s)
+
+
+# 1.2, 1.8 and 1.9 rounds of tiles: dealt in runs of 64 and in one run per XCD,
+# by the size of the pool and the last round's fill
+@pytest.mark.parametrize("L,m,linear", [(18000, 12, False), (22016, 12, False), (22016, 19, False),
+                                        (22528, 12, True), (23000, 12, True)])
+def test_pools_in_uneven_rounds_of_tiles(I, L, m, linear):
+    n, T = 2, 2.25
+    lat = I.Lattice(L, seed=8, stream_id=1, init=workloads.INIT_HOT, beta=1 / T)
+    lat.use_pool(m, linear=linear)
+    assert lat.sweep_plan(n) == (I.ISING_FORM_TILE, 2 * n)
+    em = lat.sweep_em(n).cpu().numpy()
+    assert tuple(em[-1]) == lat.measure()
+    pool = oracle.pool_fill(1 / T, 8, 1, m)
+    for (x0, y0) in [(0, 0), (L - 20, L - 5), (L - 7, 1000), (L // 2, L // 2 + 1)]:
+        want = oracle.pool_window(L, 1 / T, 8, 1, workloads.INIT_HOT, 0, n, m, linear, x0, y0, 40,
+                                  12, pool)
+        rows = [lat.get_window(0, (y0 + i) % L, L, 1)[0] for i in range(12)]
+        xs = (x0 + np.arange(40)) % L
+        assert np.array_equal(np.stack([r[xs] for r in rows]), want), (x0, y0)
