@@ -14,6 +14,7 @@ constexpr double kLaunch = 5e-6;   // a launch: gap, loads, stores
 constexpr double kBarrier = 1e-7;  // of a colour step
 constexpr double kCuBytes = 2.5e10;  // bytes per second of one compute unit's share
 constexpr double kPatternLatency = 1e-6;
+constexpr double kAdvance = 3.5e-6;  // generators moved on, once per call
 
 // Instructions of one wave's pass with ls lanes per half; `any`: rows that
 // start anywhere in a Philox block.
@@ -139,12 +140,13 @@ struct Search {
   Sides sides;
   int64_t lattices, lds;
   int cus;
+  int64_t n;          // sweeps per call
   BlockPlan best, p;  // a shape per side
   CutOf cut;           // best's
   std::vector<std::pair<double, int64_t>> of;
 
-  Search(int kind_, const Sides& sides_, int64_t lattices_, int cus_, double limit)
-      : kind(kind_), sides(sides_), lattices(lattices_), cus(cus_) {
+  Search(int kind_, const Sides& sides_, int64_t lattices_, int cus_, int64_t n_, double limit)
+      : kind(kind_), sides(sides_), lattices(lattices_), cus(cus_), n(n_) {
     // a lone lattice's strips have a compute unit each
     lds = lattices == 1 ? block_lone_lds(kind) : kBlockMaxLds;
     best.sweep_s = limit;
@@ -153,7 +155,11 @@ struct Search {
   void consider(const CutOf& c) {
     const bool singles = c.target == 0;
     const int K = c.K;
-    const double fixed = singles ? 0.0 : kLaunch / K, units = std::max(cus, 1);
+    // launches per sweep of a lattice of several strips
+    const bool few = few_sweeps();
+    const double per = few ? (double)(2 * ((n + 2 * K - 1) / (2 * K))) / n : 1.0 / K;
+    const double call = few && kind == kBlockLcg ? kAdvance / n : 0.0;
+    const double fixed = (singles ? 0.0 : kLaunch * per) + call, units = std::max(cus, 1);
     double longest = 0, move = 0, issue = 0;
     int64_t strips = 0;
     p.shapes.clear();
@@ -185,30 +191,53 @@ struct Search {
     p.sweeps = K;
     p.tasks = strips;
     const double step = std::max(longest, busiest_issue(p.shapes, sides, cus, of));
-    p.sweep_s = 2 * step + (singles ? 0.0 : (kLaunch + move) / K);
+    p.sweep_s = 2 * step + fixed + (singles ? 0.0 : move * per);
     if (p.sweep_s < best.sweep_s) {
       std::swap(best, p);
       cut = c;
     }
   }
 
-  // Calls of n sweeps.  With more lattices than compute units a lattice's own
+  // A call of few sweeps counts its launches one by one: they share the sweeps
+  // evenly (5 sweeps: 3 and 2, or 2, 1, 1, 1), and generators have one of their
+  // own.  As if every launch had K sweeps, calls of 2 to 8 sweeps took blocks
+  // where tiles are up to 13 % faster (5 sweeps of 4002^2 13.3 and 15.0 us each),
+  // or too many launches (1400^2 6.5 -> 5.2).  Pools stay with that: their steps
+  // cost less than the model has them at, and counted so they would be left to
+  // tiles that are up to 40 % slower.
+  bool few_sweeps() const { return n < kBlockPlanN && kind <= kBlockLcg; }
+
+  std::vector<int> sweeps_per_launch() const {
+    std::vector<int> Ks;
+    if (!few_sweeps()) {
+      for (int K : {1, 2, 3, 4, 6, 8, 12})
+        if (K <= (n + 1) / 2) Ks.push_back(K);
+      return Ks;
+    }
+    for (int64_t K = 1; K <= (n + 1) / 2; ++K) {
+      const int64_t m = 2 * ((n + 2 * K - 1) / (2 * K));
+      if ((n + m - 1) / m == K) Ks.push_back((int)K);
+    }
+    return Ks;
+  }
+
+  // With more lattices than compute units a lattice's own
   // step counts for less than the instructions in all, so that fewer lanes per
   // half can win: 300 sweeps of 600 lattices of 64^2 3.3 -> 1.1 ms, of 128^2
   // 5.3 -> 1.95.
-  void all(int64_t n) {
+  void all() {
     const int least = lattices > cus ? 1 : 8;
     for (int max_ls = 8; max_ls >= least; max_ls /= 2) consider(CutOf{1, 0, max_ls});
     if (n < 2) return;
     std::vector<int64_t> targets;
     for (int64_t target = 32; target <= 20000; target += target / 4) targets.push_back(target);
     // every fourth target first, so that the others are measured by a good cut
+    const std::vector<int> Ks = sweeps_per_launch();
     for (size_t step : {4, 1})
       for (int max_ls = 8; max_ls >= least; max_ls /= 2)
-        for (int K : {1, 2, 3, 4, 6, 8, 12})
-          if (K <= (n + 1) / 2)
-            for (size_t i = 0; i < targets.size(); i += step)
-              if (step == 4 || i % 4) consider(CutOf{K, targets[i], max_ls});
+        for (int K : Ks)
+          for (size_t i = 0; i < targets.size(); i += step)
+            if (step == 4 || i % 4) consider(CutOf{K, targets[i], max_ls});
   }
 };
 
@@ -244,21 +273,21 @@ BlockPlan plan_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int c
     ++sides.back().second;
   }
   const int64_t lattices = (int64_t)Ls.size();
-  Search s(kind, sides, lattices, cus, limit);
+  Search s(kind, sides, lattices, cus, n, limit);
   // (grouped, a cut is up to a tenth dearer: 87 sides 12.5 us per sweep, each
   // by itself 11.6, in four times the planning)
   if (sides.size() <= kBlockPlanSides || n >= 8 * (int64_t)sides.size()) {
-    s.all(n);
+    s.all();
   } else {
     // the cut of the groups, with strips as long and around that
-    Search g(kind, grouped(sides), lattices, cus, 1.1 * limit);
-    g.all(n);
+    Search g(kind, grouped(sides), lattices, cus, n, 1.1 * limit);
+    g.all();
     if (g.best.shapes.empty()) return BlockPlan();
     s.consider(g.cut);
     for (double f : {1.25, 0.8, 1.5, 0.65, 1.9})
       if (g.cut.target)
         s.consider(CutOf{g.cut.K, (int64_t)(f * (double)g.cut.target), g.cut.max_ls});
-    if (s.best.shapes.empty()) s.all(n);
+    if (s.best.shapes.empty()) s.all();
   }
   BlockPlan best;
   if (s.best.shapes.empty()) return best;

@@ -14,8 +14,8 @@ PHILOX, LCG, POOL, POOL_LINEAR = range(4)
 CU_LDS = 160 * 1024
 STATIC_LDS = {PHILOX: 32 * 16 * 8, LCG: 32 * 16 * 8 + 2 * 64 * 4}
 STATIC_LDS[POOL] = STATIC_LDS[POOL_LINEAR] = STATIC_LDS[LCG]
-# calls whose sweeps allow other launches: K <= (n + 1) / 2 of 1, 2, 3, 4, 6, 8, 12
-SWEEPS = [2, 3, 5, 7, 11, 15, 24]
+# calls of fewer sweeps are planned each by itself, of 24 and more alike
+SWEEPS = range(2, 25)
 
 
 @pytest.fixture(scope="module")

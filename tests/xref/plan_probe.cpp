@@ -1,8 +1,8 @@
 // Prints the plans of ising_plan.cpp: reads lines "kind n cus count L...",
 // prints "plan_us sweep_us tasks count" and, per lattice, "rows strips ls pass
 // threads sweeps lds" (count 0: no plan), and 1 if that is cheaper than a launch
-// per colour step.  plan_us: microseconds that the planning takes when it is
-// held to that, the best of three.
+// per colour step.  plan_us: microseconds that the planning of several
+// lattices takes when it is held to that, the best of three.
 #include <chrono>
 #include <cstdio>
 
@@ -20,7 +20,7 @@ int main() {
     }
     double words = 0, us = 1e9;
     for (int64_t L : Ls) words += (double)(L * ising::words_per_row(L));
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < 3 && count > 1; ++i) {
       const auto t0 = std::chrono::steady_clock::now();
       ising::plan_blocks(kind, Ls, n, cus, ising::launch_per_step_seconds(kind, words, cus));
       const std::chrono::duration<double, std::micro> d = std::chrono::steady_clock::now() - t0;
