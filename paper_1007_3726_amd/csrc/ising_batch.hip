@@ -105,7 +105,7 @@ int device_cus(int device) {
 // A batch of more sites than kBlockMaxSites fills the chip in every colour
 // step: only single strips, which have no halo rows, can still be cheaper.
 // (And only they run any number of sweeps.)
-bool choose_blocks(const std::vector<int64_t>& Ls, int64_t n, int cus, BlockPlan* plan) {
+bool choose_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int cus, BlockPlan* plan) {
   double sites = 0, words = 0;
   bool all_single = true;
   for (int64_t L : Ls) {
@@ -118,8 +118,7 @@ bool choose_blocks(const std::vector<int64_t>& Ls, int64_t n, int cus, BlockPlan
     if (!all_single) return false;
     n = 1;
   }
-  *plan = plan_blocks(kBlockPhilox, Ls, n, cus,
-                      launch_per_step_seconds(kBlockPhilox, words, cus));
+  *plan = plan_blocks(kind, Ls, n, cus, launch_per_step_seconds(kind, words, cus));
   return !plan->shapes.empty();
 }
 
@@ -424,6 +423,9 @@ ising_status batch_sweeps(ising_lattice* const* hs, int32_t count, int64_t n,
   // launches.)  Their tables may need more than the work buffer holds: then
   // the other forms run.
   const int cus = device_cus(device);
+  int kind = kBlockCompare;
+  for (int i = 0; i < count; ++i)
+    if (hs[i]->cut.x) kind = kBlockPhilox;
   if (opt.force_form < 0 && work && ((uintptr_t)work & 255) == 0) {
     std::vector<int> all(count);
     std::iota(all.begin(), all.end(), 0);
@@ -434,7 +436,7 @@ ising_status batch_sweeps(ising_lattice* const* hs, int32_t count, int64_t n,
       spares = spares && (hs[i]->spare || block_fits_single(hs[i]->L));
     }
     BlockPlan plan;
-    if (spares && choose_blocks(Ls, n, cus, &plan)) {
+    if (spares && choose_blocks(kind, Ls, n, cus, &plan)) {
       if (block_layout(count, plan.tasks).bytes <= work_bytes && own_spares(hs, plan)) {
         if (form_out) *form_out = plan.all_single ? 1 : 0;
         return run_blocks(hs, all, n, nsw, dev_EM, plan, (char*)work, opt.keep_image);
@@ -456,7 +458,7 @@ ising_status batch_sweeps(ising_lattice* const* hs, int32_t count, int64_t n,
       Ls.push_back(hs[i]->L);
     }
     const bool packed = opt.force_form == 1 ||
-                        (opt.force_form < 0 && rest.empty() && choose_blocks(Ls, 1, cus, &singles));
+                        (opt.force_form < 0 && rest.empty() && choose_blocks(kind, Ls, 1, cus, &singles));
     if (form_out) *form_out = packed ? 1 : 0;
     if (packed) {
       tiled.swap(rest);
@@ -512,7 +514,8 @@ extern "C" ising_status ising_batch_plan(const int64_t* Ls, int32_t count, int32
     words += (double)(L * W);
   }
   BlockPlan plan;
-  const bool blocks = choose_blocks(std::vector<int64_t>(Ls, Ls + count), kBlockPlanN, cus, &plan);
+  const bool blocks = choose_blocks(kBlockPhilox, std::vector<int64_t>(Ls, Ls + count),
+                                    kBlockPlanN, cus, &plan);
   *form_out = blocks && plan.all_single ? 1 : 0;
   *blocks_out = blocks ? (int32_t)plan.tasks
                        : fused_grid(tiles, default_batch_options().wg_per_cu, cus);

@@ -30,8 +30,9 @@ BatchOptions default_batch_options();
 // Argument checks shared by the batched entry points (n: sweeps to come).
 ising_status check_batch(ising_t* const* hs, int32_t count, int64_t n, const char* who);
 // Whether these lattices together are cheaper in blocks than in a launch per
-// colour step, for n sweeps (the cut in *plan).
-bool choose_blocks(const std::vector<int64_t>& Ls, int64_t n, int cus, BlockPlan* plan);
+// colour step, for n sweeps (the cut in *plan); kind: kBlockPhilox, or
+// kBlockCompare where none of them has a cut of its thresholds.
+bool choose_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int cus, BlockPlan* plan);
 // Device bytes of the work buffer batch_sweeps needs for these handles
 // (0 when every lattice takes the plain path).
 size_t batch_work_bytes(ising_lattice* const* hs, int32_t count, const BatchOptions& opt);

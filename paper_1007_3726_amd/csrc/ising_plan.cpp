@@ -22,8 +22,10 @@ static double pass_instructions(int kind, int ls, bool any) {
   if (kind == kBlockLcg) return ls == 8 ? 85 : ls == 4 ? 105 : ls == 2 ? 140 : 210;
   if (kind == kBlockPool) return ls == 0 ? 165 : 115;
   if (kind == kBlockPoolLinear) return ls == 0 ? 105 : 75;
-  if (any) return ls == 8 ? 155 : ls == 4 ? 220 : ls == 2 ? 335 : 515;
-  return ls == 8 ? 115 : ls == 4 ? 180 : ls == 2 ? 290 : 460;
+  // (four and eight lanes compare anyway)
+  const double more = kind == kBlockCompare && ls <= 2 ? 1.13 : 1.0;
+  if (any) return more * (ls == 8 ? 155 : ls == 4 ? 220 : ls == 2 ? 335 : 515);
+  return more * (ls == 8 ? 115 : ls == 4 ? 180 : ls == 2 ? 290 : 460);
 }
 
 static double waves_of(double halves, int ls) { return std::ceil(halves * (ls ? ls : 0.5) / 64); }
@@ -82,13 +84,17 @@ static BlockShape shape_of(int kind, int64_t L, int64_t rows, int K, int max_ls 
 
 // Measured: 3 us per launch (gap, ramp and drain) and 1.45 us per word of the
 // busiest SIMD's waves, at least 2.2 us for a word alone: us per sweep 15.3 at
-// 4104^2, 20.7 at 6000^2, 29.3 at 8192^2, 74 for the 56-lattice grid.
-// Generators 0.58 us and 1.5 us (their chain is serial), patterns 0.35 us
-// (random 1.4 us) and 1 us: 16384^2 24.0, 14.2 and 45.7 us per colour step.
+// 4104^2, 20.7 at 6000^2, 29.3 at 8192^2, 74 for the 56-lattice grid.  Without a
+// cut of the thresholds 1.645 us, against 1.13 of the blocks' instructions: 16
+// sweeps of 6144^2 at T = 1.5 22.5 us each in tiles, 23.4 in blocks (at 2.3 20.5
+// and 20.7).  Generators 0.58 us and 1.5 us (their chain is serial), patterns
+// 0.35 us (random 1.4 us) and 1 us: 16384^2 24.0, 14.2 and 45.7 us per colour
+// step.
 double launch_per_step_seconds(int kind, double words, int cus) {
-  static const double word[] = {1.45e-6, 0.65e-6, 1.35e-6, 0.35e-6};
-  static const double alone[] = {2.2e-6, 1.5e-6, 1.0e-6, 1.0e-6};
-  return 2 * (3e-6 + std::max(alone[kind], word[kind] * std::ceil(words / 256 / std::max(cus, 1))));
+  static const double word[] = {1.645e-6, 1.45e-6, 0.65e-6, 1.35e-6, 0.35e-6};
+  static const double alone[] = {2.2e-6, 2.2e-6, 1.5e-6, 1.0e-6, 1.0e-6};
+  const int k = kind - kBlockCompare;
+  return 2 * (3e-6 + std::max(alone[k], word[k] * std::ceil(words / 256 / std::max(cus, 1))));
 }
 
 BlockShape block_shape_single(int kind, int64_t L) { return shape_of(kind, L, L, 1); }

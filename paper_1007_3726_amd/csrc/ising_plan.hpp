@@ -28,8 +28,9 @@ constexpr int64_t kBlockMaxL = 16384;
 // two share a compute unit.
 constexpr int64_t kBlockMaxLds = 65536;
 
-// Dynamics of a block.
-enum { kBlockPhilox = 0, kBlockLcg = 1, kBlockPool = 2, kBlockPoolLinear = 3 };
+// Dynamics of a block; kBlockCompare: Philox at thresholds without a cut, for
+// plans.
+enum { kBlockCompare = -1, kBlockPhilox = 0, kBlockLcg = 1, kBlockPool = 2, kBlockPoolLinear = 3 };
 
 constexpr int kMaxWaves = 16;  // of one workgroup
 constexpr int kEmSlots = 32;   // sweeps whose counts are kept in LDS at a time
@@ -38,7 +39,7 @@ constexpr int kMaxGroups = 64;
 // LDS that the kernels take beside the rows: a pair of counts per sweep and
 // wave, and for generators and pools (one kernel) two starts per group.
 constexpr int64_t block_static_lds(int kind) {
-  return 8 * kEmSlots * kMaxWaves + (kind == kBlockPhilox ? 0 : 2 * 4 * kMaxGroups);
+  return 8 * kEmSlots * kMaxWaves + (kind <= kBlockPhilox ? 0 : 2 * 4 * kMaxGroups);
 }
 // Rows of a strip that has a compute unit of its own: all that is left.
 constexpr int64_t block_lone_lds(int kind) { return 160 * 1024 - block_static_lds(kind); }

@@ -326,14 +326,15 @@ static SweepPlan plan_sweeps(ising_lattice* h, int64_t n) {
   }
   if (use_block_path(h, n)) {
     const int64_t per_call = std::min(n, kBlockPlanN);
-    if (h->block_of != kind) h->block_planned = 0;
-    h->block_of = kind;
+    const int plan_kind = kind == kBlockPhilox && !h->cut.x ? kBlockCompare : kind;
+    if (h->block_of != plan_kind) h->block_planned = 0;
+    h->block_of = plan_kind;
     BlockShape& shape = h->block[per_call];
     if (!(h->block_planned >> per_call & 1)) {
       const int cus = device_cus(h->device);
       const BlockPlan plan =
-          plan_blocks(kind, {h->L}, per_call, cus,
-                      launch_per_step_seconds(kind, (double)h->plane_words, cus));
+          plan_blocks(plan_kind, {h->L}, per_call, cus,
+                      launch_per_step_seconds(plan_kind, (double)h->plane_words, cus));
       shape = plan.shapes.empty() ? BlockShape() : plan.shapes[0];
       h->block_planned |= 1u << per_call;
     }

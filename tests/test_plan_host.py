@@ -9,10 +9,12 @@ import pytest
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 PHILOX, LCG, POOL, POOL_LINEAR = range(4)
+COMPARE = -1  # Philox at thresholds without a cut
 # 160 KiB of LDS per compute unit; the kernels' own: 32 sweeps' counts of 16
 # waves, and where generators or pools are compiled in the starts of 64 groups
 CU_LDS = 160 * 1024
 STATIC_LDS = {PHILOX: 32 * 16 * 8, LCG: 32 * 16 * 8 + 2 * 64 * 4}
+STATIC_LDS[COMPARE] = STATIC_LDS[PHILOX]
 STATIC_LDS[POOL] = STATIC_LDS[POOL_LINEAR] = STATIC_LDS[LCG]
 # calls of fewer sweeps are planned each by itself, of 24 and more alike
 SWEEPS = range(2, 25)
@@ -48,10 +50,10 @@ def plans():
 
 def _sides(kind):
     # generators and pools need sides that are multiples of 8
-    return range(4, 16385, 2) if kind == PHILOX else range(8, 16385, 8)
+    return range(4, 16385, 2) if kind <= PHILOX else range(8, 16385, 8)
 
 
-@pytest.mark.parametrize("kind", [PHILOX, LCG, POOL, POOL_LINEAR])
+@pytest.mark.parametrize("kind", [COMPARE, PHILOX, LCG, POOL, POOL_LINEAR])
 def test_every_lone_plan_can_be_launched(plans, kind):
     """Side by side over all sides: the strips fit a compute unit's LDS with
     the kernel's own part of it, and the halos stay inside the lattice."""
@@ -104,3 +106,13 @@ def test_second_copies_are_for_sides_that_use_them(plans):
         assert used and max(used) <= limit, kind
     # no batch with a larger side is cut into strips
     assert limits[0] ** 2 <= 6.4e7 < (limits[0] + 2) ** 2
+
+
+def test_blocks_end_earlier_without_a_cut(plans):
+    """Without the cut a block's instructions grow by more than a tile's: at
+    6144^2 tiles are ahead then (16 sweeps at T = 1.5 22.5 us each in tiles and
+    23.4 in blocks, at T = 2.3 as long in both), at 5120^2 and 7680^2 blocks."""
+    sides = (1024, 4096, 5120, 6144, 7680)
+    chosen = [r[4] for r in plans([(COMPARE, 24, 256, [L]) for L in sides])]
+    assert chosen == [True, True, True, False, True]
+    assert all(r[4] for r in plans([(PHILOX, 24, 256, [L]) for L in sides]))
