@@ -105,7 +105,8 @@ int device_cus(int device) {
 // A batch of more sites than kBlockMaxSites fills the chip in every colour
 // step: only single strips, which have no halo rows, can still be cheaper.
 // (And only they run any number of sweeps.)
-bool choose_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int cus, BlockPlan* plan) {
+bool choose_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int cus,
+                   size_t table_bytes, BlockPlan* plan) {
   double sites = 0, words = 0;
   bool all_single = true;
   for (int64_t L : Ls) {
@@ -118,7 +119,12 @@ bool choose_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int cus,
     if (!all_single) return false;
     n = 1;
   }
-  *plan = plan_blocks(kind, Ls, n, cus, launch_per_step_seconds(kind, words, cus));
+  // a batch of few lattices has tables for fewer strips than the chip has units:
+  // 200 sweeps of 3 x 336^2 2.13 ms where the best cut did not fit and the fused
+  // form ran, 0.62 with the best that fits
+  const size_t off = block_layout(Ls.size(), 0).off_tasks, room = table_bytes / 256 * 256;
+  const int64_t most = room > off ? (int64_t)((room - off) / sizeof(BlockTask)) : 0;
+  *plan = plan_blocks(kind, Ls, n, cus, launch_per_step_seconds(kind, words, cus), most);
   return !plan->shapes.empty();
 }
 
@@ -436,8 +442,8 @@ ising_status batch_sweeps(ising_lattice* const* hs, int32_t count, int64_t n,
       spares = spares && (hs[i]->spare || block_fits_single(hs[i]->L));
     }
     BlockPlan plan;
-    if (spares && choose_blocks(kind, Ls, n, cus, &plan)) {
-      if (block_layout(count, plan.tasks).bytes <= work_bytes && own_spares(hs, plan)) {
+    if (spares && choose_blocks(kind, Ls, n, cus, work_bytes, &plan)) {
+      if (own_spares(hs, plan)) {
         if (form_out) *form_out = plan.all_single ? 1 : 0;
         return run_blocks(hs, all, n, nsw, dev_EM, plan, (char*)work, opt.keep_image);
       }
@@ -457,8 +463,9 @@ ising_status batch_sweeps(ising_lattice* const* hs, int32_t count, int64_t n,
       (block_fits_single(hs[i]->L) ? fits : rest).push_back(i);
       Ls.push_back(hs[i]->L);
     }
-    const bool packed = opt.force_form == 1 ||
-                        (opt.force_form < 0 && rest.empty() && choose_blocks(kind, Ls, 1, cus, &singles));
+    const bool packed =
+        opt.force_form == 1 || (opt.force_form < 0 && rest.empty() &&
+                                choose_blocks(kind, Ls, 1, cus, work_bytes, &singles));
     if (form_out) *form_out = packed ? 1 : 0;
     if (packed) {
       tiled.swap(rest);
@@ -515,7 +522,7 @@ extern "C" ising_status ising_batch_plan(const int64_t* Ls, int32_t count, int32
   }
   BlockPlan plan;
   const bool blocks = choose_blocks(kBlockPhilox, std::vector<int64_t>(Ls, Ls + count),
-                                    kBlockPlanN, cus, &plan);
+                                    kBlockPlanN, cus, SIZE_MAX, &plan);
   *form_out = blocks && plan.all_single ? 1 : 0;
   *blocks_out = blocks ? (int32_t)plan.tasks
                        : fused_grid(tiles, default_batch_options().wg_per_cu, cus);

@@ -31,8 +31,10 @@ BatchOptions default_batch_options();
 ising_status check_batch(ising_t* const* hs, int32_t count, int64_t n, const char* who);
 // Whether these lattices together are cheaper in blocks than in a launch per
 // colour step, for n sweeps (the cut in *plan); kind: kBlockPhilox, or
-// kBlockCompare where none of them has a cut of its thresholds.
-bool choose_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int cus, BlockPlan* plan);
+// kBlockCompare where none of them has a cut of its thresholds; table_bytes: room
+// for the plan's tables.
+bool choose_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int cus,
+                   size_t table_bytes, BlockPlan* plan);
 // Device bytes of the work buffer batch_sweeps needs for these handles
 // (0 when every lattice takes the plain path).
 size_t batch_work_bytes(ising_lattice* const* hs, int32_t count, const BatchOptions& opt);

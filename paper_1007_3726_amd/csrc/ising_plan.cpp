@@ -144,15 +144,17 @@ struct CutOf {  // sweeps per launch, halves per strip, lanes; target 0: one str
 struct Search {
   int kind;
   Sides sides;
-  int64_t lattices, lds;
+  int64_t lattices, lds, most;  // most: strips
   int cus;
   int64_t n;          // sweeps per call
   BlockPlan best, p;  // a shape per side
   CutOf cut;           // best's
   std::vector<std::pair<double, int64_t>> of;
 
-  Search(int kind_, const Sides& sides_, int64_t lattices_, int cus_, int64_t n_, double limit)
+  Search(int kind_, const Sides& sides_, int64_t lattices_, int cus_, int64_t n_, double limit,
+         int64_t max_tasks)
       : kind(kind_), sides(sides_), lattices(lattices_), cus(cus_), n(n_) {
+    most = std::min(kBlockMaxTasks + lattices, max_tasks);
     // a lone lattice's strips have a compute unit each
     lds = lattices == 1 ? block_lone_lds(kind) : kBlockMaxLds;
     best.sweep_s = limit;
@@ -185,7 +187,7 @@ struct Search {
       if (s.lds > (size_t)lds || (!single && K > s.strips)) return;
       if (kind == kBlockPoolLinear && (int64_t)(s.lds / 16) / 256 + 3 > kMaxGroups) return;
       strips += s.strips * side.second;
-      if (strips > kBlockMaxTasks + lattices) return;
+      if (strips > most) return;
       longest = std::max(longest, s.step_s);
       issue += s.issue_s * (double)(s.strips * side.second);
       // no cheaper than the best even if no other strip is longer and all of
@@ -270,7 +272,7 @@ Sides grouped(const Sides& sides) {
 // of 24 sweeps of 24, 87 or 120 distinct sides is planned in 0.06, 0.10 and
 // 0.14 ms, 0.34, 1.8 and 10.5 with every cut of every side.
 BlockPlan plan_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int cus,
-                      double limit) {
+                      double limit, int64_t max_tasks) {
   std::vector<int64_t> sorted(Ls);
   std::sort(sorted.begin(), sorted.end(), std::greater<int64_t>());
   Sides sides;
@@ -279,14 +281,14 @@ BlockPlan plan_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int c
     ++sides.back().second;
   }
   const int64_t lattices = (int64_t)Ls.size();
-  Search s(kind, sides, lattices, cus, n, limit);
+  Search s(kind, sides, lattices, cus, n, limit, max_tasks);
   // (grouped, a cut is up to a tenth dearer: 87 sides 12.5 us per sweep, each
   // by itself 11.6, in four times the planning)
   if (sides.size() <= kBlockPlanSides || n >= 8 * (int64_t)sides.size()) {
     s.all();
   } else {
     // the cut of the groups, with strips as long and around that
-    Search g(kind, grouped(sides), lattices, cus, n, 1.1 * limit);
+    Search g(kind, grouped(sides), lattices, cus, n, 1.1 * limit, max_tasks);
     g.all();
     if (g.best.shapes.empty()) return BlockPlan();
     s.consider(g.cut);

@@ -82,9 +82,9 @@ bool block_fits_single(int64_t L);
 // Model: seconds per sweep of lattices with `words` words per colour in all
 // when every colour step is a launch.
 double launch_per_step_seconds(int kind, double words, int cus);
-// The cheapest cut for calls of n sweeps; empty if none takes less than
-// `limit` seconds per sweep.
+// The cheapest cut for calls of n sweeps into at most max_tasks strips; empty if
+// none takes less than `limit` seconds per sweep.
 BlockPlan plan_blocks(int kind, const std::vector<int64_t>& Ls, int64_t n, int cus,
-                      double limit = 1e9);
+                      double limit = 1e9, int64_t max_tasks = INT64_MAX);
 
 }  // namespace ising

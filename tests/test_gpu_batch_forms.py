@@ -62,6 +62,29 @@ def test_batches_beyond_the_sites_of_blocks(I, L, count):
         assert np.array_equal(lats[i].get_spins(), s)
 
 
+# (with tables for fewer strips than the best cut has)
+@pytest.mark.parametrize("Ls", [[336] * 3, [512, 336], [200] * 4 + [640]])
+def test_few_lattices_take_strips_within_their_tables(I, Ls):
+    import torch
+    n, T = 60, 2.25
+    lats = [I.Lattice(L, seed=3, stream_id=i, init=workloads.INIT_HOT, beta=1 / T)
+            for i, L in enumerate(Ls)]
+    EMs = [torch.empty((n, 2), dtype=torch.int64, device="cuda") for _ in Ls]
+    best, t = {}, 0
+    for form in ("fused", None) * 3:
+        t0 = time.perf_counter()
+        I.multi_sweep(lats, n, EMs, form=form)
+        dt = time.perf_counter() - t0
+        best[form] = min(best.get(form, dt), dt)
+        t += n
+    print("fused %.3f ms, chosen %.3f ms" % (1e3 * best["fused"], 1e3 * best[None]), flush=True)
+    assert best[None] < 0.7 * best["fused"]
+    for i, L in enumerate(Ls):
+        s, oem = oracle.run(L, 1 / T, 3, i, workloads.INIT_HOT, t)
+        assert np.array_equal(EMs[i].cpu().numpy(), oem[-n:])
+        assert np.array_equal(lats[i].get_spins(), s)
+
+
 def test_static_tables_of_many_small_lattices(I):
     """13400 lattices of 8^2 by the entry point that allocates nothing: within
     its 4 MiB by the record of 240 bytes that its limit was set with."""
